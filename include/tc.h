@@ -117,12 +117,13 @@ typedef struct tc_batch {
 typedef struct tc_tuning {
   /* tc_count_batch */
   int32_t batch_block;        /* threads per block of the counting kernel:
-                                 64 (one block per piece, not persistent),
-                                 256 (default) or 512 */
-  int32_t batch_piece;        /* CSR entries per work piece (>= 1024,
-                                 default 16384) */
-  int32_t batch_blocks_per_cu;/* resident blocks per CU of the persistent
-                                 counting kernel (0 = as many as LDS allows) */
+                                 64, 256 or 512 (default: 64 while a default
+                                 piece is under 128 entries, else 256) */
+  int32_t batch_piece;        /* CSR entries per work piece (>= 1024;
+                                 default total_nnz / 2048, within 16..512) */
+  int32_t batch_blocks_per_cu;/* blocks per CU the counting kernel is launched
+                                 with, each taking several pieces (0 = one
+                                 block per piece) */
   /* tc_count_tuned: which path a graph takes */
   int32_t small_max_n;        /* a graph with 0 < n <= small_max_n and
                                  nnz <= small_max_nnz is levelled and counted
@@ -325,7 +326,7 @@ int tc_count_edge_baseline(const tc_csr* g, uint32_t flags, int64_t* triangles, 
 int tc_count_edge_baseline_tuned(const tc_csr* g, uint32_t flags, const tc_tuning* tuning,
                                  int64_t* triangles, void* ws, size_t ws_bytes, tc_stream_t stream);
 
-/* Cover-edge counts of many small graphs in one persistent launch: per graph,
+/* Cover-edge counts of many small graphs in one call: per graph,
  * the levels of tc_bfs_levels (root = largest degree), H and T.
  *   triangles    device int64 [G] (output); -1 for a graph of more than
  *                TC_BATCH_MAX_N vertices, which is skipped (its levels are
@@ -350,9 +351,10 @@ int tc_count_batch(const tc_batch* b, const tc_tuning* tuning, uint32_t flags,
  * tc_count_batch takes from `ws` lives instead in a static device array of
  * tc_noalloc_scratch_bytes() bytes (32 MiB) that each GPU holds until the
  * process ends.  The call allocates and frees nothing.
- *   - A batch needing more scratch than that (tc_workspace_bytes(
- *     TC_OP_COUNT_BATCH, ...) above the array's size) gives TC_ERR_TOO_LARGE
- *     before any device work; about 1.3 G entries in total fit.
+ *   - A batch needing more scratch than that (a bit per vertex and 8 bytes
+ *     per 512 entries; tc_count_batch's 8-byte records per vertex are used
+ *     only where they fit as well) gives TC_ERR_TOO_LARGE before any device
+ *     work; about 1.3 G entries in total fit.
  *   - TC_VALIDATE is not supported (TC_ERR_INVALID_ARG): check a batch with
  *     tc_count_batch first.
  *   - Every call on one GPU shares that GPU's array: calls that overlap on

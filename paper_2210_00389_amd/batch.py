@@ -3,7 +3,7 @@
 A :class:`Batch` is the concatenated device CSR of the ``tc_batch`` ABI:
 ``vbase`` (int64, G+1 vertex bases), global ``row_offsets`` (int64) and
 ``cols`` holding local vertex ids (int32, < 65536).  :func:`count_batch`
-runs the library's two kernels; :class:`CapturedBatch` records that call
+runs the library's kernels; :class:`CapturedBatch` records that call
 once in a CUDA/HIP graph and replays it; :func:`autotune` times the tuning
 knobs of the counting kernel on a given batch and keeps the fastest.
 """
@@ -166,7 +166,7 @@ class CapturedBatch:
 
 
 _TUNE_CANDIDATES = [
-    dict(batch_block=256, batch_piece=4096), dict(batch_block=256, batch_piece=16384),
+    dict(batch_block=256), dict(batch_block=512), dict(batch_block=256, batch_piece=4096), dict(batch_block=256, batch_piece=16384),
     dict(batch_block=256, batch_piece=65536), dict(batch_block=512, batch_piece=4096),
     dict(batch_block=512, batch_piece=16384), dict(batch_block=512, batch_piece=65536),
     dict(batch_block=256, batch_piece=16384, batch_blocks_per_cu=2),

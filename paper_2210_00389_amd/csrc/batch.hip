@@ -1,8 +1,8 @@
 // batch.hip -- tc_count_batch: Alg. 1 on many small graphs (n <= 65536 each)
-// in two kernels that issue no host synchronisation and no memset, so a
+// in three kernels that issue no host synchronisation and no memset, so a
 // caller can capture the whole call in one hipGraph.
 //
-// Kernel 1 (one block per graph): BFS levels of Alg. 1 with the level array
+// The level kernel (one block per graph): BFS levels of Alg. 1 with the level array
 // resident in LDS as uint16 (128 KB for 65536 vertices).  The first root is
 // the highest-degree vertex (smallest id on ties); every other component is
 // then searched from its smallest unvisited id, as in the scan order of
@@ -10,21 +10,21 @@
 // vertices: top-down from the frontier (vertices of degree above kBigDeg are
 // expanded by a whole wave) or, when the last level was large, bottom-up.
 // The block writes the level parity as a bit array (Lemma 1: for adjacent
-// vertices L(x) = L(y) iff their parities agree, so the parity is all the
-// count needs), the optional int32 levels, and the graph's work pieces:
-// piece p is the range [p * piece, (p + 1) * piece) of the graph's CSR
-// entries, so a vertex of large degree is spread over several pieces.
+// vertices L(x) = L(y) iff their parities agree, so the parity is all that
+// |H| needs) and the optional int32 levels.
 //
-// Kernel 2 (persistent blocks of 256 or 512 threads claiming pieces from a
-// counter, or one 64-thread block per piece): a wave takes one
-// vertex u of the piece at a time, sets the bits of N(u) in its own
-// 65536-bit LDS bitmap, and for every cover edge (u, v), v > u with equal
-// parity, whose entry v of N(u) lies in the piece, streams N(v) in
-// chunks of kBChunk consecutive entries per lane (the stream of a lane's
-// chunk comes from a 64-bit mask of stream starts, no search) and counts the
-// w whose bit is set and that pass the test of Alg. 1 (parity of w differs
-// from u's, or w > v).  Counts and
-// |H| are reduced per block and added to the graph's outputs.
+// Before it, one grid-wide kernel cuts every graph's CSR entries into work
+// pieces and finds, per vertex, where the neighbours above it start
+// (the forward list N+(v): a suffix of the sorted row).
+//
+// The counting kernel gives a block one piece.  |H| is the number of entries
+// v > u of equal parity.  T is summed at the smallest edge of each triangle:
+// a triangle a < b < c has one or three horizontal edges, so every triangle
+// of the graph is one of Alg. 1's (edge, apex) pairs exactly once, and it is
+// found once at its edge (a, b) as an element c of N+(b) that lies in N(a).
+// The lists streamed are N+(v) instead of N(v): 2.3 times fewer elements on
+// G(n, p) graphs (n = 20000, mean degree 36: 4.3 M against 10.2 M for the
+// whole lists of the horizontal edges) and on R-MAT scale 10 to 13.
 #include "tc_internal.h"
 
 namespace tc {
@@ -36,10 +36,9 @@ constexpr uint16_t kUnvisited = 0xFFFF;
 constexpr int kBigDeg = 64;      // frontier vertices above this degree are expanded by a wave
 constexpr int kBigCap = 1024;    // LDS list of such vertices per pass (overflow: expanded by the thread)
 constexpr int kRowLoads = 8;     // row entries a thread loads at once in the level passes
-constexpr int kBitmapWords = TC_BATCH_MAX_N / 32;
-constexpr int kPieceMin = 1024;  // smallest piece size accepted (sizes the piece slots)
-constexpr int kSmallPieceMin = 16;  // the same for the one-graph path of tc_count
-constexpr int kClaim = 2;        // pieces a block of 256 or 512 threads claims at once
+constexpr int kPieceMin = 1024;  // smallest piece size a caller may ask for
+constexpr int kAutoMin = 16;     // smallest and largest piece size chosen by auto_piece
+constexpr int kTile = 512;       // entries of a piece counted together (their streams are kept in LDS)
 
 // Piece slots of graph g start at row_offsets[vbase[g]] / piece + g, parity
 // words at vbase[g] / 32 + g: both leave room for ceil(size / unit) entries.
@@ -161,9 +160,8 @@ __device__ void bfs_levels_lds(uint16_t* L, const int64_t* rows, const int32_t* 
 // root0 >= 0 replaces the default root of graph 0 (the one-graph path of
 // tc_count); batches pass -1.
 __global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* vbase, const int64_t* row_offsets,
-                                                                const int32_t* cols, int piece, int32_t* levels,
-                                                                uint32_t* parity, int4* pieces, int64_t* T,
-                                                                int64_t* H, int32_t root0) {
+                                                                const int32_t* cols, int32_t* levels, uint32_t* parity,
+                                                                int64_t* T, int64_t* H, int32_t root0) {
   __shared__ uint16_t L[TC_BATCH_MAX_N];
   __shared__ int32_t s_big[kBigCap];
   __shared__ int64_t sh[kBfsThreads / kWave + 1];
@@ -173,7 +171,6 @@ __global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* v
   const int64_t v0 = vbase[g];
   const int n = static_cast<int>(vbase[g + 1] - v0);
   const int64_t* rows = row_offsets + v0;  // rows[i] = global position of local row i
-  const int64_t e0 = rows[0];
   // a graph beyond the on-chip level array is skipped and flagged with -1
   // (the host rejects it first when validation is on); it gets no pieces
   const bool too_big = n > TC_BATCH_MAX_N;
@@ -215,7 +212,7 @@ __global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* v
     __syncthreads();
     bfs_levels_lds(L, rows, cols, n, &s_cnt, s_big, &s_nbig, 1);
   }
-  // outputs: parity bits, levels, pieces
+  // outputs: parity bits, levels
   uint32_t* par = parity + parity_base(v0, g);
   const int words = (n + 31) / 32;
   for (int wi = tid; wi < words; wi += nt) {
@@ -228,379 +225,467 @@ __global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* v
   }
   if (levels)
     for (int i = tid; i < n; i += nt) levels[v0 + i] = L[i];
-  const int64_t nnz = rows[n] - e0;
-  const int64_t np = (nnz + piece - 1) / piece;
-  int4* pc = pieces + piece_base(e0, piece, g);
-  for (int64_t p = tid; p < np; p += nt) {
-    // piece p holds the entries [ps, ps + piece): its vertices run from the
-    // one whose row holds entry ps (the last row starting at or before it;
-    // rows[n] > ps, so that row is not empty) up to the last row starting
-    // before ps + piece (ve: the first row starting at or after it, or n)
-    const int64_t ps = e0 + p * piece;
-    const int vb = static_cast<int>(upper_bound_dev(rows, 0, static_cast<int64_t>(n) + 1, ps)) - 1;
-    const int ve = static_cast<int>(lower_bound_dev(rows, 0, static_cast<int64_t>(n), ps + piece));
-    pc[p] = make_int4(g, vb, ve, static_cast<int>(p));
-  }
 }
 
 __device__ __forceinline__ uint32_t par_bit(const uint32_t* p, int32_t i) { return (p[i >> 5] >> (i & 31)) & 1u; }
 
-constexpr int kBChunk = 8;  // consecutive list entries a lane takes at once
-
-__device__ __forceinline__ uint64_t wave_or_u64(uint64_t x) {
-  uint32_t lo = static_cast<uint32_t>(x), hi = static_cast<uint32_t>(x >> 32);
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    lo |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), d, kWave));
-    hi |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), d, kWave));
-  }
-  return (static_cast<uint64_t>(hi) << 32) | lo;
+// Forward list of a vertex, N+(v) = its neighbours above it: first entry
+// (40 bits, absolute) and length (at most TC_BATCH_MAX_N - 1) in 8 bytes.
+struct FwdRec {
+  uint32_t lo, hi_len;  // hi_len = first >> 32 | length << 8
+};
+constexpr int64_t kFwdLenMax = TC_BATCH_MAX_N - 1;  // a simple graph's lists are no longer
+__device__ __forceinline__ FwdRec pack_fwd(int64_t first, int len) {
+  return FwdRec{static_cast<uint32_t>(first),
+                static_cast<uint32_t>(static_cast<uint64_t>(first) >> 32) | (static_cast<uint32_t>(len) << 8)};
 }
 
-// One chunk of up to 64 neighbours v = N(u)[base + lane], kept when base +
-// lane lies in [klo, khi), of vertex u, in one
-// wave: the cover edges (u, v), v > u with u's parity, are compacted into
-// this wave's LDS lists (s_beg / s_v / s_off / s_len) and their lists N(v)
-// streamed in chunks of kBChunk entries per lane, each entry w counted when
-// its bit is set in the wave's bitmap of N(u) and it passes the test of
-// Alg. 1 (parity of w differs from u's, or w > v).  A short row (du <= 64)
-// passes its neighbours in registers (nbr, one per lane).
-__device__ __forceinline__ void count_chunk(int u, int64_t ru, int64_t klo, int64_t khi, int64_t base, bool shortrow,
-                                            int32_t nbr,
-                                            uint32_t pu, const int64_t* rows, const int32_t* cols,
-                                            const uint32_t* s_par, const uint32_t* bm, int64_t* s_beg, int32_t* s_v,
-                                            int32_t* s_off, int32_t* s_len, int64_t& cnt, int64_t& hc) {
-  const int ln = lane();
-  const int64_t k = base + ln;
-  int32_t v = -1;
-  int len = 0;
-  int64_t vb = 0;
-  if (k >= klo && k < khi) {
-    v = shortrow ? nbr : cols[ru + k];
-    if (v > u && par_bit(s_par, v) == pu) {
-      vb = rows[v];
-      len = static_cast<int>(rows[v + 1] - vb);
-      ++hc;
-    }
-  }
-  // N(v) of these edges in chunks of kBChunk consecutive entries; the
-  // non-empty streams are compacted in LDS with their first chunk
-  const int nch = (len + kBChunk - 1) / kBChunk;
-  const uint64_t ne = __ballot(nch > 0);
-  const int incl = wave_incl_scan(nch);
-  const int cst = incl - nch;
-  const int C = __shfl(incl, kWave - 1, kWave);
-  if (nch > 0) {
-    const int r = __popcll(ne & lanemask_lt());
-    s_beg[r] = vb;
-    s_v[r] = v;
-    s_off[r] = cst;
-    s_len[r] = len;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  for (int t0 = 0; t0 < C; t0 += kWave) {
-    // streams whose first chunk lies in [t0, t0 + 64): a 64-bit mask of
-    // those first chunks, and the number of streams begun before t0; lane
-    // i's chunk t0 + i then belongs to stream before + |{starts <= i}| - 1
-    const bool starts_here = nch > 0 && cst >= t0 && cst < t0 + kWave;
-    const uint64_t M = wave_or_u64(starts_here ? (1ull << (cst - t0)) : 0ull);
-    const int before = __popcll(__ballot(nch > 0 && cst < t0));
-    const int c = t0 + ln;
-    if (c < C) {
-      const int j = before + __popcll(M & ((2ull << ln) - 1ull)) - 1;
-      const int kk = c - s_off[j];
-      const int64_t p0 = s_beg[j] + static_cast<int64_t>(kk) * kBChunk;
-      const int rem = s_len[j] - kk * kBChunk;
-      const int32_t vv = s_v[j];
-      int32_t w[kBChunk];
-#pragma unroll
-      for (int q = 0; q < kBChunk; ++q) w[q] = q < rem ? cols[p0 + q] : -1;
-#pragma unroll
-      for (int q = 0; q < kBChunk; ++q)
-        if (w[q] >= 0 && ((bm[w[q] >> 5] >> (w[q] & 31)) & 1u) && (par_bit(s_par, w[q]) != pu || w[q] > vv))
-          ++cnt;
-    }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
+// One launch before the levels: forward records of every vertex (kRec), the
+// piece slots (slot -> graph, first row; graph -1: empty), and for the
+// one-graph path the vertex bases {0, n} and the work statistics.  A wave
+// takes 64 consecutive vertices: one search of the vertex bases finds the
+// first one's graph, the lanes step on from there.
+struct OneGraph {
+  int64_t* vbase;  // written {0, n}; null for a batch
+  int64_t* stats;
+  int64_t n, nnz;
+};
 
-// Vertices with more than kLongDeg neighbours inside the piece are left to
-// a phase at the end of the piece in which every wave of the block takes a
-// share of their 64-neighbour chunks (each wave with its own bitmap of
-// N(u)), so one hub does not keep a single wave busy while the others wait.
-constexpr int kLongDeg = 4 * kWave;
-constexpr int kLongCap = 64;  // deferred vertices per piece (more: counted by the claiming wave)
-
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vbase, const int64_t* row_offsets,
-                                                              const int32_t* cols, const uint32_t* parity,
-                                                              const int4* pieces, int64_t nslots, int piece,
-                                                              int claim_n, unsigned long long* ctr, int64_t* T,
-                                                              int64_t* H) {
-  constexpr int NW = THREADS / kWave;
-  __shared__ uint32_t s_bm[NW][kBitmapWords];
-  __shared__ int32_t s_off[NW][kWave];  // first chunk of each compacted stream
-  __shared__ int32_t s_len[NW][kWave];
-  __shared__ int64_t s_beg[NW][kWave];
-  __shared__ int32_t s_v[NW][kWave];
-  __shared__ int64_t sh[NW + 1];
-  __shared__ int32_t s_long[kLongCap];
-  __shared__ unsigned long long s_claim;
-  __shared__ int s_next, s_nlong;
-  const int tid = threadIdx.x, wv = tid / kWave, ln = lane();
-  uint32_t* bm = s_bm[wv];
-  for (int i = ln; i < kBitmapWords; i += kWave) bm[i] = 0u;
-  // claim_n > 0: persistent blocks claim claim_n slots at a time from the
-  // counter; claim_n = 0: block b takes slot b alone (one block per slot,
-  // no shared counter for a single small graph's many one-wave blocks)
-  if (tid == 0)
-    s_claim = claim_n > 0 ? atomicAdd(ctr, static_cast<unsigned long long>(claim_n))
-                          : static_cast<unsigned long long>(blockIdx.x);
-  __syncthreads();
-  unsigned long long claim = s_claim;
-  while (claim < static_cast<unsigned long long>(nslots)) {
-    unsigned long long next = 0;
-    if (tid == 0)
-      next = claim_n > 0 ? atomicAdd(ctr, static_cast<unsigned long long>(claim_n))
-                         : static_cast<unsigned long long>(nslots);
-    const unsigned long long cend =
-        min(claim + static_cast<unsigned long long>(claim_n > 0 ? claim_n : 1), static_cast<unsigned long long>(nslots));
-    for (unsigned long long sl = claim; sl < cend; ++sl) {
-      const int4 pc = pieces[sl];
-      if (pc.x < 0 || pc.y >= pc.z) continue;  // empty slot (block-uniform)
-      const int g = pc.x;
-      const int64_t v0 = vbase[g];
-      const int64_t* rows = row_offsets + v0;
-      // the graph's parity bits stay in global memory (at most 8 KB, cached):
-      // keeping them out of LDS leaves room for more blocks per CU
-      const uint32_t* s_par = parity + parity_base(v0, g);
-      // the piece's entries [ps, ps + piece): vertex u takes the neighbours
-      // N(u)[k] with ru + k inside them (its whole row sets the bitmap)
-      const int64_t ps = rows[0] + static_cast<int64_t>(pc.w) * piece;
-      if (tid == 0) {
-        s_next = pc.y;
-        s_nlong = 0;
-      }
-      __syncthreads();
-      int64_t cnt = 0, hc = 0;
-      // one vertex ahead: the next vertex's row bounds, and for a row of at
-      // most 64 entries its neighbours, are loaded while the current vertex
-      // is counted; a short row's neighbours stay in registers (one a lane)
-      int u = 0;
-      if (ln == 0) u = atomicAdd(&s_next, 1);
-      u = __shfl(u, 0, kWave);
-      int64_t ru = 0, du = 0;
-      int32_t nbr = -1;
-      if (u < pc.z) {
-        ru = rows[u];
-        du = rows[u + 1] - ru;
-        if (du <= kWave && ln < du) nbr = cols[ru + ln];
-      }
-      while (u < pc.z) {
-        int un = 0;
-        if (ln == 0) un = atomicAdd(&s_next, 1);
-        un = __shfl(un, 0, kWave);
-        int64_t run = 0, dun = 0;
-        if (un < pc.z) {
-          run = rows[un];
-          dun = rows[un + 1] - run;
-        }
-        const int64_t klo = ps > ru ? ps - ru : 0;
-        const int64_t khi = ps + piece - ru < du ? ps + piece - ru : du;
-        int deferred = 0;
-        if (khi - klo > kLongDeg) {
-          if (ln == 0) {
-            const int q = atomicAdd(&s_nlong, 1);
-            if (q < kLongCap) {
-              s_long[q] = u;
-              deferred = 1;
-            }
-          }
-          deferred = __shfl(deferred, 0, kWave);
-        }
-        if (!deferred) {
-          const uint32_t pu = par_bit(s_par, u);
-          const bool shortrow = du <= kWave;
-          if (shortrow) {
-            if (nbr >= 0) atomicOr(&bm[nbr >> 5], 1u << (nbr & 31));
-          } else {
-            for (int64_t k = ln; k < du; k += kWave) {
-              const int32_t w = cols[ru + k];
-              atomicOr(&bm[w >> 5], 1u << (w & 31));
-            }
-          }
-          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-          // a short row's neighbours sit in lanes 0 .. du - 1 (one chunk
-          // from 0); a long row's chunks start at klo
-          for (int64_t base = shortrow ? 0 : klo; base < khi; base += kWave)
-            count_chunk(u, ru, klo, khi, base, shortrow, nbr, pu, rows, cols, s_par, bm, s_beg[wv], s_v[wv],
-                        s_off[wv], s_len[wv], cnt, hc);
-          if (shortrow) {
-            if (nbr >= 0) bm[nbr >> 5] = 0u;
-          } else {
-            for (int64_t k = ln; k < du; k += kWave) bm[cols[ru + k] >> 5] = 0u;
-          }
-          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        }
-        // the next vertex's neighbours (short rows) for the next round
-        int32_t nbn = -1;
-        if (un < pc.z && dun <= kWave && ln < dun) nbn = cols[run + ln];
-        u = un;
-        ru = run;
-        du = dun;
-        nbr = nbn;
-      }
-      // the deferred long rows: every wave sets N(u) in its own bitmap and
-      // takes the chunks wv, wv + NW, ... of N(u)
-      __syncthreads();
-      const int nlong = min(s_nlong, kLongCap);
-      for (int j = 0; j < nlong; ++j) {
-        const int lu = s_long[j];
-        const int64_t lr = rows[lu], ld = rows[lu + 1] - lr;
-        const int64_t klo = ps > lr ? ps - lr : 0;
-        const int64_t khi = ps + piece - lr < ld ? ps + piece - lr : ld;
-        const uint32_t pu = par_bit(s_par, lu);
-        for (int64_t k = ln; k < ld; k += kWave) {
-          const int32_t w = cols[lr + k];
-          atomicOr(&bm[w >> 5], 1u << (w & 31));
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        for (int64_t base = klo + static_cast<int64_t>(wv) * kWave; base < khi;
-             base += static_cast<int64_t>(NW) * kWave)
-          count_chunk(lu, lr, klo, khi, base, false, -1, pu, rows, cols, s_par, bm, s_beg[wv], s_v[wv], s_off[wv],
-                      s_len[wv], cnt, hc);
-        for (int64_t k = ln; k < ld; k += kWave) bm[cols[lr + k] >> 5] = 0u;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      }
-      cnt = block_sum(cnt, sh);
-      hc = block_sum(hc, sh);
-      if (tid == 0) {
-        if (cnt) atomicAdd(reinterpret_cast<unsigned long long*>(&T[g]), static_cast<unsigned long long>(cnt));
-        if (hc && H) atomicAdd(reinterpret_cast<unsigned long long*>(&H[g]), static_cast<unsigned long long>(hc));
-      }
-    }
-    __syncthreads();
-    if (tid == 0) s_claim = next;
-    __syncthreads();
-    claim = s_claim;
-  }
-}
-
-// Clears the claim counters and marks every piece slot empty, in one launch;
-// the one-graph path of tc_count also has its vertex bases {0, n} written
-// here (vbase not null).
-__global__ void batch_prep_kernel(unsigned long long* ctr, int4* pieces, int64_t nslots, int64_t* vbase,
-                                  int64_t one_n) {
+template <bool kRec>
+__global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* row_offsets, const int32_t* cols,
+                                  int64_t total_n, int64_t nslots, int piece, FwdRec* rec, int2* pieces,
+                                  OneGraph one) {
   const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t0 < 4) ctr[t0] = 0ull;
-  if (vbase && t0 == 0) {
-    vbase[0] = 0;
-    vbase[1] = one_n;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const bool single = one.vbase != nullptr;
+  if (single && blockIdx.x == 0) {
+    if (threadIdx.x < 2) one.vbase[threadIdx.x] = threadIdx.x ? one.n : 0;
+    if (threadIdx.x < 24) one.stats[threadIdx.x] = threadIdx.x == 0 ? one.n : (threadIdx.x == 1 ? one.nnz : 0);
   }
-  for (int64_t i = t0; i < nslots; i += (int64_t)gridDim.x * blockDim.x) pieces[i] = make_int4(-1, 0, 0, 0);
+  auto base_of = [&](int g) -> int64_t { return single ? (g ? one.n : 0) : vbase[g]; };
+  if (kRec) {
+    for (int64_t w0 = t0 - lane(); w0 < total_n; w0 += stride) {
+      int g = 0;
+      if (!single) {
+        int lo = 0, hi = G;  // last g with vbase[g] <= w0
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (vbase[mid] <= w0) lo = mid;
+          else hi = mid;
+        }
+        g = lo;
+      }
+      const int64_t v = w0 + lane();
+      if (v >= total_n) continue;
+      while (g + 1 < G && base_of(g + 1) <= v) ++g;
+      const int64_t v0 = base_of(g);
+      if (base_of(g + 1) - v0 > TC_BATCH_MAX_N) continue;  // a skipped graph has no pieces
+      const int64_t b = row_offsets[v], e = row_offsets[v + 1];
+      const int64_t f = upper_bound_dev(cols, b, e, static_cast<int32_t>(v - v0));
+      rec[v] = pack_fwd(f, static_cast<int>(min(e - f, kFwdLenMax)));
+    }
+  }
+  for (int64_t s = t0; s < nslots; s += stride) {
+    int g = 0;
+    if (!single) {
+      int lo = 0, hi = G;  // last g whose first slot is at or before s
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (piece_base(row_offsets[vbase[mid]], piece, mid) <= s) lo = mid;
+        else hi = mid;
+      }
+      g = lo;
+    }
+    const int64_t v0 = base_of(g);
+    const int64_t n = base_of(g + 1) - v0;
+    const int64_t* rows = row_offsets + v0;
+    const int64_t e0 = rows[0];
+    const int64_t p = s - piece_base(e0, piece, g), ps = e0 + p * piece;
+    int2 out = make_int2(-1, 0);
+    // the piece's first row is the last one starting at or before entry ps
+    // (rows[n] > ps, so that row is not empty)
+    if (n > 0 && n <= TC_BATCH_MAX_N && p >= 0 && ps < rows[n])
+      out = make_int2(g, static_cast<int>(upper_bound_dev(rows, 0, n + 1, ps)) - 1);
+    pieces[s] = out;
+  }
+}
+
+constexpr int kBChunk = 8;  // consecutive list entries a lane takes at once
+constexpr int kRowCap = 1024;            // row starts of a tile kept in LDS
+constexpr int kFilterBits = TC_BATCH_MAX_N;
+constexpr int kWinTiles = 64;            // 64-chunk groups whose stream starts are marked at once
+constexpr uint32_t kRowStep = 40503u;    // odd: rows of a tile start at spread places of the filter
+
+// Streams of one tile, in LDS: first chunk, entry position of the list
+// (relative to the graph), length | filter offset of the row << 16, position
+// of the edge in the tile | row << 16.
+struct TileStreams {
+  int32_t first[kTile];
+  uint32_t beg[kTile];
+  uint32_t len_off[kTile];
+  uint32_t at_row[kTile];
+};
+
+// The counting kernel: a block takes one piece (or, where the caller limits
+// the grid, every gridDim.x-th), kTile entries at a time.
+//   1. the tile's row starts go to LDS, each entry finds its row u there;
+//   2. an entry v > u counts towards |H| if the parities agree; its forward
+//      list N+(v) becomes a stream, and v itself is set in the tile's filter:
+//      one bit at (v + offset of u) mod 65536 (the rest of the tile's last
+//      row, beyond the tile, is set as well);
+//   3. all streams are cut into chunks of kBChunk entries, dealt to the lanes
+//      in order; an element w whose bit is set lies in N(u) above v if the
+//      rows' ranges of the filter are disjoint (few rows, or one), else the
+//      hit is looked up in the row.
+// A tile's dependent loads (row starts, entries, forward records, streams)
+// are taken once for 512 edges, where a wave per vertex with a 65536-bit map
+// of its own (8 KB a wave) paid them per vertex: on 4096 graphs of 64 to
+// 65536 vertices (1.08 G entries) that version took 43.1 ms, bound by those
+// latencies at 16 waves per CU; this one takes 21.7 ms, and 0.053 ms in place
+// of 1.74 on 48 graphs of 64 to 8192 vertices, whose 16384-entry pieces
+// filled a quarter of the CUs.
+template <int THREADS, bool kRec>
+__global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vbase, const int64_t* row_offsets,
+                                                              const int32_t* cols, int64_t total_nnz,
+                                                              const uint32_t* parity, const FwdRec* rec,
+                                                              const int2* pieces, int64_t nslots, int piece,
+                                                              int group, int64_t* T, int64_t* H, int64_t* H2) {
+  constexpr int NW = THREADS / kWave;
+  constexpr int kPer = kTile / THREADS;  // entries per thread
+  static_assert(kPer * THREADS == kTile, "whole entries per thread");
+  __shared__ alignas(16) uint32_t s_filt[kFilterBits / 32];
+  __shared__ TileStreams st;
+  __shared__ uint16_t s_col[kTile];
+  __shared__ int32_t s_row[kRowCap];
+  __shared__ uint32_t s_M[kWinTiles][2];
+  __shared__ int32_t s_tb[kWinTiles];
+  __shared__ int64_t sh[NW + 1];
+  __shared__ int s_last;
+  const int tid = threadIdx.x, wv = tid / kWave, ln = lane();
+  for (int64_t bi = blockIdx.x;; bi += gridDim.x) {
+    // group > 0: consecutive blocks go to different XCDs, so `group`
+    // consecutive slots are given to the blocks of one XCD: the pieces of a
+    // graph then share one L2
+    int64_t sl = bi;
+    if (group > 0) {
+      const int64_t r = bi >> 3;
+      sl = (r / group) * (8 * static_cast<int64_t>(group)) + (bi & 7) * group + r % group;
+      if (bi >= ((nslots + 8 * group - 1) / (8 * group)) * (8 * group)) break;
+      if (sl >= nslots) continue;
+    } else if (sl >= nslots) {
+      break;
+    }
+    const int2 pc = pieces[sl];
+    if (pc.x < 0) continue;  // empty slot (block-uniform)
+    const int g = pc.x;
+    const int64_t v0 = vbase[g];
+    const int n = static_cast<int>(vbase[g + 1] - v0);
+    const int64_t* rows = row_offsets + v0;
+    const int64_t e0 = rows[0];
+    const uint32_t* par = parity + parity_base(v0, g);
+    const int64_t ps = e0 + (sl - piece_base(e0, piece, g)) * piece;
+    const int64_t pe = min(ps + piece, rows[n]);
+    int64_t cnt = 0, hc = 0;
+    int vb = pc.y;
+    for (int64_t tb = ps; tb < pe; tb += kTile) {
+      const int tn = static_cast<int>(min(static_cast<int64_t>(kTile), pe - tb));
+      // entries and the filter's clearing are in flight while the row starts arrive
+      int32_t v[kPer];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int e = tid + j * THREADS;
+        v[j] = e < tn ? cols[tb + e] : -1;
+      }
+      __syncthreads();  // the previous tile is done with the LDS
+      for (int i = tid; i < kFilterBits / 128; i += THREADS)
+        reinterpret_cast<uint4*>(s_filt)[i] = make_uint4(0u, 0u, 0u, 0u);
+      const int nrow = min(kRowCap, n - vb + 1);
+      int have = 0;
+      do {
+        const int i = have + tid;
+        if (i < nrow) s_row[i] = static_cast<int32_t>(min(rows[vb + i] - tb, static_cast<int64_t>(1 << 30)));
+        __syncthreads();
+        have = min(have + THREADS, nrow);
+      } while (have < nrow && s_row[have - 1] < tn);
+      const bool staged = have > 0 && s_row[have - 1] >= tn;  // every row of the tile ends inside s_row
+      // row r (relative to vb) starts at tile position start_of(r)
+      auto start_of = [&](int r) -> int32_t {
+        if (r < have) return s_row[r];
+        return static_cast<int32_t>(min(rows[vb + r] - tb, static_cast<int64_t>(1 << 30)));
+      };
+      int ui[kPer];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int e = tid + j * THREADS;
+        ui[j] = 0;
+        if (e >= tn) continue;
+        int lo = 0, hi = staged ? have : n - vb + 1;  // last row with start <= e
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (start_of(mid) <= e) lo = mid;
+          else hi = mid;
+        }
+        ui[j] = lo;
+        s_col[e] = static_cast<uint16_t>(v[j]);
+        if (e == tn - 1) s_last = lo;
+      }
+      __syncthreads();
+      const int last = s_last;
+      // disjoint ranges of the filter per row where they fit: a set bit is then exact
+      const bool exact = static_cast<int64_t>(last + 1) * n <= kFilterBits;
+      const uint32_t step = exact ? static_cast<uint32_t>(n) : kRowStep;
+      uint32_t beg[kPer], len[kPer];
+      int64_t mine = 0;  // chunks | streams << 32
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        len[j] = beg[j] = 0;
+        const int u = vb + ui[j];
+        if (v[j] <= u) continue;  // also the positions past the tile (-1)
+        hc += par_bit(par, v[j]) == par_bit(par, u);
+        if (kRec) {
+          const FwdRec r = rec[v0 + v[j]];
+          const int64_t f = static_cast<int64_t>(r.lo) | (static_cast<int64_t>(r.hi_len & 0xFFu) << 32);
+          beg[j] = static_cast<uint32_t>(f - e0);
+          len[j] = r.hi_len >> 8;
+        } else {
+          const int64_t b = rows[v[j]], e = rows[v[j] + 1];
+          const int64_t f = upper_bound_dev(cols, b, e, v[j]);
+          beg[j] = static_cast<uint32_t>(f - e0);
+          len[j] = static_cast<uint32_t>(min(e - f, kFwdLenMax));
+        }
+        const uint32_t h = (static_cast<uint32_t>(v[j]) + static_cast<uint32_t>(ui[j]) * step) & (kFilterBits - 1);
+        atomicOr(&s_filt[h >> 5], 1u << (h & 31));
+        if (len[j]) mine += static_cast<int64_t>((len[j] + kBChunk - 1) / kBChunk) | (int64_t(1) << 32);
+      }
+      const int32_t tail = start_of(last + 1);  // end of the last row
+      {
+        const uint32_t off = static_cast<uint32_t>(last) * step;
+        for (int k = tn + tid; k < tail; k += THREADS) {
+          const int32_t w = cols[tb + k];
+          if (w <= vb + last) continue;
+          const uint32_t h = (static_cast<uint32_t>(w) + off) & (kFilterBits - 1);
+          atomicOr(&s_filt[h >> 5], 1u << (h & 31));
+        }
+      }
+      int64_t tot;
+      const int64_t pre = block_excl_scan(mine, sh, &tot);
+      const int C = static_cast<int>(tot & 0xFFFFFFFF), nst = static_cast<int>(tot >> 32);
+      {
+        int slot = static_cast<int>(pre >> 32), ch = static_cast<int>(pre & 0xFFFFFFFF);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          if (!len[j]) continue;
+          const uint32_t off = (static_cast<uint32_t>(ui[j]) * step) & (kFilterBits - 1);
+          st.first[slot] = ch;
+          st.beg[slot] = beg[j];
+          st.len_off[slot] = len[j] | (off << 16);
+          st.at_row[slot] = static_cast<uint32_t>(tid + j * THREADS) | (static_cast<uint32_t>(ui[j]) << 16);
+          ++slot;
+          ch += static_cast<int>((len[j] + kBChunk - 1) / kBChunk);
+        }
+      }
+      for (int w0 = 0; w0 < C; w0 += kWinTiles * kWave) {
+        for (int i = tid; i < kWinTiles * 2; i += THREADS) (&s_M[0][0])[i] = 0u;
+        __syncthreads();
+        for (int i = tid; i < nst; i += THREADS) {
+          const int f = st.first[i] - w0;
+          if (f >= 0 && f < kWinTiles * kWave) atomicOr(&s_M[f >> 6][(f >> 5) & 1], 1u << (f & 31));
+        }
+        // streams begun before the window: the first whose first chunk is in or past it
+        __syncthreads();
+        if (wv == 0) {
+          int lo = 0, hi = nst;
+          while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (st.first[mid] < w0) lo = mid + 1;
+            else hi = mid;
+          }
+          const int k = __popc(s_M[ln][0]) + __popc(s_M[ln][1]);
+          s_tb[ln] = lo + wave_incl_scan(k) - k;
+        }
+        __syncthreads();
+        const int tiles = min(kWinTiles, (C - w0 + kWave - 1) / kWave);
+        for (int t = wv; t < tiles; t += NW) {
+          const int c = w0 + t * kWave + ln;
+          if (c >= C) continue;
+          const uint32_t m0 = s_M[t][0], m1 = s_M[t][1];
+          const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(m1, __builtin_amdgcn_mbcnt_lo(m0, 0u)));
+          const int own = static_cast<int>(((ln < 32 ? m0 : m1) >> (ln & 31)) & 1u);
+          const int j = s_tb[t] + below + own - 1;
+          const uint32_t lo_ = st.len_off[j];
+          const int k0 = (c - st.first[j]) * kBChunk;
+          const int rem = static_cast<int>(lo_ & 0xFFFFu) - k0;
+          const uint32_t off = lo_ >> 16;
+          int64_t p0 = e0 + st.beg[j] + k0;
+          uint32_t valid = rem >= kBChunk ? (1u << kBChunk) - 1u : (1u << rem) - 1u;
+          int32_t w[kBChunk];
+          if (total_nnz >= kBChunk) {
+            // the whole chunk is loaded; past the list's end only inside the columns
+            const int64_t over = p0 + kBChunk - total_nnz;
+            if (over > 0) {
+              p0 -= over;
+              valid <<= over;
+            }
+#pragma unroll
+            for (int q = 0; q < kBChunk; ++q) w[q] = cols[p0 + q];
+          } else {
+#pragma unroll
+            for (int q = 0; q < kBChunk; ++q) w[q] = q < rem ? cols[p0 + q] : 0;
+          }
+          uint32_t hits = 0;
+#pragma unroll
+          for (int q = 0; q < kBChunk; ++q) {
+            const uint32_t h = (static_cast<uint32_t>(w[q]) + off) & (kFilterBits - 1);
+            hits |= ((s_filt[h >> 5] >> (h & 31)) & 1u) << q;
+          }
+          hits &= valid;
+          if (exact) {
+            cnt += __popc(hits);
+          } else if (hits) {
+            // the row's entries after v: [a, z) in the tile, then up to `end`
+            const uint32_t ar = st.at_row[j];
+            const int a = static_cast<int>(ar & 0xFFFFu) + 1, r = static_cast<int>(ar >> 16);
+            const int end = start_of(r + 1), z = min(end, tn);
+            while (hits) {
+              const int32_t x = cols[p0 + __ffs(hits) - 1];
+              hits &= hits - 1;
+              int lo = a, hi = z;
+              while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (s_col[mid] < x) lo = mid + 1;
+                else hi = mid;
+              }
+              if (lo < z) cnt += s_col[lo] == x;
+              else if (end > z) {
+                const int64_t q0 = lower_bound_dev(cols, tb + z, tb + end, x);
+                cnt += q0 < tb + end && cols[q0] == x;
+              }
+            }
+          }
+        }
+        __syncthreads();
+      }
+      // the row of the next tile's first entry
+      if (tail > tn) vb += last;
+      else vb += last + 1;
+    }
+    cnt = block_sum(cnt, sh);
+    hc = block_sum(hc, sh);
+    if (tid == 0) {
+      if (cnt) atomicAdd(reinterpret_cast<unsigned long long*>(&T[g]), static_cast<unsigned long long>(cnt));
+      if (hc && H) atomicAdd(reinterpret_cast<unsigned long long*>(&H[g]), static_cast<unsigned long long>(hc));
+      if (hc && H2) atomicAdd(reinterpret_cast<unsigned long long*>(H2), static_cast<unsigned long long>(hc));
+    }
+  }
+}
+
+// Piece size where the caller names none: the entries are spread over about
+// kAutoSlots blocks (eight per CU, what their LDS allows), one wave each for
+// the smallest graphs, until a piece is one whole tile.
+constexpr int64_t kAutoSlots = 2048;
+
+int auto_piece(int64_t total_nnz) {
+  const int64_t share = total_nnz / kAutoSlots;
+  return static_cast<int>(share < kAutoMin ? kAutoMin : (share > kTile ? kTile : share));
 }
 
 struct BatchPlan {
   uint32_t* parity;
-  int4* pieces;
-  unsigned long long* ctr;
-  int64_t nslots_cap;
+  int2* pieces;
+  FwdRec* rec;  // null: the counting kernel finds the forward lists itself
   size_t bytes;
 };
 
-BatchPlan plan_batch(void* base, int64_t total_n, int64_t total_nnz, int32_t G, int piece_min = kPieceMin) {
+BatchPlan plan_batch(void* base, int64_t total_n, int64_t total_nnz, int32_t G, bool with_rec) {
   BatchPlan p;
   Carver c(base);
-  p.ctr = c.take<unsigned long long>(4);
   p.parity = c.take<uint32_t>(total_n / 32 + G + 2);
-  p.nslots_cap = total_nnz / piece_min + G + 2;
-  p.pieces = c.take<int4>(p.nslots_cap);
+  p.pieces = c.take<int2>(total_nnz / auto_piece(total_nnz) + G + 2);
+  p.rec = with_rec ? c.take<FwdRec>(total_n + 1) : nullptr;
   p.bytes = c.used();
   return p;
 }
 
 template <int THREADS>
 int launch_count(const tc_batch* b, const BatchPlan& p, int64_t nslots, int piece, int blocks_per_cu, int64_t* T,
-                 int64_t* H, hipStream_t s) {
-  // persistent blocks, no more than there are piece slots to claim; or,
-  // for one-wave blocks, one block per slot with no shared counter (the
-  // pieces of a single small graph then spread over as many waves as there
-  // are pieces, and no claim waits on thousands of others) while that grid
-  // stays far below 2^32 work-items
-  const int claim_n = THREADS == kWave && nslots <= (int64_t(1) << 24) ? 0 : kClaim;
-  const int64_t full = static_cast<int64_t>(num_cus()) * blocks_per_cu;
-  const int64_t want = claim_n > 0 ? (nslots + claim_n - 1) / claim_n : nslots;
-  const int64_t blocks = claim_n == 0 || want < full ? want : full;
-  batch_count_kernel<THREADS><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
-      b->vbase, b->row_offsets, b->cols, p.parity, p.pieces, nslots, piece, claim_n, p.ctr, T, H);
+                 int64_t* H, int64_t* H2, hipStream_t s) {
+  // slots of one XCD in runs of 256 (about the blocks it holds at once) once
+  // there are many more than the chip holds
+  const int group = nslots >= 16384 ? 256 : 0;
+  int64_t blocks = group ? (nslots + 8 * group - 1) / (8 * group) * (8 * group) : nslots;
+  if (blocks_per_cu > 0) blocks = std::min<int64_t>(blocks, 8 * ((static_cast<int64_t>(num_cus()) * blocks_per_cu + 7) / 8));
+  blocks = std::min<int64_t>(blocks, int64_t(1) << 23);  // far below 2^32 work-items; a multiple of 8
+  if (p.rec)
+    batch_count_kernel<THREADS, true><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
+        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, group, T, H, H2);
+  else
+    batch_count_kernel<THREADS, false><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
+        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, group, T, H, H2);
   TC_HIP(hipGetLastError());
   return TC_OK;
 }
 
-}  // namespace
-
-size_t batch_ws_bytes(int64_t total_n, int64_t total_nnz, int32_t num_graphs, int piece_min) {
-  return plan_batch(nullptr, total_n, total_nnz, num_graphs, piece_min).bytes;
-}
-
-namespace {
-
 // The launches of a batch (tuning checked here, validation done by the
-// caller); one_vbase: the one-graph path's vertex bases, written first.
+// caller); one: the one-graph path's vertex bases and statistics, written
+// first, and H2 (nullable) receives |H| of all graphs.
 int batch_launch(const tc_batch* b, const tc_tuning* t, int64_t* triangles, int64_t* h_count, int32_t* levels,
-                 void* ws, size_t ws_bytes, hipStream_t s, int32_t root0, int piece_min, int64_t* one_vbase) {
+                 void* ws, size_t ws_bytes, hipStream_t s, int32_t root0, bool with_rec, OneGraph one, int64_t* H2) {
   const int G = b->num_graphs;
-  int threads = 256, piece = 16384, bpc = 0;
+  int piece = auto_piece(b->total_nnz), bpc = 0;
+  // one wave per piece while a piece is a handful of edges, else four
+  int threads = piece < 128 ? kWave : 256;
   if (t) {
+    if (t->batch_piece) {
+      piece = t->batch_piece;
+      threads = 256;
+      if (piece < kPieceMin) return fail(TC_ERR_INVALID_ARG, "tc_count_batch: batch_piece must be >= %d", kPieceMin);
+    }
     if (t->batch_block) threads = t->batch_block;
-    if (t->batch_piece) piece = t->batch_piece;
     bpc = t->batch_blocks_per_cu;
   }
   if (threads != kWave && threads != 256 && threads != 512)
     return fail(TC_ERR_INVALID_ARG, "tc_count_batch: batch_block must be 64, 256 or 512 (got %d)", threads);
-  if (piece < piece_min) return fail(TC_ERR_INVALID_ARG, "tc_count_batch: batch_piece must be >= %d", piece_min);
-  // LDS per block: one bitmap per wave of 8 KB, plus staging
-  const int max_bpc = threads == kWave ? 16 : (threads == 256 ? 4 : 2);  // blocks that fit a CU's LDS
-  if (bpc <= 0 || bpc > max_bpc) bpc = max_bpc;
-  BatchPlan p = plan_batch(ws, b->total_vertices, b->total_nnz, G, piece_min);
+  BatchPlan p = plan_batch(ws, b->total_vertices, b->total_nnz, G, with_rec);
   if (ws_bytes < p.bytes) return fail(TC_ERR_WORKSPACE, "tc_count_batch: workspace %zu < %zu", ws_bytes, p.bytes);
   const int64_t nslots = b->total_nnz / piece + G + 2;
   prof_stage("batch_bfs");
-  batch_prep_kernel<<<grid_for(nslots, 256, 8192), 256, 0, s>>>(p.ctr, p.pieces, nslots, one_vbase,
-                                                                 b->total_vertices);
+  const int64_t work = std::max<int64_t>(nslots, with_rec ? b->total_vertices : 0);
+  if (with_rec)
+    batch_prep_kernel<true><<<grid_for(work, 256, 16384), 256, 0, s>>>(b->vbase, G, b->row_offsets, b->cols,
+                                                                       b->total_vertices, nslots, piece, p.rec,
+                                                                       p.pieces, one);
+  else
+    batch_prep_kernel<false><<<grid_for(work, 256, 16384), 256, 0, s>>>(b->vbase, G, b->row_offsets, b->cols,
+                                                                        b->total_vertices, nslots, piece, p.rec,
+                                                                        p.pieces, one);
   TC_HIP(hipGetLastError());
-  batch_bfs_kernel<<<static_cast<unsigned>(G), kBfsThreads, 0, s>>>(b->vbase, b->row_offsets, b->cols, piece, levels,
-                                                                    p.parity, p.pieces, triangles, h_count, root0);
+  batch_bfs_kernel<<<static_cast<unsigned>(G), kBfsThreads, 0, s>>>(b->vbase, b->row_offsets, b->cols, levels,
+                                                                    p.parity, triangles, h_count, root0);
   TC_HIP(hipGetLastError());
   prof_stage("batch_count");
-  if (threads == kWave) TC_TRY(launch_count<kWave>(b, p, nslots, piece, bpc, triangles, h_count, s));
-  else if (threads == 256) TC_TRY(launch_count<256>(b, p, nslots, piece, bpc, triangles, h_count, s));
-  else TC_TRY(launch_count<512>(b, p, nslots, piece, bpc, triangles, h_count, s));
-  return TC_OK;
+  if (threads == kWave) return launch_count<kWave>(b, p, nslots, piece, bpc, triangles, h_count, H2, s);
+  if (threads == 256) return launch_count<256>(b, p, nslots, piece, bpc, triangles, h_count, H2, s);
+  return launch_count<512>(b, p, nslots, piece, bpc, triangles, h_count, H2, s);
 }
 
 }  // namespace
 
+size_t batch_ws_bytes(int64_t total_n, int64_t total_nnz, int32_t num_graphs, bool with_rec) {
+  return plan_batch(nullptr, total_n, total_nnz, num_graphs, with_rec).bytes;
+}
+
 int batch_run(const tc_batch* b, const tc_tuning* t, uint32_t flags, int64_t* triangles, int64_t* h_count,
-              int32_t* levels, void* ws, size_t ws_bytes, hipStream_t s, int32_t root0, int piece_min) {
+              int32_t* levels, void* ws, size_t ws_bytes, hipStream_t s, bool with_rec) {
   if (b->num_graphs == 0) return TC_OK;
   if (flags & TC_VALIDATE) TC_TRY(validate_batch_run(b, ws, s));
-  return batch_launch(b, t, triangles, h_count, levels, ws, ws_bytes, s, root0, piece_min, nullptr);
+  return batch_launch(b, t, triangles, h_count, levels, ws, ws_bytes, s, -1, with_rec, OneGraph{}, nullptr);
 }
 
 namespace {
 
-__global__ void small_stats_kernel(int64_t* stats, int64_t n, int64_t nnz, const int64_t* H) {
-  for (int i = 0; i < 24; ++i) stats[i] = 0;
-  stats[0] = n;
-  stats[1] = nnz;
-  stats[2] = *H;
-}
-
 struct SmallPlan {
   int64_t* stats;  // the tc_stats mirror, first in the workspace like the count plan's
   int64_t* vbase;  // {0, n}
-  int64_t* h;      // |H| when the caller passes no h_count
   char* batch;
   size_t bytes;
 };
@@ -610,9 +695,8 @@ SmallPlan plan_small(void* base, int64_t n, int64_t nnz) {
   Carver c(base);
   p.stats = c.take<int64_t>(24);
   p.vbase = c.take<int64_t>(2);
-  p.h = c.take<int64_t>(1);
   p.batch = c.take<char>(0);
-  p.bytes = c.used() + batch_ws_bytes(n, nnz, 1, kSmallPieceMin);
+  p.bytes = c.used() + batch_ws_bytes(n, nnz, 1, true);
   return p;
 }
 
@@ -628,7 +712,6 @@ int small_count_run(const tc_csr* g, int64_t root, int64_t* triangles, int64_t* 
                     size_t ws_bytes, hipStream_t s) {
   SmallPlan p = plan_small(ws, g->n, g->nnz);
   if (ws_bytes < p.bytes) return fail(TC_ERR_WORKSPACE, "tc_count: workspace %zu < %zu", ws_bytes, p.bytes);
-  int64_t* H = h_count ? h_count : p.h;
   prof_stage("small_count");
   tc_batch b;
   b.num_graphs = 1;
@@ -638,19 +721,9 @@ int small_count_run(const tc_csr* g, int64_t root, int64_t* triangles, int64_t* 
   b.row_offsets = g->row_offsets;
   b.cols = g->cols;
   b.max_graph_vertices = static_cast<int32_t>(g->n);
-  // one-wave counting blocks (sixteen per CU), each taking one piece at a
-  // time, and pieces of one such block's share of the CSR entries (at least
-  // kSmallPieceMin): a graph's vertices of large degree are cut across many
-  // waves instead of keeping one block busy
-  tc_tuning t{};
-  t.batch_block = kWave;
-  const int64_t share = g->nnz / (16 * static_cast<int64_t>(num_cus()));
-  t.batch_piece = static_cast<int32_t>(share < kSmallPieceMin ? kSmallPieceMin : (share > 16384 ? 16384 : share));
-  TC_TRY(batch_launch(&b, &t, triangles, H, levels, p.batch, p.bytes - (p.batch - static_cast<char*>(ws)), s,
-                      static_cast<int32_t>(root), kSmallPieceMin, p.vbase));
-  small_stats_kernel<<<1, 1, 0, s>>>(p.stats, g->n, g->nnz, H);
-  TC_HIP(hipGetLastError());
-  return TC_OK;
+  // |H| of the statistics (tc_stats::h) is summed beside the caller's
+  return batch_launch(&b, nullptr, triangles, h_count, levels, p.batch, p.bytes - (p.batch - static_cast<char*>(ws)), s,
+                      static_cast<int32_t>(root), true, OneGraph{p.vbase, p.stats, g->n, g->nnz}, p.stats + 2);
 }
 
 }  // namespace tc

@@ -1,7 +1,7 @@
 // noalloc.hip -- tc_count_batch_noalloc: tc_count_batch for callers that
 // cannot allocate device memory (code under stream capture, tight serving
-// loops, harnesses that forbid hipMalloc).  The call's scratch (claim
-// counter, parity bits, work-piece slots) lives in a file-scope device
+// loops, harnesses that forbid hipMalloc).  The call's scratch (parity
+// bits, work-piece slots, forward records where they fit) lives in a file-scope device
 // array instead of a caller workspace; the kernels are tc_count_batch's.
 //
 // The array's name is a host-side stand-in in host code: its device
@@ -59,7 +59,10 @@ int tc_count_batch_noalloc(const tc_batch* b, const tc_tuning* tuning, uint32_t 
   if (flags & TC_VALIDATE)
     return tc::fail(TC_ERR_INVALID_ARG,
                     "tc_count_batch_noalloc: TC_VALIDATE is not supported (check the batch with tc_count_batch)");
-  const size_t need = tc::batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs);
+  // a batch takes the forward records where they fit; the rest (parity bits,
+  // piece slots) is at most a bit per vertex and a byte per 64 entries
+  const bool with_rec = tc::batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs, true) <= kScratchBytes;
+  const size_t need = tc::batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs, with_rec);
   if (need > kScratchBytes)
     return tc::fail(TC_ERR_TOO_LARGE,
                     "tc_count_batch_noalloc: the batch needs %zu bytes of scratch, the static array holds %zu",
@@ -67,7 +70,7 @@ int tc_count_batch_noalloc(const tc_batch* b, const tc_tuning* tuning, uint32_t 
   void* ptr = nullptr;
   TC_TRY(scratch_address(&ptr));
   return tc::batch_run(b, tuning, 0, triangles, h_count, levels, ptr, kScratchBytes,
-                       static_cast<hipStream_t>(stream));
+                       static_cast<hipStream_t>(stream), with_rec);
 }
 
 }  // extern "C"

@@ -157,7 +157,7 @@ size_t tc_workspace_bytes(int op, int64_t n, int64_t nnz, int32_t num_graphs) {
       b = a > sm ? a : sm;
       break;
     }
-    case TC_OP_COUNT_BATCH: b = batch_ws_bytes(n, nnz, num_graphs); break;
+    case TC_OP_COUNT_BATCH: b = batch_ws_bytes(n, nnz, num_graphs, true); break;
     case TC_OP_EDGE_BASELINE: b = plan_baseline(nullptr, n, nnz).bytes; break;
     case TC_OP_VALIDATE: b = validate_ws_bytes(n, nnz); break;
     case TC_OP_SELECT_ROOT: b = select_root_ws_bytes(n); break;
@@ -386,11 +386,12 @@ int tc_count_batch(const tc_batch* b, const tc_tuning* tuning, uint32_t flags, i
     return fail(TC_ERR_TOO_LARGE, "tc_count_batch: a graph has more than %d vertices", TC_BATCH_MAX_N);
   if (b->num_graphs > 0 && (!b->vbase || !b->row_offsets || (b->total_nnz > 0 && !b->cols)))
     return fail(TC_ERR_INVALID_ARG, "tc_count_batch: NULL batch array");
-  TC_TRY(check_ws(ws, ws_bytes, batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs), "tc_count_batch"));
+  TC_TRY(check_ws(ws, ws_bytes, batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs, true),
+                  "tc_count_batch"));
   hipStream_t s = static_cast<hipStream_t>(stream);
   CallScope scope(s);
   prof_stage("batch");
-  return batch_run(b, tuning, flags, triangles, h_count, levels, ws, ws_bytes, s);
+  return batch_run(b, tuning, flags, triangles, h_count, levels, ws, ws_bytes, s, true);
 }
 
 const char* tc_status_string(int status) {

@@ -457,7 +457,7 @@ class GpuExecutor:
             # one-wave counting blocks over pieces of 1024 entries: a handful of
             # small graphs then spreads over many waves instead of one block
             # per graph
-            res = B.count_batch(b, BATCH_TUNING, ws=self.ws[slot], stream=s, return_levels=self.levels_hash)
+            res = B.count_batch(b, ws=self.ws[slot], stream=s, return_levels=self.levels_hash)
             T = res.triangles[: len(reqs)].cpu().tolist()
             H = res.h_count[: len(reqs)].cpu().tolist()
             if self.levels_hash:
@@ -471,7 +471,6 @@ class GpuExecutor:
 
 
 SMALL_N = 65536        # the batched kernels' per-graph vertex limit
-BATCH_TUNING = {"batch_block": 64, "batch_piece": 1024}  # coalesced launches of a few graphs
 SMALL_NNZ = 1 << 18    # entries up to which a graph is coalesced into a batch
 
 
