@@ -311,20 +311,15 @@ __global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* ro
 }
 
 constexpr int kBChunk = 8;  // consecutive list entries a lane takes at once
-constexpr int kRowCap = 1024;            // row starts of a tile kept in LDS
+constexpr int kRowCap = 512;             // row starts of a tile kept in LDS
 constexpr int kFilterBits = TC_BATCH_MAX_N;
 constexpr int kWinTiles = 64;            // 64-chunk groups whose stream starts are marked at once
 constexpr uint32_t kRowStep = 40503u;    // odd: rows of a tile start at spread places of the filter
 
-// Streams of one tile, in LDS: first chunk, entry position of the list
-// (relative to the graph), length | filter offset of the row << 16, position
-// of the edge in the tile | row << 16.
-struct TileStreams {
-  int32_t first[kTile];
-  uint32_t beg[kTile];
-  uint32_t len_off[kTile];
-  uint32_t at_row[kTile];
-};
+// Slots of an XCD given to consecutive blocks of that XCD (about the blocks
+// it holds at once), where there are many more slots than the chip holds:
+// without it the 4096 graphs named below take 3 ms more.
+constexpr int kXcds = 8, kXcdRun = 256;
 
 // The counting kernel: a block takes one piece (or, where the caller limits
 // the grid, every gridDim.x-th), kTile entries at a time.
@@ -343,34 +338,40 @@ struct TileStreams {
 // 65536 vertices (1.08 G entries) that version took 43.1 ms, bound by those
 // latencies at 16 waves per CU; this one takes 21.7 ms, and 0.053 ms in place
 // of 1.74 on 48 graphs of 64 to 8192 vertices, whose 16384-entry pieces
-// filled a quarter of the CUs.
+// filled a quarter of the CUs (VALU busy for 56% of the time, at five waves per
+// SIMD; with the entries' rows from marks instead of a search, scans on DPP
+// and seven waves, which their 21 KB of LDS allow, 15.6 ms).
 template <int THREADS, bool kRec>
-__global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vbase, const int64_t* row_offsets,
+__global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count_kernel(const int64_t* vbase, const int64_t* row_offsets,
                                                               const int32_t* cols, int64_t total_nnz,
                                                               const uint32_t* parity, const FwdRec* rec,
                                                               const int2* pieces, int64_t nslots, int piece,
-                                                              int group, int64_t* T, int64_t* H, int64_t* H2) {
+                                                              bool by_xcd, int64_t* T, int64_t* H, int64_t* H2) {
   constexpr int NW = THREADS / kWave;
   constexpr int kPer = kTile / THREADS;  // entries per thread
   static_assert(kPer * THREADS == kTile, "whole entries per thread");
   __shared__ alignas(16) uint32_t s_filt[kFilterBits / 32];
-  __shared__ TileStreams st;
+  // streams of the tile: first chunk, entry position of the list (relative to
+  // the graph), length | filter offset of the row << 16, position of the edge
+  // in the tile | row << 16
+  __shared__ uint4 s_st[kTile];
   __shared__ uint16_t s_col[kTile];
+  __shared__ uint16_t s_own[kTile];  // at a row's first entry in the tile: the row
+  __shared__ alignas(8) uint32_t s_beg[kTile / 32];  // bits of those entries
   __shared__ int32_t s_row[kRowCap];
   __shared__ uint32_t s_M[kWinTiles][2];
   __shared__ int32_t s_tb[kWinTiles];
   __shared__ int64_t sh[NW + 1];
-  __shared__ int s_last;
-  const int tid = threadIdx.x, wv = tid / kWave, ln = lane();
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / kWave), ln = lane();
   for (int64_t bi = blockIdx.x;; bi += gridDim.x) {
-    // group > 0: consecutive blocks go to different XCDs, so `group`
-    // consecutive slots are given to the blocks of one XCD: the pieces of a
-    // graph then share one L2
+    // consecutive blocks go to different XCDs: by_xcd gives the blocks of one
+    // XCD kXcdRun consecutive slots, so the pieces of a graph share one L2
     int64_t sl = bi;
-    if (group > 0) {
-      const int64_t r = bi >> 3;
-      sl = (r / group) * (8 * static_cast<int64_t>(group)) + (bi & 7) * group + r % group;
-      if (bi >= ((nslots + 8 * group - 1) / (8 * group)) * (8 * group)) break;
+    if (by_xcd) {
+      constexpr int64_t kAll = static_cast<int64_t>(kXcds) * kXcdRun;
+      const int64_t r = bi / kXcds;
+      sl = (r / kXcdRun) * kAll + (bi % kXcds) * kXcdRun + r % kXcdRun;
+      if (bi >= (nslots + kAll - 1) / kAll * kAll) break;
       if (sl >= nslots) continue;
     } else if (sl >= nslots) {
       break;
@@ -385,6 +386,8 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
     const uint32_t* par = parity + parity_base(v0, g);
     const int64_t ps = e0 + (sl - piece_base(e0, piece, g)) * piece;
     const int64_t pe = min(ps + piece, rows[n]);
+    // every list ends a whole chunk before the columns do
+    const bool inside = rows[n] + kBChunk <= total_nnz;
     int64_t cnt = 0, hc = 0;
     int vb = pc.y;
     for (int64_t tb = ps; tb < pe; tb += kTile) {
@@ -399,6 +402,7 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
       __syncthreads();  // the previous tile is done with the LDS
       for (int i = tid; i < kFilterBits / 128; i += THREADS)
         reinterpret_cast<uint4*>(s_filt)[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (tid < kTile / 32) s_beg[tid] = 0u;
       const int nrow = min(kRowCap, n - vb + 1);
       int have = 0;
       do {
@@ -413,24 +417,40 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
         if (r < have) return s_row[r];
         return static_cast<int32_t>(min(rows[vb + r] - tb, static_cast<int64_t>(1 << 30)));
       };
+      // rows with entries in the tile mark their first one
+      for (int r = tid; r < (staged ? have - 1 : n - vb); r += THREADS) {
+        const int32_t b = max(start_of(r), 0);
+        if (b >= tn) break;
+        if (start_of(r + 1) > b) {
+          s_own[b] = static_cast<uint16_t>(r);
+          atomicOr(&s_beg[b >> 5], 1u << (b & 31));
+        }
+      }
+      __syncthreads();
+      // an entry's row is that of the last mark at or before it: in its own
+      // 64 entries (one wave's), else in the last group before with a mark
+      const uint64_t marks = ln < kTile / 64 ? reinterpret_cast<const uint64_t*>(s_beg)[ln] : 0ull;
+      const uint64_t some = __ballot(marks != 0ull);
+      auto last_mark = [&](uint64_t groups) {  // of the highest group in the mask (uniform, not empty)
+        const int q = 63 - __clzll(static_cast<long long>(groups));
+        return q * kWave + 63 - __clzll(static_cast<long long>(wave_read(marks, q)));
+      };
       int ui[kPer];
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
-        const int e = tid + j * THREADS;
+        const int e = tid + j * THREADS, q = wv + j * NW;
         ui[j] = 0;
-        if (e >= tn) continue;
-        int lo = 0, hi = staged ? have : n - vb + 1;  // last row with start <= e
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (start_of(mid) <= e) lo = mid;
-          else hi = mid;
+        if (q * kWave >= tn) continue;  // uniform per wave
+        const uint64_t below = some & ((1ull << q) - 1ull);
+        const int before = below ? last_mark(below) : 0;
+        const uint64_t own = wave_read(marks, q) & ((2ull << ln) - 1ull);
+        const int at = own ? q * kWave + 63 - __clzll(static_cast<long long>(own)) : before;
+        if (e < tn) {
+          ui[j] = s_own[at];
+          s_col[e] = static_cast<uint16_t>(v[j]);
         }
-        ui[j] = lo;
-        s_col[e] = static_cast<uint16_t>(v[j]);
-        if (e == tn - 1) s_last = lo;
       }
-      __syncthreads();
-      const int last = s_last;
+      const int last = s_own[last_mark(some)];
       // disjoint ranges of the filter per row where they fit: a set bit is then exact
       const bool exact = static_cast<int64_t>(last + 1) * n <= kFilterBits;
       const uint32_t step = exact ? static_cast<uint32_t>(n) : kRowStep;
@@ -476,10 +496,8 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
         for (int j = 0; j < kPer; ++j) {
           if (!len[j]) continue;
           const uint32_t off = (static_cast<uint32_t>(ui[j]) * step) & (kFilterBits - 1);
-          st.first[slot] = ch;
-          st.beg[slot] = beg[j];
-          st.len_off[slot] = len[j] | (off << 16);
-          st.at_row[slot] = static_cast<uint32_t>(tid + j * THREADS) | (static_cast<uint32_t>(ui[j]) << 16);
+          s_st[slot] = make_uint4(static_cast<uint32_t>(ch), beg[j], len[j] | (off << 16),
+                                  static_cast<uint32_t>(tid + j * THREADS) | (static_cast<uint32_t>(ui[j]) << 16));
           ++slot;
           ch += static_cast<int>((len[j] + kBChunk - 1) / kBChunk);
         }
@@ -488,16 +506,15 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
         for (int i = tid; i < kWinTiles * 2; i += THREADS) (&s_M[0][0])[i] = 0u;
         __syncthreads();
         for (int i = tid; i < nst; i += THREADS) {
-          const int f = st.first[i] - w0;
+          const int f = static_cast<int>(s_st[i].x) - w0;
           if (f >= 0 && f < kWinTiles * kWave) atomicOr(&s_M[f >> 6][(f >> 5) & 1], 1u << (f & 31));
         }
-        // streams begun before the window: the first whose first chunk is in or past it
         __syncthreads();
         if (wv == 0) {
-          int lo = 0, hi = nst;
+          int lo = 0, hi = w0 > 0 ? nst : 0;  // streams begun before the window
           while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (st.first[mid] < w0) lo = mid + 1;
+            if (static_cast<int>(s_st[mid].x) < w0) lo = mid + 1;
             else hi = mid;
           }
           const int k = __popc(s_M[ln][0]) + __popc(s_M[ln][1]);
@@ -512,15 +529,17 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
           const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(m1, __builtin_amdgcn_mbcnt_lo(m0, 0u)));
           const int own = static_cast<int>(((ln < 32 ? m0 : m1) >> (ln & 31)) & 1u);
           const int j = s_tb[t] + below + own - 1;
-          const uint32_t lo_ = st.len_off[j];
-          const int k0 = (c - st.first[j]) * kBChunk;
-          const int rem = static_cast<int>(lo_ & 0xFFFFu) - k0;
-          const uint32_t off = lo_ >> 16;
-          int64_t p0 = e0 + st.beg[j] + k0;
+          const uint4 st = s_st[j];
+          const int k0 = (c - static_cast<int>(st.x)) * kBChunk;
+          const int rem = static_cast<int>(st.z & 0xFFFFu) - k0;
+          const uint32_t off = st.z >> 16;
+          int64_t p0 = e0 + st.y + k0;
           uint32_t valid = rem >= kBChunk ? (1u << kBChunk) - 1u : (1u << rem) - 1u;
           int32_t w[kBChunk];
-          if (total_nnz >= kBChunk) {
-            // the whole chunk is loaded; past the list's end only inside the columns
+          if (inside) {  // the whole chunk is loaded
+#pragma unroll
+            for (int q = 0; q < kBChunk; ++q) w[q] = cols[p0 + q];
+          } else if (total_nnz >= kBChunk) {  // moved back where it would pass the columns' end
             const int64_t over = p0 + kBChunk - total_nnz;
             if (over > 0) {
               p0 -= over;
@@ -533,18 +552,18 @@ __global__ __launch_bounds__(THREADS) void batch_count_kernel(const int64_t* vba
             for (int q = 0; q < kBChunk; ++q) w[q] = q < rem ? cols[p0 + q] : 0;
           }
           uint32_t hits = 0;
+          const uint8_t* bytes = reinterpret_cast<const uint8_t*>(s_filt);
 #pragma unroll
           for (int q = 0; q < kBChunk; ++q) {
             const uint32_t h = (static_cast<uint32_t>(w[q]) + off) & (kFilterBits - 1);
-            hits |= ((s_filt[h >> 5] >> (h & 31)) & 1u) << q;
+            hits |= ((static_cast<uint32_t>(bytes[h >> 3]) >> (h & 7)) & 1u) << q;
           }
           hits &= valid;
           if (exact) {
             cnt += __popc(hits);
           } else if (hits) {
             // the row's entries after v: [a, z) in the tile, then up to `end`
-            const uint32_t ar = st.at_row[j];
-            const int a = static_cast<int>(ar & 0xFFFFu) + 1, r = static_cast<int>(ar >> 16);
+            const int a = static_cast<int>(st.w & 0xFFFFu) + 1, r = static_cast<int>(st.w >> 16);
             const int end = start_of(r + 1), z = min(end, tn);
             while (hits) {
               const int32_t x = cols[p0 + __ffs(hits) - 1];
@@ -609,18 +628,16 @@ BatchPlan plan_batch(void* base, int64_t total_n, int64_t total_nnz, int32_t G, 
 template <int THREADS>
 int launch_count(const tc_batch* b, const BatchPlan& p, int64_t nslots, int piece, int blocks_per_cu, int64_t* T,
                  int64_t* H, int64_t* H2, hipStream_t s) {
-  // slots of one XCD in runs of 256 (about the blocks it holds at once) once
-  // there are many more than the chip holds
-  const int group = nslots >= 16384 ? 256 : 0;
-  int64_t blocks = group ? (nslots + 8 * group - 1) / (8 * group) * (8 * group) : nslots;
+  const bool by_xcd = nslots >= 4 * kXcds * kXcdRun;
+  int64_t blocks = by_xcd ? (nslots + kXcds * kXcdRun - 1) / (kXcds * kXcdRun) * (kXcds * kXcdRun) : nslots;
   if (blocks_per_cu > 0) blocks = std::min<int64_t>(blocks, 8 * ((static_cast<int64_t>(num_cus()) * blocks_per_cu + 7) / 8));
   blocks = std::min<int64_t>(blocks, int64_t(1) << 23);  // far below 2^32 work-items; a multiple of 8
   if (p.rec)
     batch_count_kernel<THREADS, true><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
-        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, group, T, H, H2);
+        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, by_xcd, T, H, H2);
   else
     batch_count_kernel<THREADS, false><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
-        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, group, T, H, H2);
+        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, by_xcd, T, H, H2);
   TC_HIP(hipGetLastError());
   return TC_OK;
 }

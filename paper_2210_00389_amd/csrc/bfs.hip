@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(const int64_t* off, cons
           }
         }
         const int incl = wave_incl_scan(d);
-        const int total = __shfl(incl, kWave - 1, kWave);
+        const int total = wave_read(incl, kWave - 1);
         s_off[wv][lane()] = incl - d;
         s_beg[wv][lane()] = b;
         if (lane() == 0) s_off[wv][kWave] = total;

@@ -567,7 +567,7 @@ __global__ void twolevel_words_kernel(const int32_t* lc, const VMeta* meta, cons
           atomicOr(&wx[carry + incl - 1], 1u << (d & 31));
           if (start) atomicOr(&lx[b >> 5], 1u << (b & 31));
         }
-        carry += __shfl(incl, kWave - 1, kWave);
+        carry += wave_read(incl, kWave - 1);
         prevb = __shfl(b, kWave - 1, kWave);  // a later round exists only if all 64 lanes were members
       }
     }
@@ -1048,7 +1048,7 @@ __device__ __forceinline__ uint32_t chunk_probe(const int32_t (&v)[kChunk], int 
       // stepping all 8 of its slots until the wave's longest walk ends.
       const int np = __popc(pend);
       const int incl = wave_incl_scan(np);
-      const int total = __shfl(incl, kWave - 1, kWave);
+      const int total = wave_read(incl, kWave - 1);
       uint32_t walked = 0;
       for (int base = 0; base < total; base += kWave) {  // uniform across the wave
         int pos = incl - np - base;
@@ -1106,12 +1106,7 @@ __device__ __forceinline__ uint32_t chunk_probe(const int32_t (&v)[kChunk], int 
     // wave takes one range per round and its lanes write consecutive parts
     // of it (called by every lane of the wave).
     const int nh = __popc(hits);
-    int incl = nh;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      const int t = __shfl_up(incl, d, kWave);
-      if (lane() >= d) incl += t;
-    }
+    const int incl = wave_incl_scan(nh);
     int wbase = 0;
     if (lane() == kWave - 1 && incl > 0) wbase = atomicAdd(s_pos, incl);
     wbase = __shfl(wbase, kWave - 1, kWave);

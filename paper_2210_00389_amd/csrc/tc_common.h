@@ -83,57 +83,85 @@ int fork_end(Fork* f, hipStream_t s);    // s waits for the aux streams
 __device__ __forceinline__ int lane() { return static_cast<int>(__lane_id()); }
 __device__ __forceinline__ uint64_t lanemask_lt() { return __lanemask_lt(); }
 
+// Moves a value between lanes with a DPP control (row shifts of 16 lanes,
+// row broadcasts) where a shuffle would go through the LDS unit; a lane
+// without a source, or outside RMASK's rows, keeps `old`.  All 64 lanes take
+// part.
+template <int CTRL, int RMASK, class T>
+__device__ __forceinline__ T dpp_move(T old, T v) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+  if constexpr (sizeof(T) == 4) {
+    return static_cast<T>(__builtin_amdgcn_update_dpp(static_cast<int>(old), static_cast<int>(v), CTRL, RMASK, 0xf, false));
+  } else {
+    const uint64_t o = static_cast<uint64_t>(old), x = static_cast<uint64_t>(v);
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+        static_cast<int>(o), static_cast<int>(x), CTRL, RMASK, 0xf, false));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+        static_cast<int>(o >> 32), static_cast<int>(x >> 32), CTRL, RMASK, 0xf, false));
+    return static_cast<T>((static_cast<uint64_t>(hi) << 32) | lo);
+  }
+}
+
+// The value of one lane (the same in every lane's argument), in all of them.
+template <class T>
+__device__ __forceinline__ T wave_read(T v, int src) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+  if constexpr (sizeof(T) == 4) {
+    return static_cast<T>(__builtin_amdgcn_readlane(static_cast<int>(v), src));
+  } else {
+    const uint64_t x = static_cast<uint64_t>(v);
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), src));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x >> 32), src));
+    return static_cast<T>((static_cast<uint64_t>(hi) << 32) | lo);
+  }
+}
+
+// Inclusive prefix sum across the 64 lanes: shifts by 1, 2, 4 and 8 within
+// rows of 16 lanes, then the last lane of a row added to the next one and
+// that of the lower half to the upper.
+template <class T>
+__device__ __forceinline__ T wave_incl_scan(T v) {
+  v += dpp_move<0x111, 0xf>(T(0), v);
+  v += dpp_move<0x112, 0xf>(T(0), v);
+  v += dpp_move<0x114, 0xf>(T(0), v);
+  v += dpp_move<0x118, 0xf>(T(0), v);
+  v += dpp_move<0x142, 0xa>(T(0), v);
+  v += dpp_move<0x143, 0xc>(T(0), v);
+  return v;
+}
+
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  return wave_read(wave_incl_scan(v), kWave - 1);
 }
 
 template <class T>
 __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, kWave);
-    v = w > v ? w : v;
-  }
-  return v;
-}
-
-// Inclusive prefix sum across the 64 lanes.
-template <class T>
-__device__ __forceinline__ T wave_incl_scan(T v) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    T u = __shfl_up(v, o, kWave);
-    if (lane() >= o) v += u;
-  }
-  return v;
+  const auto up = [](T a, T b) { return b > a ? b : a; };
+  v = up(v, dpp_move<0x111, 0xf>(v, v));
+  v = up(v, dpp_move<0x112, 0xf>(v, v));
+  v = up(v, dpp_move<0x114, 0xf>(v, v));
+  v = up(v, dpp_move<0x118, 0xf>(v, v));
+  v = up(v, dpp_move<0x142, 0xa>(v, v));
+  v = up(v, dpp_move<0x143, 0xc>(v, v));
+  return wave_read(v, kWave - 1);
 }
 
 // Block-wide exclusive scan of one value per thread; `sh` must hold
 // blockDim.x / 64 + 1 elements of T.  Returns the exclusive prefix and writes
-// the block total to *total.  Contains __syncthreads.
+// the block total to *total.  Contains __syncthreads.  Every wave scans the
+// waves' sums for itself (at most 16), so two barriers do.
 template <class T>
 __device__ __forceinline__ T block_excl_scan(T v, T* sh, T* total) {
-  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-  T inc = wave_incl_scan(v);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), nw = blockDim.x / kWave;
+  const T inc = wave_incl_scan(v);
   if (lane() == kWave - 1) sh[w] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T run = 0;
-    for (int i = 0; i < nw; ++i) {
-      T t = sh[i];
-      sh[i] = run;
-      run += t;
-    }
-    sh[nw] = run;
-  }
+  const T sums = wave_incl_scan(lane() < nw ? sh[lane()] : T(0));
+  *total = wave_read(sums, nw - 1);
+  const T before = w > 0 ? wave_read(sums, w - 1) : T(0);
   __syncthreads();
-  T res = inc - v + sh[w];
-  *total = sh[nw];
-  __syncthreads();
-  return res;
+  return inc - v + before;
 }
 
 // Block-wide sum (result valid in every thread).  `sh` holds nw + 1 elements.
@@ -143,13 +171,7 @@ __device__ __forceinline__ T block_sum(T v, T* sh) {
   v = wave_sum(v);
   if (lane() == 0) sh[w] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T run = 0;
-    for (int i = 0; i < nw; ++i) run += sh[i];
-    sh[nw] = run;
-  }
-  __syncthreads();
-  T r = sh[nw];
+  const T r = wave_sum(lane() < nw ? sh[lane()] : T(0));
   __syncthreads();
   return r;
 }
