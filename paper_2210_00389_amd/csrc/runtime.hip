@@ -170,11 +170,16 @@ int fill_i64(int64_t* p, int64_t v, int64_t count, hipStream_t s) {
 }
 
 // --------------------------------------------------------------- scan
-// Reduce-then-scan over tiles of kScanTile values (256 threads x 8 items,
-// each thread owning 8 consecutive values).
+// Up to kOneBlock values: one block.  Beyond: tiles of kScanTile values (256
+// threads x 8 items, each thread owning 8 consecutive values) are summed, and
+// every tile adds the sums of the tiles before it (up to kDirectTiles of
+// them; their scan otherwise) to its own scan.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int64_t kScanTile = kScanThreads * kScanItems;
+constexpr int kOneThreads = 1024;
+constexpr int64_t kOneBlock = kOneThreads * kScanItems;
+constexpr int64_t kDirectTiles = 1024;  // 1024 sums are one 8 KB read per block, cheaper than a launch more
 
 template <class T>
 struct LoadAll {
@@ -197,39 +202,61 @@ struct LoadStrided {
   __device__ __forceinline__ int64_t operator()(int64_t i) const { return static_cast<int64_t>(p[i * stride]); }
 };
 
+// A thread's consecutive values, zero past the end; whole groups are loaded
+// without a test per value.
+template <class F>
+__device__ __forceinline__ int64_t load_items(const F& in, int64_t base, int64_t count, int64_t (&v)[kScanItems]) {
+  if (base + kScanItems <= count) {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) v[i] = in(base + i);
+  } else {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) v[i] = base + i < count ? in(base + i) : 0;
+  }
+  int64_t s = 0;
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) s += v[i];
+  return s;
+}
+
 template <class F>
 __global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(F in, int64_t count, int64_t* partial) {
   __shared__ int64_t sh[kScanThreads / kWave + 1];
-  const int64_t base = blockIdx.x * kScanTile + threadIdx.x * (int64_t)kScanItems;
-  int64_t s = 0;
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < count) s += in(base + i);
-  s = block_sum(s, sh);
+  int64_t v[kScanItems];
+  const int64_t s = block_sum(load_items(in, blockIdx.x * kScanTile + threadIdx.x * (int64_t)kScanItems, count, v), sh);
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// Scans each tile; adds the scanned tile offset (nullable -> 0); writes
-// out[count] = total when this tile holds the last element.
-template <class F>
-__global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(F in, int64_t count, const int64_t* tile_off,
-                                                                   int64_t* out) {
-  __shared__ int64_t sh[kScanThreads / kWave + 1];
-  const int64_t base = blockIdx.x * kScanTile + threadIdx.x * (int64_t)kScanItems;
+// Scans each tile; adds the sum of the tiles before it, from their sums
+// (kSums) or their scan; writes out[count] = total when this tile holds the
+// last element.
+template <int THREADS, bool kSums, class F>
+__global__ __launch_bounds__(THREADS) void scan_apply_kernel(F in, int64_t count, const int64_t* tiles, int64_t* out) {
+  __shared__ int64_t sh[THREADS / kWave + 1];
+  const int64_t base = blockIdx.x * static_cast<int64_t>(THREADS * kScanItems) + threadIdx.x * (int64_t)kScanItems;
   int64_t v[kScanItems];
-  int64_t s = 0;
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    v[i] = (base + i < count) ? in(base + i) : 0;
-    s += v[i];
+  const int64_t s = load_items(in, base, count, v);
+  int64_t before = 0;
+  if (kSums) {
+    for (int64_t i = threadIdx.x; i < blockIdx.x; i += THREADS) before += tiles[i];
+    before = block_sum(before, sh);
+  } else if (tiles) {
+    before = tiles[blockIdx.x];
   }
   int64_t tot;
-  int64_t run = block_excl_scan(s, sh, &tot);
-  if (tile_off) run += tile_off[blockIdx.x];
+  int64_t run = block_excl_scan(s, sh, &tot) + before;
+  if (base + kScanItems <= count) {
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < count) out[base + i] = run;
-    run += v[i];
+    for (int i = 0; i < kScanItems; ++i) {
+      out[base + i] = run;
+      run += v[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      if (base + i < count) out[base + i] = run;
+      run += v[i];
+    }
   }
   if (base < count && base + kScanItems >= count) out[count] = run;
 }
@@ -248,18 +275,23 @@ template <class F>
 static int scan_impl(F in, int64_t* out, int64_t count, Carver& ws, hipStream_t s) {
   if (count <= 0) return fill_i64(out, 0, 1, s);
   const int64_t tiles = (count + kScanTile - 1) / kScanTile;
-  if (tiles == 1) {
-    scan_apply_kernel<F><<<1, kScanThreads, 0, s>>>(in, count, nullptr, out);
+  if (count <= kOneBlock) {
+    scan_apply_kernel<kOneThreads, false, F><<<1, kOneThreads, 0, s>>>(in, count, nullptr, out);
     TC_HIP(hipGetLastError());
     return TC_OK;
   }
   int64_t* partial = ws.take<int64_t>(tiles + 1);
   scan_reduce_kernel<F><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, count, partial);
   TC_HIP(hipGetLastError());
+  if (tiles <= kDirectTiles) {
+    scan_apply_kernel<kScanThreads, true, F><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, count, partial, out);
+    TC_HIP(hipGetLastError());
+    return TC_OK;
+  }
   // the tile sums are scanned into a fresh buffer (recursively)
   int64_t* partial_scan = ws.take<int64_t>(tiles + 1);
   TC_TRY(scan_impl(LoadAll<int64_t>{partial}, partial_scan, tiles, ws, s));
-  scan_apply_kernel<F><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, count, partial_scan, out);
+  scan_apply_kernel<kScanThreads, false, F><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, count, partial_scan, out);
   TC_HIP(hipGetLastError());
   return TC_OK;
 }
