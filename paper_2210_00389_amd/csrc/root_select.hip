@@ -113,7 +113,8 @@ int select_root_run(const tc_csr* g, int num, int64_t* root_out, int64_t* cand_o
   for (int i = 0; i < num; ++i) cand[i] = static_cast<int64_t>(0xFFFFFFFFull - (keys[i] & 0xFFFFFFFFull));
   const unsigned gh = static_cast<unsigned>(num_cus() * 4);
   for (int i = 0; i < num; ++i) {
-    TC_TRY(bfs_run(g, cand[i], w.L, nullptr, w.bfs, s));
+    BfsInfo info;
+    TC_TRY(bfs_run(g, cand[i], w.L, w.bfs, s, &info));
     hsize_kernel<<<gh, kThreads, 0, s>>>(g->row_offsets, g->cols, n, w.L, w.h + i);
     TC_HIP(hipGetLastError());
   }

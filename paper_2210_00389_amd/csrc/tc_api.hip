@@ -198,7 +198,10 @@ int tc_bfs_levels(const tc_csr* g, int64_t root, uint32_t flags, int32_t* levels
   Carver c(ws);
   BfsWs w = bfs_reserve(c, g->n);
   prof_stage("bfs");
-  return bfs_run(g, root, levels, num_levels, w, s);
+  BfsInfo info;
+  TC_TRY(bfs_run(g, root, levels, w, s, &info));
+  if (num_levels) *num_levels = info.num_levels;
+  return TC_OK;
 }
 
 int tc_cover_edges(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t* h_v, int64_t* h_count, void* ws,
@@ -228,9 +231,10 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   TC_TRY(maybe_validate(g, flags, ws, s));
   CountPlan p = plan_count(ws, g->n, g->nnz);
   int32_t* L = levels ? levels : p.L;
-  int32_t nl = 0, d0 = 0;
   prof_stage("bfs");
-  TC_TRY(bfs_run(g, root, L, &nl, p.bfs, s, &d0));
+  BfsInfo info;
+  TC_TRY(bfs_run(g, root, L, p.bfs, s, &info));
+  const int32_t nl = info.num_levels, d0 = info.first_levels;
   tc_csr rg = *g;  // the relabelled graph
   if (g->n > 0) {
     prof_stage("relabel");

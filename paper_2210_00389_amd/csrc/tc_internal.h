@@ -14,18 +14,22 @@ void prof_enable(int on);
 struct BfsWs {
   uint32_t* vis;     // visited bitmap [n/32 + 1]
   uint32_t* bms;     // three rotating frontier bitmaps
-  int32_t* big;      // long frontier rows of the current level
+  int32_t* big;      // long frontier rows of two levels
   int32_t* parent;   // union-find over the unreached vertices
-  int64_t* part;     // per-block (count, entries) of the last step
+  int32_t* list;     // the unreached vertices, when they are few
+  unsigned long long* keys;  // per block: largest (degree, id) key, sum of squared degrees
   char* st;          // device state of the running BFS
-  unsigned long long* key;
-  int64_t* root;
+  char* host;        // what the host reads of it
   uint32_t* comp0;  // optional (caller-owned, n/32+1 words): r0's component
 };
 BfsWs bfs_reserve(Carver& c, int64_t n);
-// *first_levels (nullable) receives the level count of the BFS from r0.
-int bfs_run(const tc_csr* g, int64_t root, int32_t* L, int32_t* num_levels, BfsWs& w,
-            hipStream_t s, int32_t* first_levels = nullptr);
+struct BfsInfo {
+  int32_t num_levels = 0;    // the largest level count of any one BFS
+  int32_t first_levels = 0;  // of the BFS from r0
+  int64_t maxdeg = 0;        // largest degree
+  uint64_t deg2 = 0;         // sum of squared degrees
+};
+int bfs_run(const tc_csr* g, int64_t root, int32_t* L, BfsWs& w, hipStream_t s, BfsInfo* info);
 
 // Root choice by |H| over the vertices of largest degree (root_select.hip).
 constexpr int kMaxRootCandidates = 64;
