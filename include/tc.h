@@ -243,7 +243,10 @@ int tc_cover_edges(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t
  * Synchronises `stream` during the BFS as tc_bfs_levels does; the rest
  * (relabelling, layout, count) is asynchronous.  Graphs within the
  * small-graph bounds (TC_SMALL_MAX_N vertices, TC_SMALL_MAX_NNZ entries)
- * take the path of tc_count_tuned, which never synchronises.  A graph in
+ * take the path of tc_count_tuned, which never synchronises.  A larger graph
+ * whose degrees are even enough (sum of squared degrees at most about 288
+ * per entry) is counted on the caller's CSR by the kernels of tc_count_batch
+ * after its BFS, without the relabelling.  A graph in
  * which a vertex could reach degree 2^29 (n - 1 and nnz / 2 both at least
  * 2^29) gives TC_ERR_TOO_LARGE: the count keeps list lengths below 2^29
  * (tc_list_triangles and tc_count_edge_baseline share the limit). */
@@ -256,7 +259,10 @@ int tc_count(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles,
  * LDS and counted by the kernels of tc_count_batch, with no host
  * synchronisation; T, |H| and the levels are the same on either path
  * (TC_PER_VERTEX always takes the general path).  After the small-graph
- * path tc_read_stats reports n, nnz and |H| only. */
+ * path tc_read_stats reports n, nnz and |H| only; after a count without
+ * relabelling (see tc_count) n, nnz, |H| and the level count.  A call that
+ * sets a knob of the intersection stage, or small_max_n = -1, takes the
+ * relabelled path. */
 int tc_count_tuned(const tc_csr* g, int64_t root, uint32_t flags, const tc_tuning* tuning,
                    int64_t* triangles, int64_t* h_count, int32_t* levels, int64_t* per_vertex,
                    void* ws, size_t ws_bytes, tc_stream_t stream);

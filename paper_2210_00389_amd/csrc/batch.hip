@@ -240,15 +240,21 @@ __device__ __forceinline__ FwdRec pack_fwd(int64_t first, int len) {
                 static_cast<uint32_t>(static_cast<uint64_t>(first) >> 32) | (static_cast<uint32_t>(len) << 8)};
 }
 
-// One launch before the levels: forward records of every vertex (kRec), the
-// piece slots (slot -> graph, first row; graph -1: empty), and for the
-// one-graph path the vertex bases {0, n} and the work statistics.  A wave
-// takes 64 consecutive vertices: one search of the vertex bases finds the
-// first one's graph, the lanes step on from there.
+// One launch before the counting kernel: forward records of every vertex
+// (kRec), the piece slots (slot -> graph, first row; graph -1: empty), and
+// where one graph is counted alone its vertex bases {0, n}, the work
+// statistics and, if its levels are given, the outputs' zeros and the parity
+// bits.  A wave takes 64 consecutive vertices: one search of the vertex bases
+// finds the first one's graph, the lanes step on from there.
 struct OneGraph {
-  int64_t* vbase;  // written {0, n}; null for a batch
+  int64_t* vbase;     // written {0, n}; null for a batch
   int64_t* stats;
   int64_t n, nnz;
+  const int32_t* L;   // levels already known (null: batch_bfs_kernel writes parity, T and H)
+  int64_t num_levels;
+  uint32_t* parity;
+  int64_t* T;
+  int64_t* H;         // nullable
 };
 
 template <bool kRec>
@@ -260,8 +266,14 @@ __global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* ro
   const bool single = one.vbase != nullptr;
   if (single && blockIdx.x == 0) {
     if (threadIdx.x < 2) one.vbase[threadIdx.x] = threadIdx.x ? one.n : 0;
-    if (threadIdx.x < 24) one.stats[threadIdx.x] = threadIdx.x == 0 ? one.n : (threadIdx.x == 1 ? one.nnz : 0);
+    if (threadIdx.x < 24)
+      one.stats[threadIdx.x] = threadIdx.x == 0 ? one.n : (threadIdx.x == 1 ? one.nnz : (threadIdx.x == 3 ? one.num_levels : 0));
+    if (one.L && threadIdx.x == 0) {
+      *one.T = 0;
+      if (one.H) *one.H = 0;
+    }
   }
+  const int64_t max_n = one.L ? INT64_MAX : TC_BATCH_MAX_N;
   auto base_of = [&](int g) -> int64_t { return single ? (g ? one.n : 0) : vbase[g]; };
   if (kRec) {
     for (int64_t w0 = t0 - lane(); w0 < total_n; w0 += stride) {
@@ -276,10 +288,14 @@ __global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* ro
         g = lo;
       }
       const int64_t v = w0 + lane();
+      if (one.L) {
+        const uint64_t odd = __ballot(v < total_n && (one.L[v] & 1));
+        if ((lane() & 31) == 0 && v < total_n) one.parity[v >> 5] = static_cast<uint32_t>(odd >> lane());
+      }
       if (v >= total_n) continue;
       while (g + 1 < G && base_of(g + 1) <= v) ++g;
       const int64_t v0 = base_of(g);
-      if (base_of(g + 1) - v0 > TC_BATCH_MAX_N) continue;  // a skipped graph has no pieces
+      if (base_of(g + 1) - v0 > max_n) continue;  // a skipped graph has no pieces
       const int64_t b = row_offsets[v], e = row_offsets[v + 1];
       const int64_t f = upper_bound_dev(cols, b, e, static_cast<int32_t>(v - v0));
       rec[v] = pack_fwd(f, static_cast<int>(min(e - f, kFwdLenMax)));
@@ -304,7 +320,7 @@ __global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* ro
     int2 out = make_int2(-1, 0);
     // the piece's first row is the last one starting at or before entry ps
     // (rows[n] > ps, so that row is not empty)
-    if (n > 0 && n <= TC_BATCH_MAX_N && p >= 0 && ps < rows[n])
+    if (n > 0 && n <= max_n && p >= 0 && ps < rows[n])
       out = make_int2(g, static_cast<int>(upper_bound_dev(rows, 0, n + 1, ps)) - 1);
     pieces[s] = out;
   }
@@ -341,8 +357,10 @@ constexpr int kXcds = 8, kXcdRun = 256;
 // filled a quarter of the CUs (VALU busy for 56% of the time, at five waves per
 // SIMD; with the entries' rows from marks instead of a search, scans on DPP
 // and seven waves, which their 21 KB of LDS allow, 15.6 ms).
-template <int THREADS, bool kRec>
-__global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count_kernel(const int64_t* vbase, const int64_t* row_offsets,
+// kWide: one graph of any number of vertices (ids of 32 bits in LDS; a bit of
+// the filter then also stands for the ids 65536 apart).
+template <int THREADS, bool kRec, bool kWide>
+__global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) void batch_count_kernel(const int64_t* vbase, const int64_t* row_offsets,
                                                               const int32_t* cols, int64_t total_nnz,
                                                               const uint32_t* parity, const FwdRec* rec,
                                                               const int2* pieces, int64_t nslots, int piece,
@@ -353,10 +371,11 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
   __shared__ alignas(16) uint32_t s_filt[kFilterBits / 32];
   // streams of the tile: first chunk, entry position of the list (relative to
   // the graph), length | filter offset of the row << 16, position of the edge
-  // in the tile | row << 16
+  // in the tile
+  using Id = typename std::conditional<kWide, int32_t, uint16_t>::type;
   __shared__ uint4 s_st[kTile];
-  __shared__ uint16_t s_col[kTile];
-  __shared__ uint16_t s_own[kTile];  // at a row's first entry in the tile: the row
+  __shared__ Id s_col[kTile];
+  __shared__ Id s_own[kTile];  // at a row's first entry in the tile: the row
   __shared__ alignas(8) uint32_t s_beg[kTile / 32];  // bits of those entries
   __shared__ int32_t s_row[kRowCap];
   __shared__ uint32_t s_M[kWinTiles][2];
@@ -403,7 +422,7 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
       for (int i = tid; i < kFilterBits / 128; i += THREADS)
         reinterpret_cast<uint4*>(s_filt)[i] = make_uint4(0u, 0u, 0u, 0u);
       if (tid < kTile / 32) s_beg[tid] = 0u;
-      const int nrow = min(kRowCap, n - vb + 1);
+      const int nrow = static_cast<int>(min(static_cast<int64_t>(kRowCap), static_cast<int64_t>(n) - vb + 1));
       int have = 0;
       do {
         const int i = have + tid;
@@ -422,46 +441,49 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
         const int32_t b = max(start_of(r), 0);
         if (b >= tn) break;
         if (start_of(r + 1) > b) {
-          s_own[b] = static_cast<uint16_t>(r);
+          s_own[b] = static_cast<Id>(r);
           atomicOr(&s_beg[b >> 5], 1u << (b & 31));
         }
       }
       __syncthreads();
       // an entry's row is that of the last mark at or before it: in its own
-      // 64 entries (one wave's), else in the last group before with a mark
+      // 64 entries (one wave's), else in the last group before with a mark;
+      // the mark's rank places the row in the filter
       const uint64_t marks = ln < kTile / 64 ? reinterpret_cast<const uint64_t*>(s_beg)[ln] : 0ull;
       const uint64_t some = __ballot(marks != 0ull);
       auto last_mark = [&](uint64_t groups) {  // of the highest group in the mask (uniform, not empty)
         const int q = 63 - __clzll(static_cast<long long>(groups));
         return q * kWave + 63 - __clzll(static_cast<long long>(wave_read(marks, q)));
       };
-      int ui[kPer];
+      const int upto = wave_incl_scan(__popcll(marks));
+      const int nrows = wave_read(upto, kTile / kWave - 1);
+      int u[kPer], rk[kPer];
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         const int e = tid + j * THREADS, q = wv + j * NW;
-        ui[j] = 0;
+        u[j] = rk[j] = 0;
         if (q * kWave >= tn) continue;  // uniform per wave
         const uint64_t below = some & ((1ull << q) - 1ull);
         const int before = below ? last_mark(below) : 0;
         const uint64_t own = wave_read(marks, q) & ((2ull << ln) - 1ull);
         const int at = own ? q * kWave + 63 - __clzll(static_cast<long long>(own)) : before;
+        rk[j] = (q > 0 ? wave_read(upto, q - 1) : 0) + __popcll(own) - 1;
         if (e < tn) {
-          ui[j] = s_own[at];
-          s_col[e] = static_cast<uint16_t>(v[j]);
+          u[j] = vb + static_cast<int>(s_own[at]);
+          s_col[e] = static_cast<Id>(v[j]);
         }
       }
       const int last = s_own[last_mark(some)];
       // disjoint ranges of the filter per row where they fit: a set bit is then exact
-      const bool exact = static_cast<int64_t>(last + 1) * n <= kFilterBits;
+      const bool exact = static_cast<int64_t>(nrows) * n <= kFilterBits;
       const uint32_t step = exact ? static_cast<uint32_t>(n) : kRowStep;
       uint32_t beg[kPer], len[kPer];
       int64_t mine = 0;  // chunks | streams << 32
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         len[j] = beg[j] = 0;
-        const int u = vb + ui[j];
-        if (v[j] <= u) continue;  // also the positions past the tile (-1)
-        hc += par_bit(par, v[j]) == par_bit(par, u);
+        if (v[j] <= u[j]) continue;  // also the positions past the tile (-1)
+        hc += par_bit(par, v[j]) == par_bit(par, u[j]);
         if (kRec) {
           const FwdRec r = rec[v0 + v[j]];
           const int64_t f = static_cast<int64_t>(r.lo) | (static_cast<int64_t>(r.hi_len & 0xFFu) << 32);
@@ -473,13 +495,13 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
           beg[j] = static_cast<uint32_t>(f - e0);
           len[j] = static_cast<uint32_t>(min(e - f, kFwdLenMax));
         }
-        const uint32_t h = (static_cast<uint32_t>(v[j]) + static_cast<uint32_t>(ui[j]) * step) & (kFilterBits - 1);
+        const uint32_t h = (static_cast<uint32_t>(v[j]) + static_cast<uint32_t>(rk[j]) * step) & (kFilterBits - 1);
         atomicOr(&s_filt[h >> 5], 1u << (h & 31));
         if (len[j]) mine += static_cast<int64_t>((len[j] + kBChunk - 1) / kBChunk) | (int64_t(1) << 32);
       }
       const int32_t tail = start_of(last + 1);  // end of the last row
       {
-        const uint32_t off = static_cast<uint32_t>(last) * step;
+        const uint32_t off = static_cast<uint32_t>(nrows - 1) * step;
         for (int k = tn + tid; k < tail; k += THREADS) {
           const int32_t w = cols[tb + k];
           if (w <= vb + last) continue;
@@ -495,9 +517,9 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           if (!len[j]) continue;
-          const uint32_t off = (static_cast<uint32_t>(ui[j]) * step) & (kFilterBits - 1);
+          const uint32_t off = (static_cast<uint32_t>(rk[j]) * step) & (kFilterBits - 1);
           s_st[slot] = make_uint4(static_cast<uint32_t>(ch), beg[j], len[j] | (off << 16),
-                                  static_cast<uint32_t>(tid + j * THREADS) | (static_cast<uint32_t>(ui[j]) << 16));
+                                  static_cast<uint32_t>(tid + j * THREADS));
           ++slot;
           ch += static_cast<int>((len[j] + kBChunk - 1) / kBChunk);
         }
@@ -562,9 +584,17 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
           if (exact) {
             cnt += __popc(hits);
           } else if (hits) {
-            // the row's entries after v: [a, z) in the tile, then up to `end`
-            const int a = static_cast<int>(st.w & 0xFFFFu) + 1, r = static_cast<int>(st.w >> 16);
-            const int end = start_of(r + 1), z = min(end, tn);
+            // the row's entries after v: from a to the next mark, or to the
+            // tile's end and on to the last row's
+            const int a = static_cast<int>(st.w) + 1;
+            int z = tn;
+            for (int q = a >> 5; q < kTile / 32; ++q) {
+              const uint32_t m = s_beg[q] & (q == (a >> 5) ? ~0u << (a & 31) : ~0u);
+              if (m) {
+                z = q * 32 + __ffs(m) - 1;
+                break;
+              }
+            }
             while (hits) {
               const int32_t x = cols[p0 + __ffs(hits) - 1];
               hits &= hits - 1;
@@ -575,9 +605,9 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : 7) void batch_count
                 else hi = mid;
               }
               if (lo < z) cnt += s_col[lo] == x;
-              else if (end > z) {
-                const int64_t q0 = lower_bound_dev(cols, tb + z, tb + end, x);
-                cnt += q0 < tb + end && cols[q0] == x;
+              else if (z == tn && tail > tn) {
+                const int64_t q0 = lower_bound_dev(cols, tb + tn, tb + tail, x);
+                cnt += q0 < tb + tail && cols[q0] == x;
               }
             }
           }
@@ -627,16 +657,19 @@ BatchPlan plan_batch(void* base, int64_t total_n, int64_t total_nnz, int32_t G, 
 
 template <int THREADS>
 int launch_count(const tc_batch* b, const BatchPlan& p, int64_t nslots, int piece, int blocks_per_cu, int64_t* T,
-                 int64_t* H, int64_t* H2, hipStream_t s) {
+                 int64_t* H, int64_t* H2, hipStream_t s, bool wide = false) {
   const bool by_xcd = nslots >= 4 * kXcds * kXcdRun;
   int64_t blocks = by_xcd ? (nslots + kXcds * kXcdRun - 1) / (kXcds * kXcdRun) * (kXcds * kXcdRun) : nslots;
   if (blocks_per_cu > 0) blocks = std::min<int64_t>(blocks, 8 * ((static_cast<int64_t>(num_cus()) * blocks_per_cu + 7) / 8));
   blocks = std::min<int64_t>(blocks, int64_t(1) << 23);  // far below 2^32 work-items; a multiple of 8
-  if (p.rec)
-    batch_count_kernel<THREADS, true><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
+  if (wide)
+    batch_count_kernel<THREADS, true, true><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
+        b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, by_xcd, T, H, H2);
+  else if (p.rec)
+    batch_count_kernel<THREADS, true, false><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
         b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, by_xcd, T, H, H2);
   else
-    batch_count_kernel<THREADS, false><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
+    batch_count_kernel<THREADS, false, false><<<static_cast<unsigned>(blocks), THREADS, 0, s>>>(
         b->vbase, b->row_offsets, b->cols, b->total_nnz, p.parity, p.rec, p.pieces, nslots, piece, by_xcd, T, H, H2);
   TC_HIP(hipGetLastError());
   return TC_OK;
@@ -741,6 +774,67 @@ int small_count_run(const tc_csr* g, int64_t root, int64_t* triangles, int64_t* 
   // |H| of the statistics (tc_stats::h) is summed beside the caller's
   return batch_launch(&b, nullptr, triangles, h_count, levels, p.batch, p.bytes - (p.batch - static_cast<char*>(ws)), s,
                       static_cast<int32_t>(root), true, OneGraph{p.vbase, p.stats, g->n, g->nnz}, p.stats + 2);
+}
+
+// ------------------------------------------------ one graph, levels known
+namespace {
+
+struct DirectPlan {
+  int64_t* vbase;
+  BatchPlan batch;
+  size_t bytes;
+};
+
+DirectPlan plan_direct(void* base, int64_t n, int64_t nnz) {
+  DirectPlan p;
+  Carver c(base);
+  p.vbase = c.take<int64_t>(2);
+  char* at = c.take<char>(0);
+  p.batch = plan_batch(at, n, nnz, 1, true);
+  p.bytes = c.used() + p.batch.bytes;
+  return p;
+}
+
+}  // namespace
+
+size_t direct_ws_bytes(int64_t n, int64_t nnz) { return plan_direct(nullptr, n, nnz).bytes; }
+
+// The streams are sum over v of d+(v) (d(v) - d+(v)) elements, about a sixth
+// of the squared degrees whatever the graph (within 10% on G(n, p), Chung-Lu
+// and R-MAT graphs).  The relabelled path streams fewer on graphs with hubs
+// but has its layout, plan and resolution to pay.  Measured, both ways, ms
+// (relabelled / direct): G(300007, d 24) 0.91 / 0.36, G(2000003, d 40) 12.5 /
+// 3.1; Chung-Lu n = 300007 mean degree 20 (48 elements an entry) 0.96 / 0.79,
+// degree 40 (73) 1.38 / 1.73; n = 2000003 degree 12 (74) 2.75 / 2.78; R-MAT
+// scale 14 (61) 0.49 / 0.23, 15 (84) 0.57 / 0.67, 16 (114) 0.60 / 0.92, 17
+// with edge factor 6 (75) 0.59 / 0.70.  The line lies at 48 elements an entry
+// and 2^24 more, which is what the launches alone are worth.
+bool direct_fits(int64_t n, int64_t nnz, const BfsInfo& info) {
+  // list lengths of 16 bits and positions of 32 in the streams
+  if (n >= INT32_MAX || nnz >= (int64_t(1) << 31) || info.maxdeg > kFwdLenMax) return false;
+  return info.deg2 / 6 <= 48ull * static_cast<uint64_t>(nnz) + (1ull << 24);
+}
+
+int direct_count_run(const tc_csr* g, const int32_t* L, const BfsInfo& info, int64_t* stats, int64_t* triangles,
+                     int64_t* h_count, void* ws, hipStream_t s) {
+  DirectPlan p = plan_direct(ws, g->n, g->nnz);
+  tc_batch b;
+  b.num_graphs = 1;
+  b.total_vertices = g->n;
+  b.total_nnz = g->nnz;
+  b.vbase = p.vbase;
+  b.row_offsets = g->row_offsets;
+  b.cols = g->cols;
+  b.max_graph_vertices = 0;
+  const int piece = auto_piece(g->nnz);
+  const int64_t nslots = g->nnz / piece + 1 + 2;
+  prof_stage("direct_prep");
+  batch_prep_kernel<true><<<grid_for(std::max(nslots, g->n), 256, 16384), 256, 0, s>>>(
+      p.vbase, 1, g->row_offsets, g->cols, g->n, nslots, piece, p.batch.rec, p.batch.pieces,
+      OneGraph{p.vbase, stats, g->n, g->nnz, L, info.num_levels, p.batch.parity, triangles, h_count});
+  TC_HIP(hipGetLastError());
+  prof_stage("direct_count");
+  return launch_count<256>(&b, p.batch, nslots, piece, 0, triangles, h_count, stats + 2, s, true);
 }
 
 }  // namespace tc

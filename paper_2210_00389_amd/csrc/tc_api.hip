@@ -73,7 +73,7 @@ CountPlan plan_count(void* base, int64_t n, int64_t nnz) {
   p.count = count_reserve(b, n, nnz);
   p.count.stats = p.stats;
   p.pv_new = b.take<int64_t>(n + 1);
-  p.bytes = head + (a.used() > b.used() ? a.used() : b.used());
+  p.bytes = head + std::max(std::max(a.used(), b.used()), direct_ws_bytes(n, nnz));
   return p;
 }
 
@@ -225,7 +225,7 @@ namespace {
 // BFS, relabel and layout, then the count or (list) triangle finding into
 // tri[3 * cap].
 int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles, int64_t* h_count, int32_t* levels,
-               int64_t* per_vertex, bool list, int32_t* tri, int64_t cap, void* ws, hipStream_t s,
+               int64_t* per_vertex, bool list, int32_t* tri, int64_t cap, bool direct, void* ws, hipStream_t s,
                const CountParams& prm) {
   const bool pv = flags & TC_PER_VERTEX;
   TC_TRY(maybe_validate(g, flags, ws, s));
@@ -234,6 +234,8 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   prof_stage("bfs");
   BfsInfo info;
   TC_TRY(bfs_run(g, root, L, p.bfs, s, &info));
+  if (direct && direct_fits(g->n, g->nnz, info))
+    return direct_count_run(g, L, info, p.stats, triangles, h_count, p.region, s);
   const int32_t nl = info.num_levels, d0 = info.first_levels;
   tc_csr rg = *g;  // the relabelled graph
   if (g->n > 0) {
@@ -289,7 +291,17 @@ int tc_count_tuned(const tc_csr* g, int64_t root, uint32_t flags, const tc_tunin
     TC_TRY(maybe_validate(g, flags, ws, s));
     return small_count_run(g, root, triangles, h_count, levels, ws, ws_bytes, s);
   }
-  return cover_call(g, root, flags, triangles, h_count, levels, per_vertex, false, nullptr, 0, ws, s, prm);
+  // a caller that sets a knob of the intersection stage, or rules the batched
+  // kernels out, gets that stage
+  tc_tuning stage{};
+  if (tuning) {
+    stage = *tuning;
+    stage.batch_block = stage.batch_piece = stage.batch_blocks_per_cu = stage.small_max_nnz = 0;
+    if (stage.small_max_n > 0) stage.small_max_n = 0;
+  }
+  const tc_tuning none{};
+  const bool direct = !pv && g->n > 0 && memcmp(&stage, &none, sizeof none) == 0;
+  return cover_call(g, root, flags, triangles, h_count, levels, per_vertex, false, nullptr, 0, direct, ws, s, prm);
 }
 
 int tc_count(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles, int64_t* h_count, int32_t* levels,
@@ -312,7 +324,7 @@ int tc_list_triangles(const tc_csr* g, int64_t root, uint32_t flags, int32_t* tr
   TC_TRY(count_params(nullptr, true, g->nnz, &prm));
   hipStream_t s = static_cast<hipStream_t>(stream);
   CallScope scope(s);
-  return cover_call(g, root, flags, triangles, h_count, levels, nullptr, true, tri, cap, ws, s, prm);
+  return cover_call(g, root, flags, triangles, h_count, levels, nullptr, true, tri, cap, false, ws, s, prm);
 }
 
 int tc_select_root(const tc_csr* g, int32_t num_candidates, uint32_t flags, int64_t* root_out,
