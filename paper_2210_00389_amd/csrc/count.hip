@@ -132,15 +132,47 @@ constexpr uint8_t kViHeavy = 0x80;
 constexpr uint8_t kViTwoLevel = 0x08;
 constexpr uint8_t kViBitmap = 0x04;
 
-__device__ __forceinline__ void add_pv(int64_t* pv, int32_t a, int32_t b, int32_t c) {
-  atomicAdd(reinterpret_cast<unsigned long long*>(&pv[a]), 1ull);
-  atomicAdd(reinterpret_cast<unsigned long long*>(&pv[b]), 1ull);
-  atomicAdd(reinterpret_cast<unsigned long long*>(&pv[c]), 1ull);
+__device__ __forceinline__ void add_pv(int64_t* pv, int32_t v, int64_t count) {
+  atomicAdd(reinterpret_cast<unsigned long long*>(&pv[v]), static_cast<unsigned long long>(count));
 }
+
+// Per-vertex counts of the apexes a block finds, in LDS: a slot holds the
+// first vertex that hashes to it, others go to memory.  The apexes of an
+// anchor are its probe set, so they repeat; the sums go out when the anchor
+// changes.  (With three atomics to memory per triangle the 32 KB bin took
+// 3.67 ms on a Chung-Lu graph of 500009 vertices.)
+constexpr uint32_t kPvFree = 0xFFFFFFFFu;
+
+template <int SLOTS>
+struct PvCache {
+  uint32_t* key;
+  int32_t* sum;
+  __device__ __forceinline__ void add(int64_t* pv, int32_t v) const {
+    if (SLOTS > 0) {
+      const uint32_t slot = (static_cast<uint32_t>(v) * 0x9E3779B1u) >> (32 - __builtin_ctz(SLOTS > 0 ? SLOTS : 2));
+      const uint32_t was = atomicCAS(&key[slot], kPvFree, static_cast<uint32_t>(v));
+      if (was == kPvFree || was == static_cast<uint32_t>(v)) {
+        atomicAdd(&sum[slot], 1);
+        return;
+      }
+    }
+    add_pv(pv, v, 1);
+  }
+  // All threads; the caller has synchronised the block and does so after.
+  __device__ __forceinline__ void flush(int64_t* pv, int threads) const {
+    for (int i = threadIdx.x; i < SLOTS; i += threads) {
+      if (sum[i]) add_pv(pv, static_cast<int32_t>(key[i]), sum[i]);
+      key[i] = kPvFree;
+      sum[i] = 0;
+    }
+  }
+};
 
 // What the counting kernels do with each triangle they find:
 //   kOutNone  count only;
-//   kOutPV    also add one to each of its three vertices (per-vertex counts);
+//   kOutPV    also add one to each of its three vertices (per-vertex counts:
+//             the anchor's per item or task, the streamed list's per chunk or
+//             task, the apex's here);
 //   kOutRec   also record every work unit's count (ucnt: heavy items by their
 //             index in the item array, then light tasks by their index);
 //   kOutEmit  write it at its work unit's offset (uoff) as three caller ids,
@@ -178,7 +210,7 @@ __device__ __forceinline__ int32_t caller_id(const Out& o, int32_t v) { return o
 // kOutEmit x and oth are caller ids, w a layout id).
 template <int kOut>
 __device__ __forceinline__ void on_hit(const Out& o, int32_t x, int32_t oth, int32_t w, int64_t& at) {
-  if (kOut == kOutPV) add_pv(o.pv, x, oth, w);
+  if (kOut == kOutPV) add_pv(o.pv, w, 1);
   else if (kOut == kOutEmit) write_tri(o, at++, x, oth, w);
 }
 
@@ -855,6 +887,10 @@ __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, cons
       elems += np;
     }
     cnt += tc;
+    if (kOut == kOutPV && tc) {
+      add_pv(o.pv, x, tc);
+      add_pv(o.pv, oth, tc);
+    }
     if (kOut == kOutRec) o.ucnt[ubase + i] = static_cast<int32_t>(tc);
   }
   if (kOut != kOutEmit) {
@@ -1016,12 +1052,12 @@ constexpr int ahead_of() { return (WORDS == kBinWords2 || WORDS == 0) ? 2 : 1; }
 static_assert(kChunk <= kColPad, "chunk tail must stay inside the padded columns");
 
 // Hits of one chunk whose entries v (len of them valid) are loaded.
-template <int MODE, int kOut>
+template <int MODE, int kOut, int SLOTS>
 // Called by every lane of the wave (a lane with no chunk passes len = 0);
 // wq: the wave's queue of kWave ids in LDS (hash tables, counting only).
 __device__ __forceinline__ uint32_t chunk_probe(const int32_t (&v)[kChunk], int len, const ProbeSet& ps, bool up_side,
                                                 int32_t x, int32_t oth, const Out& o, int64_t ebase, int* s_pos,
-                                                int32_t* wq) {
+                                                int32_t* wq, const PvCache<SLOTS>& pvc) {
   const uint32_t lenmask = len >= kChunk ? ((1u << kChunk) - 1u) : ((1u << len) - 1u);
   uint32_t hits = 0;
   if (MODE == kHash) {
@@ -1097,9 +1133,10 @@ __device__ __forceinline__ uint32_t chunk_probe(const int32_t (&v)[kChunk], int 
   }
   hits &= lenmask;
   if (kOut == kOutPV && hits) {
+    add_pv(o.pv, oth, __popc(hits));
 #pragma unroll
     for (int q = 0; q < kChunk; ++q)
-      if ((hits >> q) & 1u) add_pv(o.pv, x, oth, v[q]);
+      if ((hits >> q) & 1u) pvc.add(o.pv, v[q]);
   }
   if (kOut == kOutEmit) {
     // The item's triangles fill [ebase, ebase + its count) in any order; a
@@ -1118,14 +1155,14 @@ __device__ __forceinline__ uint32_t chunk_probe(const int32_t (&v)[kChunk], int 
   return static_cast<uint32_t>(__popc(hits));
 }
 
-template <int MODE, int kOut>
+template <int MODE, int kOut, int SLOTS>
 __device__ __forceinline__ uint32_t chunk_hits(const int32_t* p, int len, const ProbeSet& ps, bool up_side,
                                                int32_t x, int32_t oth, const Out& o, int64_t ebase, int* s_pos,
-                                               int32_t* wq) {
+                                               int32_t* wq, const PvCache<SLOTS>& pvc) {
   int32_t v[kChunk];
 #pragma unroll
   for (int q = 0; q < kChunk; ++q) v[q] = p[q];
-  return chunk_probe<MODE, kOut>(v, len, ps, up_side, x, oth, o, ebase, s_pos, wq);
+  return chunk_probe<MODE, kOut>(v, len, ps, up_side, x, oth, o, ebase, s_pos, wq, pvc);
 }
 
 // All chunks of one batch of streams.  The chunk space [0, C) is walked in
@@ -1134,11 +1171,12 @@ __device__ __forceinline__ uint32_t chunk_hits(const int32_t* p, int len, const 
 // the number of streams that start before it (s_tb) and a 64-bit mask of the
 // streams that start inside it (s_M).  Lane i of a wave then finds the
 // stream of its chunk as s_tb + popcount(mask bits <= i) - 1, with no search.
-template <int MODE, int THREADS, int kOut, int kAhead>
+template <int MODE, int THREADS, int kOut, int kAhead, int SLOTS>
 __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_cl, const int64_t* s_beg,
                                                const int32_t* s_oth, uint64_t* s_M,
                                                int32_t* s_tb, const int32_t* lc, const ProbeSet& ps, int32_t x,
-                                               const Out& o, int64_t ebase, int* s_pos, int32_t* s_q) {
+                                               const Out& o, int64_t ebase, int* s_pos, int32_t* s_q,
+                                               const PvCache<SLOTS>& pvc) {
   constexpr int kWin = THREADS * kWinIters;
   constexpr int kTiles = kWin / kWave;
   static_assert(THREADS % kWave == 0, "block must be whole waves");
@@ -1193,7 +1231,7 @@ __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_
           if (needs_oth(kOut)) ot = s_oth[j];
           upside = (cl.y & kClUp) != 0;
         }
-        cnt += chunk_hits<MODE, kOut>(p, len, ps, upside, x, ot, o, ebase, s_pos, wq);
+        cnt += chunk_hits<MODE, kOut>(p, len, ps, upside, x, ot, o, ebase, s_pos, wq, pvc);
       }
     } else if (kOut != kOutEmit) {
       // kAhead chunk slots per lane at a time: every slot's loads are issued
@@ -1234,7 +1272,7 @@ __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_
           for (int q = 0; q < kChunk; ++q) v[u][q] = lc[e[u] + q];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
-          cnt += chunk_probe<MODE, kOut>(v[u], len[u], ps, up[u], x, oth[u], o, ebase, s_pos, wq);
+          cnt += chunk_probe<MODE, kOut>(v[u], len[u], ps, up[u], x, oth[u], o, ebase, s_pos, wq, pvc);
       }
     } else {
       // writing triangles: the whole wave takes part in every round (the
@@ -1260,7 +1298,7 @@ __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_
           ot = s_oth[j];
           upside = (cl.y & kClUp) != 0;
         }
-        cnt += chunk_hits<MODE, kOut>(p, len, ps, upside, x, ot, o, ebase, s_pos, wq);
+        cnt += chunk_hits<MODE, kOut>(p, len, ps, upside, x, ot, o, ebase, s_pos, wq, pvc);
       }
     }
     __syncthreads();
@@ -1293,9 +1331,22 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
   __shared__ int64_t sh[THREADS / kWave + 1];
   __shared__ int32_t shi[THREADS / kWave + 1];
   __shared__ unsigned long long s_item;
+  // slots for the apexes' counts where the LDS of the bin leaves room and its
+  // items are long enough to repeat them
+  constexpr int kPv = kOut != kOutPV ? 0 : (WORDS == kBinWords0 ? 0 : (WORDS == kBinWords2 ? 512 : 2048));
+  __shared__ uint32_t s_pk[kPv > 0 ? kPv : 1];
+  __shared__ int32_t s_ps[kPv > 0 ? kPv : 1];
+  const PvCache<kPv> pvc{s_pk, s_ps};
+  int32_t pv_x = -1;
+  for (int i = threadIdx.x; i < kPv; i += THREADS) {
+    s_pk[i] = kPvFree;
+    s_ps[i] = 0;
+  }
 
   const unsigned long long first = acc[kAccBinOff + bin];
   const unsigned long long count = acc[kAccBinCount + bin];
+  // nothing for this block (all of an empty bin's, whose sums took 16 us)
+  if (kRoundRobin ? blockIdx.x >= count : count == 0) return;
   const int tid = threadIdx.x;
   int64_t cnt = 0, elems = 0, builds = 0, tl_elems = 0;
   int32_t cur_x = -1;
@@ -1322,6 +1373,11 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
     const int64_t sa = static_cast<int64_t>(static_cast<uint32_t>(item.y)) | (static_cast<int64_t>(item.z) << 32);
     const int64_t sb = sa + (item.w & kItemCountMask);
     const VMeta mx = meta[x];
+    if (kPv > 0 && x != pv_x) {  // the last item's barriers are behind its additions
+      pvc.flush(o.pv, THREADS);
+      __syncthreads();
+      pv_x = x;
+    }
     const int P = mx.up + (mx.sfe - mx.hfb);
     ProbeSet ps;
     ps.tab = tab;
@@ -1458,25 +1514,26 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
       uint32_t got;
       if (WORDS == 0) {
         got = run_chunks<kSearch, THREADS, kOut, ahead_of<WORDS>()>(C, nslots, s_cl, s_beg, s_oth, s_M, s_tb, lc, ps, hx, o,
-                                                 ebase, &s_pos, s_q);
+                                                 ebase, &s_pos, s_q, pvc);
       } else if (mode == kBitmap) {
         got = run_chunks<kBitmap, THREADS, kOut, ahead_of<WORDS>()>(C, nslots, s_cl, s_beg, s_oth, s_M, s_tb, lc, ps, hx, o,
-                                                 ebase, &s_pos, s_q);
+                                                 ebase, &s_pos, s_q, pvc);
       } else if (WORDS == kBinWords2 && mode == kTwoLevel) {
         got = run_chunks<kTwoLevel, THREADS, kOut, ahead_of<WORDS>()>(C, nslots, s_cl, s_beg, s_oth, s_M, s_tb, lc, ps, hx, o,
-                                                   ebase, &s_pos, s_q);
+                                                   ebase, &s_pos, s_q, pvc);
       } else {
         got = run_chunks<kHash, THREADS, kOut, ahead_of<WORDS>()>(C, nslots, s_cl, s_beg, s_oth, s_M, s_tb, lc, ps, hx, o,
-                                               ebase, &s_pos, s_q);
+                                               ebase, &s_pos, s_q, pvc);
       }
       // the per-item count is kept only where it is recorded
-      if (kOut == kOutRec) icnt += got;
+      if (kOut == kOutRec || kOut == kOutPV) icnt += got;
       else cnt += got;
     }
-    if (kOut == kOutRec) {
+    if (kOut == kOutRec || kOut == kOutPV) {
       cnt += icnt;
       const int64_t t = block_sum(icnt, sh);
-      if (tid == 0) o.ucnt[gi] = static_cast<int32_t>(t);
+      if (kOut == kOutRec && tid == 0) o.ucnt[gi] = static_cast<int32_t>(t);
+      if (kOut == kOutPV && tid == 0 && t) add_pv(o.pv, x, t);
     }
     }
     __syncthreads();
@@ -1484,6 +1541,7 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
     __syncthreads();
     claim = s_item;
   }
+  if (kPv > 0) pvc.flush(o.pv, THREADS);
   if (kOut == kOutEmit) return;
   block_acc(acc, kAccT, cnt, sh);
   block_acc(acc, kAccHeavyElems, elems, sh);
