@@ -808,11 +808,15 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
 }
 
 // Tasks of light anchors, read from the back of every chunk's region; one
-// thread per task, found from the scan lpre of the per-chunk task counts.
-// The probe segment (at most kLightMax ids) and a stream of at most
-// kLightMax ids are loaded into registers with independent loads and
-// compared pairwise; a longer stream (down class) is searched for every
-// probe id, all searches advancing together.
+// thread per task, found from the scan lpre of the per-chunk task counts (the
+// chunks of a wave's first and last task are searched once, a lane looks
+// between them).  The probe segment (at most kLightMax ids) and a stream of
+// at most kLightMax ids are loaded into registers with independent loads and
+// compared pairwise, eight by eight up to the wave's longest segment and
+// stream (comparing all 32 x 32 for lists of six ids on average took 195 us
+// at R-MAT scale 20, VALU-bound); a longer stream (down class) is searched
+// for every probe id, all searches advancing together.
+constexpr int kLightStep = 8;
 
 template <int kOut>
 __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, const VMeta* meta, const int64_t* so,
@@ -826,38 +830,71 @@ __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, cons
   // light tasks follow the heavy items in the unit numbering
   const int64_t ubase = (kOut == kOutRec || kOut == kOutEmit) ? static_cast<int64_t>(acc[kAccItems]) : 0;
   int64_t cnt = 0, elems = 0;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nl; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c = upper_bound_dev(lpre, 0, nchunk_cap + 1, i) - 1;
-    const int64_t pos = 2 * min((c + 1) * kResChunk, total) - 1 - (i - lpre[c]);
-    const int32_t x = sx[pos];
-    const int32_t lf = slen[pos];
-    const int32_t oth = needs_oth(kOut) ? soth[pos] : 0;
-    int64_t at = kOut == kOutEmit ? o.uoff[ubase + i] : 0;
+  const int64_t wave0 = blockIdx.x * static_cast<int64_t>(kThreads / kWave) +
+                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  for (int64_t w0 = wave0 * kWave; w0 < nl; w0 += (int64_t)gridDim.x * kThreads) {  // the whole wave takes part
+    const int64_t i = w0 + lane();
+    const bool mine = i < nl;
+    const int64_t ca = upper_bound_dev(lpre, 0, nchunk_cap + 1, w0) - 1;
+    const int64_t cz = upper_bound_dev(lpre, ca, nchunk_cap + 1, min(w0 + kWave, nl) - 1);
+    int32_t x = 0, oth = 0, lf = 0;
+    int64_t at = 0;
+    const int32_t* P = lc;
+    const int32_t* S = lc;
+    int np = 0, len = 0;
+    if (mine) {
+      const int64_t c = upper_bound_dev(lpre, ca + 1, cz, i) - 1;
+      const int64_t pos = 2 * min((c + 1) * kResChunk, total) - 1 - (i - lpre[c]);
+      x = sx[pos];
+      lf = slen[pos];
+      if (needs_oth(kOut)) oth = soth[pos];
+      if (kOut == kOutEmit) at = o.uoff[ubase + i];
+      const VMeta mx = meta[x];
+      len = lf & kLenMask;
+      const bool up = (lf & kFlagUp) != 0;
+      P = lc + mx.begin + (up ? 0 : mx.hfb);
+      np = up ? mx.up : mx.sfe - mx.hfb;
+      S = lc + sbeg[pos];
+    }
     // the ids a hit reports: caller ids when writing triangles
     const int32_t hx = kOut == kOutEmit ? caller_id(o, x) : x;
     const int32_t ho = kOut == kOutEmit ? caller_id(o, oth) : oth;
     int64_t tc = 0;
-    const VMeta mx = meta[x];
-    const int len = lf & kLenMask;
-    const bool up = (lf & kFlagUp) != 0;
-    const int32_t* P = lc + mx.begin + (up ? 0 : mx.hfb);
-    const int np = up ? mx.up : mx.sfe - mx.hfb;
-    const int32_t* S = lc + sbeg[pos];
+    const bool pairs = len <= kLightMax;
+    const int maxp = wave_max(np), maxs = wave_max(pairs ? len : 0);
     int32_t pr[kLightMax];
 #pragma unroll
-    for (int q = 0; q < kLightMax; ++q) pr[q] = q < np ? P[q] : -1;
-    if (len <= kLightMax) {
-      int32_t sv[kLightMax];
+    for (int g = 0; g < kLightMax; g += kLightStep) {
+      if (g >= maxp) break;  // uniform
 #pragma unroll
-      for (int q = 0; q < kLightMax; ++q) sv[q] = q < len ? S[q] : -2;
+      for (int q = g; q < g + kLightStep; ++q) pr[q] = q < np ? P[q] : -1;
+    }
 #pragma unroll
-      for (int q = 0; q < kLightMax; ++q) {
-        int m = 0;
+    for (int gs = 0; gs < kLightMax; gs += kLightStep) {
+      if (gs >= maxs) break;  // uniform
+      int32_t sv[kLightStep];
+      uint32_t m = 0;
 #pragma unroll
-        for (int j = 0; j < kLightMax; ++j) m |= sv[q] == pr[j];
-        tc += m;
-        if (m) on_hit<kOut>(o, hx, ho, sv[q], at);
+      for (int q = 0; q < kLightStep; ++q) sv[q] = pairs && gs + q < len ? S[gs + q] : -2;
+#pragma unroll
+      for (int g = 0; g < kLightMax; g += kLightStep) {
+        if (g >= maxp) break;  // uniform
+#pragma unroll
+        for (int q = 0; q < kLightStep; ++q) {
+          bool eq = false;
+#pragma unroll
+          for (int j = 0; j < kLightStep; ++j) eq |= sv[q] == pr[g + j];
+          m |= static_cast<uint32_t>(eq) << q;
+        }
       }
+      tc += __popc(m);
+      if (kOut == kOutPV || kOut == kOutEmit) {
+#pragma unroll
+        for (int q = 0; q < kLightStep; ++q)
+          if ((m >> q) & 1u) on_hit<kOut>(o, hx, ho, sv[q], at);
+      }
+    }
+    if (pairs) {
       elems += len;
     } else {
       // probes in groups of 8: lower bound of each in S by binary lifting
@@ -891,7 +928,7 @@ __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, cons
       add_pv(o.pv, x, tc);
       add_pv(o.pv, oth, tc);
     }
-    if (kOut == kOutRec) o.ucnt[ubase + i] = static_cast<int32_t>(tc);
+    if (kOut == kOutRec && mine) o.ucnt[ubase + i] = static_cast<int32_t>(tc);
   }
   if (kOut != kOutEmit) {
     block_acc(acc, kAccT, cnt, sh);
@@ -1331,9 +1368,9 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
   __shared__ int64_t sh[THREADS / kWave + 1];
   __shared__ int32_t shi[THREADS / kWave + 1];
   __shared__ unsigned long long s_item;
-  // slots for the apexes' counts where the LDS of the bin leaves room and its
-  // items are long enough to repeat them
-  constexpr int kPv = kOut != kOutPV ? 0 : (WORDS == kBinWords0 ? 0 : (WORDS == kBinWords2 ? 512 : 2048));
+  // slots for the apexes' counts, as many as the LDS leaves room for (256 for
+  // the 2 KB bin, whose probe sets are small: 2.17 -> 1.85 ms on the graph above)
+  constexpr int kPv = kOut != kOutPV ? 0 : (WORDS == kBinWords0 ? 256 : (WORDS == kBinWords2 ? 512 : 2048));
   __shared__ uint32_t s_pk[kPv > 0 ? kPv : 1];
   __shared__ int32_t s_ps[kPv > 0 ? kPv : 1];
   const PvCache<kPv> pvc{s_pk, s_ps};
@@ -1592,6 +1629,18 @@ int launch_heavy(const CountArgs& a, CountWs& w, const Out& o, int bin, int bloc
   return TC_OK;
 }
 
+// Bin 0: blocks taking items round robin, or one-wave blocks claiming them
+// (count_params picks by graph size).  Round robin, four waves a block while
+// the items are too few to go round many times (8185 of up to 2^14 elements
+// at R-MAT scale 16: whole count 0.60 -> 0.56 ms; scale 18 1.09 -> 1.08),
+// two beyond (scale 19 1.79 ms against 1.82 with four).
+template <int kOut>
+int launch_bin0(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
+  if (a.prm.bin0_mode != 2) return launch_heavy<kBinWords0, 64, 256, 6, kOut>(a, w, o, 0, 24, s);
+  if (a.g->nnz < (int64_t(1) << 23)) return launch_heavy<kBinWords0, 256, 256, 6, kOut, true>(a, w, o, 0, 6, s);
+  return launch_heavy<kBinWords0, 128, 256, 6, kOut, true>(a, w, o, 0, 12, s);
+}
+
 // The four bins of heavy items, one after another on the call's stream
 // (bins_mode 1) or side by side on forked streams (2).
 template <int kOut>
@@ -1599,10 +1648,7 @@ int launch_bins(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
   if (a.prm.bins_mode == 1) {
     TC_TRY((launch_heavy<kBinWords2, 1024, 1024, 4, kOut>(a, w, o, 2, 1, s)));
     TC_TRY((launch_heavy<kBinWords1, 512, 1024, 6, kOut>(a, w, o, 1, 3, s)));
-    // bin 0: two-wave blocks taking items round robin, or one-wave blocks
-    // claiming them (count_params picks by graph size)
-    if (a.prm.bin0_mode == 2) TC_TRY((launch_heavy<kBinWords0, 128, 256, 6, kOut, true>(a, w, o, 0, 12, s)));
-    else TC_TRY((launch_heavy<kBinWords0, 64, 256, 6, kOut>(a, w, o, 0, 24, s)));
+    TC_TRY(launch_bin0<kOut>(a, w, o, s));
     return launch_heavy<0, 512, 1024, 4, kOut>(a, w, o, 3, 4, s);
   }
   Fork* f = fork_for_device();
@@ -1610,8 +1656,7 @@ int launch_bins(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
   TC_TRY(fork_begin(f, s));
   TC_TRY((launch_heavy<kBinWords2, 1024, 1024, 4, kOut>(a, w, o, 2, 1, s)));
   TC_TRY((launch_heavy<kBinWords1, 512, 1024, 6, kOut>(a, w, o, 1, 3, f->aux[0])));
-  if (a.prm.bin0_mode == 2) TC_TRY((launch_heavy<kBinWords0, 128, 256, 6, kOut, true>(a, w, o, 0, 12, f->aux[1])));
-  else TC_TRY((launch_heavy<kBinWords0, 64, 256, 6, kOut>(a, w, o, 0, 24, f->aux[1])));
+  TC_TRY(launch_bin0<kOut>(a, w, o, f->aux[1]));
   TC_TRY((launch_heavy<0, 512, 1024, 4, kOut>(a, w, o, 3, 4, f->aux[2])));
   return fork_end(f, s);
 }
