@@ -81,8 +81,10 @@ def stage_bytes(name, st, n, nnz, cover):
         d = st.get("descriptors", 0)
         return 20 * d + 4 * st["light_elems"] + 16 * st["heavy_desc"] + 48 * st["heavy_items"]
     if name == "heavy":
-        # streamed list elements + records + probe-set inserts + items
-        return 4 * st["heavy_elems"] + 16 * st["heavy_desc"] + 4 * st["heavy_builds"] + 16 * st["heavy_items"]
+        # streamed list elements (the core parts, which no bin counts, are 16-bit
+        # ids) + records + probe-set inserts + items
+        core = st["heavy_elems"] - sum(st["bin_elems"])
+        return 4 * sum(st["bin_elems"]) + 2 * core + 16 * st["heavy_desc"] + 4 * st["heavy_builds"] + 16 * st["heavy_items"]
     return None
 
 

@@ -407,7 +407,9 @@ typedef struct tc_stats {
   int64_t heavy_builds;    /* probe-set elements inserted into on-chip tables */
   int64_t light_elems;     /* list elements streamed by the per-task merges */
   int64_t bin_elems[4];    /* anchored-kernel elements per table bin (2 KB,
-                              32 KB, 128 KB, row search) */
+                              32 KB, 128 KB, row search); heavy_elems beyond
+                              their sum were streamed as 16-bit ids of the
+                              lists' core parts */
   int64_t bin_items[4];    /* work items per table bin */
   int64_t descriptors;     /* per-vertex task descriptors examined */
   int64_t twolevel_elems;  /* anchored-kernel elements probed in two-level

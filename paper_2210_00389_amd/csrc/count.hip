@@ -34,7 +34,9 @@
 // table the anchor needs (2 KB .. 128 KB of the 160 KB LDS: a bitmap over the
 // probe set's id window, or a hash table) or row search beyond that.  The
 // streaming kernel builds the table once per item and hands each lane chunks
-// of 8 elements of one stream.  Per-lane counts are reduced wave -> block ->
+// of 8 elements of one stream.  On larger graphs (kCoreNnz) the anchors beyond
+// the 2 KB tables stream their lists as 16-bit offsets into the core of a
+// level (core_kernel), and what lies outside the core apart.  Per-lane counts are reduced wave -> block ->
 // one 64-bit atomic; the count runs without a host synchronisation.
 //
 // The comparator (plain direction-oriented edge iterator) runs through the
@@ -49,7 +51,8 @@ constexpr int kThreads = 256;
 constexpr int kDnLight = 32;  // default: light anchors have at most this many down-neighbours
 constexpr int kLightMax = 32; // and a probe set of at most this many ids (the register capacity
                               // of light_kernel, so the tuned bound never exceeds it)
-constexpr int kBins = 4;
+constexpr int kBins = 5;      // the four bins below, then the core items
+constexpr int kBinCore = 4;
 
 // Bins of heavy anchors by the LDS table they need: 2 KB, 32 KB, 128 KB, or
 // none (bin 3: search the sorted rows).  The probe set P(x) lies in the id
@@ -113,24 +116,30 @@ __device__ __forceinline__ int choose_bin(int64_t need, int64_t R, int P, int64_
 
 enum Acc {
   kAccT = 0, kAccElems = 1, kAccBuild = 3, kAccRecs = 4, kAccItems = 5, kAccHeavyElems = 6,
-  kAccH = 7, kAccBinCount = 8, kAccBinOff = 12, kAccBinCur = 16, kAccBinNext = 20, kAccBinElems = 24,
-  kAccTwoLevelElems = 28
+  kAccH = 7, kAccTwoLevelElems = 8, kAccBinCount = 9, kAccBinOff = kAccBinCount + kBins,
+  kAccBinCur = kAccBinOff + kBins, kAccBinNext = kAccBinCur + kBins, kAccBinElems = kAccBinNext + kBins
 };
-constexpr int kAccSlots = 29;
+constexpr int kAccSlots = kAccBinElems + kBins;
 constexpr int kElemChunkLog = 19;  // default: 2^19 elements per work item (target)
 // stream record flag (in the length word): probe the anchor's Up list
 constexpr int32_t kFlagUp = 1 << 29;
 constexpr int32_t kLenMask = kFlagUp - 1;
 // stream slot in LDS (s_cl.y): length | kClUp when the stream probes Up(x)
 constexpr int32_t kClUp = 1 << 30;
-// work item word: stream count | bin << 28 | kItemBitmap | kItemTwoLevel
-constexpr int32_t kItemCountMask = (1 << 28) - 1;
+// work item word: stream count | bin << 24 | kItemRest | kItemBitmap | kItemTwoLevel
+constexpr int32_t kItemCountMask = (1 << 24) - 1;
+constexpr int kItemBinShift = 24;
+constexpr int32_t kItemRest = 1 << 27;  // the parts outside the core of a core anchor's lists
 constexpr int32_t kItemBitmap = 1 << 30;
 constexpr int32_t kItemTwoLevel = static_cast<int32_t>(0x80000000u);
-// per-vertex plan byte: kViHeavy | two-level << 3 | bitmap << 2 | bin
-constexpr uint8_t kViHeavy = 0x80;
-constexpr uint8_t kViTwoLevel = 0x08;
-constexpr uint8_t kViBitmap = 0x04;
+// per-vertex plan: kViHeavy | two-level << 3 | bitmap << 2 | bin for the whole
+// probe set, and where the anchor streams the core parts of its lists apart,
+// kViCore | bitmap << 10 | bin << 8 for its members outside the core
+constexpr uint16_t kViHeavy = 0x80;
+constexpr uint16_t kViTwoLevel = 0x08;
+constexpr uint16_t kViBitmap = 0x04;
+constexpr uint16_t kViCore = 0x8000;
+constexpr int kViRestShift = 8;
 
 __device__ __forceinline__ void add_pv(int64_t* pv, int32_t v, int64_t count) {
   atomicAdd(reinterpret_cast<unsigned long long*>(&pv[v]), static_cast<unsigned long long>(count));
@@ -227,6 +236,13 @@ __device__ __forceinline__ bool gsearch(const int32_t* p, int len, int32_t t) {
 
 __device__ __forceinline__ int probe_size(const VMeta& m) { return m.up + (m.sfe - m.hfb); }
 
+// The record of the part of x's probe set outside the core.
+__device__ __forceinline__ VMeta rest_meta(VMeta m) {
+  m.up = m.ncu;
+  m.sfe = m.hfb + m.nch;
+  return m;
+}
+
 // Heavy anchors get work items; every task of a light anchor is merged by
 // the planning kernels.  Must be the same predicate everywhere.
 __device__ __forceinline__ bool is_heavy(const VMeta& m, bool cover, const CountParams& prm) {
@@ -305,28 +321,34 @@ __device__ __forceinline__ void joint_window(const SplitWindow& w, int32_t& lo, 
 // (begin, up, hfb, sfe) in one 16-byte word, so that the random read of a
 // neighbour's record is one request instead of two:
 //   x = begin bits 0..31, y = begin bits 32..39 | up << 8, z = hfb, w = sfe.
-// A record whose begin needs more than 40 bits or whose up is 2^24 - 1 or
-// more gets y = kPmFull: the reader then takes the full record.
+// Bit 31 of z and w say that Up and Hfwd have entries outside the core (list
+// lengths are below 2^29).  A record whose begin needs more than 40 bits or
+// whose up is 2^24 - 1 or more gets y = kPmFull: the reader then takes the
+// full record.
 constexpr uint32_t kPmFull = 0xFFFFFFFFu;
+constexpr uint32_t kPmRest = 0x80000000u;
 
 __device__ __forceinline__ uint4 pack_record(const VMeta& m) {
   const uint64_t b = static_cast<uint64_t>(m.begin);
   if ((b >> 40) != 0 || m.up >= 0xFFFFFF) return make_uint4(0u, kPmFull, 0u, 0u);
   return make_uint4(static_cast<uint32_t>(b), static_cast<uint32_t>(b >> 32) | (static_cast<uint32_t>(m.up) << 8),
-                    static_cast<uint32_t>(m.hfb), static_cast<uint32_t>(m.sfe));
+                    static_cast<uint32_t>(m.hfb) | (m.ncu > 0 ? kPmRest : 0u),
+                    static_cast<uint32_t>(m.sfe) | (m.nch > 0 ? kPmRest : 0u));
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // loaded whole, in one instruction
 
-// Record of vertex v for the resolution from its packed word q = pm[v]
-// (deg is not filled in).
+// Record of vertex v for the resolution from its packed word q = pm[v] (deg
+// is not filled in, ncu and nch are 0 or not 0 only).
 __device__ __forceinline__ VMeta unpack_record(u32x4 q, const VMeta* meta, int32_t v) {
   VMeta m;
   m.begin = static_cast<int64_t>(q.x | (static_cast<uint64_t>(q.y & 0xFFu) << 32));
   m.up = static_cast<int32_t>(q.y >> 8);
-  m.hfb = static_cast<int32_t>(q.z);
-  m.sfe = static_cast<int32_t>(q.w);
+  m.hfb = static_cast<int32_t>(q.z & ~kPmRest);
+  m.sfe = static_cast<int32_t>(q.w & ~kPmRest);
   m.deg = 0;
+  m.ncu = static_cast<int32_t>(q.z >> 31);
+  m.nch = static_cast<int32_t>(q.w >> 31);
   if (q.y == kPmFull) m = meta[v];
   return m;
 }
@@ -336,8 +358,8 @@ __device__ __forceinline__ VMeta unpack_record(u32x4 q, const VMeta* meta, int32
 // anchors the table bin.
 template <bool kCover>
 __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t* lc, const VMeta* meta, int64_t n,
-                                                        int32_t* ndesc, uint8_t* vinfo, uint4* pm,
-                                                        unsigned long long* acc, CountParams prm) {
+                                                        int32_t* ndesc, uint16_t* vinfo, uint4* pm,
+                                                        unsigned long long* acc, CountParams prm, bool core) {
   __shared__ int64_t sh[kThreads / kWave + 1];
   int64_t h = 0;
   for (int64_t x0 = blockIdx.x * (int64_t)blockDim.x; x0 < n; x0 += (int64_t)gridDim.x * blockDim.x) {
@@ -349,7 +371,7 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t* lc, const
     const int nU = (kCover && prm.up_anchor_min >= 0 && m.up > prm.up_anchor_min) ? m.up : 0;
     const int D = nB + hf + (m.hfb - m.up) + nU;
     h += hf;
-    uint8_t vi = 0;
+    uint16_t vi = 0;
     if (D > 0 && is_heavy(m, kCover, prm)) {
       const SplitWindow sw = split_window(lc, m);
       int32_t lo;
@@ -357,8 +379,22 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t* lc, const
       joint_window(sw, lo, R);
       int kind = kKindHash;
       const int b = choose_bin(split_words(sw), R, probe_size(m), D, m.deg, &kind, prm);
-      vi = static_cast<uint8_t>(kViHeavy | (kind == kKindBitmap ? kViBitmap : 0) |
-                                (kind == kKindTwoLevel ? kViTwoLevel : 0) | b);
+      vi = static_cast<uint16_t>(kViHeavy | (kind == kKindBitmap ? kViBitmap : 0) |
+                                 (kind == kKindTwoLevel ? kViTwoLevel : 0) | b);
+      // anchors beyond the smallest tables stream the core parts of their
+      // lists against a 16 KB bitmap of the core; what they hold outside it
+      // has to fit an LDS table of its own
+      if (kCover && core && b > 0) {
+        const VMeta mr = rest_meta(m);
+        int rest = 0;
+        if (probe_size(mr) > 0) {
+          const SplitWindow rw = split_window(lc, mr);
+          joint_window(rw, lo, R);
+          rest = choose_bin(split_words(rw), R, probe_size(mr), D, 0, &kind, prm);
+          if (kind == kKindBitmap) rest |= kViBitmap;
+        }
+        if ((rest & 3) < 3) vi |= kViCore | static_cast<uint16_t>(rest << kViRestShift);
+      }
     }
     ndesc[x] = D;
     vinfo[x] = vi;
@@ -381,9 +417,10 @@ constexpr int kResRecs = 2 * kResChunk;
 constexpr int kResSpan = 2 * kResChunk;  // vertex offsets staged in LDS
 
 struct Task {
-  int64_t beg;  // stream begin in the columns
-  int32_t len;  // stream length (0: no task) | kFlagUp
-  int32_t oth;  // vertex whose list is streamed
+  int64_t beg;   // stream begin in the columns
+  int32_t len;   // stream length (0: no task) | kFlagUp
+  int32_t oth;   // vertex whose list is streamed
+  int32_t rest;  // its first entries outside the core that the anchor's own may meet (core anchors)
 };
 
 enum DescKind { kDown = 0, kFwd = 1, kBwd = 2, kNone = 3, kUpD = 4 };
@@ -398,7 +435,7 @@ enum DescKind { kDown = 0, kFwd = 1, kBwd = 2, kNone = 3, kUpD = 4 };
 template <bool kCover>
 __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* samp, const VMeta* meta,
                                              const uint4* pm, const int32_t* x, const VMeta* mx, const int* kin,
-                                             int upa, Task* ta, Task* tb) {
+                                             int upa, const bool* core, Task* ta, Task* tb) {
   int kind[kResPer], k[kResPer];
   int32_t nb[kResPer];
   int64_t pos[kResPer];
@@ -406,8 +443,8 @@ __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* s
   // descriptors are in flight together (an idle slot reads column 0)
 #pragma unroll
   for (int j = 0; j < kResPer; ++j) {
-    ta[j] = Task{0, 0, 0};
-    tb[j] = Task{0, 0, 0};
+    ta[j] = Task{0, 0, 0, 0};
+    tb[j] = Task{0, 0, 0, 0};
     const int hf = mx[j].sfe - mx[j].hfb;
     const int nB = (kCover && hf > 0) ? mx[j].deg - mx[j].sfe : 0;
     const int nS = mx[j].hfb - mx[j].up;
@@ -527,24 +564,42 @@ __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* s
     const VMeta& o = mo[j];
     const int hf = m.sfe - m.hfb;
     if (kind[j] == kDown) {  // stream Up(w), unless w anchors the pair (see kUpD)
-      if (o.up > 0 && !(upa >= 0 && o.up > upa && o.up > hf)) ta[j] = Task{o.begin, o.up, nb[j]};
+      if (o.up > 0 && !(upa >= 0 && o.up > upa && o.up > hf)) ta[j] = Task{o.begin, o.up, nb[j], 0};
     } else if (kind[j] == kUpD) {
       // u = nb in Up(x), x one level below u: when Up(x) (longer than upa)
       // is also longer than Hfwd(u), x anchors the down-class pair (u, x)
       // and streams Hfwd(u) against the Up part of its table; every cover
       // edge (u, v) with v in Up(x) closes a triangle
       const int hu = o.sfe - o.hfb;
-      if (kCover && hu > 0 && m.up > hu) ta[j] = Task{o.begin + o.hfb, hu | kFlagUp, nb[j]};
+      if (kCover && hu > 0 && m.up > hu) ta[j] = Task{o.begin + o.hfb, hu | kFlagUp, nb[j], 0};
     } else if (kind[j] == kFwd) {  // forward cover edge (x, v)
-      if (kCover && o.up > 0 && o.up <= m.up) ta[j] = Task{o.begin, o.up | kFlagUp, nb[j]};
+      if (kCover && o.up > 0 && o.up <= m.up) ta[j] = Task{o.begin, o.up | kFlagUp, nb[j], 0};
       const int a = hf - k[j] - 1, b = o.sfe - o.hfb;
-      if (a > 0 && b > 0 && b < a) tb[j] = Task{o.begin + o.hfb, b, nb[j]};
+      if (a > 0 && b > 0 && b < a) tb[j] = Task{o.begin + o.hfb, b, nb[j], 0};
     } else if (kind[j] == kBwd) {  // backward cover edge (u, x), u < x
-      if (kCover && o.up > 0 && o.up < m.up) ta[j] = Task{o.begin, o.up | kFlagUp, nb[j]};
+      if (kCover && o.up > 0 && o.up < m.up) ta[j] = Task{o.begin, o.up | kFlagUp, nb[j], 0};
       if (srch[j]) {
         const int a = static_cast<int>(o.begin + o.sfe - lo[j]) - 1;  // lo = position of x
-        if (a > 0 && hf >= a) tb[j] = Task{lo[j] + 1, a, nb[j]};
+        if (a > 0 && hf >= a) tb[j] = Task{lo[j] + 1, a, nb[j], 0};
       }
+    }
+  }
+  // Where both the streamed list and the anchor's segment have entries
+  // outside the core, the list's are streamed apart: their number is read
+  // from the neighbour's record (at most a prefix of the task's stream).
+#pragma unroll
+  for (int j = 0; j < kResPer; ++j) {
+    if (!kCover || !core[j]) continue;
+    const bool hfl = kind[j] == kUpD;  // slot 0 streams Hfwd(nb), not Up(nb)
+    const bool ra = ta[j].len != 0 && (hfl ? mo[j].nch : mo[j].ncu) != 0 &&
+                    ((ta[j].len & kFlagUp) ? mx[j].ncu : mx[j].nch) > 0;
+    const bool rb = tb[j].len != 0 && mo[j].nch != 0 && mx[j].nch > 0;
+    if (!ra && !rb) continue;
+    const int2 nc = *reinterpret_cast<const int2*>(&meta[nb[j]].ncu);
+    if (ra) ta[j].rest = hfl ? nc.y : nc.x;
+    if (rb) {
+      const int64_t end = mo[j].begin + mo[j].hfb + nc.y;  // of Hfwd(nb)'s entries outside the core
+      tb[j].rest = static_cast<int32_t>(max(end - tb[j].beg, static_cast<int64_t>(0)));
     }
   }
 }
@@ -558,7 +613,7 @@ __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* s
 //                           a member), copied into LDS by every item of x
 //                           (nw <= deg(x) by the bin rule).
 // One wave per anchor; the anchors are found 64 vertices at a time.
-__global__ void twolevel_words_kernel(const int32_t* lc, const VMeta* meta, const uint8_t* vinfo, int64_t n,
+__global__ void twolevel_words_kernel(const int32_t* lc, const VMeta* meta, const uint16_t* vinfo, int64_t n,
                                       uint32_t* words, uint32_t* l1) {
   const int64_t wid = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) / kWave;
   const int64_t nwv = (static_cast<int64_t>(gridDim.x) * blockDim.x) / kWave;
@@ -634,10 +689,11 @@ __global__ void chunk_start_kernel(const int64_t* so, int64_t n, int32_t* cx0) {
 // descriptor order (j-major).
 template <bool kCover>
 __global__ __launch_bounds__(kResThreads) void resolve_kernel(
-    const int32_t* lc, const int32_t* samp, const VMeta* meta, const uint4* pm, const uint8_t* vinfo,
+    const int32_t* lc, const int32_t* samp, const VMeta* meta, const uint4* pm, const uint16_t* vinfo,
     const int64_t* so, const int32_t* cx0, int64_t n, int64_t* sbeg, int32_t* slen, int32_t* soth, int32_t* sx,
     int4* items_raw, int4* ccnt, int item_log2, int upa) {
   __shared__ int64_t sh[kResThreads / kWave + 1];
+  __shared__ int32_t shi[kResThreads / kWave + 1];
   __shared__ int64_t s_so[kResSpan];
   __shared__ int32_t s_x[kResRecs];
   __shared__ int64_t s_pre[kResRecs];
@@ -682,16 +738,26 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
       kk[j] = static_cast<int>(d - xb);
     }
     VMeta mx[kResPer];
-    uint8_t vi[kResPer];
+    uint16_t vi[kResPer];
+    bool core[kResPer];
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {  // loads of all slots together (an idle slot reads vertex 0's)
       mx[j] = meta[xi[j]];
       vi[j] = vinfo[xi[j]];
     }
 #pragma unroll
-    for (int j = 0; j < kResPer; ++j) heavy[j] = kk[j] >= 0 && (vi[j] & kViHeavy) != 0;
+    for (int j = 0; j < kResPer; ++j) {
+      heavy[j] = kk[j] >= 0 && (vi[j] & kViHeavy) != 0;
+      core[j] = heavy[j] && (vi[j] & kViCore) != 0;
+    }
     Task ta[kResPer], tb[kResPer];
-    describe_all<kCover>(lc, samp, meta, pm, xi, mx, kk, upa, ta, tb);
+    describe_all<kCover>(lc, samp, meta, pm, xi, mx, kk, upa, core, ta, tb);
+    // Records outside the core follow the heavy records; where the region has
+    // no room for them the chunk's core anchors stream whole lists.
+    int64_t nr = 0;
+#pragma unroll
+    for (int j = 0; j < kResPer; ++j)
+      nr |= static_cast<int64_t>((ta[j].rest > 0) + (tb[j].rest > 0)) << (16 * j);
     // ---- counts: light tasks, heavy records, heavy elements (per j, j-major)
     int64_t nl = 0, nh = 0;
     int64_t he[kResPer];
@@ -702,16 +768,19 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
       nl |= (heavy[j] ? 0 : cnt) << (16 * j);  // kResPer * 16 bits: counts <= 2 per descriptor
       nh |= (heavy[j] ? cnt : 0) << (16 * j);
     }
-    int64_t ltot_p, htot_p;
+    int64_t ltot_p, htot_p, rtot_p = 0, rpre_p = 0;
     const int64_t lpre_p = block_excl_scan(nl, sh, &ltot_p);
     const int64_t hpre_p = block_excl_scan(nh, sh, &htot_p);
-    int32_t lslot[kResPer], hslot[kResPer];
-    int32_t ltot = 0, htot = 0;
+    if (kCover) rpre_p = block_excl_scan(nr, sh, &rtot_p);
+    int32_t lslot[kResPer], hslot[kResPer], rslot[kResPer];
+    int32_t ltot = 0, htot = 0, rtot = 0;
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
       // slots of descriptor group j start after all groups before it
       lslot[j] = ltot + static_cast<int32_t>((lpre_p >> (16 * j)) & 0xFFFF);
       hslot[j] = htot + static_cast<int32_t>((hpre_p >> (16 * j)) & 0xFFFF);
+      rslot[j] = rtot + static_cast<int32_t>((rpre_p >> (16 * j)) & 0xFFFF);
+      rtot += static_cast<int32_t>((rtot_p >> (16 * j)) & 0xFFFF);
       ltot += static_cast<int32_t>((ltot_p >> (16 * j)) & 0xFFFF);
       htot += static_cast<int32_t>((htot_p >> (16 * j)) & 0xFFFF);
     }
@@ -724,6 +793,8 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
       ebase += et;
     }
     const int64_t rbase = 2 * d0, rend = 2 * d1;
+    const bool apart = htot + rtot + ltot <= static_cast<int>(rend - rbase);  // block-uniform
+    if (!apart) rtot = 0;
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
       const Task* tt[2] = {&ta[j], &tb[j]};
@@ -739,18 +810,27 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
           --pos;
         }
       } else {  // heavy records to the front
-        int sl = hslot[j];
+        int sl = hslot[j], rs = htot + rslot[j];
         int64_t e = epre[j];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           if (!tt[q]->len) continue;
-          sbeg[rbase + sl] = tt[q]->beg;
-          slen[rbase + sl] = tt[q]->len;
+          const int32_t rest = apart ? tt[q]->rest : 0;
+          sbeg[rbase + sl] = tt[q]->beg + rest;
+          slen[rbase + sl] = tt[q]->len - rest;
           soth[rbase + sl] = tt[q]->oth;
           s_x[sl] = xi[j];
           s_pre[sl] = e;
           e += tt[q]->len & kLenMask;
           ++sl;
+          if (rest > 0) {
+            sbeg[rbase + rs] = tt[q]->beg;
+            slen[rbase + rs] = rest | (tt[q]->len & kFlagUp);
+            soth[rbase + rs] = tt[q]->oth;
+            s_x[rs] = xi[j];
+            s_pre[rs] = 0;  // one item per anchor and chunk
+            ++rs;
+          }
         }
       }
     }
@@ -761,46 +841,45 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
     __syncthreads();
     // ---- cut into work items: a new item starts where the anchor changes
     // or the record's element offset enters the next 2^item_log2
-    // item starts are numbered in slot order: per descriptor group j (the
-    // slots of group j follow all of group j - 1), like the records
-    int64_t ns = 0;
+    // The slots are taken kResRecs / kResThreads consecutive ones a thread.
+    auto starts = [&](int q) {
+      return q == 0 || q == htot || s_x[q] != s_x[q - 1] || (s_pre[q] >> item_log2) != (s_pre[q - 1] >> item_log2);
+    };
+    constexpr int kPerThread = kResRecs / kResThreads;
+    const int nrec = htot + rtot;
+    int ns = 0;
 #pragma unroll
-    for (int j = 0; j < kResPer; ++j) {
-      const int cnt = heavy[j] ? (ta[j].len != 0) + (tb[j].len != 0) : 0;
-      int64_t nsj = 0;
-      for (int q = hslot[j]; q < hslot[j] + cnt; ++q)
-        nsj += (q == 0 || s_x[q] != s_x[q - 1] || (s_pre[q] >> item_log2) != (s_pre[q - 1] >> item_log2));
-      ns |= nsj << (16 * j);  // at most 2 per thread, at most kResRecs per group
+    for (int i = 0; i < kPerThread; ++i) {
+      const int q = tid * kPerThread + i;
+      ns += q < nrec && starts(q);
     }
-    int64_t ns_tot;
-    const int64_t ns_pre = block_excl_scan(ns, sh, &ns_tot);
-    int nitems = 0;
-    int itj[kResPer];
+    int nitems;
+    int it = block_excl_scan(ns, shi, &nitems);
 #pragma unroll
-    for (int j = 0; j < kResPer; ++j) {
-      itj[j] = nitems + static_cast<int>((ns_pre >> (16 * j)) & 0xFFFF);
-      nitems += static_cast<int>((ns_tot >> (16 * j)) & 0xFFFF);
-    }
-#pragma unroll
-    for (int j = 0; j < kResPer; ++j) {
-      const int cnt = heavy[j] ? (ta[j].len != 0) + (tb[j].len != 0) : 0;
-      int it = itj[j];
-      for (int q = hslot[j]; q < hslot[j] + cnt; ++q)
-        if (q == 0 || s_x[q] != s_x[q - 1] || (s_pre[q] >> item_log2) != (s_pre[q - 1] >> item_log2))
-          s_first[it++] = q;
+    for (int i = 0; i < kPerThread; ++i) {
+      const int q = tid * kPerThread + i;
+      if (q < nrec && starts(q)) s_first[it++] = q;
     }
     if (tid == 0) {
-      s_first[nitems] = htot;
-      ccnt[c] = make_int4(htot, ltot, nitems, 0);
+      s_first[nitems] = nrec;
+      ccnt[c] = make_int4(nrec, ltot, nitems, 0);
     }
     __syncthreads();
     for (int i = tid; i < nitems; i += kResThreads) {
       const int32_t x = s_x[s_first[i]];
-      const uint8_t vi = vinfo[x];
+      const uint16_t vi = vinfo[x];
       const int64_t r0 = rbase + s_first[i];
       const int cntr = s_first[i + 1] - s_first[i];
-      const int32_t w = cntr | ((vi & 3) << 28) | ((vi & kViBitmap) ? kItemBitmap : 0) |
-                        ((vi & kViTwoLevel) ? kItemTwoLevel : 0);
+      int32_t w;
+      if (s_first[i] >= htot) {
+        const int rest = vi >> kViRestShift;
+        w = cntr | ((rest & 3) << kItemBinShift) | ((rest & kViBitmap) ? kItemBitmap : 0) | kItemRest;
+      } else if (kCover && apart && (vi & kViCore)) {
+        w = cntr | (kBinCore << kItemBinShift);
+      } else {
+        w = cntr | ((vi & 3) << kItemBinShift) | ((vi & kViBitmap) ? kItemBitmap : 0) |
+            ((vi & kViTwoLevel) ? kItemTwoLevel : 0);
+      }
       items_raw[rbase + i] = make_int4(x, static_cast<int>(r0 & 0xFFFFFFFF), static_cast<int>(r0 >> 32), w);
     }
     __syncthreads();
@@ -951,20 +1030,30 @@ __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, 
   for (int64_t c0 = blockIdx.x * (int64_t)blockDim.x; c0 < nch; c0 += (int64_t)gridDim.x * blockDim.x) {
     const int64_t c = c0 + threadIdx.x;
     int ni = 0;
-    int k[kBins] = {0, 0, 0, 0};
+    int k[kBins] = {};
     if (c < nch) {
       ni = ccnt[c].z;
       if (!kFill) recs += ccnt[c].x;
-      for (int i = 0; i < ni; ++i) k[(items_raw[2 * c * kResChunk + i].w >> 28) & 3] += 1;
+      for (int i = 0; i < ni; ++i) {
+        const int b = (items_raw[2 * c * kResChunk + i].w >> kItemBinShift) & 7;
+#pragma unroll
+        for (int q = 0; q < kBins; ++q) k[q] += b == q;
+      }
     }
     // per-bin exclusive offsets within the block, two bins per 64-bit word
-    // (at most 2^17 items per bin and block)
-    int64_t t01, t23;
-    const int64_t p01 = block_excl_scan(static_cast<int64_t>(k[0]) | (static_cast<int64_t>(k[1]) << 32), sh, &t01);
-    const int64_t p23 = block_excl_scan(static_cast<int64_t>(k[2]) | (static_cast<int64_t>(k[3]) << 32), sh, &t23);
+    // (at most 2^18 items per bin and block)
+    constexpr int kWords = (kBins + 1) / 2;
+    int64_t tot[kWords], pre[kWords];
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+      const int64_t hi = 2 * i + 1 < kBins ? k[2 * i + 1] : 0;
+      pre[i] = block_excl_scan(static_cast<int64_t>(k[2 * i]) | (hi << 32), sh, &tot[i]);
+    }
     if (threadIdx.x < kBins) {
-      const int64_t t = threadIdx.x < 2 ? t01 : t23;
-      const unsigned long long kb = static_cast<unsigned long long>((t >> (32 * (threadIdx.x & 1))) & 0xFFFFFFFF);
+      unsigned long long kb = 0;
+#pragma unroll
+      for (int q = 0; q < kBins; ++q)
+        if (threadIdx.x == q) kb = static_cast<unsigned long long>((tot[q >> 1] >> (32 * (q & 1))) & 0xFFFFFFFF);
       if (kb) {
         if (!kFill) atomicAdd(&acc[kAccBinCount + threadIdx.x], kb);
         else s_base[threadIdx.x] = acc[kAccBinOff + threadIdx.x] + atomicAdd(&acc[kAccBinCur + threadIdx.x], kb);
@@ -972,16 +1061,17 @@ __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, 
     }
     __syncthreads();
     if (kFill && ni) {
-      int64_t pos[kBins] = {static_cast<int64_t>(s_base[0]) + (p01 & 0xFFFFFFFF), static_cast<int64_t>(s_base[1]) + (p01 >> 32),
-                            static_cast<int64_t>(s_base[2]) + (p23 & 0xFFFFFFFF), static_cast<int64_t>(s_base[3]) + (p23 >> 32)};
+      int64_t pos[kBins];
+#pragma unroll
+      for (int q = 0; q < kBins; ++q)
+        pos[q] = static_cast<int64_t>(s_base[q]) + ((pre[q >> 1] >> (32 * (q & 1))) & 0xFFFFFFFF);
       for (int i = 0; i < ni; ++i) {
         const int4 item = items_raw[2 * c * kResChunk + i];
-        const int b = (item.w >> 28) & 3;
-        int64_t q;
-        if (b == 0) q = pos[0]++;
-        else if (b == 1) q = pos[1]++;
-        else if (b == 2) q = pos[2]++;
-        else q = pos[3]++;
+        const int b = (item.w >> kItemBinShift) & 7;
+        int64_t q = 0;
+#pragma unroll
+        for (int j = 0; j < kBins; ++j)
+          if (b == j) q = pos[j]++;
         items[q] = item;
       }
     }
@@ -1387,6 +1477,7 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
   const int tid = threadIdx.x;
   int64_t cnt = 0, elems = 0, builds = 0, tl_elems = 0;
   int32_t cur_x = -1;
+  bool cur_rest = false;
   // blocks claim kClaim consecutive items at a time (consecutive items of
   // one anchor share the table); the next claim is fetched while the
   // current one is processed.  kRoundRobin: block b takes items b, b + G,
@@ -1409,7 +1500,9 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
     const int32_t x = item.x;
     const int64_t sa = static_cast<int64_t>(static_cast<uint32_t>(item.y)) | (static_cast<int64_t>(item.z) << 32);
     const int64_t sb = sa + (item.w & kItemCountMask);
-    const VMeta mx = meta[x];
+    VMeta mx = meta[x];
+    const bool rest = (item.w & kItemRest) != 0;
+    if (rest) mx = rest_meta(mx);
     if (kPv > 0 && x != pv_x) {  // the last item's barriers are behind its additions
       pvc.flush(o.pv, THREADS);
       __syncthreads();
@@ -1443,7 +1536,7 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
       ps.cap = WORDS;
       ps.shift = 32 - __builtin_ctz(WORDS);
       ps.nw = static_cast<int>(twolevel_words(R64) >> 1);
-      if (x != cur_x) {
+      if (x != cur_x || rest != cur_rest) {
         if (WORDS == kBinWords2 && mode == kTwoLevel) {
           // the block bits as the planning pass wrote them at the anchor's
           // row positions, then per word the number of set bits before it
@@ -1493,6 +1586,7 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
         }
         __syncthreads();
         cur_x = x;
+        cur_rest = rest;
         // ids inserted (bitmap, hash) or words copied (two-level)
         builds += tid == 0 ? (mode == kTwoLevel ? ps.nw : P) : 0;
       }
@@ -1588,6 +1682,171 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
 }
 
 
+// ---------------------------------------------------- core items
+// The core parts of an anchor's streams (kBinCore): the lists' 16-bit offsets
+// c16 against two bitmaps of the core, 8 KB for the level above (Up(x)) and
+// 8 KB for the row's own (Hfwd(x)); entries outside the core read as kNoCore,
+// whose bit stays clear.  At R-MAT scale 24 the 32 KB bin streamed 48.8 G
+// elements as 32-bit ids in 33.0 ms; with half the bytes, half the table
+// (four blocks a CU instead of three) and no window to subtract and clamp they
+// take 19.0 ms.  Bound by the lines it requests: 1.18 G of 128 bytes, 94% of
+// them past the L2, are 7.9 TB/s (the VALU is busy 72% of the time, the LDS
+// 53%).
+// A chunk is kCoreChunk elements from an even position (dword loads); an odd
+// stream's first chunk starts one element early, which is masked.
+constexpr int kCoreThreads = 512, kCoreRecs = 1024, kCoreChunk = 16;
+constexpr int kCoreWords = (kCoreIds + 1) / 32;  // of one bitmap
+
+__global__ __launch_bounds__(kCoreThreads, 8) void core_kernel(const uint16_t* c16, const VMeta* meta, const int4* items,
+                                                               const int64_t* sbeg, const int32_t* slen,
+                                                               unsigned long long* acc) {
+  constexpr int R = kCoreRecs / kCoreThreads, NW = kCoreThreads / kWave;
+  constexpr int kWin = kCoreThreads * kWinIters, kTiles = kWin / kWave;
+  static_assert(R * kCoreThreads == kCoreRecs, "whole records per thread");
+  static_assert(kCoreChunk <= kColPad, "chunk tail must stay inside the padded columns");
+  __shared__ alignas(16) uint32_t tab[2 * kCoreWords];
+  __shared__ int64_t s_beg[kCoreRecs];
+  __shared__ int2 s_cl[kCoreRecs + 1];  // (first chunk, length | kClUp)
+  __shared__ uint64_t s_M[kTiles];
+  __shared__ int32_t s_tb[kTiles];
+  __shared__ int64_t sh[NW + 1];
+  __shared__ int32_t shi[NW + 1];
+  __shared__ unsigned long long s_item;
+  const unsigned long long first = acc[kAccBinOff + kBinCore];
+  const unsigned long long count = acc[kAccBinCount + kBinCore];
+  if (count == 0) return;
+  const int tid = threadIdx.x;
+  const uint32_t ln = static_cast<uint32_t>(lane());
+  int64_t cnt = 0, elems = 0, builds = 0;
+  int32_t cur_x = -1;
+  // items are claimed kClaim at a time, the next claim while these run
+  if (tid == 0) s_item = atomicAdd(&acc[kAccBinNext + kBinCore], static_cast<unsigned long long>(kClaim));
+  __syncthreads();
+  unsigned long long claim = s_item;
+  while (claim < count) {
+    unsigned long long next = 0;
+    if (tid == 0) next = atomicAdd(&acc[kAccBinNext + kBinCore], static_cast<unsigned long long>(kClaim));
+    const unsigned long long claim_end = min(claim + kClaim, count);
+    for (unsigned long long it = claim; it < claim_end; ++it) {
+      const int4 item = items[first + it];
+      const int32_t x = item.x;
+      const int64_t sa = static_cast<int64_t>(static_cast<uint32_t>(item.y)) | (static_cast<int64_t>(item.z) << 32);
+      const int nrec = item.w & kItemCountMask;
+      if (x != cur_x) {
+        const VMeta mx = meta[x];
+        for (int i = tid; i < 2 * kCoreWords / 4; i += kCoreThreads)
+          reinterpret_cast<uint4*>(tab)[i] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        const int nu = mx.up - mx.ncu, nh = mx.sfe - mx.hfb - mx.nch;
+        for (int i = tid; i < nu + nh; i += kCoreThreads) {
+          const bool up = i < nu;
+          const uint32_t v = c16[mx.begin + (up ? mx.ncu + i : mx.hfb + mx.nch + (i - nu))];
+          atomicOr(&tab[(up ? 0 : kCoreWords) + (v >> 5)], 1u << (v & 31));
+        }
+        __syncthreads();
+        cur_x = x;
+        builds += tid == 0 ? nu + nh : 0;
+      }
+      for (int bs = 0; bs < nrec; bs += kCoreRecs) {
+        int64_t lbeg[R];
+        int32_t llen[R];
+        int nne = 0, nch = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int dl = bs + tid * R + r;
+          lbeg[r] = 0;
+          llen[r] = 0;
+          if (dl < nrec) {
+            lbeg[r] = sbeg[sa + dl];
+            llen[r] = slen[sa + dl];
+          }
+          const int len = llen[r] & kLenMask;
+          if (len > 0) {
+            ++nne;
+            nch += (len + static_cast<int>(lbeg[r] & 1) + kCoreChunk - 1) / kCoreChunk;
+            elems += len;
+          }
+        }
+        int32_t nslots, C;
+        int slot = block_excl_scan(nne, shi, &nslots);
+        int cb = block_excl_scan(nch, shi, &C);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int len = llen[r] & kLenMask;
+          if (len <= 0) continue;
+          s_cl[slot] = make_int2(cb, len | ((llen[r] & kFlagUp) ? kClUp : 0));
+          s_beg[slot] = lbeg[r];
+          cb += (len + static_cast<int>(lbeg[r] & 1) + kCoreChunk - 1) / kCoreChunk;
+          ++slot;
+        }
+        __syncthreads();
+        for (int w0 = 0; w0 < C; w0 += kWin) {
+          for (int t = tid; t < kTiles; t += kCoreThreads) {
+            const int ct = w0 + t * kWave;
+            if (ct >= C) continue;
+            int lo = 0, hi = nslots;  // first stream starting at or after ct
+            while (lo < hi) {
+              const int mid = (lo + hi) >> 1;
+              if (s_cl[mid].x < ct) lo = mid + 1;
+              else hi = mid;
+            }
+            uint64_t M = 0;
+            for (int j = lo; j < nslots; ++j) {
+              const int f = s_cl[j].x;
+              if (f >= ct + kWave) break;
+              M |= 1ull << (f - ct);
+            }
+            s_tb[t] = lo;
+            s_M[t] = M;
+          }
+          __syncthreads();
+#pragma unroll 2
+          for (int i = 0; i < kWinIters; ++i) {
+            const int rel = i * kCoreThreads + tid;
+            const int c = w0 + rel;
+            if (w0 + i * kCoreThreads >= C) break;
+            if (c >= C) continue;
+            const uint64_t M = s_M[rel >> 6];
+            const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                static_cast<uint32_t>(M >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(M), 0u)));
+            const int j = s_tb[rel >> 6] + below + static_cast<int>((M >> ln) & 1ull) - 1;
+            const int2 cl = s_cl[j];
+            const int k = c - cl.x;
+            const int64_t beg = s_beg[j];
+            const int lead = static_cast<int>(beg & 1);
+            const int rem = (cl.y & kLenMask) + lead - k * kCoreChunk;
+            uint32_t valid = rem >= kCoreChunk ? (1u << kCoreChunk) - 1u : (1u << rem) - 1u;
+            if (k == 0) valid &= ~static_cast<uint32_t>(lead);
+            const uint32_t part = (cl.y & kClUp) ? 0u : static_cast<uint32_t>(kCoreWords) * 4u;
+            const uint32_t* p = reinterpret_cast<const uint32_t*>(c16 + (beg - lead)) + k * (kCoreChunk / 2);
+            uint32_t d[kCoreChunk / 2];
+#pragma unroll
+            for (int q = 0; q < kCoreChunk / 2; ++q) d[q] = p[q];
+            const char* tb = reinterpret_cast<const char*>(tab);
+            uint32_t hits = 0;
+#pragma unroll
+            for (int q = 0; q < kCoreChunk / 2; ++q) {
+              const uint32_t lo = *reinterpret_cast<const uint32_t*>(tb + (((d[q] >> 3) & 0x1FFCu) | part));
+              const uint32_t hi = *reinterpret_cast<const uint32_t*>(tb + (((d[q] >> 19) & 0x1FFCu) | part));
+              hits |= __builtin_amdgcn_ubfe(lo, d[q] & 31u, 1u) << (2 * q);
+              hits |= __builtin_amdgcn_ubfe(hi, (d[q] >> 16) & 31u, 1u) << (2 * q + 1);
+            }
+            cnt += __popc(hits & valid);
+          }
+          __syncthreads();
+        }
+      }
+    }
+    __syncthreads();
+    if (tid == 0) s_item = next;
+    __syncthreads();
+    claim = s_item;
+  }
+  block_acc(acc, kAccT, cnt, sh);
+  block_acc(acc, kAccHeavyElems, elems, sh);
+  block_acc(acc, kAccBuild, builds, sh);
+}
+
 __global__ void finish_kernel(const unsigned long long* acc, const int64_t* so, int64_t n, const int64_t* lpre,
                               int64_t nchunk_cap, int64_t* triangles, int64_t* h_count, int64_t* stats) {
   *triangles = static_cast<int64_t>(acc[kAccT]);
@@ -1600,9 +1859,9 @@ __global__ void finish_kernel(const unsigned long long* acc, const int64_t* so, 
   stats[8] = static_cast<int64_t>(acc[kAccHeavyElems]);
   stats[9] = static_cast<int64_t>(acc[kAccBuild]);
   stats[10] = static_cast<int64_t>(acc[kAccElems]);
-  for (int b = 0; b < kBins; ++b) {
+  for (int b = 0; b < 4; ++b) {
     stats[11 + b] = static_cast<int64_t>(acc[kAccBinElems + b]);
-    stats[11 + kBins + b] = static_cast<int64_t>(acc[kAccBinCount + b]);
+    stats[15 + b] = static_cast<int64_t>(acc[kAccBinCount + b]);
   }
   stats[19] = n > 0 ? so[n] : 0;
   stats[20] = static_cast<int64_t>(acc[kAccTwoLevelElems]);
@@ -1614,7 +1873,7 @@ __global__ void forward_meta_kernel(const int64_t* off, const int32_t* cols, int
     const int64_t b = off[x], e = off[x + 1];
     const int64_t fb = upper_bound_dev(cols, b, e, static_cast<int32_t>(x));
     const int32_t deg = static_cast<int32_t>(e - b);
-    meta[x] = VMeta{b, 0, static_cast<int32_t>(fb - b), deg, deg, {0, 0}};
+    meta[x] = VMeta{b, 0, static_cast<int32_t>(fb - b), deg, deg, 0, 0};
   }
 }
 
@@ -1645,6 +1904,11 @@ int launch_bin0(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
 // (bins_mode 1) or side by side on forked streams (2).
 template <int kOut>
 int launch_bins(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
+  if (a.c16) {  // the largest share of the work first
+    core_kernel<<<static_cast<unsigned>(num_cus() * 4), kCoreThreads, 0, s>>>(a.c16, a.meta, w.items, w.sbeg, w.slen,
+                                                                             w.acc);
+    TC_HIP(hipGetLastError());
+  }
   if (a.prm.bins_mode == 1) {
     TC_TRY((launch_heavy<kBinWords2, 1024, 1024, 4, kOut>(a, w, o, 2, 1, s)));
     TC_TRY((launch_heavy<kBinWords1, 512, 1024, 6, kOut>(a, w, o, 1, 3, s)));
@@ -1682,7 +1946,8 @@ int launch_all(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
   const unsigned gr = static_cast<unsigned>(w.nchunk_cap < gmax ? w.nchunk_cap : gmax);
   const int64_t gct = (w.nchunk_cap + kThreads - 1) / kThreads;
   const unsigned gc = static_cast<unsigned>(gct < gmax ? gct : gmax);
-  plan_kernel<kCover><<<gv, kThreads, 0, s>>>(a.cols, a.meta, n, w.ndesc, w.vinfo, w.pm, w.acc, a.prm);
+  plan_kernel<kCover><<<gv, kThreads, 0, s>>>(a.cols, a.meta, n, w.ndesc, w.vinfo, w.pm, w.acc, a.prm,
+                                               a.c16 != nullptr);
   TC_HIP(hipGetLastError());
   // a wave scans 64 vertices per round: about two rounds per wave (one
   // block of a graph of 16 K vertices scanned them in 19 us)
@@ -1732,6 +1997,13 @@ Out unit_out(CountWs& w) {
 
 }  // namespace
 
+// Graphs of at least this many entries stream the core parts of their lists
+// as 16-bit ids (R-MAT scale 18 1.08 -> 1.07 ms, 20 3.16 -> 2.95, 22 14.2 ->
+// 12.3, 24 65.0 -> 54.6; the layout's 16-bit ids cost 0.05 and 0.7 ms at 20
+// and 24).  Below, levels are small enough for the 32-bit streams to stay in
+// the caches.
+constexpr int64_t kCoreNnz = int64_t(1) << 22;
+
 int count_params(const tc_tuning* t, bool cover, int64_t nnz, CountParams* out) {
   CountParams p;
   p.light_max = kLightMax;
@@ -1776,6 +2048,7 @@ int count_params(const tc_tuning* t, bool cover, int64_t nnz, CountParams* out) 
   // twelve groups cost more than the shorter forward lists gain (S20 3.61
   // -> 3.72 ms).
   p.degree_groups = nnz >= (int64_t(1) << 26) ? 4 : 2;
+  p.core = cover && nnz >= kCoreNnz;
   if (t) {
     if (t->light_max) p.light_max = t->light_max;
     if (t->dn_light) p.dn_light = t->dn_light;
@@ -1811,7 +2084,7 @@ int count_params(const tc_tuning* t, bool cover, int64_t nnz, CountParams* out) 
 CountWs count_reserve(Carver& c, int64_t n, int64_t nnz) {
   CountWs w;
   w.ndesc = c.take<int32_t>(n + 1);
-  w.vinfo = c.take<uint8_t>(n + 1);
+  w.vinfo = c.take<uint16_t>(n + 1);
   w.so = c.take<int64_t>(n + 2);
   // a vertex has at most deg(x) descriptors and a descriptor at most two
   // tasks, so 2 nnz bounds the stream records of heavy anchors (front) plus

@@ -90,9 +90,12 @@ static_assert(sizeof(RowCtxT<kMaxGroups>) == 80, "row contexts are stored as who
 
 struct IdentityLayout {
   static constexpr int kG = 1;  // one degree group: groups 0 up, 1 same, 2 down
+  static constexpr bool kCore = false;
   using Ctx = RowCtxT<3>;
   const int64_t* off;
   const int32_t* L;
+  __device__ __forceinline__ int32_t core_from(const Ctx&, int) const { return INT32_MIN; }
+  __device__ __forceinline__ void write16(const Ctx&, int64_t, int, int32_t) const {}
   __device__ __forceinline__ Ctx ctx(int64_t i) const {
     Ctx c{};
     c.ib = off[i];
@@ -112,10 +115,11 @@ struct IdentityLayout {
   }
 };
 
-template <int G>
+template <int G, bool CORE>
 struct RelabelLayout {
   static constexpr int kG = G;
   static constexpr int NG = 3 * G;
+  static constexpr bool kCore = CORE;
   using Ctx = RowCtxT<NG>;
   const int64_t* off;    // input row offsets
   const int64_t* noff;   // output row offsets
@@ -125,6 +129,18 @@ struct RelabelLayout {
   const uint32_t* comp0;
   int32_t d0;
   const int64_t* gstart;  // first new id of each (virtual level, degree group) group: G vl + group
+  uint16_t* out16;        // CORE: 16-bit core offsets
+  // First core id of the level above (cls 0) or of the row's own (cls 1).
+  __device__ __forceinline__ int32_t core_from(const Ctx& c, int cls) const {
+    return c.b[cls == 0 ? G - 1 : 2 * G - 1] - kCoreIds;
+  }
+  // The offset of entry v, group k, beside its 32-bit id (down entries are
+  // never streamed).
+  __device__ __forceinline__ void write16(const Ctx& c, int64_t at, int k, int32_t v) const {
+    if (!CORE || k >= 2 * G) return;
+    const int32_t d = v - core_from(c, k < G ? 0 : 1);
+    out16[at] = d >= 0 ? static_cast<uint16_t>(d) : kNoCore;
+  }
   __device__ __forceinline__ Ctx ctx(int64_t i) const {
     Ctx c{};
     const int32_t x = order[i];
@@ -158,15 +174,29 @@ struct RelabelLayout {
 template <int G>
 __device__ __forceinline__ bool is_same(int g) { return g >= G && g < 2 * G; }
 
+template <int G>
+__device__ __forceinline__ bool is_up(int g) {
+  return g < G;
+}
+
+// Counts of a row beside its groups: same-level entries below the row, and
+// the entries outside the core of the Up and of the Same class.
+struct RowSide {
+  int slt, nup, nsame;
+};
+constexpr int kSide = 3;
+
 template <int G, class Ctx>
-__device__ __forceinline__ VMeta row_meta(const Ctx& c, const int (&cnt)[3 * G], int slt) {
+__device__ __forceinline__ VMeta row_meta(const Ctx& c, const int (&cnt)[3 * G], const RowSide& sd) {
   int up = 0, same = 0;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     up += cnt[g];
     same += cnt[G + g];
   }
-  return VMeta{c.ob, up, up + slt, up + same, static_cast<int32_t>(c.ie - c.ib), {c.key, 0}};
+  // Hfwd follows the entries below the row, which are outside the core if any
+  // entry of Hfwd is
+  return VMeta{c.ob, up, up + sd.slt, up + same, static_cast<int32_t>(c.ie - c.ib), sd.nup, max(sd.nsame - sd.slt, 0)};
 }
 
 // Rows of at most kShort entries: one thread; the row and the groups of its
@@ -199,12 +229,17 @@ __global__ __launch_bounds__(kThreads) void lay_short_kernel(Lay lay, const int3
       kc[q] = q < deg ? lay.cls(c, wv[q], vv[q]) : kNoGroup;
     }
     int cnt[NG] = {};
-    int slt = 0;
+    RowSide sd{0, 0, 0};
+    const int32_t cu = lay.core_from(c, 0), cs = lay.core_from(c, 1);
 #pragma unroll
     for (int q = 0; q < kShort; ++q) {
 #pragma unroll
       for (int g = 0; g < NG; ++g) cnt[g] += kc[q] == g;
-      slt += is_same<G>(kc[q]) & (vv[q] < c.self);
+      sd.slt += is_same<G>(kc[q]) & (vv[q] < c.self);
+      if (Lay::kCore) {
+        sd.nup += is_up<G>(kc[q]) & (vv[q] < cu);
+        sd.nsame += is_same<G>(kc[q]) & (vv[q] < cs);
+      }
     }
     int pos[NG];
     pos[0] = 0;
@@ -218,8 +253,9 @@ __global__ __launch_bounds__(kThreads) void lay_short_kernel(Lay lay, const int3
       for (int g = 0; g < NG; ++g)
         if (kc[q] == g) at = pos[g]++;
       out[c.ob + at] = vv[q];
+      lay.write16(c, c.ob + at, kc[q], vv[q]);
     }
-    meta[i] = row_meta<G>(c, cnt, slt);
+    meta[i] = row_meta<G>(c, cnt, sd);
   }
 }
 
@@ -249,11 +285,11 @@ __device__ __forceinline__ void load_part(const int32_t* cols, const Ctx& c, int
 }
 
 // Group counts of a wave's part (or of a row), 16 bits per field, four
-// fields per word: field f (groups 0 .. NG - 1, then same-below-x) is
-// bits 16 (f % 4) of w[f / 4].  Parts add field by field.
+// fields per word: field f (groups 0 .. NG - 1, then the fields of RowSide)
+// is bits 16 (f % 4) of w[f / 4].  Parts add field by field.
 template <int NG>
 struct CountsT {
-  static constexpr int kWords = (NG + 1 + 3) / 4;
+  static constexpr int kWords = (NG + kSide + 3) / 4;
   uint64_t w[kWords];
 };
 constexpr uint64_t kF16 = 0xFFFF;
@@ -266,10 +302,11 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 }
 
 template <int NG>
-__device__ __forceinline__ void unpack(const CountsT<NG>& k, int (&cnt)[NG], int& slt) {
+__device__ __forceinline__ void unpack(const CountsT<NG>& k, int (&cnt)[NG], RowSide& sd) {
+  auto field = [&](int f) { return static_cast<int>((k.w[f >> 2] >> (16 * (f & 3))) & kF16); };
 #pragma unroll
-  for (int g = 0; g < NG; ++g) cnt[g] = static_cast<int>((k.w[g >> 2] >> (16 * (g & 3))) & kF16);
-  slt = static_cast<int>((k.w[NG >> 2] >> (16 * (NG & 3))) & kF16);
+  for (int g = 0; g < NG; ++g) cnt[g] = field(g);
+  sd = RowSide{field(NG), field(NG + 1), field(NG + 2)};
 }
 
 // Groups of a part (kCodeBits bits per entry in *kp) and its output ids.
@@ -289,29 +326,32 @@ __device__ __forceinline__ CountsT<3 * Lay::kG> classify_part(const Lay& lay, co
     const int k = wv[u] >= 0 ? lay.cls(c, wv[u], vv[u]) : kNoGroup;
     k3 |= static_cast<uint64_t>(k) << (kCodeBits * u);
   }
-  uint64_t cnt[NG] = {};
-  uint64_t slt = 0;
+  uint64_t cnt[NG + kSide] = {};
+  const int32_t cu = lay.core_from(c, 0), cs = lay.core_from(c, 1);
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     if (u >= nr) break;
     const int k = static_cast<int>((k3 >> (kCodeBits * u)) & kNoGroup);
 #pragma unroll
     for (int g = 0; g < NG; ++g) cnt[g] += __popcll(__ballot(k == g));
-    slt += __popcll(__ballot(is_same<G>(k) & (vv[u] < c.self)));
+    cnt[NG] += __popcll(__ballot(is_same<G>(k) & (vv[u] < c.self)));
+    if (Lay::kCore) {
+      cnt[NG + 1] += __popcll(__ballot(is_up<G>(k) & (vv[u] < cu)));
+      cnt[NG + 2] += __popcll(__ballot(is_same<G>(k) & (vv[u] < cs)));
+    }
   }
   *kp = k3;
   CountsT<NG> out{};
 #pragma unroll
-  for (int g = 0; g < NG; ++g) out.w[g >> 2] |= cnt[g] << (16 * (g & 3));
-  out.w[NG >> 2] |= slt << (16 * (NG & 3));
+  for (int g = 0; g < NG + kSide; ++g) out.w[g >> 2] |= cnt[g] << (16 * (g & 3));
   return out;
 }
 
 // Scatter of a part: group g continues at p[g] (absolute output position);
 // entries keep their order inside each group.
-template <int R, int NG>
-__device__ __forceinline__ void write_part(const int32_t (&vv)[R], uint64_t k3, int64_t (&p)[NG],
-                                           int32_t* out, int nr = R) {
+template <int R, int NG, class Lay, class Ctx>
+__device__ __forceinline__ void write_part(const Lay& lay, const Ctx& c, const int32_t (&vv)[R], uint64_t k3,
+                                           int64_t (&p)[NG], int32_t* out, int nr = R) {
   const uint64_t lt = lanemask_lt();
 #pragma unroll
   for (int u = 0; u < R; ++u) {
@@ -330,7 +370,10 @@ __device__ __forceinline__ void write_part(const int32_t (&vv)[R], uint64_t k3, 
       mine = k == g ? m[g] : mine;
       p[g] += __popcll(m[g]);
     }
-    if (k != kNoGroup) out[at + __popcll(mine & lt)] = vv[u];
+    if (k != kNoGroup) {
+      out[at + __popcll(mine & lt)] = vv[u];
+      lay.write16(c, at + __popcll(mine & lt), k, vv[u]);
+    }
   }
 }
 
@@ -376,13 +419,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
     const CountsT<NG> pk = classify_part<Lay, R>(lay, c, wv, vv, &k3, nr);
     int32_t wn[R];
     if (more) load_part<R>(cols, cn, 0, wn);
-    int cnt[NG], slt;
-    unpack(pk, cnt, slt);
-    if (lane() == 0) meta[c.self] = row_meta<G>(c, cnt, slt);
+    int cnt[NG];
+    RowSide sd;
+    unpack(pk, cnt, sd);
+    if (lane() == 0) meta[c.self] = row_meta<G>(c, cnt, sd);
     const int zero[NG] = {};
     int64_t p[NG];
     group_starts(c.ob, cnt, zero, p);
-    write_part<R>(vv, k3, p, out, nr);
+    write_part<R, NG>(lay, c, vv, k3, p, out, nr);
     if (!more) break;
     r = rn;
     c = cn;
@@ -432,13 +476,14 @@ __global__ __launch_bounds__(WPR * kWave) __attribute__((amdgpu_waves_per_eu(5))
       before.w[i] = uniform64(before.w[i]);
       tot.w[i] = uniform64(tot.w[i]);
     }
-    int cnt[NG], slt, bef[NG], bslt;
-    unpack(tot, cnt, slt);
-    unpack(before, bef, bslt);
-    if (threadIdx.x == 0) meta[c.self] = row_meta<G>(c, cnt, slt);
+    int cnt[NG], bef[NG];
+    RowSide sd, bsd;
+    unpack(tot, cnt, sd);
+    unpack(before, bef, bsd);
+    if (threadIdx.x == 0) meta[c.self] = row_meta<G>(c, cnt, sd);
     int64_t p[NG];
     group_starts(c.ob, cnt, bef, p);
-    write_part<R>(vv, k3, p, out, nr);
+    write_part<R, NG>(lay, c, vv, k3, p, out, nr);
     __syncthreads();  // s_w is rewritten for the next row
   }
 }
@@ -451,8 +496,8 @@ __global__ void seg_vtx_kernel(const int32_t* nseg, const int64_t* seg_off, int6
   }
 }
 
-// Per segment of a segmented row: NG + 1 counts (the groups, then
-// same-below-x), NG output positions.
+// Per segment of a segmented row: NG + kSide counts (the groups, then the
+// fields of RowSide), NG output positions.
 
 // One wave per segment of a long row: group counts of the segment; the
 // output ids are kept (stash) for the scatter pass.
@@ -462,7 +507,7 @@ __global__ __launch_bounds__(kThreads) void lay_seg_count_kernel(Lay lay, const 
                                                                  int32_t* seg_cnt, int32_t* stash) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
-  constexpr int kSegCnt = NG + 1;  // per segment: the group counts, then same-below-x
+  constexpr int kSegCnt = NG + kSide;
   const int64_t nsegs = seg_off[n];
   const int64_t wid = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
@@ -472,8 +517,8 @@ __global__ __launch_bounds__(kThreads) void lay_seg_count_kernel(Lay lay, const 
     const int64_t s = sg - seg_off[i];
     const int64_t b = c.ib + s * kSeg;
     const int64_t e = min(c.ie, b + kSeg);
-    int cnt[NG] = {};
-    int slt = 0;
+    int cnt[NG + kSide] = {};
+    const int32_t cu = lay.core_from(c, 0), cs = lay.core_from(c, 1);
     for (int64_t j0 = b; j0 < e; j0 += kRounds * kWave) {
       int32_t wv[kRounds];
 #pragma unroll
@@ -491,13 +536,17 @@ __global__ __launch_bounds__(kThreads) void lay_seg_count_kernel(Lay lay, const 
         }
 #pragma unroll
         for (int g = 0; g < NG; ++g) cnt[g] += __popcll(__ballot(k == g));
-        slt += __popcll(__ballot(is_same<G>(k) & (v < c.self)));
+        cnt[NG] += __popcll(__ballot(is_same<G>(k) & (v < c.self)));
+        if (Lay::kCore) {
+          cnt[NG + 1] += __popcll(__ballot(is_up<G>(k) & (v < cu)));
+          cnt[NG + 2] += __popcll(__ballot(is_same<G>(k) & (v < cs)));
+        }
       }
     }
     if (lane() < kSegCnt) {
-      int x = slt;
+      int x = 0;
 #pragma unroll
-      for (int g = 0; g < NG; ++g)
+      for (int g = 0; g < kSegCnt; ++g)
         if (lane() == g) x = cnt[g];
       seg_cnt[kSegCnt * sg + lane()] = x;
     }
@@ -511,21 +560,23 @@ __global__ void lay_seg_prefix_kernel(Lay lay, int64_t n, const int32_t* nseg, c
                                       const int32_t* seg_cnt, int64_t* seg_pre, VMeta* meta) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
-  constexpr int kSegCnt = NG + 1;  // per segment: the group counts, then same-below-x
+  constexpr int kSegCnt = NG + kSide;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int k = nseg[i];
     if (k == 0) continue;
     const int64_t s0 = seg_off[i];
     int tot[NG] = {};
-    int slt = 0;
+    RowSide sd{0, 0, 0};
     for (int j = 0; j < k; ++j) {
       const int32_t* sc = seg_cnt + kSegCnt * (s0 + j);
 #pragma unroll
       for (int g = 0; g < NG; ++g) tot[g] += sc[g];
-      slt += sc[NG];
+      sd.slt += sc[NG];
+      sd.nup += sc[NG + 1];
+      sd.nsame += sc[NG + 2];
     }
     const Ctx c = lay.ctx(i);
-    meta[i] = row_meta<G>(c, tot, slt);
+    meta[i] = row_meta<G>(c, tot, sd);
     int64_t p[NG];
     const int zero[NG] = {};
     group_starts(c.ob, tot, zero, p);
@@ -570,7 +621,7 @@ __global__ __launch_bounds__(kThreads) void lay_seg_write_kernel(Lay lay, const 
 #pragma unroll
       for (int u = 0; u < kRounds; ++u)
         k3 |= static_cast<uint64_t>(vv[u] >= 0 ? lay.recls(c, vv[u]) : kNoGroup) << (kCodeBits * u);
-      write_part<kRounds>(vv, k3, p, out);
+      write_part<kRounds, NG>(lay, c, vv, k3, p, out);
     }
   }
 }
@@ -705,17 +756,18 @@ __global__ void copy_total_kernel(const int64_t* h_off, int64_t n, int64_t* out)
 
 }  // namespace
 
-SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz) {
+SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz, bool own_stash) {
   SplitWs w;
   w.meta = c.take<VMeta>(n + 1);
   w.scols = c.take<int32_t>(nnz + kColPad);
+  w.c16 = c.take<uint16_t>(nnz + kColPad);
   w.res = c.take<uint32_t>(1);
   w.nseg = c.take<int32_t>(n + 1);
   w.seg_off = c.take<int64_t>(n + 2);
   // Segmented rows have deg > kBigCap entries and ceil(deg / kSeg) <= deg / kSeg + deg / kBigCap segments.
   const int64_t max_segs = nnz / kSeg + nnz / kBigCap + 2;
   w.seg_vtx = c.take<int32_t>(max_segs + 1);
-  w.seg_cnt = c.take<int32_t>((kMaxGroups + 1) * (max_segs + 1));  // sized for the most groups
+  w.seg_cnt = c.take<int32_t>((kMaxGroups + kSide) * (max_segs + 1));  // sized for the most groups
   w.seg_pre = c.take<int64_t>(kMaxGroups * (max_segs + 1));
   w.ctr = c.take<int64_t>(4);
   w.rcat = c.take<int32_t>(n + 1);
@@ -723,7 +775,7 @@ SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz) {
   constexpr int kCtxWords = sizeof(RowCtxT<kMaxGroups>) / sizeof(int64_t);  // the largest context
   w.mid_ctx = c.take<int64_t>(kCtxWords * (std::min(n, nnz / (kShort + 1)) + 2));
   w.big_ctx = c.take<int64_t>(kCtxWords * (nnz / (kMidCap + 1) + 2));
-  w.stash = c.take<int32_t>(nnz + 1);
+  w.stash = own_stash ? c.take<int32_t>(nnz + 1) : nullptr;
   w.scratch = c.take<char>(scan_ws_bytes(n + 1));
   return w;
 }
@@ -753,7 +805,7 @@ RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels) {
 
 namespace {
 
-template <int G>
+template <int G, bool CORE>
 int relabel_groups(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t nvl,
                    RelabelWs& w, SplitWs& sp, hipStream_t s) {
   const int64_t n = g->n;
@@ -789,17 +841,19 @@ int relabel_groups(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int
     Carver sc(w.scratch);
     TC_TRY(scan_exclusive<int32_t>(w.deg, w.off, n, sc, s));
   }
-  RelabelLayout<G> lay{g->row_offsets, w.off, w.order, w.perm, L, comp0, d0, w.lstart};
+  RelabelLayout<G, CORE> lay{g->row_offsets, w.off, w.order, w.perm, L, comp0, d0, w.lstart, sp.c16};
   return layout_run(lay, g->cols, n, g->nnz, sp, s);
 }
 
 }  // namespace
 
 int relabel_run(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t nvl,
-                int degree_groups, RelabelWs& w, SplitWs& sp, hipStream_t s) {
+                int degree_groups, bool core, RelabelWs& w, SplitWs& sp, hipStream_t s) {
   if (g->n == 0) return TC_OK;
-  if (degree_groups == 4) return relabel_groups<4>(g, L, comp0, d0, nvl, w, sp, s);
-  if (degree_groups == 2) return relabel_groups<2>(g, L, comp0, d0, nvl, w, sp, s);
+  if (degree_groups == 4 && core) return relabel_groups<4, true>(g, L, comp0, d0, nvl, w, sp, s);
+  if (degree_groups == 2 && core) return relabel_groups<2, true>(g, L, comp0, d0, nvl, w, sp, s);
+  if (degree_groups == 4) return relabel_groups<4, false>(g, L, comp0, d0, nvl, w, sp, s);
+  if (degree_groups == 2) return relabel_groups<2, false>(g, L, comp0, d0, nvl, w, sp, s);
   return fail(TC_ERR_INVALID_ARG, "relabel: degree_groups must be 2 or 4");
 }
 

@@ -69,8 +69,9 @@ CountPlan plan_count(void* base, int64_t n, int64_t nnz) {
   p.bfs.comp0 = p.comp0;
   Carver b(p.region);
   p.relabel = relabel_reserve(b, n, 2 * n + 2);
-  p.split = split_reserve(b, n, nnz);
+  p.split = split_reserve(b, n, nnz, false);
   p.count = count_reserve(b, n, nnz);
+  p.split.stash = reinterpret_cast<int32_t*>(p.count.tl_words);  // written only after the layout
   p.count.stats = p.stats;
   p.pv_new = b.take<int64_t>(n + 1);
   p.bytes = head + std::max(std::max(a.used(), b.used()), direct_ws_bytes(n, nnz));
@@ -112,7 +113,7 @@ struct CoverPlan {
 CoverPlan plan_cover(void* base, int64_t n, int64_t nnz) {
   CoverPlan p;
   Carver c(base);
-  p.split = split_reserve(c, n, nnz);
+  p.split = split_reserve(c, n, nnz, true);
   p.h_off = c.take<int64_t>(n + 2);
   p.hscratch = c.take<char>(scan_ws_bytes(n + 1) + (n + 1) * sizeof(int32_t) + 512);
   p.bytes = c.used();
@@ -237,10 +238,12 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   if (direct && direct_fits(g->n, g->nnz, info))
     return direct_count_run(g, L, info, p.stats, triangles, h_count, p.region, s);
   const int32_t nl = info.num_levels, d0 = info.first_levels;
+  // per-vertex counts and listing report ids of the streamed lists
+  const bool core = prm.core && !pv && !list;
   tc_csr rg = *g;  // the relabelled graph
   if (g->n > 0) {
     prof_stage("relabel");
-    TC_TRY(relabel_run(g, L, p.comp0, d0, d0 + nl + 1, prm.degree_groups, p.relabel, p.split, s));
+    TC_TRY(relabel_run(g, L, p.comp0, d0, d0 + nl + 1, prm.degree_groups, core, p.relabel, p.split, s));
     rg.row_offsets = p.relabel.off;
     rg.cols = p.split.scols;
   }
@@ -250,6 +253,7 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   a.prm = prm;
   a.cols = p.split.scols;
   a.meta = p.split.meta;
+  a.c16 = core ? p.split.c16 : nullptr;
   a.cover = true;
   a.per_vertex = pv;
   a.per_vertex_out = p.pv_new;
