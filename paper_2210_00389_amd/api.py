@@ -207,8 +207,8 @@ def count(g: Graph, root: int = -1, per_vertex: bool = False, validate: bool = F
     from .batch import make_tuning
     lib = L.load()
     dev = g.cols.device
-    res = out or CountResult(torch.zeros(1, dtype=torch.int64, device=dev),
-                             torch.zeros(1, dtype=torch.int64, device=dev),
+    res = out or CountResult(torch.empty(1, dtype=torch.int64, device=dev),
+                             torch.empty(1, dtype=torch.int64, device=dev),
                              torch.empty(max(g.n, 1), dtype=torch.int32, device=dev) if return_levels else None,
                              torch.empty(max(g.n, 1), dtype=torch.int64, device=dev) if per_vertex else None)
     flags = (L.TC_VALIDATE if validate else 0) | (L.TC_PER_VERTEX if per_vertex else 0)

@@ -33,9 +33,10 @@ namespace {
 
 constexpr int kBfsThreads = 1024;
 constexpr uint16_t kUnvisited = 0xFFFF;
-constexpr int kBigDeg = 64;      // frontier vertices above this degree are expanded by a wave
-constexpr int kBigCap = 1024;    // LDS list of such vertices per pass (overflow: expanded by the thread)
-constexpr int kRowLoads = 8;     // row entries a thread loads at once in the level passes
+constexpr int kFrontCap = 2048;  // frontier vertices of a top-down level (at most n / 32 there)
+constexpr int kRowLanes = 16;    // lanes that expand a frontier row together
+constexpr int kRowLoads = 8;     // row entries a thread loads at once in a bottom-up level
+constexpr int kRestCap = 6144;   // unreached vertices of other components levelled together (LDS left beside L)
 constexpr int kPieceMin = 1024;  // smallest piece size a caller may ask for
 constexpr int kAutoMin = 16;     // smallest and largest piece size chosen by auto_piece
 constexpr int kTile = 512;       // entries of a piece counted together (their streams are kept in LDS)
@@ -50,38 +51,53 @@ __device__ __forceinline__ int64_t block_max_i64(int64_t v, int64_t* sh) {
   const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
   if (lane() == 0) sh[w] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t m = sh[0];
-    for (int i = 1; i < nw; ++i) m = sh[i] > m ? sh[i] : m;
-    sh[nw] = m;
-  }
-  __syncthreads();
-  const int64_t r = sh[nw];
+  const int64_t r = wave_max(lane() < nw ? sh[lane()] : sh[0]);
   __syncthreads();
   return r;
 }
 
-// Level-synchronous BFS over the vertices already set to level `base`
-// (the roots), with L resident in LDS.
-__device__ void bfs_levels_lds(uint16_t* L, const int64_t* rows, const int32_t* cols, int n, int* s_cnt,
-                               int32_t* s_big, int* s_nbig, int roots) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int wv = tid / kWave, nw = nt / kWave, ln = lane();
+// LDS of a level block.  L is the level array; the rest beside it serves the
+// frontier of a top-down level and, at other times, the unreached vertices.
+struct LevelLds {
+  uint16_t L[TC_BATCH_MAX_N];
+  union {
+    uint16_t front[kFrontCap];
+    struct {
+      uint16_t v[kRestCap];    // an unreached vertex
+      uint16_t low[kRestCap];  // the smallest vertex known of its component
+    } rest;
+  };
+  int64_t sh[kBfsThreads / kWave + 1];
+  int cnt, num;
+};
+
+// Level-synchronous BFS from `root` (level 0, set by the caller), with L
+// resident in LDS.
+__device__ void bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
+  const int tid = threadIdx.x, nt = blockDim.x, ln = lane();
+  uint16_t* L = s.L;
   int level = 0;
-  int last = roots;  // vertices found at the previous level
+  int last = 1;  // vertices found at the previous level
   for (;;) {
-    const bool bottom_up = last > n / 32;
-    if (tid == 0) {
-      *s_cnt = 0;
-      *s_nbig = 0;
-    }
+    bool bottom_up = last > n / 32;
+    if (tid == 0) s.cnt = s.num = 0;
     __syncthreads();
     int found = 0;
     const uint16_t cur = static_cast<uint16_t>(level), nxt = static_cast<uint16_t>(level + 1);
-    // rows are read kRowLoads entries at a time (independent loads in
-    // flight together); a bottom-up scan stops after the group holding the
-    // first parent
+    if (!bottom_up) {
+      // the frontier is listed; with the same level of components searched
+      // before it may not fit (an unvisited vertex has no neighbour there)
+      for (int i = tid; i < n; i += nt)
+        if (L[i] == cur) {
+          const int q = atomicAdd(&s.num, 1);
+          if (q < kFrontCap) s.front[q] = static_cast<uint16_t>(i);
+        }
+      __syncthreads();
+      bottom_up = s.num > kFrontCap;
+    }
     if (bottom_up) {
+      // rows are read kRowLoads entries at a time (independent loads in
+      // flight together) and left after the group holding the first parent
       for (int i = tid; i < n; i += nt) {
         if (L[i] != kUnvisited) continue;
         const int64_t e = rows[i + 1];
@@ -100,44 +116,18 @@ __device__ void bfs_levels_lds(uint16_t* L, const int64_t* rows, const int32_t* 
         }
       }
     } else {
-      for (int i = tid; i < n; i += nt) {
-        if (L[i] != cur) continue;
-        const int64_t b = rows[i], e = rows[i + 1];
-        if (e - b > kBigDeg) {
-          const int q = atomicAdd(s_nbig, 1);
-          if (q < kBigCap) {
-            s_big[q] = i;
-            continue;
-          }
-        }
-        for (int64_t k = b; k < e; k += kRowLoads) {
-          int32_t w[kRowLoads];
-#pragma unroll
-          for (int q = 0; q < kRowLoads; ++q) w[q] = k + q < e ? cols[k + q] : -1;
-#pragma unroll
-          for (int q = 0; q < kRowLoads; ++q)
-            if (w[q] >= 0 && L[w[q]] == kUnvisited) {
-              L[w[q]] = nxt;
-              ++found;
-            }
-        }
-      }
-      __syncthreads();
-      const int nbig = min(*s_nbig, kBigCap);
-      // a listed row is expanded by one wave, kRowLoads entries a lane at a
-      // time (independent loads in flight)
-      for (int q = wv; q < nbig; q += nw) {
-        const int i = s_big[q];
+      // kRowLanes lanes expand a row together
+      const int m = s.num;
+      const int sub = tid % kRowLanes;
+      for (int q = tid / kRowLanes; q < m; q += nt / kRowLanes) {
+        const int i = s.front[q];
         const int64_t e = rows[i + 1];
-        for (int64_t k0 = rows[i] + ln; k0 < e; k0 += static_cast<int64_t>(kWave) * kRowLoads) {
-          int32_t w[kRowLoads];
+        for (int64_t k0 = rows[i] + sub; k0 < e; k0 += kRowLanes * 4) {
+          int32_t w[4];
 #pragma unroll
-          for (int u = 0; u < kRowLoads; ++u) {
-            const int64_t k = k0 + static_cast<int64_t>(u) * kWave;
-            w[u] = k < e ? cols[k] : -1;
-          }
+          for (int u = 0; u < 4; ++u) w[u] = k0 + u * kRowLanes < e ? cols[k0 + u * kRowLanes] : -1;
 #pragma unroll
-          for (int u = 0; u < kRowLoads; ++u)
+          for (int u = 0; u < 4; ++u)
             if (w[u] >= 0 && L[w[u]] == kUnvisited) {
               L[w[u]] = nxt;
               ++found;
@@ -148,37 +138,97 @@ __device__ void bfs_levels_lds(uint16_t* L, const int64_t* rows, const int32_t* 
     // `found` may count a vertex more than once in the top-down pass (two
     // parents in one level); it only steers the direction and the stop test
     found = wave_sum(found);
-    if (ln == 0 && found) atomicAdd(s_cnt, found);
+    if (ln == 0 && found) atomicAdd(&s.cnt, found);
     __syncthreads();
-    last = *s_cnt;
+    last = s.cnt;
     __syncthreads();
     if (last == 0) break;
     ++level;
   }
 }
 
-// root0 >= 0 replaces the default root of graph 0 (the one-graph path of
-// tc_count); batches pass -1.
-__global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* vbase, const int64_t* row_offsets,
-                                                                const int32_t* cols, int32_t* levels, uint32_t* parity,
-                                                                int64_t* T, int64_t* H, int32_t root0) {
-  __shared__ uint16_t L[TC_BATCH_MAX_N];
-  __shared__ int32_t s_big[kBigCap];
-  __shared__ int64_t sh[kBfsThreads / kWave + 1];
-  __shared__ int s_cnt, s_nbig;
-  const int g = blockIdx.x;
+// The remaining components together, when they hold at most kRestCap
+// vertices: L of a listed vertex is its place in the list while the smallest
+// vertex of every component spreads through it (each pass also jumps to the
+// label of the label), then levels from those vertices.  One search per
+// component instead took 0.94 ms on a Chung-Lu graph of 8001 vertices and mean
+// degree 6, whose hundreds of small components each cost passes over all
+// vertices.  Returns false if there are more.
+__device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
   const int tid = threadIdx.x, nt = blockDim.x;
-  const int64_t v0 = vbase[g];
-  const int n = static_cast<int>(vbase[g + 1] - v0);
+  uint16_t* L = s.L;
+  if (tid == 0) s.num = 0;
+  __syncthreads();
+  for (int i = tid; i < n; i += nt)
+    if (L[i] == kUnvisited) {
+      const int q = atomicAdd(&s.num, 1);
+      if (q < kRestCap) s.rest.v[q] = static_cast<uint16_t>(i);
+    }
+  __syncthreads();
+  const int m = s.num;
+  if (m > kRestCap) return false;
+  if (m == 0) return true;
+  for (int q = tid; q < m; q += nt) {
+    s.rest.low[q] = s.rest.v[q];
+    L[s.rest.v[q]] = static_cast<uint16_t>(q);
+  }
+  // a neighbour of an unreached vertex is unreached, so L of it is a place
+  // (min: in a list that is not symmetric it may be a level)
+  auto place = [&](int v) { return min(static_cast<int>(L[v]), m - 1); };
+  for (int more = 1; more;) {
+    __syncthreads();
+    int changed = 0;
+    for (int q = tid; q < m; q += nt) {
+      const int v = s.rest.v[q];
+      const int was = s.rest.low[q];
+      int low = was;
+      for (int64_t k = rows[v], e = rows[v + 1]; k < e; ++k) low = min(low, static_cast<int>(s.rest.low[place(cols[k])]));
+      low = min(low, static_cast<int>(s.rest.low[place(low)]));
+      if (low < was) {
+        s.rest.low[q] = static_cast<uint16_t>(low);
+        changed = 1;
+      }
+    }
+    more = __syncthreads_or(changed);
+  }
+  for (int q = tid; q < m; q += nt) {
+    const int v = s.rest.v[q];
+    L[v] = s.rest.low[q] == v ? 0 : kUnvisited;
+  }
+  for (int level = 0, more = 1; more; ++level) {
+    __syncthreads();
+    int found = 0;
+    for (int q = tid; q < m; q += nt) {
+      const int v = s.rest.v[q];
+      if (L[v] != level) continue;
+      for (int64_t k = rows[v], e = rows[v + 1]; k < e; ++k)
+        if (L[cols[k]] == kUnvisited) {
+          L[cols[k]] = static_cast<uint16_t>(level + 1);
+          found = 1;
+        }
+    }
+    more = __syncthreads_or(found);
+  }
+  return true;
+}
+
+// Levels of graph g (its vertices v0 .. v0 + n - 1), one block.  root0 >= 0
+// replaces the default root.
+__device__ void graph_levels(LevelLds& s, int g, int64_t v0, int64_t n64, const int64_t* row_offsets,
+                             const int32_t* cols, int32_t* levels, uint32_t* parity, int64_t* T, int64_t* H,
+                             int32_t root0) {
+  uint16_t* L = s.L;
+  const int tid = threadIdx.x, nt = blockDim.x;
   const int64_t* rows = row_offsets + v0;  // rows[i] = global position of local row i
   // a graph beyond the on-chip level array is skipped and flagged with -1
   // (the host rejects it first when validation is on); it gets no pieces
-  const bool too_big = n > TC_BATCH_MAX_N;
+  const bool too_big = n64 > TC_BATCH_MAX_N;
   if (tid == 0) {
     T[g] = too_big ? -1 : 0;
     if (H) H[g] = too_big ? -1 : 0;
   }
-  if (n <= 0 || too_big) return;
+  if (n64 <= 0 || too_big) return;
+  const int n = static_cast<int>(n64);
   // root: highest degree, smallest id on ties; isolated vertices get level 0
   int64_t key = -1;
   for (int i = tid; i < n; i += nt) {
@@ -187,44 +237,47 @@ __global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* v
     const int64_t k = (d << 32) | static_cast<int64_t>(0xFFFFFFFFu - static_cast<uint32_t>(i));
     key = k > key ? k : key;
   }
-  key = block_max_i64(key, sh);
-  const int root = (g == 0 && root0 >= 0 && root0 < n)
-                       ? root0
-                       : static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key & 0xFFFFFFFF));
-  __syncthreads();
+  key = block_max_i64(key, s.sh);
+  const int root = root0 >= 0 && root0 < n ? root0
+                                           : static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key & 0xFFFFFFFF));
   if (tid == 0) L[root] = 0;  // a given root of degree 0 is level 0 already
   __syncthreads();
-  bfs_levels_lds(L, rows, cols, n, &s_cnt, s_big, &s_nbig, 1);
-  // remaining components, each from its smallest unvisited id; every id
-  // below the last such root is visited, so each scan starts there
+  bfs_levels_lds(s, rows, cols, n);
+  // remaining components: together if they are few vertices, else one search
+  // from the smallest unvisited id until they are; every id below the last
+  // such root is visited, so each scan starts there
   int from = 0;
-  for (;;) {
+  while (!rest_levels_lds(s, rows, cols, n)) {
     int64_t cand = -1;  // max of (n - i) over unvisited i = smallest i
     for (int i = from + tid; i < n; i += nt)
       if (L[i] == kUnvisited) {
         cand = n - i;
         break;
       }
-    cand = block_max_i64(cand, sh);
-    if (cand < 0) break;
+    cand = block_max_i64(cand, s.sh);
     from = static_cast<int>(n - cand);
     if (tid == 0) L[from] = 0;
     __syncthreads();
-    bfs_levels_lds(L, rows, cols, n, &s_cnt, s_big, &s_nbig, 1);
+    bfs_levels_lds(s, rows, cols, n);
   }
-  // outputs: parity bits, levels
+  __syncthreads();
+  // outputs: parity bits (a wave's 64 vertices are two words), levels
   uint32_t* par = parity + parity_base(v0, g);
-  const int words = (n + 31) / 32;
-  for (int wi = tid; wi < words; wi += nt) {
-    uint32_t b = 0;
-    for (int j = 0; j < 32; ++j) {
-      const int i = wi * 32 + j;
-      if (i < n) b |= static_cast<uint32_t>(L[i] & 1) << j;
-    }
-    par[wi] = b;
+  for (int i0 = tid - lane(); i0 < n; i0 += nt) {
+    const int i = i0 + lane();
+    const uint64_t odd = __ballot(i < n && (L[i] & 1));
+    if ((lane() & 31) == 0 && i < n) par[i >> 5] = static_cast<uint32_t>(odd >> lane());
   }
   if (levels)
     for (int i = tid; i < n; i += nt) levels[v0 + i] = L[i];
+}
+
+__global__ __launch_bounds__(kBfsThreads) void batch_bfs_kernel(const int64_t* vbase, const int64_t* row_offsets,
+                                                                const int32_t* cols, int32_t* levels, uint32_t* parity,
+                                                                int64_t* T, int64_t* H) {
+  __shared__ LevelLds s;
+  const int g = blockIdx.x;
+  graph_levels(s, g, vbase[g], vbase[g + 1] - vbase[g], row_offsets, cols, levels, parity, T, H, -1);
 }
 
 __device__ __forceinline__ uint32_t par_bit(const uint32_t* p, int32_t i) { return (p[i >> 5] >> (i & 31)) & 1u; }
@@ -258,17 +311,14 @@ struct OneGraph {
 };
 
 template <bool kRec>
-__global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* row_offsets, const int32_t* cols,
-                                  int64_t total_n, int64_t nslots, int piece, FwdRec* rec, int2* pieces,
-                                  OneGraph one) {
-  const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+__device__ void batch_prep(int64_t t0, int64_t stride, const int64_t* vbase, int G, const int64_t* row_offsets,
+                           const int32_t* cols, int64_t total_n, int64_t nslots, int piece, FwdRec* rec, int2* pieces,
+                           const OneGraph& one) {
   const bool single = one.vbase != nullptr;
-  if (single && blockIdx.x == 0) {
-    if (threadIdx.x < 2) one.vbase[threadIdx.x] = threadIdx.x ? one.n : 0;
-    if (threadIdx.x < 24)
-      one.stats[threadIdx.x] = threadIdx.x == 0 ? one.n : (threadIdx.x == 1 ? one.nnz : (threadIdx.x == 3 ? one.num_levels : 0));
-    if (one.L && threadIdx.x == 0) {
+  if (single) {
+    if (t0 < 2) one.vbase[t0] = t0 ? one.n : 0;
+    if (t0 < 24) one.stats[t0] = t0 == 0 ? one.n : (t0 == 1 ? one.nnz : (t0 == 3 ? one.num_levels : 0));
+    if (one.L && t0 == 0) {
       *one.T = 0;
       if (one.H) *one.H = 0;
     }
@@ -323,6 +373,35 @@ __global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* ro
     if (n > 0 && n <= max_n && p >= 0 && ps < rows[n])
       out = make_int2(g, static_cast<int>(upper_bound_dev(rows, 0, n + 1, ps)) - 1);
     pieces[s] = out;
+  }
+}
+
+template <bool kRec>
+__global__ void batch_prep_kernel(const int64_t* vbase, int G, const int64_t* row_offsets, const int32_t* cols,
+                                  int64_t total_n, int64_t nslots, int piece, FwdRec* rec, int2* pieces,
+                                  OneGraph one) {
+  batch_prep<kRec>(blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x, vbase, G,
+                   row_offsets, cols, total_n, nslots, piece, rec, pieces, one);
+}
+
+// Few and small graphs: the levels (blocks 0 .. G - 1) and the rest of the
+// preparation (the blocks after them, on CUs the levels leave idle) in one
+// launch.
+__global__ __launch_bounds__(kBfsThreads) void batch_first_kernel(const int64_t* vbase, int G,
+                                                                  const int64_t* row_offsets, const int32_t* cols,
+                                                                  int64_t total_n, int64_t nslots, int piece,
+                                                                  FwdRec* rec, int2* pieces, OneGraph one,
+                                                                  int32_t* levels, uint32_t* parity, int64_t* T,
+                                                                  int64_t* H, int32_t root0) {
+  __shared__ LevelLds s;
+  const int g = blockIdx.x;
+  if (g < G) {
+    const int64_t v0 = one.vbase ? 0 : vbase[g], v1 = one.vbase ? one.n : vbase[g + 1];
+    graph_levels(s, g, v0, v1 - v0, row_offsets, cols, levels, parity, T, H, root0);
+  } else {
+    batch_prep<true>((blockIdx.x - G) * static_cast<int64_t>(kBfsThreads) + threadIdx.x,
+                     (gridDim.x - G) * static_cast<int64_t>(kBfsThreads), vbase, G, row_offsets, cols, total_n, nslots,
+                     piece, rec, pieces, one);
   }
 }
 
@@ -700,18 +779,28 @@ int batch_launch(const tc_batch* b, const tc_tuning* t, int64_t* triangles, int6
   const int64_t nslots = b->total_nnz / piece + G + 2;
   prof_stage("batch_bfs");
   const int64_t work = std::max<int64_t>(nslots, with_rec ? b->total_vertices : 0);
-  if (with_rec)
-    batch_prep_kernel<true><<<grid_for(work, 256, 16384), 256, 0, s>>>(b->vbase, G, b->row_offsets, b->cols,
-                                                                       b->total_vertices, nslots, piece, p.rec,
-                                                                       p.pieces, one);
-  else
-    batch_prep_kernel<false><<<grid_for(work, 256, 16384), 256, 0, s>>>(b->vbase, G, b->row_offsets, b->cols,
-                                                                        b->total_vertices, nslots, piece, p.rec,
-                                                                        p.pieces, one);
-  TC_HIP(hipGetLastError());
-  batch_bfs_kernel<<<static_cast<unsigned>(G), kBfsThreads, 0, s>>>(b->vbase, b->row_offsets, b->cols, levels,
-                                                                    p.parity, triangles, h_count, root0);
-  TC_HIP(hipGetLastError());
+  // one launch where the preparation finds CUs beside the levels' blocks
+  // (their LDS allows one a CU): R-MAT scale 10 takes 18 us so instead of
+  // 12.5 + 5.7 in a row and the gap between
+  if (with_rec && (one.vbase || (G <= 128 && work <= 128 * kBfsThreads))) {
+    const unsigned blocks = static_cast<unsigned>(G) + grid_for(work, kBfsThreads);
+    batch_first_kernel<<<blocks, kBfsThreads, 0, s>>>(b->vbase, G, b->row_offsets, b->cols, b->total_vertices, nslots,
+                                                      piece, p.rec, p.pieces, one, levels, p.parity, triangles,
+                                                      h_count, root0);
+    TC_HIP(hipGetLastError());
+  } else {
+    const unsigned blocks = grid_for(work, 256, 16384);
+    if (with_rec)
+      batch_prep_kernel<true><<<blocks, 256, 0, s>>>(b->vbase, G, b->row_offsets, b->cols, b->total_vertices, nslots,
+                                                     piece, p.rec, p.pieces, one);
+    else
+      batch_prep_kernel<false><<<blocks, 256, 0, s>>>(b->vbase, G, b->row_offsets, b->cols, b->total_vertices, nslots,
+                                                      piece, p.rec, p.pieces, one);
+    TC_HIP(hipGetLastError());
+    batch_bfs_kernel<<<static_cast<unsigned>(G), kBfsThreads, 0, s>>>(b->vbase, b->row_offsets, b->cols, levels,
+                                                                      p.parity, triangles, h_count);
+    TC_HIP(hipGetLastError());
+  }
   prof_stage("batch_count");
   if (threads == kWave) return launch_count<kWave>(b, p, nslots, piece, bpc, triangles, h_count, H2, s);
   if (threads == 256) return launch_count<256>(b, p, nslots, piece, bpc, triangles, h_count, H2, s);

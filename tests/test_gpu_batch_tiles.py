@@ -80,3 +80,38 @@ def test_one_graph_against_oracle(cases, i):
     assert np.array_equal(r.levels.cpu().numpy(), lv)
     st = tc.read_stats()
     assert (st["n"], st["nnz"], st["h"]) == (g.n, G.nnz, h)
+
+
+def _levels_cases():
+    rng = np.random.RandomState(3)
+    small = graphgen.disjoint_union([graphgen.path(int(k)) for k in rng.randint(1, 9, 900)])
+    big = graphgen.disjoint_union([graphgen.path(int(k)) for k in rng.randint(2, 9, 3000)])
+    return [
+        ("small components", graphgen.relabel(graphgen.disjoint_union([graphgen.rmat(11, 8, seed=1), small]), 2)),
+        ("more of them than listed", graphgen.relabel(graphgen.disjoint_union([graphgen.rmat(10, 8, seed=1), big]), 4)),
+        ("two halves", graphgen.relabel(graphgen.disjoint_union([graphgen.erdos_renyi(9000, 6 / 9000, 5),
+                                                                 graphgen.erdos_renyi(8000, 6 / 8000, 6)]), 7)),
+        ("isolated and a path", graphgen.relabel(_pad(graphgen.path(2500), 60000), 8)),
+        ("chung-lu", graphgen.chung_lu(8001, mean_degree=6, seed=9)),
+        ("long tail", graphgen.relabel(graphgen.disjoint_union([graphgen.complete(60), graphgen.path(6144)]), 1)),
+        ("longer tail", graphgen.relabel(graphgen.disjoint_union([graphgen.complete(60), graphgen.path(6145)]), 1)),
+    ]
+
+
+@pytest.mark.parametrize("i", range(7))
+def test_levels_of_other_components(i):
+    import paper_2210_00389_amd as tc
+    name, g = _levels_cases()[i]
+    for root in (-1, g.n // 2):
+        print(f"case: {name}, root {root}", flush=True)
+        c = oracle.from_graph(g)
+        lv = oracle.bfs_levels(c, root)
+        G = tc.from_host_pairs(g.n, g.src, g.dst)
+        r = tc.count(G, root=root, return_levels=True)
+        assert np.array_equal(r.levels.cpu().numpy(), lv.levels)
+        assert (r.T, r.h) == (oracle.count(c, lv.levels).triangles, len(oracle.cover_edges(c, lv.levels)[0]))
+    # beside other graphs, in a batch of its own launch sequence
+    b = tc.Batch.from_graphs([g] * 130)
+    lv = oracle.bfs_levels(c).levels
+    r = tc.count_batch(b, return_levels=True)
+    assert np.array_equal(r.levels.cpu().numpy(), np.tile(lv, 130))
