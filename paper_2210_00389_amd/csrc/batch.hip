@@ -409,6 +409,8 @@ constexpr int kBChunk = 8;  // consecutive list entries a lane takes at once
 constexpr int kRowCap = 512;             // row starts of a tile kept in LDS
 constexpr int kFilterBits = TC_BATCH_MAX_N;
 constexpr int kWinTiles = 64;            // 64-chunk groups whose stream starts are marked at once
+constexpr uint32_t kLongList = TC_BATCH_MAX_N - kBChunk;
+constexpr int kLongMany = 64;
 constexpr uint32_t kRowStep = 40503u;    // odd: rows of a tile start at spread places of the filter
 
 // Slots of an XCD given to consecutive blocks of that XCD (about the blocks
@@ -459,7 +461,9 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
   __shared__ int32_t s_row[kRowCap];
   __shared__ uint32_t s_M[kWinTiles][2];
   __shared__ int32_t s_tb[kWinTiles];
-  __shared__ int64_t sh[NW + 1];
+  __shared__ uint32_t sh[NW + 1];
+  __shared__ uint32_t s_sum[2][NW];
+  __shared__ int s_long;
   const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / kWave), ln = lane();
   for (int64_t bi = blockIdx.x;; bi += gridDim.x) {
     // consecutive blocks go to different XCDs: by_xcd gives the blocks of one
@@ -486,8 +490,12 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
     const int64_t pe = min(ps + piece, rows[n]);
     // every list ends a whole chunk before the columns do
     const bool inside = rows[n] + kBChunk <= total_nnz;
-    int64_t cnt = 0, hc = 0;
+    int64_t cnt = 0, hc = 0;  // of the piece, in thread 0
     int vb = pc.y;
+    // the next slot's first row bounds the piece's (the last row of the graph
+    // where that slot is empty or another graph's)
+    const int2 pn = sl + 1 < nslots ? pieces[sl + 1] : make_int2(-1, 0);
+    const int vz = pn.x == g ? pn.y : n - 1;
     for (int64_t tb = ps; tb < pe; tb += kTile) {
       const int tn = static_cast<int>(min(static_cast<int64_t>(kTile), pe - tb));
       // entries and the filter's clearing are in flight while the row starts arrive
@@ -501,7 +509,8 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
       for (int i = tid; i < kFilterBits / 128; i += THREADS)
         reinterpret_cast<uint4*>(s_filt)[i] = make_uint4(0u, 0u, 0u, 0u);
       if (tid < kTile / 32) s_beg[tid] = 0u;
-      const int nrow = static_cast<int>(min(static_cast<int64_t>(kRowCap), static_cast<int64_t>(n) - vb + 1));
+      if (tid == 0) s_long = 0;
+      const int nrow = static_cast<int>(min(static_cast<int64_t>(kRowCap), static_cast<int64_t>(vz) - vb + 2));
       int have = 0;
       do {
         const int i = have + tid;
@@ -556,13 +565,18 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
       // disjoint ranges of the filter per row where they fit: a set bit is then exact
       const bool exact = static_cast<int64_t>(nrows) * n <= kFilterBits;
       const uint32_t step = exact ? static_cast<uint32_t>(n) : kRowStep;
-      uint32_t beg[kPer], len[kPer];
-      int64_t mine = 0;  // chunks | streams << 32
+      uint32_t beg[kPer], len[kPer], off[kPer];
+      // chunks | streams << 22: fewer than 2^22 chunks in all, as at most 21
+      // entries of a tile have lists beyond kLongList in a simple graph (their
+      // ids are below 8); in any other kLongMany keep their length
+      uint32_t mine = 0;
+      uint32_t tc = 0, th = 0;
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         len[j] = beg[j] = 0;
+        off[j] = __umul24(rk[j], step) & (kFilterBits - 1);
         if (v[j] <= u[j]) continue;  // also the positions past the tile (-1)
-        hc += par_bit(par, v[j]) == par_bit(par, u[j]);
+        th += par_bit(par, v[j]) == par_bit(par, u[j]);
         if (kRec) {
           const FwdRec r = rec[v0 + v[j]];
           const int64_t f = static_cast<int64_t>(r.lo) | (static_cast<int64_t>(r.hi_len & 0xFFu) << 32);
@@ -574,30 +588,31 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
           beg[j] = static_cast<uint32_t>(f - e0);
           len[j] = static_cast<uint32_t>(min(e - f, kFwdLenMax));
         }
-        const uint32_t h = (static_cast<uint32_t>(v[j]) + static_cast<uint32_t>(rk[j]) * step) & (kFilterBits - 1);
+        if (len[j] > kLongList && atomicAdd(&s_long, 1) >= kLongMany) len[j] = kLongList;
+        const uint32_t h = (static_cast<uint32_t>(v[j]) + off[j]) & (kFilterBits - 1);
         atomicOr(&s_filt[h >> 5], 1u << (h & 31));
-        if (len[j]) mine += static_cast<int64_t>((len[j] + kBChunk - 1) / kBChunk) | (int64_t(1) << 32);
+        if (len[j]) mine += (len[j] + kBChunk - 1) / kBChunk + (1u << 22);
       }
       const int32_t tail = start_of(last + 1);  // end of the last row
       {
-        const uint32_t off = static_cast<uint32_t>(nrows - 1) * step;
+        const uint32_t toff = static_cast<uint32_t>(nrows - 1) * step;
         for (int k = tn + tid; k < tail; k += THREADS) {
           const int32_t w = cols[tb + k];
           if (w <= vb + last) continue;
-          const uint32_t h = (static_cast<uint32_t>(w) + off) & (kFilterBits - 1);
+          const uint32_t h = (static_cast<uint32_t>(w) + toff) & (kFilterBits - 1);
           atomicOr(&s_filt[h >> 5], 1u << (h & 31));
         }
       }
-      int64_t tot;
-      const int64_t pre = block_excl_scan(mine, sh, &tot);
-      const int C = static_cast<int>(tot & 0xFFFFFFFF), nst = static_cast<int>(tot >> 32);
+      uint32_t tot;
+      const uint32_t pre = block_excl_scan(mine, sh, &tot);
+      constexpr uint32_t kChunks = (1u << 22) - 1u;
+      const int C = static_cast<int>(tot & kChunks), nst = static_cast<int>(tot >> 22);
       {
-        int slot = static_cast<int>(pre >> 32), ch = static_cast<int>(pre & 0xFFFFFFFF);
+        int slot = static_cast<int>(pre >> 22), ch = static_cast<int>(pre & kChunks);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           if (!len[j]) continue;
-          const uint32_t off = (static_cast<uint32_t>(rk[j]) * step) & (kFilterBits - 1);
-          s_st[slot] = make_uint4(static_cast<uint32_t>(ch), beg[j], len[j] | (off << 16),
+          s_st[slot] = make_uint4(static_cast<uint32_t>(ch), beg[j], len[j] | (off[j] << 16),
                                   static_cast<uint32_t>(tid + j * THREADS));
           ++slot;
           ch += static_cast<int>((len[j] + kBChunk - 1) / kBChunk);
@@ -633,7 +648,7 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
           const uint4 st = s_st[j];
           const int k0 = (c - static_cast<int>(st.x)) * kBChunk;
           const int rem = static_cast<int>(st.z & 0xFFFFu) - k0;
-          const uint32_t off = st.z >> 16;
+          const uint32_t so = st.z >> 16;
           int64_t p0 = e0 + st.y + k0;
           uint32_t valid = rem >= kBChunk ? (1u << kBChunk) - 1u : (1u << rem) - 1u;
           int32_t w[kBChunk];
@@ -656,12 +671,12 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
           const uint8_t* bytes = reinterpret_cast<const uint8_t*>(s_filt);
 #pragma unroll
           for (int q = 0; q < kBChunk; ++q) {
-            const uint32_t h = (static_cast<uint32_t>(w[q]) + off) & (kFilterBits - 1);
+            const uint32_t h = (static_cast<uint32_t>(w[q]) + so) & (kFilterBits - 1);
             hits |= ((static_cast<uint32_t>(bytes[h >> 3]) >> (h & 7)) & 1u) << q;
           }
           hits &= valid;
           if (exact) {
-            cnt += __popc(hits);
+            tc += __popc(hits);
           } else if (hits) {
             // the row's entries after v: from a to the next mark, or to the
             // tile's end and on to the last row's
@@ -683,22 +698,35 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
                 if (s_col[mid] < x) lo = mid + 1;
                 else hi = mid;
               }
-              if (lo < z) cnt += s_col[lo] == x;
+              if (lo < z) tc += s_col[lo] == x;
               else if (z == tn && tail > tn) {
                 const int64_t q0 = lower_bound_dev(cols, tb + tn, tb + tail, x);
-                cnt += q0 < tb + tail && cols[q0] == x;
+                tc += q0 < tb + tail && cols[q0] == x;
               }
             }
           }
         }
         __syncthreads();
       }
+      // a tile's sums fit 32 bits (fewer than 2^22 chunks of 8)
+      tc = wave_sum(tc);
+      th = wave_sum(th);
+      if (ln == 0) {
+        s_sum[0][wv] = tc;
+        s_sum[1][wv] = th;
+      }
+      __syncthreads();
+      if (tid == 0) {
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          cnt += s_sum[0][q];
+          hc += s_sum[1][q];
+        }
+      }
       // the row of the next tile's first entry
       if (tail > tn) vb += last;
       else vb += last + 1;
     }
-    cnt = block_sum(cnt, sh);
-    hc = block_sum(hc, sh);
     if (tid == 0) {
       if (cnt) atomicAdd(reinterpret_cast<unsigned long long*>(&T[g]), static_cast<unsigned long long>(cnt));
       if (hc && H) atomicAdd(reinterpret_cast<unsigned long long*>(&H[g]), static_cast<unsigned long long>(hc));
