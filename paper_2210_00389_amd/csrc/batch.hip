@@ -43,7 +43,10 @@ constexpr int kTile = 512;       // entries of a piece counted together (their s
 
 // Piece slots of graph g start at row_offsets[vbase[g]] / piece + g, parity
 // words at vbase[g] / 32 + g: both leave room for ceil(size / unit) entries.
-__device__ __forceinline__ int64_t piece_base(int64_t e0, int piece, int g) { return e0 / piece + g; }
+__device__ __forceinline__ int64_t piece_base(int64_t e0, int piece, int g) {
+  // a 64-bit division is a hundred instructions: powers of two shift (uniform branch)
+  return ((piece & (piece - 1)) == 0 ? e0 >> (31 - __clz(piece)) : e0 / piece) + g;
+}
 __device__ __forceinline__ int64_t parity_base(int64_t v0, int g) { return v0 / 32 + g; }
 
 __device__ __forceinline__ int64_t block_max_i64(int64_t v, int64_t* sh) {
@@ -740,9 +743,10 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
 // the smallest graphs, until a piece is one whole tile.
 constexpr int64_t kAutoSlots = 2048;
 
-int auto_piece(int64_t total_nnz) {
-  const int64_t share = total_nnz / kAutoSlots;
-  return static_cast<int>(share < kAutoMin ? kAutoMin : (share > kTile ? kTile : share));
+int auto_piece(int64_t total_nnz) {  // a power of two, so that the kernels shift instead of dividing
+  int piece = kAutoMin;
+  while (piece < kTile && 2 * piece * kAutoSlots <= total_nnz) piece *= 2;
+  return piece;
 }
 
 struct BatchPlan {
