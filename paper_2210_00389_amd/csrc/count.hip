@@ -691,7 +691,7 @@ template <bool kCover>
 __global__ __launch_bounds__(kResThreads) void resolve_kernel(
     const int32_t* lc, const int32_t* samp, const VMeta* meta, const uint4* pm, const uint16_t* vinfo,
     const int64_t* so, const int32_t* cx0, int64_t n, int64_t* sbeg, int32_t* slen, int32_t* soth, int32_t* sx,
-    int4* items_raw, int4* ccnt, int item_log2, int upa) {
+    int4* items_raw, int4* ccnt, int64_t nchunk_cap, int item_log2, int upa) {
   __shared__ int64_t sh[kResThreads / kWave + 1];
   __shared__ int32_t shi[kResThreads / kWave + 1];
   __shared__ int64_t s_so[kResSpan];
@@ -701,7 +701,11 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
   const int tid = threadIdx.x;
   const int64_t total = so[n];
   const int64_t nch = (total + kResChunk - 1) / kResChunk;
-  for (int64_t c = blockIdx.x; c < nch; c += gridDim.x) {
+  for (int64_t c = blockIdx.x; c < nchunk_cap; c += gridDim.x) {
+    if (c >= nch) {  // past the descriptors: nothing for the scan of the counts
+      if (tid == 0) ccnt[c] = make_int4(0, 0, 0, 0);
+      continue;
+    }
     const int64_t d0 = c * kResChunk;
     const int64_t d1 = min(d0 + kResChunk, total);
     const int64_t xa = cx0[c], xz = cx0[c + 1];  // the vertex of d1 - 1 is in [xa, xz]
@@ -1022,8 +1026,18 @@ template <bool kFill>
 __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, int64_t n, const int4* ccnt,
                                                              const int4* items_raw, int4* items,
                                                              unsigned long long* acc) {
-  __shared__ unsigned long long s_base[kBins];
+  __shared__ unsigned long long s_base[kBins], s_off[kBins];
   __shared__ int64_t sh[kThreads / kWave + 1];
+  if (kFill && threadIdx.x == 0) {  // the bins one after another; block 0 tells the later kernels
+    unsigned long long run = 0;
+    for (int b = 0; b < kBins; ++b) {
+      s_off[b] = run;
+      if (blockIdx.x == 0) acc[kAccBinOff + b] = run;
+      run += acc[kAccBinCount + b];
+    }
+    if (blockIdx.x == 0) acc[kAccItems] = run;
+  }
+  __syncthreads();
   const int64_t total = so[n];
   const int64_t nch = (total + kResChunk - 1) / kResChunk;
   int64_t recs = 0;
@@ -1056,7 +1070,7 @@ __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, 
         if (threadIdx.x == q) kb = static_cast<unsigned long long>((tot[q >> 1] >> (32 * (q & 1))) & 0xFFFFFFFF);
       if (kb) {
         if (!kFill) atomicAdd(&acc[kAccBinCount + threadIdx.x], kb);
-        else s_base[threadIdx.x] = acc[kAccBinOff + threadIdx.x] + atomicAdd(&acc[kAccBinCur + threadIdx.x], kb);
+        else s_base[threadIdx.x] = s_off[threadIdx.x] + atomicAdd(&acc[kAccBinCur + threadIdx.x], kb);
       }
     }
     __syncthreads();
@@ -1078,15 +1092,6 @@ __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, 
     __syncthreads();
   }
   if (!kFill) block_acc(acc, kAccRecs, recs, sh);
-}
-
-__global__ void bin_offsets_kernel(unsigned long long* acc) {
-  unsigned long long run = 0;
-  for (int b = 0; b < kBins; ++b) {
-    acc[kAccBinOff + b] = run;
-    run += acc[kAccBinCount + b];
-  }
-  acc[kAccItems] = run;
 }
 
 // ------------------------------------------------------------ streaming
@@ -1847,8 +1852,18 @@ __global__ __launch_bounds__(kCoreThreads, 8) void core_kernel(const uint16_t* c
   block_acc(acc, kAccBuild, builds, sh);
 }
 
-__global__ void finish_kernel(const unsigned long long* acc, const int64_t* so, int64_t n, const int64_t* lpre,
-                              int64_t nchunk_cap, int64_t* triangles, int64_t* h_count, int64_t* stats) {
+// Clears the accumulators and the statistics.
+__global__ void count_init_kernel(unsigned long long* acc, int64_t* stats) {
+  if (threadIdx.x < kAccSlots) acc[threadIdx.x] = 0ull;
+  if (threadIdx.x < 24) stats[threadIdx.x] = 0;
+}
+
+__global__ void finish_kernel(const unsigned long long* acc, const int64_t* so, int64_t n, int64_t nnz,
+                              int64_t num_levels, const int64_t* lpre, int64_t nchunk_cap, int64_t* triangles,
+                              int64_t* h_count, int64_t* stats) {
+  stats[0] = n;
+  stats[1] = nnz;
+  stats[3] = num_levels;
   *triangles = static_cast<int64_t>(acc[kAccT]);
   if (h_count) *h_count = static_cast<int64_t>(acc[kAccH]);
   stats[2] = static_cast<int64_t>(acc[kAccH]);
@@ -1910,10 +1925,14 @@ int launch_bins(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
     TC_HIP(hipGetLastError());
   }
   if (a.prm.bins_mode == 1) {
-    TC_TRY((launch_heavy<kBinWords2, 1024, 1024, 4, kOut>(a, w, o, 2, 1, s)));
+    // by the largest degree, no probe set may need the largest tables: a hash
+    // table of 2 deg words fits 32 KB, as do two bitmaps over all ids
+    const bool bin2 = 2 * std::min(a.maxdeg, a.g->nnz) > kBinWords1 || 2 * (a.g->n / 32 + 2) > kBinWords1;
+    const bool bin3 = 2 * std::min(a.maxdeg, a.g->nnz) > kBinWords2;
+    if (bin2) TC_TRY((launch_heavy<kBinWords2, 1024, 1024, 4, kOut>(a, w, o, 2, 1, s)));
     TC_TRY((launch_heavy<kBinWords1, 512, 1024, 6, kOut>(a, w, o, 1, 3, s)));
     TC_TRY(launch_bin0<kOut>(a, w, o, s));
-    return launch_heavy<0, 512, 1024, 4, kOut>(a, w, o, 3, 4, s);
+    return bin3 ? launch_heavy<0, 512, 1024, 4, kOut>(a, w, o, 3, 4, s) : TC_OK;
   }
   Fork* f = fork_for_device();
   if (!f) return TC_ERR_HIP;
@@ -1951,29 +1970,29 @@ int launch_all(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
   TC_HIP(hipGetLastError());
   // a wave scans 64 vertices per round: about two rounds per wave (one
   // block of a graph of 16 K vertices scanned them in 19 us)
-  twolevel_words_kernel<<<grid_for(n, kThreads * 2, 4096), kThreads, 0, s>>>(a.cols, a.meta, w.vinfo, n,
-                                                                           w.tl_words, w.tl_l1);
+  // (only probe sets beyond the 32 KB hash table get a two-level one)
+  if (2 * std::min(a.maxdeg, a.g->nnz) > kBinWords1)
+    twolevel_words_kernel<<<grid_for(n, kThreads * 2, 4096), kThreads, 0, s>>>(a.cols, a.meta, w.vinfo, n, w.tl_words,
+                                                                               w.tl_l1);
   TC_HIP(hipGetLastError());
   {
     Carver sc(w.scratch);
     TC_TRY(scan_exclusive<int32_t>(w.ndesc, w.so, n, sc, s));
   }
-  TC_TRY(fill_i32(reinterpret_cast<int32_t*>(w.ccnt), 0, 4 * w.nchunk_cap, s));
   chunk_start_kernel<<<gv, kThreads, 0, s>>>(w.so, n, w.cx0);
   TC_HIP(hipGetLastError());
   prof_stage("resolve");
   sample_kernel<<<grid_for(a.g->nnz / kSampStride + 1, kThreads, 16384), kThreads, 0, s>>>(a.cols, a.g->nnz,
                                                                                            w.samp);
   resolve_kernel<kCover><<<gr, kResThreads, 0, s>>>(a.cols, w.samp, a.meta, w.pm, w.vinfo, w.so, w.cx0, n, w.sbeg,
-                                                    w.slen, w.soth, w.sx, w.items_raw, w.ccnt, a.prm.item_log2,
-                                                    a.prm.up_anchor_min);
+                                                    w.slen, w.soth, w.sx, w.items_raw, w.ccnt, w.nchunk_cap,
+                                                    a.prm.item_log2, a.prm.up_anchor_min);
   TC_HIP(hipGetLastError());
   {
     Carver sc(w.scratch);
     TC_TRY(scan_exclusive_strided(reinterpret_cast<const int32_t*>(w.ccnt) + 1, 4, w.lpre, w.nchunk_cap, sc, s));
   }
   bin_split_kernel<false><<<gc, kThreads, 0, s>>>(w.so, n, w.ccnt, w.items_raw, w.items, w.acc);
-  bin_offsets_kernel<<<1, 1, 0, s>>>(w.acc);
   bin_split_kernel<true><<<gc, kThreads, 0, s>>>(w.so, n, w.ccnt, w.items_raw, w.items, w.acc);
   TC_HIP(hipGetLastError());
   // after the item split: kOutRec keeps its unit counts where the raw items were
@@ -2121,8 +2140,8 @@ int forward_meta_run(const tc_csr* g, VMeta* meta, hipStream_t s) {
 
 int count_run(const CountArgs& a, CountWs& w, int64_t* triangles, int64_t* h_count, hipStream_t s) {
   const int64_t n = a.g->n;
-  TC_TRY(fill_i64(reinterpret_cast<int64_t*>(w.acc), 0, kAccSlots, s));
-  TC_TRY(fill_i64(w.stats, 0, 24, s));
+  static_assert(kAccSlots <= kWave, "one wave clears them");
+  count_init_kernel<<<1, kWave, 0, s>>>(w.acc, w.stats);
   prof_stage("plan");
   if (n > 0) {
     Out o = unit_out(w);
@@ -2133,7 +2152,7 @@ int count_run(const CountArgs& a, CountWs& w, int64_t* triangles, int64_t* h_cou
     else if (a.per_vertex) TC_TRY((launch_all<true, kOutPV>(a, w, o, s)));
     else TC_TRY((launch_all<true, kOutNone>(a, w, o, s)));
   }
-  finish_kernel<<<1, 1, 0, s>>>(w.acc, w.so, n, w.lpre, w.nchunk_cap, triangles, h_count, w.stats);
+  finish_kernel<<<1, 1, 0, s>>>(w.acc, w.so, n, a.g->nnz, a.num_levels, w.lpre, w.nchunk_cap, triangles, h_count, w.stats);
   TC_HIP(hipGetLastError());
   return TC_OK;
 }

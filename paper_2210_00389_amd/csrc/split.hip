@@ -48,7 +48,6 @@ constexpr int kBigWaves = 4;                     // block of 256 threads per row
 constexpr int kBigR = 16;
 constexpr int kBigCap = kBigWaves * kBigR * 64;  // 4096
 static_assert(kBigCap >= kSeg, "a segmented row has at least one full segment");
-enum RowCat { kRowShort = 0, kRowMid = 1, kRowBig = 2, kRowHuge = 3 };
 
 // ---------------------------------------------------------- layouts
 // A row is written as [Up | Same | Down], each ascending in the output
@@ -199,25 +198,76 @@ __device__ __forceinline__ VMeta row_meta(const Ctx& c, const int (&cnt)[3 * G],
   return VMeta{c.ob, up, up + sd.slt, up + same, static_cast<int32_t>(c.ie - c.ib), sd.nup, max(sd.nsame - sd.slt, 0)};
 }
 
+// Lists of the longer rows, filled while the short ones are laid out.
+struct RowLists {
+  unsigned long long* mid_big;  // rows so far: mid in the low half, block rows in the high half
+  unsigned long long* huge;     // segments so far in the low 40 bits, segmented rows above
+  int64_t* seg_off;             // per segmented row (by list place): its first segment
+  int32_t* huge_row;            // per segmented row: the row
+  int32_t* seg_vtx;             // per segment: place of its row in the list
+};
+constexpr int kHugeShift = 40;
+
 // Rows of at most kShort entries: one thread; the row and the groups of its
 // entries are loaded into registers first (all gathers in flight at once),
-// then counted and scattered.
+// then counted and scattered.  Longer rows go to their category's list as
+// row contexts (the kernels that lay them out then start with one load
+// instead of the chain of dependent loads ctx() makes), one addition to the
+// counter per block and round; segmented rows, a handful, one each.
 template <class Lay>
 __global__ __launch_bounds__(kThreads) void lay_short_kernel(Lay lay, const int32_t* cols, int64_t n, int32_t* out,
-                                                             VMeta* meta, int32_t* nseg, int32_t* rcat) {
+                                                             VMeta* meta, RowLists lists, typename Lay::Ctx* mid_ctx,
+                                                             typename Lay::Ctx* big_ctx) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const Ctx c = lay.ctx(i);
+  constexpr int kW = kThreads / kWave;
+  __shared__ uint32_t s_mid[kW], s_big[kW];
+  __shared__ unsigned long long s_at;
+  const int wv = threadIdx.x / kWave;
+  for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x; i0 < n; i0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = i0 + threadIdx.x;
+    const bool row = i < n;
+    Ctx c{};
+    if (row) c = lay.ctx(i);
     const int32_t deg = static_cast<int32_t>(c.ie - c.ib);
-    if (deg > kShort) {
-      const int cat = deg <= kMidCap ? kRowMid : (deg <= kBigCap ? kRowBig : kRowHuge);
-      rcat[i] = cat;
-      nseg[i] = cat == kRowHuge ? (deg + kSeg - 1) / kSeg : 0;
-      continue;
+    const bool mid = deg > kShort && deg <= kMidCap, big = deg > kMidCap && deg <= kBigCap;
+    const uint64_t mm = __ballot(mid), mb = __ballot(big);
+    if (lane() == 0) {
+      s_mid[wv] = __popcll(mm);
+      s_big[wv] = __popcll(mb);
     }
-    rcat[i] = kRowShort;
-    nseg[i] = 0;
+    __syncthreads();
+    uint32_t tm = 0, tb = 0, pm = 0, pb = 0;
+#pragma unroll
+    for (int q = 0; q < kW; ++q) {
+      if (q < wv) {
+        pm += s_mid[q];
+        pb += s_big[q];
+      }
+      tm += s_mid[q];
+      tb += s_big[q];
+    }
+    if (tm | tb) {  // uniform per block
+      if (threadIdx.x == 0)
+        s_at = atomicAdd(lists.mid_big,
+                         static_cast<unsigned long long>(tm) | (static_cast<unsigned long long>(tb) << 32));
+      __syncthreads();
+      const uint64_t lt = lanemask_lt();
+      if (mid) mid_ctx[(s_at & 0xFFFFFFFFull) + pm + __popcll(mm & lt)] = c;
+      if (big) big_ctx[(s_at >> 32) + pb + __popcll(mb & lt)] = c;
+    }
+    __syncthreads();  // the counts are rewritten in the next round
+    if (deg > kBigCap) {
+      const int segs = (deg + kSeg - 1) / kSeg;
+      const unsigned long long at =
+          atomicAdd(lists.huge, static_cast<unsigned long long>(segs) | (1ull << kHugeShift));
+      const int64_t s0 = static_cast<int64_t>(at & ((1ull << kHugeShift) - 1ull));
+      const int64_t q = static_cast<int64_t>(at >> kHugeShift);
+      lists.seg_off[q] = s0;
+      lists.huge_row[q] = static_cast<int32_t>(i);
+      for (int j = 0; j < segs; ++j) lists.seg_vtx[s0 + j] = static_cast<int32_t>(q);
+    }
+    if (!row || deg > kShort) continue;
     int32_t wv[kShort];
 #pragma unroll
     for (int q = 0; q < kShort; ++q) wv[q] = q < deg ? cols[c.ib + q] : 0;
@@ -256,19 +306,6 @@ __global__ __launch_bounds__(kThreads) void lay_short_kernel(Lay lay, const int3
       lay.write16(c, c.ob + at, kc[q], vv[q]);
     }
     meta[i] = row_meta<G>(c, cnt, sd);
-  }
-}
-
-// Row lists of the two staged categories from their packed scan, as row
-// contexts: the kernels that lay these rows out then start with one load
-// instead of the chain of dependent loads ctx() makes.
-template <class Lay>
-__global__ void row_list_kernel(Lay lay, const int32_t* rcat, int64_t n, const int64_t* pre, typename Lay::Ctx* mid_ctx,
-                                typename Lay::Ctx* big_ctx) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = rcat[i];
-    if (c == kRowMid) mid_ctx[pre[i] & 0xFFFFFFFFll] = lay.ctx(i);
-    else if (c == kRowBig) big_ctx[pre[i] >> 32] = lay.ctx(i);
   }
 }
 
@@ -395,11 +432,11 @@ __device__ __forceinline__ void group_starts(int64_t base, const int (&tot)[NG],
 // one, so the memory latencies of two rows overlap.
 template <class Lay, int R>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void lay_mid_kernel(Lay lay, const int32_t* cols, const typename Lay::Ctx* rows,
-                                                           const int64_t* count, int32_t* out, VMeta* meta) {
+                                                           const unsigned long long* count, int32_t* out, VMeta* meta) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
   static_assert(R * kWave < (1 << 16), "part counts are packed in 16-bit fields");
-  const int64_t nrows = *count & 0xFFFFFFFFll;
+  const int64_t nrows = static_cast<int64_t>(*count & 0xFFFFFFFFull);
   const int64_t nw = (int64_t)gridDim.x * (kThreads / kWave);
   // one row per wave: a wave-uniform index lets the row contexts load into
   // scalar registers
@@ -440,14 +477,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 // are combined through LDS.
 template <class Lay, int WPR, int R>
 __global__ __launch_bounds__(WPR * kWave) __attribute__((amdgpu_waves_per_eu(5))) void lay_block_kernel(Lay lay, const int32_t* cols, const typename Lay::Ctx* rows,
-                                                                const int64_t* count, int32_t* out, VMeta* meta) {
+                                                                const unsigned long long* count, int32_t* out, VMeta* meta) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
   constexpr int kPart = R * kWave;
   static_assert(WPR * kPart < (1 << 16), "row counts are packed in 16-bit fields");
   __shared__ uint64_t s_w[WPR][CountsT<NG>::kWords];
   const int wave = threadIdx.x / kWave;
-  const int64_t nrows = *count >> 32;
+  const int64_t nrows = static_cast<int64_t>(*count >> 32);
   for (int64_t r = blockIdx.x; r < nrows; r += gridDim.x) {
     const Ctx c = rows[r];
     int32_t wv[R], vv[R];
@@ -488,33 +525,24 @@ __global__ __launch_bounds__(WPR * kWave) __attribute__((amdgpu_waves_per_eu(5))
   }
 }
 
-__global__ void seg_vtx_kernel(const int32_t* nseg, const int64_t* seg_off, int64_t n, int32_t* seg_vtx) {
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
-    const int k = nseg[x];
-    const int64_t s0 = seg_off[x];
-    for (int i = 0; i < k; ++i) seg_vtx[s0 + i] = static_cast<int32_t>(x);
-  }
-}
-
 // Per segment of a segmented row: NG + kSide counts (the groups, then the
 // fields of RowSide), NG output positions.
 
 // One wave per segment of a long row: group counts of the segment; the
 // output ids are kept (stash) for the scatter pass.
 template <class Lay>
-__global__ __launch_bounds__(kThreads) void lay_seg_count_kernel(Lay lay, const int32_t* cols, int64_t n,
-                                                                 const int64_t* seg_off, const int32_t* seg_vtx,
+__global__ __launch_bounds__(kThreads) void lay_seg_count_kernel(Lay lay, const int32_t* cols, RowLists lists,
                                                                  int32_t* seg_cnt, int32_t* stash) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
   constexpr int kSegCnt = NG + kSide;
-  const int64_t nsegs = seg_off[n];
+  const int64_t nsegs = static_cast<int64_t>(*lists.huge & ((1ull << kHugeShift) - 1ull));
   const int64_t wid = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
   for (int64_t sg = wid; sg < nsegs; sg += nw) {
-    const int32_t i = seg_vtx[sg];
-    const Ctx c = lay.ctx(i);
-    const int64_t s = sg - seg_off[i];
+    const int32_t q = lists.seg_vtx[sg];
+    const Ctx c = lay.ctx(lists.huge_row[q]);
+    const int64_t s = sg - lists.seg_off[q];
     const int64_t b = c.ib + s * kSeg;
     const int64_t e = min(c.ie, b + kSeg);
     int cnt[NG + kSide] = {};
@@ -556,15 +584,17 @@ __global__ __launch_bounds__(kThreads) void lay_seg_count_kernel(Lay lay, const 
 // Per segmented row: the row record, and per segment the absolute output
 // position of each of its groups.
 template <class Lay>
-__global__ void lay_seg_prefix_kernel(Lay lay, int64_t n, const int32_t* nseg, const int64_t* seg_off,
-                                      const int32_t* seg_cnt, int64_t* seg_pre, VMeta* meta) {
+__global__ void lay_seg_prefix_kernel(Lay lay, RowLists lists, const int32_t* seg_cnt, int64_t* seg_pre,
+                                      VMeta* meta) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
   constexpr int kSegCnt = NG + kSide;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int k = nseg[i];
-    if (k == 0) continue;
-    const int64_t s0 = seg_off[i];
+  const int64_t rows = static_cast<int64_t>(*lists.huge >> kHugeShift);
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < rows; q += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t i = lists.huge_row[q];
+    const int64_t s0 = lists.seg_off[q];
+    const Ctx c = lay.ctx(i);
+    const int k = static_cast<int>((c.ie - c.ib + kSeg - 1) / kSeg);
     int tot[NG] = {};
     RowSide sd{0, 0, 0};
     for (int j = 0; j < k; ++j) {
@@ -575,7 +605,6 @@ __global__ void lay_seg_prefix_kernel(Lay lay, int64_t n, const int32_t* nseg, c
       sd.nup += sc[NG + 1];
       sd.nsame += sc[NG + 2];
     }
-    const Ctx c = lay.ctx(i);
     meta[i] = row_meta<G>(c, tot, sd);
     int64_t p[NG];
     const int zero[NG] = {};
@@ -593,18 +622,17 @@ __global__ void lay_seg_prefix_kernel(Lay lay, int64_t n, const int32_t* nseg, c
 
 // One wave per segment: stable scatter of the segment's entries.
 template <class Lay>
-__global__ __launch_bounds__(kThreads) void lay_seg_write_kernel(Lay lay, const int32_t* stash, int64_t n,
-                                                                 const int64_t* seg_off, const int32_t* seg_vtx,
+__global__ __launch_bounds__(kThreads) void lay_seg_write_kernel(Lay lay, const int32_t* stash, RowLists lists,
                                                                  const int64_t* seg_pre, int32_t* out) {
   constexpr int G = Lay::kG, NG = 3 * G;
   using Ctx = typename Lay::Ctx;
-  const int64_t nsegs = seg_off[n];
+  const int64_t nsegs = static_cast<int64_t>(*lists.huge & ((1ull << kHugeShift) - 1ull));
   const int64_t wid = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
   for (int64_t sg = wid; sg < nsegs; sg += nw) {
-    const int32_t i = seg_vtx[sg];
-    const Ctx c = lay.ctx(i);
-    const int64_t s = sg - seg_off[i];
+    const int32_t q = lists.seg_vtx[sg];
+    const Ctx c = lay.ctx(lists.huge_row[q]);
+    const int64_t s = sg - lists.seg_off[q];
     const int64_t b = c.ib + s * kSeg;
     const int64_t e = min(c.ie, b + kSeg);
     int64_t p[NG];
@@ -631,37 +659,37 @@ inline unsigned capped_grid(int64_t need, int64_t cap) {
   return static_cast<unsigned>(need < 1 ? 1 : (need < cap ? need : cap));
 }
 
+// The list counters (w.ctr) are zero on entry.  maxdeg: no row is longer, and
+// the kernels of categories beyond it are not launched.
 template <class Lay>
-int layout_run(const Lay& lay, const int32_t* cols, int64_t n, int64_t nnz, SplitWs& w, hipStream_t s) {
+int layout_run(const Lay& lay, const int32_t* cols, int64_t n, int64_t nnz, int64_t maxdeg, SplitWs& w,
+               hipStream_t s) {
   const unsigned gv = grid_for(n, kThreads, 16384);
   // the row classes hold at most nnz / (least row length) rows: a small
   // graph launches only the blocks its mid, block and segment rows can use
   const int64_t wpb = kThreads / kWave;
-  const int64_t mid_rows = nnz / (kShort + 1), big_rows = nnz / (kMidCap + 1);
-  const int64_t segs = nnz / kSeg + nnz / (kBigCap + 1) + 1;
+  const int64_t mid_rows = nnz / (kShort + 1), big_rows = nnz / (kMidCap + 1), huge_rows = nnz / (kBigCap + 1);
+  const int64_t segs = nnz / kSeg + huge_rows + 1;
   const unsigned gmid = capped_grid((mid_rows + wpb - 1) / wpb, static_cast<int64_t>(num_cus()) * 8);
   const unsigned gbig = capped_grid(big_rows, static_cast<int64_t>(num_cus()) * 4);
   const unsigned gw = capped_grid((segs + wpb - 1) / wpb, static_cast<int64_t>(num_cus()) * 8);
-  lay_short_kernel<Lay><<<gv, kThreads, 0, s>>>(lay, cols, n, w.scols, w.meta, w.nseg, w.rcat);
-  TC_HIP(hipGetLastError());
-  {
-    Carver sc(w.scratch);
-    TC_TRY(scan_exclusive_pair(w.rcat, kRowMid, kRowBig, w.cat_pre, n, sc, s));
-  }
   typename Lay::Ctx* mid_ctx = reinterpret_cast<typename Lay::Ctx*>(w.mid_ctx);
   typename Lay::Ctx* big_ctx = reinterpret_cast<typename Lay::Ctx*>(w.big_ctx);
-  row_list_kernel<Lay><<<gv, kThreads, 0, s>>>(lay, w.rcat, n, w.cat_pre, mid_ctx, big_ctx);
-  lay_mid_kernel<Lay, kMidR><<<gmid, kThreads, 0, s>>>(lay, cols, mid_ctx,
-                                                                                      w.cat_pre + n, w.scols, w.meta);
-  lay_block_kernel<Lay, kBigWaves, kBigR><<<gbig, kBigWaves * kWave, 0, s>>>(
-      lay, cols, big_ctx, w.cat_pre + n, w.scols, w.meta);
+  unsigned long long* ctr = reinterpret_cast<unsigned long long*>(w.ctr);
+  const RowLists lists{ctr, ctr + 1, w.seg_off, w.huge_row, w.seg_vtx};
+  lay_short_kernel<Lay><<<gv, kThreads, 0, s>>>(lay, cols, n, w.scols, w.meta, lists, mid_ctx, big_ctx);
   TC_HIP(hipGetLastError());
-  Carver sc(w.scratch);
-  TC_TRY(scan_exclusive<int32_t>(w.nseg, w.seg_off, n, sc, s));
-  seg_vtx_kernel<<<gv, kThreads, 0, s>>>(w.nseg, w.seg_off, n, w.seg_vtx);
-  lay_seg_count_kernel<Lay><<<gw, kThreads, 0, s>>>(lay, cols, n, w.seg_off, w.seg_vtx, w.seg_cnt, w.stash);
-  lay_seg_prefix_kernel<Lay><<<gv, kThreads, 0, s>>>(lay, n, w.nseg, w.seg_off, w.seg_cnt, w.seg_pre, w.meta);
-  lay_seg_write_kernel<Lay><<<gw, kThreads, 0, s>>>(lay, w.stash, n, w.seg_off, w.seg_vtx, w.seg_pre, w.scols);
+  if (maxdeg > kShort && mid_rows > 0)
+    lay_mid_kernel<Lay, kMidR><<<gmid, kThreads, 0, s>>>(lay, cols, mid_ctx, ctr, w.scols, w.meta);
+  if (maxdeg > kMidCap && big_rows > 0)
+    lay_block_kernel<Lay, kBigWaves, kBigR><<<gbig, kBigWaves * kWave, 0, s>>>(lay, cols, big_ctx, ctr, w.scols,
+                                                                               w.meta);
+  if (maxdeg > kBigCap && huge_rows > 0) {
+    lay_seg_count_kernel<Lay><<<gw, kThreads, 0, s>>>(lay, cols, lists, w.seg_cnt, w.stash);
+    lay_seg_prefix_kernel<Lay><<<grid_for(huge_rows, kThreads, 1024), kThreads, 0, s>>>(lay, lists, w.seg_cnt,
+                                                                                        w.seg_pre, w.meta);
+    lay_seg_write_kernel<Lay><<<gw, kThreads, 0, s>>>(lay, w.stash, lists, w.seg_pre, w.scols);
+  }
   TC_HIP(hipGetLastError());
   return TC_OK;
 }
@@ -717,6 +745,101 @@ __global__ void order_kernel(const uint64_t* sorted, int64_t n, const int64_t* o
   }
 }
 
+// The numbering in one counting-sort pass where there are at most kVgCap
+// groups (all but deep graphs): per tile of ITEMS * 256 vertices the groups'
+// counts, their scan, then each vertex's place from the lanes of its group (a
+// wave's rounds need no barrier: its counts have an LDS row of their own).
+// Deep graphs sort (group, id) keys: a histogram, its scan, the keys, their
+// radix passes and the numbering, ten launches for these four, which bound
+// small graphs (with the row lists made while the short rows are laid out:
+// R-MAT scale 16 518 -> 474 us, scale 24 54.6 -> 53.7 ms).
+constexpr int kVgCap = 256;
+
+template <int G, int ITEMS>
+__global__ __launch_bounds__(kThreads) void vg_count_kernel(const int64_t* off, const int32_t* L, const uint32_t* comp0,
+                                                            int32_t d0, int64_t n, int ngroups, int64_t nblocks,
+                                                            int32_t* ghist) {
+  constexpr int kW = kThreads / kWave;
+  __shared__ int32_t h[kW][kVgCap];
+  const int w = threadIdx.x / kWave;
+  for (int i = threadIdx.x; i < kW * kVgCap; i += kThreads) (&h[0][0])[i] = 0;
+  __syncthreads();
+  const int64_t base = blockIdx.x * static_cast<int64_t>(kThreads * ITEMS) + w * (ITEMS * kWave) + lane();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const int64_t v = base + j * kWave;
+    if (v < n) atomicAdd(&h[w][vgroup<G>(off, L, comp0, d0, v)], 1);
+  }
+  __syncthreads();
+  for (int g = threadIdx.x; g < ngroups; g += kThreads) {
+    int32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < kW; ++q) c += h[q][g];
+    ghist[g * nblocks + blockIdx.x] = c;
+  }
+}
+
+template <int G, int ITEMS>
+__global__ __launch_bounds__(kThreads) void vg_place_kernel(const int64_t* off, const int32_t* L, const uint32_t* comp0,
+                                                            int32_t d0, int64_t n, int ngroups, int bits,
+                                                            int64_t nblocks, const int64_t* gpos, int32_t* order,
+                                                            int32_t* perm, int32_t* ndeg, int64_t* lstart,
+                                                            int64_t* clear4) {
+  constexpr int kW = kThreads / kWave;
+  __shared__ int32_t s_cnt[kW][kVgCap];
+  __shared__ int64_t s_to[kVgCap];
+  const int tid = threadIdx.x, w = tid / kWave;
+  const uint64_t lt = lanemask_lt();
+  const int64_t base = blockIdx.x * static_cast<int64_t>(kThreads * ITEMS) + w * (ITEMS * kWave) + lane();
+  int gr[ITEMS];
+  int32_t dg[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const int64_t v = base + j * kWave;
+    gr[j] = dg[j] = 0;
+    if (v < n) {
+      const int64_t d = off[v + 1] - off[v];
+      dg[j] = static_cast<int32_t>(d);
+      gr[j] = G * vlevel(L, comp0, d0, v) + deg_group<G>(d);
+    }
+  }
+  for (int i = lane(); i < kVgCap; i += kWave) s_cnt[w][i] = 0;
+  if (tid < ngroups) s_to[tid] = gpos[tid * nblocks + blockIdx.x];
+  if (blockIdx.x == 0) {
+    if (tid < ngroups) lstart[tid] = gpos[tid * nblocks];
+    if (tid < 4) clear4[tid] = 0;  // the layout's list counters
+  }
+  volatile int32_t* cnt = s_cnt[w];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const bool valid = base + j * kWave < n;
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (gr[j] >> b) & 1;
+      const uint64_t m = __ballot(bit);
+      peers &= bit ? m : ~m;
+    }
+    rank[j] = 0;
+    if (valid) {
+      const int32_t before = cnt[gr[j]];
+      rank[j] = before + __popcll(peers & lt);
+      if ((peers & lt) == 0) cnt[gr[j]] = before + __popcll(peers);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const int64_t v = base + j * kWave;
+    if (v >= n) continue;
+    int64_t at = s_to[gr[j]] + rank[j];
+    for (int q = 0; q < w; ++q) at += s_cnt[q][gr[j]];
+    order[at] = static_cast<int32_t>(v);
+    perm[v] = static_cast<int32_t>(at);
+    ndeg[at] = dg[j];
+  }
+}
+
 // ------------------------------------------------------- H list
 __global__ void hcount_kernel(const VMeta* meta, int64_t n, int32_t* hc) {
   for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
@@ -761,22 +884,18 @@ SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz, bool own_stash) {
   w.meta = c.take<VMeta>(n + 1);
   w.scols = c.take<int32_t>(nnz + kColPad);
   w.c16 = c.take<uint16_t>(nnz + kColPad);
-  w.res = c.take<uint32_t>(1);
-  w.nseg = c.take<int32_t>(n + 1);
-  w.seg_off = c.take<int64_t>(n + 2);
+  w.seg_off = c.take<int64_t>(nnz / (kBigCap + 1) + 2);
+  w.huge_row = c.take<int32_t>(nnz / (kBigCap + 1) + 2);
   // Segmented rows have deg > kBigCap entries and ceil(deg / kSeg) <= deg / kSeg + deg / kBigCap segments.
   const int64_t max_segs = nnz / kSeg + nnz / kBigCap + 2;
   w.seg_vtx = c.take<int32_t>(max_segs + 1);
   w.seg_cnt = c.take<int32_t>((kMaxGroups + kSide) * (max_segs + 1));  // sized for the most groups
   w.seg_pre = c.take<int64_t>(kMaxGroups * (max_segs + 1));
   w.ctr = c.take<int64_t>(4);
-  w.rcat = c.take<int32_t>(n + 1);
-  w.cat_pre = c.take<int64_t>(n + 1);
   constexpr int kCtxWords = sizeof(RowCtxT<kMaxGroups>) / sizeof(int64_t);  // the largest context
   w.mid_ctx = c.take<int64_t>(kCtxWords * (std::min(n, nnz / (kShort + 1)) + 2));
   w.big_ctx = c.take<int64_t>(kCtxWords * (nnz / (kMidCap + 1) + 2));
   w.stash = own_stash ? c.take<int32_t>(nnz + 1) : nullptr;
-  w.scratch = c.take<char>(scan_ws_bytes(n + 1));
   return w;
 }
 
@@ -784,7 +903,8 @@ int split_run(const tc_csr* g, const int32_t* L, bool full_levels, SplitWs& w, h
   (void)full_levels;
   if (g->n == 0) return TC_OK;
   IdentityLayout lay{g->row_offsets, L};
-  return layout_run(lay, g->cols, g->n, g->nnz, w, s);
+  TC_TRY(fill_i64(w.ctr, 0, 4, s));
+  return layout_run(lay, g->cols, g->n, g->nnz, g->nnz, w, s);
 }
 
 RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels) {
@@ -798,7 +918,10 @@ RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels) {
   w.keys = c.take<uint64_t>(n + 1);
   w.keys_tmp = c.take<uint64_t>(n + 1);
   w.deg = c.take<int32_t>(n + 1);
-  const size_t a = radix_ws_bytes(n), b = scan_ws_bytes(n + 2);
+  // radix_ws_bytes holds 256 digits a tile of 4096 vertices; the one-pass
+  // numbering up to 256 groups a tile of 1024 below 2^20 vertices
+  const int64_t m = n < (int64_t(1) << 20) ? 4 * n : n;
+  const size_t a = radix_ws_bytes(m + 4096), b = scan_ws_bytes(n + 2);
   w.scratch = c.take<char>(a > b ? a : b);
   return w;
 }
@@ -806,7 +929,7 @@ RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels) {
 namespace {
 
 template <int G, bool CORE>
-int relabel_groups(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t nvl,
+int relabel_groups(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t nvl, int64_t maxdeg,
                    RelabelWs& w, SplitWs& sp, hipStream_t s) {
   const int64_t n = g->n;
   const unsigned gv = grid_for(n, kThreads, 16384);
@@ -821,39 +944,63 @@ int relabel_groups(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int
   // split at degree 2048); on graphs under 2^26 entries two groups (a split
   // at degree 2048) lay out faster and count as fast.
   const int32_t ngroups = G * (nvl + 1);
-  TC_TRY(fill_i32(w.lstart_cnt, 0, ngroups + 1, s));
-  // few blocks: each adds its LDS histogram to the shared counts once
-  vl_hist_kernel<G><<<grid_for(n, kThreads, static_cast<unsigned>(num_cus() * 2)), kThreads, 0, s>>>(
-      g->row_offsets, L, comp0, d0, n, ngroups, w.lstart_cnt);
-  TC_HIP(hipGetLastError());
-  {
-    Carver sc(w.scratch);
-    TC_TRY(scan_exclusive<int32_t>(w.lstart_cnt, w.lstart, ngroups, sc, s));
-  }
-  vl_keys_kernel<G><<<gv, kThreads, 0, s>>>(g->row_offsets, L, comp0, d0, n, w.keys);
   int bits = 0;
   while ((int64_t(1) << bits) < ngroups) ++bits;
-  uint64_t* sorted = w.keys;
-  TC_TRY(radix_sort_u64(w.keys, w.keys_tmp, n, 32, 32 + bits, w.scratch, s, &sorted));
-  order_kernel<<<gv, kThreads, 0, s>>>(sorted, n, g->row_offsets, w.order, w.perm, w.deg);
-  TC_HIP(hipGetLastError());
+  if (ngroups <= kVgCap) {
+    // tiles of 1024 vertices until they fill the chip a few times, else 4096
+    const bool fine = n < (int64_t(1) << 20);
+    const int64_t tile = kThreads * (fine ? 4 : 16), nblocks = (n + tile - 1) / tile;
+    Carver sc(w.scratch);
+    int32_t* ghist = sc.take<int32_t>(ngroups * nblocks + 1);
+    int64_t* gpos = sc.take<int64_t>(ngroups * nblocks + 2);
+    const unsigned gb = static_cast<unsigned>(nblocks);
+    if (fine)
+      vg_count_kernel<G, 4><<<gb, kThreads, 0, s>>>(g->row_offsets, L, comp0, d0, n, ngroups, nblocks, ghist);
+    else
+      vg_count_kernel<G, 16><<<gb, kThreads, 0, s>>>(g->row_offsets, L, comp0, d0, n, ngroups, nblocks, ghist);
+    TC_HIP(hipGetLastError());
+    TC_TRY(scan_exclusive<int32_t>(ghist, gpos, ngroups * nblocks, sc, s));
+    if (fine)
+      vg_place_kernel<G, 4><<<gb, kThreads, 0, s>>>(g->row_offsets, L, comp0, d0, n, ngroups, bits, nblocks, gpos,
+                                                    w.order, w.perm, w.deg, w.lstart, sp.ctr);
+    else
+      vg_place_kernel<G, 16><<<gb, kThreads, 0, s>>>(g->row_offsets, L, comp0, d0, n, ngroups, bits, nblocks, gpos,
+                                                     w.order, w.perm, w.deg, w.lstart, sp.ctr);
+    TC_HIP(hipGetLastError());
+  } else {
+    TC_TRY(fill_i64(sp.ctr, 0, 4, s));
+    TC_TRY(fill_i32(w.lstart_cnt, 0, ngroups + 1, s));
+    // few blocks: each adds its LDS histogram to the shared counts once
+    vl_hist_kernel<G><<<grid_for(n, kThreads, static_cast<unsigned>(num_cus() * 2)), kThreads, 0, s>>>(
+        g->row_offsets, L, comp0, d0, n, ngroups, w.lstart_cnt);
+    TC_HIP(hipGetLastError());
+    {
+      Carver sc(w.scratch);
+      TC_TRY(scan_exclusive<int32_t>(w.lstart_cnt, w.lstart, ngroups, sc, s));
+    }
+    vl_keys_kernel<G><<<gv, kThreads, 0, s>>>(g->row_offsets, L, comp0, d0, n, w.keys);
+    uint64_t* sorted = w.keys;
+    TC_TRY(radix_sort_u64(w.keys, w.keys_tmp, n, 32, 32 + bits, w.scratch, s, &sorted));
+    order_kernel<<<gv, kThreads, 0, s>>>(sorted, n, g->row_offsets, w.order, w.perm, w.deg);
+    TC_HIP(hipGetLastError());
+  }
   {
     Carver sc(w.scratch);
     TC_TRY(scan_exclusive<int32_t>(w.deg, w.off, n, sc, s));
   }
   RelabelLayout<G, CORE> lay{g->row_offsets, w.off, w.order, w.perm, L, comp0, d0, w.lstart, sp.c16};
-  return layout_run(lay, g->cols, n, g->nnz, sp, s);
+  return layout_run(lay, g->cols, n, g->nnz, maxdeg, sp, s);
 }
 
 }  // namespace
 
 int relabel_run(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t nvl,
-                int degree_groups, bool core, RelabelWs& w, SplitWs& sp, hipStream_t s) {
+                int degree_groups, bool core, int64_t maxdeg, RelabelWs& w, SplitWs& sp, hipStream_t s) {
   if (g->n == 0) return TC_OK;
-  if (degree_groups == 4 && core) return relabel_groups<4, true>(g, L, comp0, d0, nvl, w, sp, s);
-  if (degree_groups == 2 && core) return relabel_groups<2, true>(g, L, comp0, d0, nvl, w, sp, s);
-  if (degree_groups == 4) return relabel_groups<4, false>(g, L, comp0, d0, nvl, w, sp, s);
-  if (degree_groups == 2) return relabel_groups<2, false>(g, L, comp0, d0, nvl, w, sp, s);
+  if (degree_groups == 4 && core) return relabel_groups<4, true>(g, L, comp0, d0, nvl, maxdeg, w, sp, s);
+  if (degree_groups == 2 && core) return relabel_groups<2, true>(g, L, comp0, d0, nvl, maxdeg, w, sp, s);
+  if (degree_groups == 4) return relabel_groups<4, false>(g, L, comp0, d0, nvl, maxdeg, w, sp, s);
+  if (degree_groups == 2) return relabel_groups<2, false>(g, L, comp0, d0, nvl, maxdeg, w, sp, s);
   return fail(TC_ERR_INVALID_ARG, "relabel: degree_groups must be 2 or 4");
 }
 

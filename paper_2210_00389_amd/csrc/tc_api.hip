@@ -126,12 +126,6 @@ size_t bfs_bytes(int64_t n) {
   return c.used();
 }
 
-__global__ void stats_kernel(int64_t* stats, int64_t n, int64_t nnz, int64_t levels) {
-  stats[0] = n;
-  stats[1] = nnz;
-  stats[3] = levels;
-}
-
 int maybe_validate(const tc_csr* g, uint32_t flags, void* ws, hipStream_t s) {
   if (!(flags & TC_VALIDATE)) return TC_OK;
   return validate_run(g, ws, s);
@@ -243,7 +237,8 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   tc_csr rg = *g;  // the relabelled graph
   if (g->n > 0) {
     prof_stage("relabel");
-    TC_TRY(relabel_run(g, L, p.comp0, d0, d0 + nl + 1, prm.degree_groups, core, p.relabel, p.split, s));
+    TC_TRY(relabel_run(g, L, p.comp0, d0, d0 + nl + 1, prm.degree_groups, core, info.maxdeg, p.relabel, p.split,
+                       s));
     rg.row_offsets = p.relabel.off;
     rg.cols = p.split.scols;
   }
@@ -253,6 +248,8 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   a.prm = prm;
   a.cols = p.split.scols;
   a.meta = p.split.meta;
+  a.maxdeg = info.maxdeg;
+  a.num_levels = nl;
   a.c16 = core ? p.split.c16 : nullptr;
   a.cover = true;
   a.per_vertex = pv;
@@ -264,8 +261,6 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
     pv_back_kernel<<<grid_for(g->n, 256, 16384), 256, 0, s>>>(p.pv_new, p.relabel.order, g->n, per_vertex);
     TC_HIP(hipGetLastError());
   }
-  stats_kernel<<<1, 1, 0, s>>>(p.stats, g->n, g->nnz, nl);
-  TC_HIP(hipGetLastError());
   return TC_OK;
 }
 
@@ -392,8 +387,6 @@ int tc_count_edge_baseline_tuned(const tc_csr* g, uint32_t flags, const tc_tunin
   a.per_vertex = false;
   a.per_vertex_out = nullptr;
   TC_TRY(count_run(a, p.count, triangles, nullptr, s));
-  stats_kernel<<<1, 1, 0, s>>>(p.stats, g->n, g->nnz, 0);
-  TC_HIP(hipGetLastError());
   return TC_OK;
 }
 

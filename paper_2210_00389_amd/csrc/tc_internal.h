@@ -73,19 +73,15 @@ struct SplitWs {
   VMeta* meta;
   int32_t* scols;     // re-laid-out columns [nnz]
   uint16_t* c16;      // 16-bit core offsets of the Up and Same entries [nnz]
-  uint32_t* res;      // packed 2-bit level residues (L mod 4)
-  int32_t* nseg;      // per vertex: segments of a long row
-  int64_t* seg_off;   // scan of nseg
-  int32_t* seg_vtx;   // segment -> vertex
-  int32_t* seg_cnt;   // per segment: six group counts and same-below-x (x7)
-  int64_t* seg_pre;   // per segment: output position of each group (x6)
-  int64_t* ctr;
-  int32_t* rcat;      // per vertex: row category (short, mid, big, segmented)
-  int64_t* cat_pre;   // packed scans of the mid (low half) / big (high half) categories
+  int64_t* seg_off;   // per segmented row: its first segment
+  int32_t* huge_row;  // per segmented row: the row
+  int32_t* seg_vtx;   // segment -> place of its row in the list
+  int32_t* seg_cnt;   // per segment: group and side counts
+  int64_t* seg_pre;   // per segment: output position of each group
+  int64_t* ctr;       // list counters [4]
   int64_t* mid_ctx;   // per-row contexts of each category (seven words per row)
   int64_t* big_ctx;
   int32_t* stash;     // output ids of segmented rows, in input order [nnz]
-  char* scratch;
 };
 // own_stash false: the caller sets w.stash to memory that is free while the
 // rows are laid out.
@@ -115,9 +111,9 @@ RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels);
 // Writes the relabelled rows into split.scols and records into split.meta
 // (indexed by new ids); fills w.off, w.order, w.perm.
 // degree_groups: 2 or 4 degree groups per level (see tc_tuning).
-// core: fill split.c16 and the records' ncu, nch.
+// core: fill split.c16 and the records' ncu, nch.  maxdeg: the largest degree.
 int relabel_run(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t max_vl,
-                int degree_groups, bool core, RelabelWs& w, SplitWs& sp, hipStream_t s);
+                int degree_groups, bool core, int64_t maxdeg, RelabelWs& w, SplitWs& sp, hipStream_t s);
 
 // Explicit horizontal-edge list from the layout: h_off = scan of
 // (sfe - hfb), then (x, scols[..]) for every cover edge, lexicographic.
@@ -186,6 +182,8 @@ struct CountArgs {
   bool cover;           // cover edges (three classes) or the comparator
   bool per_vertex;
   int64_t* per_vertex_out;
+  int64_t maxdeg = INT64_MAX;      // no vertex has a larger degree
+  int64_t num_levels = 0;          // for the statistics
   const int32_t* order = nullptr;  // layout id -> caller id (cover layout)
   bool record_units = false;       // first pass of triangle finding
 };
