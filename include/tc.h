@@ -120,7 +120,8 @@ typedef struct tc_tuning {
                                  64, 256 or 512 (default: 64 while a default
                                  piece is under 128 entries, else 256) */
   int32_t batch_piece;        /* CSR entries per work piece (>= 1024;
-                                 default total_nnz / 2048, within 16..512) */
+                                 default a power of two near total_nnz / 2048,
+                                 within 16..2048) */
   int32_t batch_blocks_per_cu;/* blocks per CU the counting kernel is launched
                                  with, each taking several pieces (0 = one
                                  block per piece) */

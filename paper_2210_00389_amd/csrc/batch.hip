@@ -38,7 +38,7 @@ constexpr int kRowLanes = 16;    // lanes that expand a frontier row together
 constexpr int kRowLoads = 8;     // row entries a thread loads at once in a bottom-up level
 constexpr int kRestCap = 6144;   // unreached vertices of other components levelled together (LDS left beside L)
 constexpr int kPieceMin = 1024;  // smallest piece size a caller may ask for
-constexpr int kAutoMin = 16;     // smallest and largest piece size chosen by auto_piece
+constexpr int kAutoMin = 16;     // smallest piece size chosen by auto_piece
 constexpr int kTile = 512;       // entries of a piece counted together (their streams are kept in LDS)
 
 // Piece slots of graph g start at row_offsets[vbase[g]] / piece + g, parity
@@ -409,7 +409,10 @@ __global__ __launch_bounds__(kBfsThreads) void batch_first_kernel(const int64_t*
 }
 
 constexpr int kBChunk = 8;  // consecutive list entries a lane takes at once
-constexpr int kRowCap = 512;             // row starts of a tile kept in LDS
+constexpr int kRows = 2;                 // rows a thread looks at for a tile
+constexpr int kCols = 1024;
+constexpr int kQueue = 256;              // hits of a tile looked up together
+constexpr int kSumTiles = 64;            // tiles added up in 32 bits (fewer than 2^22 chunks of 8 each)
 constexpr int kFilterBits = TC_BATCH_MAX_N;
 constexpr int kWinTiles = 64;            // 64-chunk groups whose stream starts are marked at once
 constexpr uint32_t kLongList = TC_BATCH_MAX_N - kBChunk;
@@ -422,8 +425,10 @@ constexpr uint32_t kRowStep = 40503u;    // odd: rows of a tile start at spread 
 constexpr int kXcds = 8, kXcdRun = 256;
 
 // The counting kernel: a block takes one piece (or, where the caller limits
-// the grid, every gridDim.x-th), kTile entries at a time.
-//   1. the tile's row starts go to LDS, each entry finds its row u there;
+// the grid, every gridDim.x-th), kTile of its forward entries at a time.
+//   1. the next rows' forward parts are laid end to end: a scan of their
+//      lengths places them in the tile, a mark at each row's first place
+//      gives every entry its row;
 //   2. an entry v > u counts towards |H| if the parities agree; its forward
 //      list N+(v) becomes a stream, and v itself is set in the tile's filter:
 //      one bit at (v + offset of u) mod 65536 (the rest of the tile's last
@@ -431,16 +436,16 @@ constexpr int kXcds = 8, kXcdRun = 256;
 //   3. all streams are cut into chunks of kBChunk entries, dealt to the lanes
 //      in order; an element w whose bit is set lies in N(u) above v if the
 //      rows' ranges of the filter are disjoint (few rows, or one), else the
-//      hit is looked up in the row.
-// A tile's dependent loads (row starts, entries, forward records, streams)
-// are taken once for 512 edges, where a wave per vertex with a 65536-bit map
-// of its own (8 KB a wave) paid them per vertex: on 4096 graphs of 64 to
-// 65536 vertices (1.08 G entries) that version took 43.1 ms, bound by those
-// latencies at 16 waves per CU; this one takes 21.7 ms, and 0.053 ms in place
-// of 1.74 on 48 graphs of 64 to 8192 vertices, whose 16384-entry pieces
-// filled a quarter of the CUs (VALU busy for 56% of the time, at five waves per
-// SIMD; with the entries' rows from marks instead of a search, scans on DPP
-// and seven waves, which their 21 KB of LDS allow, 15.6 ms).
+//      hit is queued and looked up in the row with the others of the window.
+// A tile's dependent loads (forward records, entries, their records, streams)
+// are taken once for 512 edges.  Measured on 4096 graphs of 64 to 65536
+// vertices (1.08 G entries) and one Chung-Lu graph (n = 30011, mean degree
+// 20): a wave per vertex with a 65536-bit map of its own took 43.1 ms and
+// 0.54 ms; tiles of 512 entries of both directions, hits looked up where they
+// were found, 15.3 ms (6.8 of them the tiles' set-up, half of it for entries
+// that have no stream) and 94 us (45 of them the look-ups of the few lanes
+// with hits, the other lanes waiting); this form 9.6 ms and 52 us.  VALU
+// bound, at seven waves per SIMD, which the 22 KB of LDS allow.
 // kWide: one graph of any number of vertices (ids of 32 bits in LDS; a bit of
 // the filter then also stands for the ids 65536 apart).
 template <int THREADS, bool kRec, bool kWide>
@@ -454,19 +459,23 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
   static_assert(kPer * THREADS == kTile, "whole entries per thread");
   __shared__ alignas(16) uint32_t s_filt[kFilterBits / 32];
   // streams of the tile: first chunk, entry position of the list (relative to
-  // the graph), length | filter offset of the row << 16, position of the edge
-  // in the tile
+  // the graph), length | filter offset of the row << 16, the places of the
+  // row's entries after the edge's (first | end << 16)
   using Id = typename std::conditional<kWide, int32_t, uint16_t>::type;
   __shared__ uint4 s_st[kTile];
-  __shared__ Id s_col[kTile];
-  __shared__ Id s_own[kTile];  // at a row's first entry in the tile: the row
+  __shared__ Id s_col[kCols];  // ids of the tile's entries, then of the last row's beyond it as far as they fit
+  __shared__ uint16_t s_own[kTile];  // at a row's first entry in the tile: the row (from the tile's first one)
   __shared__ alignas(8) uint32_t s_beg[kTile / 32];  // bits of those entries
-  __shared__ int32_t s_row[kRowCap];
+  __shared__ uint2 s_q[kQueue];  // list entries with a hit, and their stream's places
+  uint32_t* s_src = reinterpret_cast<uint32_t*>(s_q);  // before the hits: a row's first position less its place
+  static_assert(sizeof(s_q) >= sizeof(uint32_t) * kTile, "s_src fits");
   __shared__ uint32_t s_M[kWinTiles][2];
   __shared__ int32_t s_tb[kWinTiles];
   __shared__ uint32_t sh[NW + 1];
   __shared__ uint32_t s_sum[2][NW];
-  __shared__ int s_long;
+  __shared__ uint2 s_cut;
+  __shared__ uint32_t s_cur;
+  __shared__ int s_long, s_qn, s_next, s_done;
   const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / kWave), ln = lane();
   for (int64_t bi = blockIdx.x;; bi += gridDim.x) {
     // consecutive blocks go to different XCDs: by_xcd gives the blocks of one
@@ -493,50 +502,110 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
     const int64_t pe = min(ps + piece, rows[n]);
     // every list ends a whole chunk before the columns do
     const bool inside = rows[n] + kBChunk <= total_nnz;
-    int64_t cnt = 0, hc = 0;  // of the piece, in thread 0
-    int vb = pc.y;
     // the next slot's first row bounds the piece's (the last row of the graph
     // where that slot is empty or another graph's)
     const int2 pn = sl + 1 < nslots ? pieces[sl + 1] : make_int2(-1, 0);
     const int vz = pn.x == g ? pn.y : n - 1;
-    for (int64_t tb = ps; tb < pe; tb += kTile) {
-      const int tn = static_cast<int>(min(static_cast<int64_t>(kTile), pe - tb));
-      // entries and the filter's clearing are in flight while the row starts arrive
-      int32_t v[kPer];
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        const int e = tid + j * THREADS;
-        v[j] = e < tn ? cols[tb + e] : -1;
+    uint32_t tc = 0, th = 0;  // of the tiles not yet added up
+    int tiles_left = kSumTiles;
+    auto add_up = [&]() {
+      tc = wave_sum(tc);
+      th = wave_sum(th);
+      if (ln == 0) {
+        s_sum[0][wv] = tc;
+        s_sum[1][wv] = th;
       }
+      __syncthreads();
+      if (tid == 0) {
+        int64_t cnt = 0, hc = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          cnt += s_sum[0][q];
+          hc += s_sum[1][q];
+        }
+        if (cnt) atomicAdd(reinterpret_cast<unsigned long long*>(&T[g]), static_cast<unsigned long long>(cnt));
+        if (hc && H) atomicAdd(reinterpret_cast<unsigned long long*>(&H[g]), static_cast<unsigned long long>(hc));
+        if (hc && H2) atomicAdd(reinterpret_cast<unsigned long long*>(H2), static_cast<unsigned long long>(hc));
+      }
+      tc = th = 0;
+      tiles_left = kSumTiles;
+    };
+    // positions are relative to the graph's first entry
+    const uint32_t end = static_cast<uint32_t>(pe - e0);
+    uint32_t cur = static_cast<uint32_t>(ps - e0);  // the piece's entries before it are done
+    int vb = pc.y;
+    for (;;) {
       __syncthreads();  // the previous tile is done with the LDS
+      // the forward parts of the next rows, as far as the piece has them
+      uint32_t fs[kRows], fl[kRows], fe[kRows];
+      uint32_t sum = 0;
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int r = vb + tid * kRows + k;
+        fs[k] = fl[k] = fe[k] = 0;
+        if (r > vz) continue;
+        if (kRec) {
+          const FwdRec q = rec[v0 + r];
+          fs[k] = static_cast<uint32_t>((static_cast<int64_t>(q.lo) | (static_cast<int64_t>(q.hi_len & 0xFFu) << 32)) - e0);
+          fe[k] = fs[k] + (q.hi_len >> 8);
+        } else {
+          const int64_t e = rows[r + 1];
+          fs[k] = static_cast<uint32_t>(upper_bound_dev(cols, rows[r], e, r) - e0);
+          fe[k] = static_cast<uint32_t>(e - e0);
+        }
+      }
       for (int i = tid; i < kFilterBits / 128; i += THREADS)
         reinterpret_cast<uint4*>(s_filt)[i] = make_uint4(0u, 0u, 0u, 0u);
       if (tid < kTile / 32) s_beg[tid] = 0u;
-      if (tid == 0) s_long = 0;
-      const int nrow = static_cast<int>(min(static_cast<int64_t>(kRowCap), static_cast<int64_t>(vz) - vb + 2));
-      int have = 0;
-      do {
-        const int i = have + tid;
-        if (i < nrow) s_row[i] = static_cast<int32_t>(min(rows[vb + i] - tb, static_cast<int64_t>(1 << 30)));
-        __syncthreads();
-        have = min(have + THREADS, nrow);
-      } while (have < nrow && s_row[have - 1] < tn);
-      const bool staged = have > 0 && s_row[have - 1] >= tn;  // every row of the tile ends inside s_row
-      // row r (relative to vb) starts at tile position start_of(r)
-      auto start_of = [&](int r) -> int32_t {
-        if (r < have) return s_row[r];
-        return static_cast<int32_t>(min(rows[vb + r] - tb, static_cast<int64_t>(1 << 30)));
-      };
-      // rows with entries in the tile mark their first one
-      for (int r = tid; r < (staged ? have - 1 : n - vb); r += THREADS) {
-        const int32_t b = max(start_of(r), 0);
-        if (b >= tn) break;
-        if (start_of(r + 1) > b) {
-          s_own[b] = static_cast<Id>(r);
-          atomicOr(&s_beg[b >> 5], 1u << (b & 31));
+      if (tid == 0) {
+        s_long = s_qn = 0;
+        s_next = vb + kRows * THREADS;
+        s_cut = make_uint2(0u, 0u);
+        s_done = 0;
+      }
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const uint32_t z = min(fe[k], end);
+        fs[k] = max(fs[k], cur);
+        fl[k] = z > fs[k] ? z - fs[k] : 0u;
+        sum += fl[k];
+      }
+      uint32_t total;
+      uint32_t at0 = block_excl_scan(sum, sh, &total);
+      const int tn = static_cast<int>(min(total, static_cast<uint32_t>(kTile)));
+      // rows mark their first entry of the tile; the row that goes on past it
+      // is the next tile's first
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        if (fe[k] >= end && vb + tid * kRows + k <= vz) s_done = 1;  // no later row has entries of the piece
+        if (fl[k] && at0 <= kTile) {
+          if (at0 < kTile) {
+            s_own[at0] = static_cast<uint16_t>(tid * kRows + k);
+            s_src[at0] = fs[k] - at0;
+            atomicOr(&s_beg[at0 >> 5], 1u << (at0 & 31));
+          }
+          const uint32_t z = min(fl[k], kTile - at0);
+          if (fl[k] > z) {
+            s_next = vb + tid * kRows + k;
+            s_cur = fs[k] + z;
+          }
+          if (z > 0 && fe[k] > fs[k] + z) s_cut = make_uint2(fs[k] + z, fe[k]);
         }
+        at0 += fl[k];
       }
       __syncthreads();
+      const bool last_tile = total <= kTile && s_done;
+      if (total == 0) {  // uniform, as all below
+        if (last_tile) break;
+        int nb = vb + kRows * THREADS;
+        if (nb > vz) break;
+        // empty rows are skipped together
+        const int64_t at = rows[nb];
+        if (at == rows[vb]) nb = static_cast<int>(upper_bound_dev(rows, nb, vz + 1, at)) - 1;
+        if (at >= pe) break;
+        vb = nb;
+        continue;
+      }
       // an entry's row is that of the last mark at or before it: in its own
       // 64 entries (one wave's), else in the last group before with a mark;
       // the mark's rank places the row in the filter
@@ -548,38 +617,49 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
       };
       const int upto = wave_incl_scan(__popcll(marks));
       const int nrows = wave_read(upto, kTile / kWave - 1);
-      int u[kPer], rk[kPer];
+      const uint2 cut = s_cut;  // the last row's entries beyond the tile, of them in s_col up to place held
+      const int held = static_cast<int>(min(static_cast<uint32_t>(tn) + (cut.y - cut.x), static_cast<uint32_t>(kCols)));
+      // disjoint ranges of the filter per row where they fit: a set bit is then exact
+      const bool exact = static_cast<int64_t>(nrows) * n <= kFilterBits;
+      const uint32_t step = exact ? static_cast<uint32_t>(n) : kRowStep;
+      int u[kPer];
+      int32_t v[kPer];
+      uint32_t off[kPer], az[kPer];  // the row's place in the filter, the places of its entries after this one
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         const int e = tid + j * THREADS, q = wv + j * NW;
-        u[j] = rk[j] = 0;
+        u[j] = 0;
+        v[j] = -1;
+        off[j] = az[j] = 0u;
         if (q * kWave >= tn) continue;  // uniform per wave
         const uint64_t below = some & ((1ull << q) - 1ull);
         const int before = below ? last_mark(below) : 0;
         const uint64_t own = wave_read(marks, q) & ((2ull << ln) - 1ull);
         const int at = own ? q * kWave + 63 - __clzll(static_cast<long long>(own)) : before;
-        rk[j] = (q > 0 ? wave_read(upto, q - 1) : 0) + __popcll(own) - 1;
+        const uint64_t rest = wave_read(marks, q) & ~((2ull << ln) - 1ull), above = some & ~((2ull << q) - 1ull);
+        int after = held;
+        if (above) {
+          const int qa = __ffsll(static_cast<unsigned long long>(above)) - 1;
+          after = qa * kWave + __ffsll(static_cast<unsigned long long>(wave_read(marks, qa))) - 1;
+        }
+        const int row_end = rest ? q * kWave + __ffsll(static_cast<unsigned long long>(rest)) - 1 : after;
+        az[j] = static_cast<uint32_t>(e + 1) | (static_cast<uint32_t>(row_end) << 16);
+        const int rank = (q > 0 ? wave_read(upto, q - 1) : 0) + __popcll(own) - 1;
+        off[j] = __umul24(rank, step) & (kFilterBits - 1);
         if (e < tn) {
           u[j] = vb + static_cast<int>(s_own[at]);
-          s_col[e] = static_cast<Id>(v[j]);
+          v[j] = cols[e0 + (s_src[at] + static_cast<uint32_t>(e))];
         }
       }
-      const int last = s_own[last_mark(some)];
-      // disjoint ranges of the filter per row where they fit: a set bit is then exact
-      const bool exact = static_cast<int64_t>(nrows) * n <= kFilterBits;
-      const uint32_t step = exact ? static_cast<uint32_t>(n) : kRowStep;
-      uint32_t beg[kPer], len[kPer], off[kPer];
-      // chunks | streams << 22: fewer than 2^22 chunks in all, as at most 21
+      uint32_t beg[kPer], len[kPer];
+      // chunks | streams << 22: fewer than 2^22 chunks in all, as at most 28
       // entries of a tile have lists beyond kLongList in a simple graph (their
       // ids are below 8); in any other kLongMany keep their length
       uint32_t mine = 0;
-      uint32_t tc = 0, th = 0;
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         len[j] = beg[j] = 0;
-        off[j] = __umul24(rk[j], step) & (kFilterBits - 1);
-        if (v[j] <= u[j]) continue;  // also the positions past the tile (-1)
-        th += par_bit(par, v[j]) == par_bit(par, u[j]);
+        if (v[j] < 0) continue;  // past the tile
         if (kRec) {
           const FwdRec r = rec[v0 + v[j]];
           const int64_t f = static_cast<int64_t>(r.lo) | (static_cast<int64_t>(r.hi_len & 0xFFu) << 32);
@@ -591,21 +671,25 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
           beg[j] = static_cast<uint32_t>(f - e0);
           len[j] = static_cast<uint32_t>(min(e - f, kFwdLenMax));
         }
-        if (len[j] > kLongList && atomicAdd(&s_long, 1) >= kLongMany) len[j] = kLongList;
+        th += par_bit(par, v[j]) == par_bit(par, u[j]);
+        s_col[tid + j * THREADS] = static_cast<Id>(v[j]);
         const uint32_t h = (static_cast<uint32_t>(v[j]) + off[j]) & (kFilterBits - 1);
         atomicOr(&s_filt[h >> 5], 1u << (h & 31));
+        if (len[j] > kLongList && atomicAdd(&s_long, 1) >= kLongMany) len[j] = kLongList;
         if (len[j]) mine += (len[j] + kBChunk - 1) / kBChunk + (1u << 22);
       }
-      const int32_t tail = start_of(last + 1);  // end of the last row
       {
         const uint32_t toff = static_cast<uint32_t>(nrows - 1) * step;
-        for (int k = tn + tid; k < tail; k += THREADS) {
-          const int32_t w = cols[tb + k];
-          if (w <= vb + last) continue;
+        for (uint32_t k = cut.x + tid; k < cut.y; k += THREADS) {
+          const int32_t w = cols[e0 + k];
           const uint32_t h = (static_cast<uint32_t>(w) + toff) & (kFilterBits - 1);
           atomicOr(&s_filt[h >> 5], 1u << (h & 31));
+          const uint32_t at = tn + (k - cut.x);
+          if (at < kCols) s_col[at] = static_cast<Id>(w);
         }
       }
+      const int next = s_next;
+      if (total > kTile) cur = s_cur;
       uint32_t tot;
       const uint32_t pre = block_excl_scan(mine, sh, &tot);
       constexpr uint32_t kChunks = (1u << 22) - 1u;
@@ -615,12 +699,26 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           if (!len[j]) continue;
-          s_st[slot] = make_uint4(static_cast<uint32_t>(ch), beg[j], len[j] | (off[j] << 16),
-                                  static_cast<uint32_t>(tid + j * THREADS));
+          s_st[slot] = make_uint4(static_cast<uint32_t>(ch), beg[j], len[j] | (off[j] << 16), az[j]);
           ++slot;
           ch += static_cast<int>((len[j] + kBChunk - 1) / kBChunk);
         }
       }
+      // whether x is among the places az (first | end << 16) of a row, or,
+      // where these are the last row's, in the rest of it past s_col
+      auto in_row = [&](int32_t x, uint32_t az) -> uint32_t {
+        const int z = static_cast<int>(az >> 16);
+        int lo = static_cast<int>(az & 0xFFFFu), hi = z;
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (s_col[mid] < x) lo = mid + 1;
+          else hi = mid;
+        }
+        if (lo < z) return s_col[lo] == x;
+        if (z != held || cut.x + (held - tn) >= cut.y) return 0u;
+        const int64_t q0 = lower_bound_dev(cols, e0 + cut.x + (held - tn), e0 + cut.y, x);
+        return q0 < e0 + cut.y && cols[q0] == x;
+      };
       for (int w0 = 0; w0 < C; w0 += kWinTiles * kWave) {
         for (int i = tid; i < kWinTiles * 2; i += THREADS) (&s_M[0][0])[i] = 0u;
         __syncthreads();
@@ -652,100 +750,81 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
           const int k0 = (c - static_cast<int>(st.x)) * kBChunk;
           const int rem = static_cast<int>(st.z & 0xFFFFu) - k0;
           const uint32_t so = st.z >> 16;
-          int64_t p0 = e0 + st.y + k0;
+          const uint32_t p0 = st.y + static_cast<uint32_t>(k0);
           uint32_t valid = rem >= kBChunk ? (1u << kBChunk) - 1u : (1u << rem) - 1u;
           int32_t w[kBChunk];
           if (inside) {  // the whole chunk is loaded
 #pragma unroll
-            for (int q = 0; q < kBChunk; ++q) w[q] = cols[p0 + q];
+            for (int q = 0; q < kBChunk; ++q) w[q] = cols[e0 + p0 + q];
           } else if (total_nnz >= kBChunk) {  // moved back where it would pass the columns' end
-            const int64_t over = p0 + kBChunk - total_nnz;
-            if (over > 0) {
-              p0 -= over;
-              valid <<= over;
-            }
+            const int64_t over = e0 + p0 + kBChunk - total_nnz;
+            const int64_t back = over > 0 ? over : 0;
+            valid <<= back;
 #pragma unroll
-            for (int q = 0; q < kBChunk; ++q) w[q] = cols[p0 + q];
+            for (int q = 0; q < kBChunk; ++q) w[q] = cols[e0 + p0 - back + q];
           } else {
 #pragma unroll
-            for (int q = 0; q < kBChunk; ++q) w[q] = q < rem ? cols[p0 + q] : 0;
+            for (int q = 0; q < kBChunk; ++q) w[q] = q < rem ? cols[e0 + p0 + q] : 0;
           }
           uint32_t hits = 0;
-          const uint8_t* bytes = reinterpret_cast<const uint8_t*>(s_filt);
 #pragma unroll
           for (int q = 0; q < kBChunk; ++q) {
-            const uint32_t h = (static_cast<uint32_t>(w[q]) + so) & (kFilterBits - 1);
-            hits |= ((static_cast<uint32_t>(bytes[h >> 3]) >> (h & 7)) & 1u) << q;
+            const uint32_t h = static_cast<uint32_t>(w[q]) + so;
+            hits |= __builtin_amdgcn_ubfe(s_filt[(h & (kFilterBits - 1)) >> 5], h & 31, 1) << q;
           }
           hits &= valid;
           if (exact) {
             tc += __popc(hits);
-          } else if (hits) {
-            // the row's entries after v: from a to the next mark, or to the
-            // tile's end and on to the last row's
-            const int a = static_cast<int>(st.w) + 1;
-            int z = tn;
-            for (int q = a >> 5; q < kTile / 32; ++q) {
-              const uint32_t m = s_beg[q] & (q == (a >> 5) ? ~0u << (a & 31) : ~0u);
-              if (m) {
-                z = q * 32 + __ffs(m) - 1;
-                break;
-              }
-            }
-            while (hits) {
-              const int32_t x = cols[p0 + __ffs(hits) - 1];
+            continue;
+          }
+          // hits, real and false ones, are looked up together after the
+          // window: one here and there, they would stop a whole wave each
+          for (uint64_t any = __ballot(hits != 0u); any; any = __ballot(hits != 0u)) {
+            const int first = __ffsll(static_cast<unsigned long long>(any)) - 1;
+            int base = 0;
+            if (ln == first) base = atomicAdd(&s_qn, __popcll(any));
+            base = wave_read(base, first);
+            if (hits) {
+              int32_t x = w[0];
+#pragma unroll
+              for (int q = 1; q < kBChunk; ++q)
+                if ((hits & ((1u << q) - 1u)) == 0u) x = w[q];
               hits &= hits - 1;
-              int lo = a, hi = z;
-              while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (s_col[mid] < x) lo = mid + 1;
-                else hi = mid;
-              }
-              if (lo < z) tc += s_col[lo] == x;
-              else if (z == tn && tail > tn) {
-                const int64_t q0 = lower_bound_dev(cols, tb + tn, tb + tail, x);
-                tc += q0 < tb + tail && cols[q0] == x;
-              }
+              const int to = base + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                                        static_cast<uint32_t>(any >> 32),
+                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(any), 0u)));
+              if (to < kQueue) s_q[to] = make_uint2(static_cast<uint32_t>(x), st.w);
+              else tc += in_row(x, st.w);
             }
           }
         }
         __syncthreads();
+        const int nq = min(s_qn, kQueue);
+        for (int i = tid; i < nq; i += THREADS) tc += in_row(static_cast<int32_t>(s_q[i].x), s_q[i].y);
+        __syncthreads();
+        if (tid == 0) s_qn = 0;
       }
-      // a tile's sums fit 32 bits (fewer than 2^22 chunks of 8)
-      tc = wave_sum(tc);
-      th = wave_sum(th);
-      if (ln == 0) {
-        s_sum[0][wv] = tc;
-        s_sum[1][wv] = th;
-      }
-      __syncthreads();
-      if (tid == 0) {
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-          cnt += s_sum[0][q];
-          hc += s_sum[1][q];
-        }
-      }
-      // the row of the next tile's first entry
-      if (tail > tn) vb += last;
-      else vb += last + 1;
+      if (last_tile) break;
+      vb = next;
+      if (vb > vz) break;
+      if (--tiles_left == 0) add_up();
     }
-    if (tid == 0) {
-      if (cnt) atomicAdd(reinterpret_cast<unsigned long long*>(&T[g]), static_cast<unsigned long long>(cnt));
-      if (hc && H) atomicAdd(reinterpret_cast<unsigned long long*>(&H[g]), static_cast<unsigned long long>(hc));
-      if (hc && H2) atomicAdd(reinterpret_cast<unsigned long long*>(H2), static_cast<unsigned long long>(hc));
-    }
+    add_up();
   }
 }
 
 // Piece size where the caller names none: the entries are spread over about
 // kAutoSlots blocks (eight per CU, what their LDS allows), one wave each for
-// the smallest graphs, until a piece is one whole tile.
-constexpr int64_t kAutoSlots = 2048;
+// the smallest graphs, until a piece is one whole tile of forward entries
+// (half its entries, on average); where there are kAutoMany of those, two
+// tiles a piece waste less of the last one (4096 graphs: 14.3 ms at 1024
+// entries, 13.5 at 2048, 14.2 at 4096, 15.1 at 8192; 17.9 at 512).
+constexpr int64_t kAutoSlots = 2048, kAutoMany = 16384;
+constexpr int kAutoMax = 2048;
 
 int auto_piece(int64_t total_nnz) {  // a power of two, so that the kernels shift instead of dividing
   int piece = kAutoMin;
-  while (piece < kTile && 2 * piece * kAutoSlots <= total_nnz) piece *= 2;
+  while (piece < kAutoMax && 2 * piece * (piece < 2 * kTile ? kAutoSlots : kAutoMany) <= total_nnz) piece *= 2;
   return piece;
 }
 
@@ -923,17 +1002,18 @@ size_t direct_ws_bytes(int64_t n, int64_t nnz) { return plan_direct(nullptr, n, 
 // The streams are sum over v of d+(v) (d(v) - d+(v)) elements, about a sixth
 // of the squared degrees whatever the graph (within 10% on G(n, p), Chung-Lu
 // and R-MAT graphs).  The relabelled path streams fewer on graphs with hubs
-// but has its layout, plan and resolution to pay.  Measured, both ways, ms
-// (relabelled / direct): G(300007, d 24) 0.91 / 0.36, G(2000003, d 40) 12.5 /
-// 3.1; Chung-Lu n = 300007 mean degree 20 (48 elements an entry) 0.96 / 0.79,
-// degree 40 (73) 1.38 / 1.73; n = 2000003 degree 12 (74) 2.75 / 2.78; R-MAT
-// scale 14 (61) 0.49 / 0.23, 15 (84) 0.57 / 0.67, 16 (114) 0.60 / 0.92, 17
-// with edge factor 6 (75) 0.59 / 0.70.  The line lies at 48 elements an entry
-// and 2^24 more, which is what the launches alone are worth.
+// but has its layout, plan and resolution to pay.  Measured, both ways, us
+// (relabelled / direct): G(300007, d 24) 783 / 293, G(2000003, d 40) 12100 /
+// 2340; Chung-Lu n = 300007 mean degree 12 (35 elements an entry) 700 / 673,
+// 20 (48) 941 / 1036, 40 (73) 1383 / 1845; n = 1000003 degree 12 (56) 1629 /
+// 1463, 20 (76) 2234 / 2440; n = 2000003 degree 6 (49) 2178 / 1809, 12 (74)
+// 2724 / 2847; R-MAT scale 14 (61) 358 / 149, 15 (84) 437 / 316, 16 (114) 501
+// / 1034, 17 with edge factor 6 (75) 492 / 712.  The line lies at 48 elements
+// an entry and 2^25 more, which is what the launches alone are worth.
 bool direct_fits(int64_t n, int64_t nnz, const BfsInfo& info) {
   // list lengths of 16 bits and positions of 32 in the streams
   if (n >= INT32_MAX || nnz >= (int64_t(1) << 31) || info.maxdeg > kFwdLenMax) return false;
-  return info.deg2 / 6 <= 48ull * static_cast<uint64_t>(nnz) + (1ull << 24);
+  return info.deg2 / 6 <= 48ull * static_cast<uint64_t>(nnz) + (1ull << 25);
 }
 
 int direct_count_run(const tc_csr* g, const int32_t* L, const BfsInfo& info, int64_t* stats, int64_t* triangles,
