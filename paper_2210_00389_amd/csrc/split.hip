@@ -1,4 +1,4 @@
-// split.hip -- level-class layout of the adjacency and the cover-edge list.
+// split.hip -- level-class layout of the adjacency.
 //
 // Alg. 1 selects the horizontal edges (L(u) = L(v), u < v) and tests every
 // common neighbour w of a cover edge against L(w) = L(u).  BFS levels of
@@ -12,16 +12,12 @@
 // leaving x.  The counting kernels then evaluate the paper's test
 // structurally (see count.hip).
 //
-// Two layouts share the row engine:
-//   * identity: same vertex ids, classes from the given int32 levels (any
-//     level function; used for the explicit cover-edge list);
-//   * relabelled (for counting): vertices renumbered by (virtual level,
-//     degree group, id), columns rewritten to the new ids, classes read off
-//     the new id ranges.  The method only compares ids inside one
-//     (component, level) class, and any total order there gives the same H
-//     (as a set), T and per-vertex counts; each level becomes a contiguous
-//     id range, which keeps the probe sets of the counting kernels inside a
-//     small id window.
+// Vertices are renumbered by (virtual level, degree group, id), columns
+// rewritten to the new ids, classes read off the new id ranges.  The method
+// only compares ids inside one (component, level) class, and any total order
+// there gives the same H (as a set), T and per-vertex counts; each level
+// becomes a contiguous id range, which keeps the probe sets of the counting
+// kernels inside a small id window.
 //
 // Rows of up to kShort entries are handled by one thread each; longer rows of
 // up to kMidCap entries by one wave, of up to kBigCap by one block, each held
@@ -49,15 +45,15 @@ constexpr int kBigR = 16;
 constexpr int kBigCap = kBigWaves * kBigR * 64;  // 4096
 static_assert(kBigCap >= kSeg, "a segmented row has at least one full segment");
 
-// ---------------------------------------------------------- layouts
+// ----------------------------------------------------------- layout
 // A row is written as [Up | Same | Down], each ascending in the output
-// numbering.  In the relabelled numbering every level is itself split in
+// numbering, where every level is itself split in
 // G id ranges by vertex degree (deg_group: G = 4 on large graphs, G = 2 on
 // the others), each in input id order, so each class region is G ascending
 // runs: the layout is a stable partition of the sorted input row into
 // NG = 3 G groups, group
-//   class * G + degree group   (class 0 up, 1 same, 2 down)
-// (the identity layout has G = 1).  Group codes take 4 bits.
+//   class * G + degree group   (class 0 up, 1 same, 2 down).
+// Group codes take 4 bits.
 constexpr int kMaxDegGroups = 4;
 constexpr int kMaxGroups = 3 * kMaxDegGroups;
 constexpr int kNoGroup = 15;
@@ -86,33 +82,6 @@ struct alignas(8) RowCtxT {
   int32_t b[NG - 1];   // relabelled: first id of groups 1 .. NG - 1 (ascending)
 };
 static_assert(sizeof(RowCtxT<kMaxGroups>) == 80, "row contexts are stored as whole int64 words");
-
-struct IdentityLayout {
-  static constexpr int kG = 1;  // one degree group: groups 0 up, 1 same, 2 down
-  static constexpr bool kCore = false;
-  using Ctx = RowCtxT<3>;
-  const int64_t* off;
-  const int32_t* L;
-  __device__ __forceinline__ int32_t core_from(const Ctx&, int) const { return INT32_MIN; }
-  __device__ __forceinline__ void write16(const Ctx&, int64_t, int, int32_t) const {}
-  __device__ __forceinline__ Ctx ctx(int64_t i) const {
-    Ctx c{};
-    c.ib = off[i];
-    c.ie = off[i + 1];
-    c.ob = c.ib;
-    c.self = static_cast<int32_t>(i);
-    c.key = L[i];
-    return c;
-  }
-  __device__ __forceinline__ int recls(const Ctx& c, int32_t v) const {
-    const int lv = L[v];
-    return lv < c.key ? 0 : (lv == c.key ? 1 : 2);
-  }
-  __device__ __forceinline__ int cls(const Ctx& c, int32_t w, int32_t& v) const {
-    v = w;
-    return recls(c, w);
-  }
-};
 
 template <int G, bool CORE>
 struct RelabelLayout {
@@ -840,46 +809,9 @@ __global__ __launch_bounds__(kThreads) void vg_place_kernel(const int64_t* off, 
   }
 }
 
-// ------------------------------------------------------- H list
-__global__ void hcount_kernel(const VMeta* meta, int64_t n, int32_t* hc) {
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
-    hc[x] = meta[x].sfe - meta[x].hfb;
-}
-
-// Rows with at most kShort cover edges: one thread; longer: one wave.
-__global__ __launch_bounds__(kThreads) void hlist_kernel(const VMeta* meta, const int32_t* cols, int64_t n,
-                                                         const int64_t* h_off, int64_t cap, int32_t* h_u,
-                                                         int32_t* h_v) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += stride) {
-    const VMeta m = meta[x];
-    const int hf = m.sfe - m.hfb;
-    if (hf == 0 || hf > kShort) continue;
-    const int64_t src = m.begin + m.hfb, dst = h_off[x];
-    for (int i = 0; i < hf && dst + i < cap; ++i) {
-      h_u[dst + i] = static_cast<int32_t>(x);
-      h_v[dst + i] = cols[src + i];
-    }
-  }
-  const int64_t wid = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = stride / kWave;
-  for (int64_t x = wid; x < n; x += nw) {
-    const VMeta m = meta[x];
-    const int hf = m.sfe - m.hfb;
-    if (hf <= kShort) continue;
-    const int64_t src = m.begin + m.hfb, dst = h_off[x];
-    for (int i = lane(); i < hf && dst + i < cap; i += kWave) {
-      h_u[dst + i] = static_cast<int32_t>(x);
-      h_v[dst + i] = cols[src + i];
-    }
-  }
-}
-
-__global__ void copy_total_kernel(const int64_t* h_off, int64_t n, int64_t* out) { *out = h_off[n]; }
-
 }  // namespace
 
-SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz, bool own_stash) {
+SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz) {
   SplitWs w;
   w.meta = c.take<VMeta>(n + 1);
   w.scols = c.take<int32_t>(nnz + kColPad);
@@ -895,16 +827,8 @@ SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz, bool own_stash) {
   constexpr int kCtxWords = sizeof(RowCtxT<kMaxGroups>) / sizeof(int64_t);  // the largest context
   w.mid_ctx = c.take<int64_t>(kCtxWords * (std::min(n, nnz / (kShort + 1)) + 2));
   w.big_ctx = c.take<int64_t>(kCtxWords * (nnz / (kMidCap + 1) + 2));
-  w.stash = own_stash ? c.take<int32_t>(nnz + 1) : nullptr;
+  w.stash = nullptr;
   return w;
-}
-
-int split_run(const tc_csr* g, const int32_t* L, bool full_levels, SplitWs& w, hipStream_t s) {
-  (void)full_levels;
-  if (g->n == 0) return TC_OK;
-  IdentityLayout lay{g->row_offsets, L};
-  TC_TRY(fill_i64(w.ctr, 0, 4, s));
-  return layout_run(lay, g->cols, g->n, g->nnz, g->nnz, w, s);
 }
 
 RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels) {
@@ -1002,25 +926,6 @@ int relabel_run(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_
   if (degree_groups == 4) return relabel_groups<4, false>(g, L, comp0, d0, nvl, maxdeg, w, sp, s);
   if (degree_groups == 2) return relabel_groups<2, false>(g, L, comp0, d0, nvl, maxdeg, w, sp, s);
   return fail(TC_ERR_INVALID_ARG, "relabel: degree_groups must be 2 or 4");
-}
-
-int hlist_run(const tc_csr* g, const VMeta* meta, const int32_t* cols, int64_t* h_off, int32_t* h_u, int32_t* h_v,
-              int64_t cap, int64_t* h_count, char* scratch, hipStream_t s) {
-  const int64_t n = g->n;
-  if (n == 0) {
-    TC_TRY(fill_i64(h_off, 0, 1, s));
-    if (h_count) TC_TRY(fill_i64(h_count, 0, 1, s));
-    return TC_OK;
-  }
-  Carver sc(scratch);
-  int32_t* hc = sc.take<int32_t>(n + 1);
-  hcount_kernel<<<grid_for(n, kThreads, 16384), kThreads, 0, s>>>(meta, n, hc);
-  TC_TRY(scan_exclusive<int32_t>(hc, h_off, n, sc, s));
-  if (h_u)
-    hlist_kernel<<<static_cast<unsigned>(num_cus() * 8), kThreads, 0, s>>>(meta, cols, n, h_off, cap, h_u, h_v);
-  if (h_count) copy_total_kernel<<<1, 1, 0, s>>>(h_off, n, h_count);
-  TC_HIP(hipGetLastError());
-  return TC_OK;
 }
 
 }  // namespace tc

@@ -69,7 +69,7 @@ CountPlan plan_count(void* base, int64_t n, int64_t nnz) {
   p.bfs.comp0 = p.comp0;
   Carver b(p.region);
   p.relabel = relabel_reserve(b, n, 2 * n + 2);
-  p.split = split_reserve(b, n, nnz, false);
+  p.split = split_reserve(b, n, nnz);
   p.count = count_reserve(b, n, nnz);
   p.split.stash = reinterpret_cast<int32_t*>(p.count.tl_words);  // written only after the layout
   p.count.stats = p.stats;
@@ -103,23 +103,6 @@ BaselinePlan plan_baseline(void* base, int64_t n, int64_t nnz) {
   return p;
 }
 
-struct CoverPlan {
-  SplitWs split;
-  int64_t* h_off;
-  char* hscratch;
-  size_t bytes;
-};
-
-CoverPlan plan_cover(void* base, int64_t n, int64_t nnz) {
-  CoverPlan p;
-  Carver c(base);
-  p.split = split_reserve(c, n, nnz, true);
-  p.h_off = c.take<int64_t>(n + 2);
-  p.hscratch = c.take<char>(scan_ws_bytes(n + 1) + (n + 1) * sizeof(int32_t) + 512);
-  p.bytes = c.used();
-  return p;
-}
-
 size_t bfs_bytes(int64_t n) {
   Carver c(nullptr);
   bfs_reserve(c, n);
@@ -146,7 +129,7 @@ size_t tc_workspace_bytes(int op, int64_t n, int64_t nnz, int32_t num_graphs) {
   switch (op) {
     case TC_OP_BUILD_CSR: b = build_ws_bytes(n, nnz); break;
     case TC_OP_BFS_LEVELS: b = bfs_bytes(n); break;
-    case TC_OP_COVER_EDGES: b = plan_cover(nullptr, n, nnz).bytes; break;
+    case TC_OP_COVER_EDGES: b = cover_ws_bytes(n, nnz); break;
     case TC_OP_COUNT: {
       const size_t a = plan_count(nullptr, n, nnz).bytes, sm = small_ws_bytes(n, nnz);
       b = a > sm ? a : sm;
@@ -204,15 +187,11 @@ int tc_cover_edges(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t
   TC_TRY(check_csr(g, "tc_cover_edges"));
   if (!h_count || (g->n > 0 && !levels) || (g->nnz > 0 && (!h_u || !h_v)))
     return fail(TC_ERR_INVALID_ARG, "tc_cover_edges: NULL argument");
-  TC_TRY(check_ws(ws, ws_bytes, plan_cover(nullptr, g->n, g->nnz).bytes, "tc_cover_edges"));
+  TC_TRY(check_ws(ws, ws_bytes, cover_ws_bytes(g->n, g->nnz), "tc_cover_edges"));
   hipStream_t s = static_cast<hipStream_t>(stream);
   CallScope scope(s);
-  if (g->n == 0) return fill_i64(h_count, 0, 1, s);
-  CoverPlan p = plan_cover(ws, g->n, g->nnz);
-  prof_stage("split");
-  TC_TRY(split_run(g, levels, true, p.split, s));
-  prof_stage("hlist");
-  return hlist_run(g, p.split.meta, p.split.scols, p.h_off, h_u, h_v, g->nnz / 2, h_count, p.hscratch, s);
+  prof_stage("cover_edges");
+  return cover_run(g, levels, h_u, h_v, g->nnz / 2, h_count, ws, s);
 }
 
 namespace {

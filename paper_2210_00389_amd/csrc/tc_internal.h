@@ -83,12 +83,8 @@ struct SplitWs {
   int64_t* big_ctx;
   int32_t* stash;     // output ids of segmented rows, in input order [nnz]
 };
-// own_stash false: the caller sets w.stash to memory that is free while the
-// rows are laid out.
-SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz, bool own_stash);
-// full_levels: classify by comparing int32 levels (any level function);
-// otherwise use packed residues (requires |L(u) - L(v)| <= 1 on edges).
-int split_run(const tc_csr* g, const int32_t* L, bool full_levels, SplitWs& w, hipStream_t s);
+// The caller sets w.stash to memory that is free while the rows are laid out.
+SplitWs split_reserve(Carver& c, int64_t n, int64_t nnz);
 
 // Relabelled layout for counting: vertices renumbered by (virtual level,
 // degree group, id) where the virtual level is L(v) in r0's component and
@@ -115,13 +111,12 @@ RelabelWs relabel_reserve(Carver& c, int64_t n, int64_t max_vlevels);
 int relabel_run(const tc_csr* g, const int32_t* L, const uint32_t* comp0, int32_t d0, int32_t max_vl,
                 int degree_groups, bool core, int64_t maxdeg, RelabelWs& w, SplitWs& sp, hipStream_t s);
 
-// Explicit horizontal-edge list from the layout: h_off = scan of
-// (sfe - hfb), then (x, scols[..]) for every cover edge, lexicographic.
-// At most `cap` entries are written (the caller's capacity); h_off[n] and
-// *h_count report the full count.
-int hlist_run(const tc_csr* g, const VMeta* meta, const int32_t* cols, int64_t* h_off,
-              int32_t* h_u, int32_t* h_v, int64_t cap, int64_t* h_count, char* scratch,
-              hipStream_t s);
+// Explicit horizontal-edge list of any int32 level function, lexicographic.
+// At most `cap` entries are written (the caller's capacity); *h_count reports
+// the full count.
+size_t cover_ws_bytes(int64_t n, int64_t nnz);
+int cover_run(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t* h_v, int64_t cap, int64_t* h_count,
+              void* ws, hipStream_t s);
 
 // ------------------------------------------------------------ count
 // Column buffers handed to count_run hold at least this many readable
