@@ -423,6 +423,21 @@ struct Task {
   int32_t rest;  // its first entries outside the core that the anchor's own may meet (core anchors)
 };
 
+// Forward lists whose backward cover edges are resolved from the column
+// samples (kLong).  Shorter ones are searched: their lines are few, and the
+// entries up to the next sample would be most of the list.  kLong goes with
+// the core streams, which read whole 128-byte lines of 16-bit ids, so that
+// starting at a sample costs them nothing (R-MAT scale 24: resolution 14.4 ->
+// 11.8 ms, core streams 18.8 ms either way); 32-bit streams lose by it what
+// the resolution wins (per-vertex counts of a Chung-Lu graph, n = 500009:
+// 1.76 -> 1.85 ms).
+template <bool kLong>
+__device__ __forceinline__ bool long_list(int len) { return kLong && len > kSampStride; }
+// The first sampled place at or past the entry b + 1 places before `end`.
+__device__ __forceinline__ int64_t taken_from(int64_t end, int b) {
+  return (end - b - 1 + kSampStride - 1) / kSampStride * kSampStride;
+}
+
 enum DescKind { kDown = 0, kFwd = 1, kBwd = 2, kNone = 3, kUpD = 4 };
 
 // Tasks of kResPer descriptors (vertex x[j], index k[j] in its descriptor
@@ -432,7 +447,7 @@ enum DescKind { kDown = 0, kFwd = 1, kBwd = 2, kNone = 3, kUpD = 4 };
 // A vertex's descriptors are [down | fwd | bwd | upd]: one per vertex of
 // Down(x) (when Hfwd(x) is not empty), of Hfwd(x), of the same-level
 // neighbours below x, and (cover count, |Up(x)| > upa) of Up(x).
-template <bool kCover>
+template <bool kCover, bool kLong>
 __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* samp, const VMeta* meta,
                                              const uint4* pm, const int32_t* x, const VMeta* mx, const int* kin,
                                              int upa, const bool* core, Task* ta, Task* tb) {
@@ -466,92 +481,87 @@ __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* s
 #pragma unroll
   for (int j = 0; j < kResPer; ++j)
     if (kind[j] != kNone) mo[j] = unpack_record(q[j], meta, nb[j]);
-  // Backward same class, cover edge (u, x) with u < x: the rule compares
-  // a = |Hfwd(u) ∩ (x, inf)| with b = |Hfwd(x)|.  The entry b + 1 places
-  // before the end of Hfwd(u) decides it with one load: above x, a > b and
-  // the forward descriptor of u takes the pair; equal to x, a = b; below,
-  // x lies among the last b entries, and only they are searched for it.
-  int64_t lo[kResPer], hi[kResPer], pp[kResPer];
-  bool srch[kResPer], prb[kResPer];
+  // Backward same class, cover edge (u, x) with u < x.  Where Hfwd(u) is
+  // short the rule compares a = |Hfwd(u) ∩ (x, inf)| with b = |Hfwd(x)|: the
+  // entry b + 1 places before the end of Hfwd(u) decides it with one load:
+  // above x, a > b and the forward descriptor of u takes the pair; equal to
+  // x, a = b; below, x lies among the last b entries, and only they are
+  // searched for it.  Where it is long (long_list) the column samples decide:
+  // x takes the pair from the first sampled entry at or past that place on,
+  // and streams Hfwd(u) from the last sampled entry at or below it (what lies
+  // below x meets nothing of Hfwd(x)), so that neither the entry nor x's
+  // place, a cache miss each, is read from the columns.
+  int64_t lo[kResPer], hi[kResPer], blo[kResPer], bhi[kResPer];
+  const int32_t* pp[kResPer];
+  bool srch[kResPer], prb[kResPer], lng[kResPer];
 #pragma unroll
   for (int j = 0; j < kResPer; ++j) {
-    srch[j] = prb[j] = false;
-    lo[j] = hi[j] = pp[j] = 0;
+    srch[j] = prb[j] = lng[j] = false;
+    lo[j] = hi[j] = blo[j] = bhi[j] = 0;
+    pp[j] = lc;
     const int b = mx[j].sfe - mx[j].hfb, lu = mo[j].sfe - mo[j].hfb;
     if (kind[j] == kBwd && b > 0 && lu > 0) {
-      srch[j] = true;
       lo[j] = mo[j].begin + mo[j].hfb;
       hi[j] = mo[j].begin + mo[j].sfe;
+      lng[j] = long_list<kLong>(lu);
       prb[j] = b + 1 < lu;
-      pp[j] = prb[j] ? hi[j] - b - 1 : 0;
+      srch[j] = !(lng[j] && prb[j]) || taken_from(hi[j], b) < hi[j];
+      prb[j] = prb[j] && srch[j];
+      blo[j] = lng[j] && prb[j] ? taken_from(hi[j], b) / kSampStride : (lo[j] + kSampStride - 1) / kSampStride;
+      bhi[j] = lng[j] ? (hi[j] - 1) / kSampStride + 1 : blo[j];
+      if (prb[j]) pp[j] = lng[j] ? samp + blo[j] : lc + (hi[j] - b - 1);
     }
   }
   {
     int32_t pv[kResPer];
 #pragma unroll
-    for (int j = 0; j < kResPer; ++j) pv[j] = lc[pp[j]];  // an idle slot reads column 0
+    for (int j = 0; j < kResPer; ++j) pv[j] = *pp[j];  // an idle slot reads column 0
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
       if (!prb[j]) continue;
-      if (pv[j] > x[j]) srch[j] = false;
-      else if (pv[j] == x[j]) lo[j] = hi[j] = pp[j];
-      else lo[j] = pp[j] + 1;
+      const int b = mx[j].sfe - mx[j].hfb;
+      if (pv[j] > x[j]) {
+        srch[j] = false;
+        bhi[j] = blo[j];
+      } else if (lng[j]) {
+        ++blo[j];
+      } else if (pv[j] == x[j]) {
+        lo[j] = hi[j] = hi[j] - b - 1;
+      } else {
+        lo[j] = hi[j] - b;
+      }
     }
   }
-  // First over the column samples (every kSampStride-th column, a compact
-  // array): the first sampled block start >= x narrows the range to one
-  // block, so the search touches about two cache lines instead of one per
-  // halving of a long list.
-  {
-    int64_t blo[kResPer], bhi[kResPer];
+  while (kLong) {  // long lists: first sample in [blo, bhi) above x
+    bool any = false;
+    int32_t v[kResPer];
+    int64_t mid[kResPer];
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
-      blo[j] = (lo[j] + kSampStride - 1) / kSampStride;  // samples inside [lo, hi)
-      bhi[j] = srch[j] ? (hi[j] - 1) / kSampStride + 1 : blo[j];
-      if (bhi[j] < blo[j]) bhi[j] = blo[j];
-    }
-    const int64_t b0[kResPer] = {blo[0], blo[1]};
-    static_assert(kResPer == 2, "the sample search is written for two descriptors");
-    for (;;) {  // first sample index in [blo, bhi) whose value is >= x
-      bool any = false;
-      int32_t v[kResPer];
-      int64_t mid[kResPer];
-#pragma unroll
-      for (int j = 0; j < kResPer; ++j) {
-        mid[j] = blo[j] + ((bhi[j] - blo[j]) >> 1);
-        v[j] = blo[j] < bhi[j] ? samp[mid[j]] : 0;
-      }
-#pragma unroll
-      for (int j = 0; j < kResPer; ++j) {
-        if (!(blo[j] < bhi[j])) continue;
-        if (v[j] < x[j]) blo[j] = mid[j] + 1;
-        else bhi[j] = mid[j];
-        any |= blo[j] < bhi[j];
-      }
-      if (!any) break;
+      mid[j] = blo[j] + ((bhi[j] - blo[j]) >> 1);
+      v[j] = blo[j] < bhi[j] ? samp[mid[j]] : 0;
     }
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
-      if (!srch[j]) continue;
-      // samples b0 .. blo-1 are < x, so entries up to (blo-1) * stride are < x;
-      // the sample at blo (if inside the range) is >= x
-      if (blo[j] > b0[j]) lo[j] = (blo[j] - 1) * kSampStride + 1;
-      const int64_t cap = blo[j] * kSampStride;
-      if (cap < hi[j]) hi[j] = cap;
+      if (!(blo[j] < bhi[j])) continue;
+      if (v[j] <= x[j]) blo[j] = mid[j] + 1;
+      else bhi[j] = mid[j];
+      any |= blo[j] < bhi[j];
     }
+    if (!any) break;
   }
-  for (;;) {
+  for (;;) {  // short lists: the place of x
     bool any = false;
     int32_t v[kResPer];
     int64_t mid[kResPer];
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
       mid[j] = lo[j] + ((hi[j] - lo[j]) >> 1);
-      v[j] = (srch[j] && lo[j] < hi[j]) ? lc[mid[j]] : 0;
+      v[j] = (srch[j] && !lng[j] && lo[j] < hi[j]) ? lc[mid[j]] : 0;
     }
 #pragma unroll
     for (int j = 0; j < kResPer; ++j) {
-      if (!(srch[j] && lo[j] < hi[j])) continue;
+      if (!(srch[j] && !lng[j] && lo[j] < hi[j])) continue;
       if (v[j] < x[j]) lo[j] = mid[j] + 1;
       else hi[j] = mid[j];
       any |= lo[j] < hi[j];
@@ -575,10 +585,14 @@ __device__ __forceinline__ void describe_all(const int32_t* lc, const int32_t* s
     } else if (kind[j] == kFwd) {  // forward cover edge (x, v)
       if (kCover && o.up > 0 && o.up <= m.up) ta[j] = Task{o.begin, o.up | kFlagUp, nb[j], 0};
       const int a = hf - k[j] - 1, b = o.sfe - o.hfb;
-      if (a > 0 && b > 0 && b < a) tb[j] = Task{o.begin + o.hfb, b, nb[j], 0};
+      const bool mine = long_list<kLong>(hf) ? b + 1 < hf && pos[j] < taken_from(m.begin + m.sfe, b) : b < a;
+      if (a > 0 && b > 0 && mine) tb[j] = Task{o.begin + o.hfb, b, nb[j], 0};
     } else if (kind[j] == kBwd) {  // backward cover edge (u, x), u < x
       if (kCover && o.up > 0 && o.up < m.up) ta[j] = Task{o.begin, o.up | kFlagUp, nb[j], 0};
-      if (srch[j]) {
+      if (srch[j] && lng[j]) {
+        const int64_t from = max(lo[j], (blo[j] - 1) * kSampStride), end = o.begin + o.sfe;
+        tb[j] = Task{from, static_cast<int32_t>(end - from), nb[j], 0};
+      } else if (srch[j]) {
         const int a = static_cast<int>(o.begin + o.sfe - lo[j]) - 1;  // lo = position of x
         if (a > 0 && hf >= a) tb[j] = Task{lo[j] + 1, a, nb[j], 0};
       }
@@ -687,7 +701,7 @@ __global__ void chunk_start_kernel(const int64_t* so, int64_t n, int32_t* cx0) {
 // records, light tasks, items).  No counter is shared between blocks.
 // Thread t takes descriptors d0 + t + j * kResThreads; records are placed in
 // descriptor order (j-major).
-template <bool kCover>
+template <bool kCover, bool kLong>
 __global__ __launch_bounds__(kResThreads) void resolve_kernel(
     const int32_t* lc, const int32_t* samp, const VMeta* meta, const uint4* pm, const uint16_t* vinfo,
     const int64_t* so, const int32_t* cx0, int64_t n, int64_t* sbeg, int32_t* slen, int32_t* soth, int32_t* sx,
@@ -755,7 +769,7 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
       core[j] = heavy[j] && (vi[j] & kViCore) != 0;
     }
     Task ta[kResPer], tb[kResPer];
-    describe_all<kCover>(lc, samp, meta, pm, xi, mx, kk, upa, core, ta, tb);
+    describe_all<kCover, kLong>(lc, samp, meta, pm, xi, mx, kk, upa, core, ta, tb);
     // Records outside the core follow the heavy records; where the region has
     // no room for them the chunk's core anchors stream whole lists.
     int64_t nr = 0;
@@ -1982,11 +1996,12 @@ int launch_all(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
   chunk_start_kernel<<<gv, kThreads, 0, s>>>(w.so, n, w.cx0);
   TC_HIP(hipGetLastError());
   prof_stage("resolve");
-  sample_kernel<<<grid_for(a.g->nnz / kSampStride + 1, kThreads, 16384), kThreads, 0, s>>>(a.cols, a.g->nnz,
-                                                                                           w.samp);
-  resolve_kernel<kCover><<<gr, kResThreads, 0, s>>>(a.cols, w.samp, a.meta, w.pm, w.vinfo, w.so, w.cx0, n, w.sbeg,
-                                                    w.slen, w.soth, w.sx, w.items_raw, w.ccnt, w.nchunk_cap,
-                                                    a.prm.item_log2, a.prm.up_anchor_min);
+  const bool lists = kCover && a.c16;
+  if (lists)
+    sample_kernel<<<grid_for(a.g->nnz / kSampStride + 1, kThreads, 16384), kThreads, 0, s>>>(a.cols, a.g->nnz, w.samp);
+  const auto resolve = lists ? resolve_kernel<kCover, kCover> : resolve_kernel<kCover, false>;
+  resolve<<<gr, kResThreads, 0, s>>>(a.cols, w.samp, a.meta, w.pm, w.vinfo, w.so, w.cx0, n, w.sbeg, w.slen, w.soth,
+                                     w.sx, w.items_raw, w.ccnt, w.nchunk_cap, a.prm.item_log2, a.prm.up_anchor_min);
   TC_HIP(hipGetLastError());
   {
     Carver sc(w.scratch);
