@@ -145,24 +145,32 @@ __device__ __forceinline__ void add_pv(int64_t* pv, int32_t v, int64_t count) {
   atomicAdd(reinterpret_cast<unsigned long long*>(&pv[v]), static_cast<unsigned long long>(count));
 }
 
-// Per-vertex counts of the apexes a block finds, in LDS: a slot holds the
-// first vertex that hashes to it, others go to memory.  The apexes of an
-// anchor are its probe set, so they repeat; the sums go out when the anchor
-// changes.  (With three atomics to memory per triangle the 32 KB bin took
-// 3.67 ms on a Chung-Lu graph of 500009 vertices.)
+// Per-vertex counts of the apexes a block finds, in LDS: an apex takes the
+// first of kPvProbes slots from its hash on that is free or its own, one that
+// finds none goes to memory.  The apexes of an anchor are its probe set, so
+// they repeat; the sums go out when the anchor changes.  Bound by the atomics
+// to memory: with three of them per triangle the 32 KB bin took 3.67 ms on a
+// Chung-Lu graph of 500009 vertices, with one slot an apex 0.27 ms; the
+// counts of R-MAT scale 20 (424 M triangles) take 8.9 ms, 9.1 with two slots
+// an apex, 11.1 with one.
 constexpr uint32_t kPvFree = 0xFFFFFFFFu;
+constexpr int kPvProbes = 4;  // slots an apex may take
 
 template <int SLOTS>
 struct PvCache {
   uint32_t* key;
   int32_t* sum;
+  int32_t* osum;  // per stream of the batch: its hits, the streamed vertex's count
   __device__ __forceinline__ void add(int64_t* pv, int32_t v) const {
     if (SLOTS > 0) {
-      const uint32_t slot = (static_cast<uint32_t>(v) * 0x9E3779B1u) >> (32 - __builtin_ctz(SLOTS > 0 ? SLOTS : 2));
-      const uint32_t was = atomicCAS(&key[slot], kPvFree, static_cast<uint32_t>(v));
-      if (was == kPvFree || was == static_cast<uint32_t>(v)) {
-        atomicAdd(&sum[slot], 1);
-        return;
+      uint32_t slot = (static_cast<uint32_t>(v) * 0x9E3779B1u) >> (32 - __builtin_ctz(SLOTS > 0 ? SLOTS : 2));
+      for (int p = 0; p < kPvProbes; ++p) {
+        const uint32_t was = atomicCAS(&key[slot], kPvFree, static_cast<uint32_t>(v));
+        if (was == kPvFree || was == static_cast<uint32_t>(v)) {
+          atomicAdd(&sum[slot], 1);
+          return;
+        }
+        slot = (slot + 1) & (SLOTS - 1);
       }
     }
     add_pv(pv, v, 1);
@@ -180,7 +188,7 @@ struct PvCache {
 // What the counting kernels do with each triangle they find:
 //   kOutNone  count only;
 //   kOutPV    also add one to each of its three vertices (per-vertex counts:
-//             the anchor's per item or task, the streamed list's per chunk or
+//             the anchor's per item or task, the streamed list's per batch or
 //             task, the apex's here);
 //   kOutRec   also record every work unit's count (ucnt: heavy items by their
 //             index in the item array, then light tasks by their index);
@@ -1279,7 +1287,7 @@ __device__ __forceinline__ uint32_t chunk_probe(const int32_t (&v)[kChunk], int 
   }
   hits &= lenmask;
   if (kOut == kOutPV && hits) {
-    add_pv(o.pv, oth, __popc(hits));
+    atomicAdd(&pvc.osum[oth], __popc(hits));
 #pragma unroll
     for (int q = 0; q < kChunk; ++q)
       if ((hits >> q) & 1u) pvc.add(o.pv, v[q]);
@@ -1374,7 +1382,7 @@ __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_
           const int k = c - cl.x;
           p = lc + s_beg[j] + static_cast<int64_t>(k) * kChunk;
           len = (cl.y & kLenMask) - k * kChunk;
-          if (needs_oth(kOut)) ot = s_oth[j];
+          if (kOut == kOutPV) ot = j;
           upside = (cl.y & kClUp) != 0;
         }
         cnt += chunk_hits<MODE, kOut>(p, len, ps, upside, x, ot, o, ebase, s_pos, wq, pvc);
@@ -1407,7 +1415,7 @@ __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_
             const int k = c - cl.x;
             e[u] = s_beg[j] + static_cast<int64_t>(k) * kChunk;
             len[u] = (cl.y & kLenMask) - k * kChunk;
-            if (needs_oth(kOut)) oth[u] = s_oth[j];
+            if (kOut == kOutPV) oth[u] = j;
             up[u] = (cl.y & kClUp) != 0;
           }
         }
@@ -1477,13 +1485,20 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
   __shared__ int64_t sh[THREADS / kWave + 1];
   __shared__ int32_t shi[THREADS / kWave + 1];
   __shared__ unsigned long long s_item;
-  // slots for the apexes' counts, as many as the LDS leaves room for (256 for
-  // the 2 KB bin, whose probe sets are small: 2.17 -> 1.85 ms on the graph above)
-  constexpr int kPv = kOut != kOutPV ? 0 : (WORDS == kBinWords0 ? 256 : (WORDS == kBinWords2 ? 512 : 2048));
+  // slots for the apexes' counts: 2 KB bin 128 / 256 / 512 / 1024 of them 15.2 /
+  // 14.6 / 11.1 / 11.2 ms at R-MAT scale 20 (one slot an apex); 32 KB bin 512 /
+  // 1024 / 2048 of them 42.5 / 22.4 / 14.6 ms, 4096 leave room for one block a
+  // CU (10.7 ms against 8.9 with four slots an apex)
+  constexpr int kPv = kOut != kOutPV ? 0 : (WORDS == kBinWords0 ? 512 : (WORDS == kBinWords2 ? 512 : 2048));
   __shared__ uint32_t s_pk[kPv > 0 ? kPv : 1];
   __shared__ int32_t s_ps[kPv > 0 ? kPv : 1];
-  const PvCache<kPv> pvc{s_pk, s_ps};
+  // the streamed lists' counts, one atomic to memory per stream (one per chunk
+  // with a hit took 6.1 ms more on the R-MAT graph above, 0.23 ms on the other)
+  __shared__ int32_t s_os[kPv > 0 ? D : 1];
+  const PvCache<kPv> pvc{s_pk, s_ps, s_os};
   int32_t pv_x = -1;
+  if (kPv > 0)
+    for (int i = threadIdx.x; i < D; i += THREADS) s_os[i] = 0;
   for (int i = threadIdx.x; i < kPv; i += THREADS) {
     s_pk[i] = kPvFree;
     s_ps[i] = 0;
@@ -1675,6 +1690,11 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
         got = run_chunks<kHash, THREADS, kOut, ahead_of<WORDS>()>(C, nslots, s_cl, s_beg, s_oth, s_M, s_tb, lc, ps, hx, o,
                                                ebase, &s_pos, s_q, pvc);
       }
+      if (kOut == kOutPV)  // (run_chunks ends with a barrier)
+        for (int i = tid; i < nslots; i += THREADS) {
+          if (s_os[i]) add_pv(o.pv, s_oth[i], s_os[i]);
+          s_os[i] = 0;
+        }
       // the per-item count is kept only where it is recorded
       if (kOut == kOutRec || kOut == kOutPV) icnt += got;
       else cnt += got;
