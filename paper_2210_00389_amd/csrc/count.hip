@@ -1319,11 +1319,46 @@ __device__ __forceinline__ uint32_t chunk_hits(const int32_t* p, int len, const 
   return chunk_probe<MODE, kOut>(v, len, ps, up_side, x, oth, o, ebase, s_pos, wq, pvc);
 }
 
+// The streams that start in a window of kTiles * 64 chunks from w0 on: a bit
+// per chunk (s_M), and per tile of 64 chunks the streams begun before it
+// (s_tb).  Every stream sets its own bit; a lane per tile that looked for its
+// streams one after another left the rest of the block waiting (R-MAT scale
+// 20: core items 0.79 -> 0.69 ms, 2 KB bin 0.38 -> 0.33 ms; scale 24: 32 KB
+// bin 1.40 -> 1.02 ms).  The caller has synchronised the block; it is synchronised
+// on return.
+template <int THREADS, int kTiles>
+__device__ __forceinline__ void mark_window(int w0, int nslots, const int2* s_cl, uint64_t* s_M, int32_t* s_tb) {
+  const int tid = threadIdx.x;
+  for (int t = tid; t < kTiles; t += THREADS) s_M[t] = 0ull;
+  __syncthreads();
+  uint32_t* m = reinterpret_cast<uint32_t*>(s_M);
+  for (int i = tid; i < nslots; i += THREADS) {
+    const int f = s_cl[i].x - w0;
+    if (f >= 0 && f < kTiles * kWave) atomicOr(&m[f >> 5], 1u << (f & 31));
+  }
+  __syncthreads();
+  if (tid < kWave) {
+    int lo = 0, hi = w0 > 0 ? nslots : 0;  // first stream starting at or after w0
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (s_cl[mid].x < w0) lo = mid + 1;
+      else hi = mid;
+    }
+#pragma unroll
+    for (int t0 = 0; t0 < kTiles; t0 += kWave) {
+      const int t = t0 + tid;
+      const int k = t < kTiles ? __popcll(s_M[t]) : 0;
+      const int incl = wave_incl_scan(k);
+      if (t < kTiles) s_tb[t] = lo + incl - k;
+      lo += wave_read(incl, kWave - 1);
+    }
+  }
+  __syncthreads();
+}
+
 // All chunks of one batch of streams.  The chunk space [0, C) is walked in
-// windows of THREADS * kWinIters chunks; a window is split into tiles of 64
-// chunks, one per wave and round, and for each tile the block first records
-// the number of streams that start before it (s_tb) and a 64-bit mask of the
-// streams that start inside it (s_M).  Lane i of a wave then finds the
+// windows of THREADS * kWinIters chunks, each split into tiles of 64 chunks,
+// one per wave and round (mark_window).  Lane i of a wave then finds the
 // stream of its chunk as s_tb + popcount(mask bits <= i) - 1, with no search.
 template <int MODE, int THREADS, int kOut, int kAhead, int SLOTS>
 __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_cl, const int64_t* s_beg,
@@ -1338,26 +1373,7 @@ __device__ __forceinline__ uint32_t run_chunks(int C, int nslots, const int2* s_
   const uint32_t ln = static_cast<uint32_t>(lane());
   uint32_t cnt = 0;
   for (int w0 = 0; w0 < C; w0 += kWin) {
-    for (int t = tid; t < kTiles; t += THREADS) {
-      const int ct = w0 + t * kWave;
-      if (ct < C) {
-        int lo = 0, hi = nslots;  // first stream starting at or after ct
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (s_cl[mid].x < ct) lo = mid + 1;
-          else hi = mid;
-        }
-        uint64_t M = 0;
-        for (int j = lo; j < nslots; ++j) {
-          const int f = s_cl[j].x;
-          if (f >= ct + kWave) break;
-          M |= 1ull << (f - ct);
-        }
-        s_tb[t] = lo;
-        s_M[t] = M;
-      }
-    }
-    __syncthreads();
+    mark_window<THREADS, kTiles>(w0, nslots, s_cl, s_M, s_tb);
     int32_t* wq = s_q + (tid & ~(kWave - 1));  // this wave's queue
     if (kOut != kOutEmit && kAhead == 1) {
       // every lane of a wave with work takes part (a lane past the end
@@ -1728,7 +1744,7 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
 // whose bit stays clear.  At R-MAT scale 24 the 32 KB bin streamed 48.8 G
 // elements as 32-bit ids in 33.0 ms; with half the bytes, half the table
 // (four blocks a CU instead of three) and no window to subtract and clamp they
-// take 19.0 ms.  Bound by the lines it requests: 1.18 G of 128 bytes, 94% of
+// take 18.4 ms.  Bound by the lines it requests: 1.18 G of 128 bytes, 94% of
 // them past the L2, are 7.9 TB/s (the VALU is busy 72% of the time, the LDS
 // 53%).
 // A chunk is kCoreChunk elements from an even position (dword loads); an odd
@@ -1820,25 +1836,7 @@ __global__ __launch_bounds__(kCoreThreads, 8) void core_kernel(const uint16_t* c
         }
         __syncthreads();
         for (int w0 = 0; w0 < C; w0 += kWin) {
-          for (int t = tid; t < kTiles; t += kCoreThreads) {
-            const int ct = w0 + t * kWave;
-            if (ct >= C) continue;
-            int lo = 0, hi = nslots;  // first stream starting at or after ct
-            while (lo < hi) {
-              const int mid = (lo + hi) >> 1;
-              if (s_cl[mid].x < ct) lo = mid + 1;
-              else hi = mid;
-            }
-            uint64_t M = 0;
-            for (int j = lo; j < nslots; ++j) {
-              const int f = s_cl[j].x;
-              if (f >= ct + kWave) break;
-              M |= 1ull << (f - ct);
-            }
-            s_tb[t] = lo;
-            s_M[t] = M;
-          }
-          __syncthreads();
+          mark_window<kCoreThreads, kTiles>(w0, nslots, s_cl, s_M, s_tb);
 #pragma unroll 2
           for (int i = 0; i < kWinIters; ++i) {
             const int rel = i * kCoreThreads + tid;
