@@ -913,9 +913,9 @@ __global__ __launch_bounds__(kResThreads) void resolve_kernel(
 }
 
 // Tasks of light anchors, read from the back of every chunk's region; one
-// thread per task, found from the scan lpre of the per-chunk task counts (the
-// chunks of a wave's first and last task are searched once, a lane looks
-// between them).  The probe segment (at most kLightMax ids) and a stream of
+// thread per task, found from the scan lpre of the per-chunk task counts
+// between the chunks ltab[g], ltab[g + 1] of the wave's and the next wave's
+// first task.  The probe segment (at most kLightMax ids) and a stream of
 // at most kLightMax ids are loaded into registers with independent loads and
 // compared pairwise, eight by eight up to the wave's longest segment and
 // stream (comparing all 32 x 32 for lists of six ids on average took 195 us
@@ -925,8 +925,8 @@ constexpr int kLightStep = 8;
 
 template <int kOut>
 __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, const VMeta* meta, const int64_t* so,
-                                                         int64_t n, const int64_t* lpre, int64_t nchunk_cap,
-                                                         const int64_t* sbeg, const int32_t* slen,
+                                                         int64_t n, const int64_t* lpre, const int32_t* ltab,
+                                                         int64_t nchunk_cap, const int64_t* sbeg, const int32_t* slen,
                                                          const int32_t* soth, const int32_t* sx,
                                                          unsigned long long* acc, Out o) {
   __shared__ int64_t sh[kThreads / kWave + 1];
@@ -940,8 +940,8 @@ __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, cons
   for (int64_t w0 = wave0 * kWave; w0 < nl; w0 += (int64_t)gridDim.x * kThreads) {  // the whole wave takes part
     const int64_t i = w0 + lane();
     const bool mine = i < nl;
-    const int64_t ca = upper_bound_dev(lpre, 0, nchunk_cap + 1, w0) - 1;
-    const int64_t cz = upper_bound_dev(lpre, ca, nchunk_cap + 1, min(w0 + kWave, nl) - 1);
+    const int64_t ca = ltab[w0 / kWave];
+    const int64_t cz = w0 + kWave < nl ? ltab[w0 / kWave + 1] + 1 : nchunk_cap + 1;
     int32_t x = 0, oth = 0, lf = 0;
     int64_t at = 0;
     const int32_t* P = lc;
@@ -1046,8 +1046,8 @@ __global__ __launch_bounds__(kThreads) void light_kernel(const int32_t* lc, cons
 // kFill = false counts per bin, kFill = true scatters.
 template <bool kFill>
 __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, int64_t n, const int4* ccnt,
-                                                             const int4* items_raw, int4* items,
-                                                             unsigned long long* acc) {
+                                                             const int4* items_raw, int4* items, const int64_t* lpre,
+                                                             int32_t* ltab, unsigned long long* acc) {
   __shared__ unsigned long long s_base[kBins], s_off[kBins];
   __shared__ int64_t sh[kThreads / kWave + 1];
   if (kFill && threadIdx.x == 0) {  // the bins one after another; block 0 tells the later kernels
@@ -1070,6 +1070,10 @@ __global__ __launch_bounds__(kThreads) void bin_split_kernel(const int64_t* so, 
     if (c < nch) {
       ni = ccnt[c].z;
       if (!kFill) recs += ccnt[c].x;
+      if (kFill) {  // the chunk of every 64th light task
+        const int64_t lz = lpre[c + 1];
+        for (int64_t g = (lpre[c] + kWave - 1) / kWave; g * kWave < lz; ++g) ltab[g] = static_cast<int32_t>(c);
+      }
       for (int i = 0; i < ni; ++i) {
         const int b = (items_raw[2 * c * kResChunk + i].w >> kItemBinShift) & 7;
 #pragma unroll
@@ -1982,7 +1986,7 @@ int launch_light(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
   const int64_t need = (2 * (a.g->nnz + 1) + kThreads - 1) / kThreads;
   const int64_t cap = static_cast<int64_t>(num_cus()) * 16;
   light_kernel<kOut><<<static_cast<unsigned>(need < cap ? need : cap), kThreads, 0, s>>>(
-      a.cols, a.meta, w.so, a.g->n, w.lpre, w.nchunk_cap, w.sbeg, w.slen, w.soth, w.sx, w.acc, o);
+      a.cols, a.meta, w.so, a.g->n, w.lpre, w.ltab, w.nchunk_cap, w.sbeg, w.slen, w.soth, w.sx, w.acc, o);
   TC_HIP(hipGetLastError());
   return TC_OK;
 }
@@ -2025,8 +2029,8 @@ int launch_all(const CountArgs& a, CountWs& w, const Out& o, hipStream_t s) {
     Carver sc(w.scratch);
     TC_TRY(scan_exclusive_strided(reinterpret_cast<const int32_t*>(w.ccnt) + 1, 4, w.lpre, w.nchunk_cap, sc, s));
   }
-  bin_split_kernel<false><<<gc, kThreads, 0, s>>>(w.so, n, w.ccnt, w.items_raw, w.items, w.acc);
-  bin_split_kernel<true><<<gc, kThreads, 0, s>>>(w.so, n, w.ccnt, w.items_raw, w.items, w.acc);
+  bin_split_kernel<false><<<gc, kThreads, 0, s>>>(w.so, n, w.ccnt, w.items_raw, w.items, w.lpre, w.ltab, w.acc);
+  bin_split_kernel<true><<<gc, kThreads, 0, s>>>(w.so, n, w.ccnt, w.items_raw, w.items, w.lpre, w.ltab, w.acc);
   TC_HIP(hipGetLastError());
   // after the item split: kOutRec keeps its unit counts where the raw items were
   TC_TRY(launch_light<kOut>(a, w, o, s));
@@ -2154,6 +2158,7 @@ CountWs count_reserve(Carver& c, int64_t n, int64_t nnz) {
   w.ccnt = c.take<int4>(w.nchunk_cap);
   w.lpre = c.take<int64_t>(w.nchunk_cap + 1);
   w.samp = c.take<int32_t>(nnz / kSampStride + 2);
+  w.ltab = c.take<int32_t>(2 * nnz / kWave + 2);
   w.pm = c.take<uint4>(n + 1);
   w.tl_words = c.take<uint32_t>(nnz + 1);
   w.tl_l1 = c.take<uint32_t>(nnz + 1);
