@@ -120,6 +120,13 @@ enum Acc {
   kAccBinCur = kAccBinOff + kBins, kAccBinNext = kAccBinCur + kBins, kAccBinElems = kAccBinNext + kBins
 };
 constexpr int kAccSlots = kAccBinElems + kBins;
+// Sums that only the last kernel reads are added in stripes of their own: the
+// blocks of a short kernel end together, and their additions to one place take
+// 4 ns each (two of them from 2800 blocks were 24 us of 169 of the light tasks
+// at R-MAT scale 20).
+constexpr int kAccStripes = 32, kAccPad = 48;
+static_assert(kAccPad >= kAccSlots, "a stripe holds every slot");
+constexpr int kAccAll = kAccPad * (1 + kAccStripes);  // the slots, then the stripes
 constexpr int kElemChunkLog = 19;  // default: 2^19 elements per work item (target)
 // stream record flag (in the length word): probe the anchor's Up list
 constexpr int32_t kFlagUp = 1 << 29;
@@ -260,7 +267,8 @@ __device__ __forceinline__ bool is_heavy(const VMeta& m, bool cover, const Count
 
 __device__ __forceinline__ void block_acc(unsigned long long* acc, int slot, int64_t v, int64_t* sh) {
   int64_t s = block_sum(v, sh);
-  if (threadIdx.x == 0 && s) atomicAdd(&acc[slot], static_cast<unsigned long long>(s));
+  if (threadIdx.x == 0 && s)
+    atomicAdd(&acc[kAccPad * (1 + blockIdx.x % kAccStripes) + slot], static_cast<unsigned long long>(s));
 }
 
 
@@ -1890,13 +1898,24 @@ __global__ __launch_bounds__(kCoreThreads, 8) void core_kernel(const uint16_t* c
 
 // Clears the accumulators and the statistics.
 __global__ void count_init_kernel(unsigned long long* acc, int64_t* stats) {
-  if (threadIdx.x < kAccSlots) acc[threadIdx.x] = 0ull;
+  for (int i = threadIdx.x; i < kAccAll; i += blockDim.x) acc[i] = 0ull;
   if (threadIdx.x < 24) stats[threadIdx.x] = 0;
 }
 
-__global__ void finish_kernel(const unsigned long long* acc, const int64_t* so, int64_t n, int64_t nnz,
-                              int64_t num_levels, const int64_t* lpre, int64_t nchunk_cap, int64_t* triangles,
-                              int64_t* h_count, int64_t* stats) {
+__global__ __launch_bounds__(kWave) void finish_kernel(const unsigned long long* sums, const int64_t* so, int64_t n,
+                                                       int64_t nnz, int64_t num_levels, const int64_t* lpre,
+                                                       int64_t nchunk_cap, int64_t* triangles, int64_t* h_count,
+                                                       int64_t* stats) {
+  __shared__ unsigned long long acc[kWave];
+  static_assert(kAccSlots <= kWave, "a lane per slot");
+  if (threadIdx.x < kAccSlots) {
+    unsigned long long v = sums[threadIdx.x];
+#pragma unroll
+    for (int i = 1; i <= kAccStripes; ++i) v += sums[kAccPad * i + threadIdx.x];
+    acc[threadIdx.x] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   stats[0] = n;
   stats[1] = nnz;
   stats[3] = num_levels;
@@ -2162,7 +2181,7 @@ CountWs count_reserve(Carver& c, int64_t n, int64_t nnz) {
   w.pm = c.take<uint4>(n + 1);
   w.tl_words = c.take<uint32_t>(nnz + 1);
   w.tl_l1 = c.take<uint32_t>(nnz + 1);
-  w.acc = c.take<unsigned long long>(kAccSlots);
+  w.acc = c.take<unsigned long long>(kAccAll);
   w.stats = c.take<int64_t>(24);
   // scans over vertices, over chunks and over the work units of triangle finding (<= rcap)
   w.scratch = c.take<char>(scan_ws_bytes(std::max(n + w.nchunk_cap + 1, w.rcap)) + 256);
@@ -2178,8 +2197,7 @@ int forward_meta_run(const tc_csr* g, VMeta* meta, hipStream_t s) {
 
 int count_run(const CountArgs& a, CountWs& w, int64_t* triangles, int64_t* h_count, hipStream_t s) {
   const int64_t n = a.g->n;
-  static_assert(kAccSlots <= kWave, "one wave clears them");
-  count_init_kernel<<<1, kWave, 0, s>>>(w.acc, w.stats);
+  count_init_kernel<<<1, 1024, 0, s>>>(w.acc, w.stats);
   prof_stage("plan");
   if (n > 0) {
     Out o = unit_out(w);
@@ -2190,7 +2208,8 @@ int count_run(const CountArgs& a, CountWs& w, int64_t* triangles, int64_t* h_cou
     else if (a.per_vertex) TC_TRY((launch_all<true, kOutPV>(a, w, o, s)));
     else TC_TRY((launch_all<true, kOutNone>(a, w, o, s)));
   }
-  finish_kernel<<<1, 1, 0, s>>>(w.acc, w.so, n, a.g->nnz, a.num_levels, w.lpre, w.nchunk_cap, triangles, h_count, w.stats);
+  finish_kernel<<<1, kWave, 0, s>>>(w.acc, w.so, n, a.g->nnz, a.num_levels, w.lpre, w.nchunk_cap, triangles, h_count,
+                                    w.stats);
   TC_HIP(hipGetLastError());
   return TC_OK;
 }
