@@ -309,9 +309,13 @@ struct OneGraph {
   const int32_t* L;   // levels already known (null: batch_bfs_kernel writes parity, T and H)
   int64_t num_levels;
   uint32_t* parity;
-  int64_t* T;
-  int64_t* H;         // nullable
+  int64_t* sums;      // then: kSumStripes of T and |H|, written 0
 };
+
+// One graph's T and |H| are added in stripes of a 128-byte line each: the
+// additions of thousands of blocks to one place take about 4 ns each (G(300007,
+// d 24): 267 -> 223 us with the launch that sums the stripes).
+constexpr int kSumStripes = 32, kSumPad = 16;
 
 template <bool kRec>
 __device__ void batch_prep(int64_t t0, int64_t stride, const int64_t* vbase, int G, const int64_t* row_offsets,
@@ -321,10 +325,8 @@ __device__ void batch_prep(int64_t t0, int64_t stride, const int64_t* vbase, int
   if (single) {
     if (t0 < 2) one.vbase[t0] = t0 ? one.n : 0;
     if (t0 < 24) one.stats[t0] = t0 == 0 ? one.n : (t0 == 1 ? one.nnz : (t0 == 3 ? one.num_levels : 0));
-    if (one.L && t0 == 0) {
-      *one.T = 0;
-      if (one.H) *one.H = 0;
-    }
+    if (one.L)
+      for (int64_t i = t0; i < kSumStripes * kSumPad; i += stride) one.sums[i] = 0;
   }
   const int64_t max_n = one.L ? INT64_MAX : TC_BATCH_MAX_N;
   auto base_of = [&](int g) -> int64_t { return single ? (g ? one.n : 0) : vbase[g]; };
@@ -454,6 +456,10 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
                                                               const uint32_t* parity, const FwdRec* rec,
                                                               const int2* pieces, int64_t nslots, int piece,
                                                               bool by_xcd, int64_t* T, int64_t* H, int64_t* H2) {
+  if (kWide) {  // this block's stripe
+    T += blockIdx.x % kSumStripes * kSumPad;
+    H += blockIdx.x % kSumStripes * kSumPad;
+  }
   constexpr int NW = THREADS / kWave;
   constexpr int kPer = kTile / THREADS;  // entries per thread
   static_assert(kPer * THREADS == kTile, "whole entries per thread");
@@ -981,6 +987,7 @@ namespace {
 
 struct DirectPlan {
   int64_t* vbase;
+  int64_t* sums;
   BatchPlan batch;
   size_t bytes;
 };
@@ -989,10 +996,22 @@ DirectPlan plan_direct(void* base, int64_t n, int64_t nnz) {
   DirectPlan p;
   Carver c(base);
   p.vbase = c.take<int64_t>(2);
+  p.sums = c.take<int64_t>(kSumStripes * kSumPad);
   char* at = c.take<char>(0);
   p.batch = plan_batch(at, n, nnz, 1, true);
   p.bytes = c.used() + p.batch.bytes;
   return p;
+}
+
+__global__ __launch_bounds__(kWave) void direct_sum_kernel(const int64_t* sums, int64_t* T, int64_t* H, int64_t* stats) {
+  static_assert(kSumStripes <= kWave, "a lane per stripe");
+  const bool one = lane() < kSumStripes;
+  const int64_t t = wave_sum(one ? sums[lane() * kSumPad] : int64_t(0));
+  const int64_t h = wave_sum(one ? sums[lane() * kSumPad + 1] : int64_t(0));
+  if (lane() != 0) return;
+  *T = t;
+  if (H) *H = h;
+  stats[2] = h;
 }
 
 }  // namespace
@@ -1032,10 +1051,13 @@ int direct_count_run(const tc_csr* g, const int32_t* L, const BfsInfo& info, int
   prof_stage("direct_prep");
   batch_prep_kernel<true><<<grid_for(std::max(nslots, g->n), 256, 16384), 256, 0, s>>>(
       p.vbase, 1, g->row_offsets, g->cols, g->n, nslots, piece, p.batch.rec, p.batch.pieces,
-      OneGraph{p.vbase, stats, g->n, g->nnz, L, info.num_levels, p.batch.parity, triangles, h_count});
+      OneGraph{p.vbase, stats, g->n, g->nnz, L, info.num_levels, p.batch.parity, p.sums});
   TC_HIP(hipGetLastError());
   prof_stage("direct_count");
-  return launch_count<256>(&b, p.batch, nslots, piece, 0, triangles, h_count, stats + 2, s, true);
+  TC_TRY(launch_count<256>(&b, p.batch, nslots, piece, 0, p.sums, p.sums + 1, nullptr, s, true));
+  direct_sum_kernel<<<1, kWave, 0, s>>>(p.sums, triangles, h_count, stats);
+  TC_HIP(hipGetLastError());
+  return TC_OK;
 }
 
 }  // namespace tc
