@@ -1208,7 +1208,14 @@ __device__ __forceinline__ uint32_t probe(const ProbeSet& ps, int32_t t, bool up
 // unconditionally and masked.
 constexpr int kChunk = 8;
 constexpr int kWinIters = 8;  // chunk rounds of the block per window
-constexpr int kClaim = 4;     // work items a block claims at once
+// Work items a block claims at once: the counter gives out 80 M claims a
+// second, which bounds the small items of the 2 KB bin (R-MAT scale 24, 1.34 M
+// items by 2 / 4 / 8 / 16: 8.52 / 4.92 / 4.27 / 4.46 ms); the others are
+// longer, and the last claims end the later the more they hold (32 KB bin at
+// scale 20 by 1 / 2 / 4 / 8: 37 / 43 / 63 / 89 us; core items 886 / 677 / 676 /
+// 710 us).  Per-vertex counts keep an anchor's sums over its items (R-MAT scale
+// 18 by 2 / 4: 4.67 / 4.18 ms).
+constexpr int kClaimSmall = 8, kClaim = 2, kClaimPv = 4;
 // Chunk slots per lane whose loads are in flight together: two where the
 // registers allow (the 128 KB bin and row search, whose blocks are limited
 // by LDS or run four waves per SIMD), one in the small-table bins compiled
@@ -1540,21 +1547,21 @@ __global__ __launch_bounds__(THREADS, WPE) void heavy_kernel(const int32_t* lc, 
   int64_t cnt = 0, elems = 0, builds = 0, tl_elems = 0;
   int32_t cur_x = -1;
   bool cur_rest = false;
-  // blocks claim kClaim consecutive items at a time (consecutive items of
+  // blocks claim kC consecutive items at a time (consecutive items of
   // one anchor share the table); the next claim is fetched while the
   // current one is processed.  kRoundRobin: block b takes items b, b + G,
   // b + 2G, ... (G blocks) one at a time, with no counter.
-  constexpr unsigned long long kC = kRoundRobin ? 1 : kClaim;
+  constexpr unsigned long long kC = kRoundRobin ? 1 : (WORDS == kBinWords0 ? kClaimSmall : (kOut == kOutPV ? kClaimPv : kClaim));
   if (tid == 0)
     s_item = kRoundRobin ? static_cast<unsigned long long>(blockIdx.x)
-                         : atomicAdd(&acc[kAccBinNext + bin], static_cast<unsigned long long>(kClaim));
+                         : atomicAdd(&acc[kAccBinNext + bin], kC);
   __syncthreads();
   unsigned long long claim = s_item;
   while (claim < count) {
     unsigned long long next = 0;
     if (tid == 0)
       next = kRoundRobin ? claim + gridDim.x
-                         : atomicAdd(&acc[kAccBinNext + bin], static_cast<unsigned long long>(kClaim));
+                         : atomicAdd(&acc[kAccBinNext + bin], kC);
     const unsigned long long claim_end = min(claim + kC, count);
     for (unsigned long long it = claim; it < claim_end; ++it) {
     const int64_t gi = static_cast<int64_t>(first + it);  // unit index of this item
