@@ -10,7 +10,7 @@
 //   3. scan of the counts, and the list from the bits.
 // Bound by the level gathers of the forward entries.  G(1000003, d 16), 16 M
 // entries: the list through a full level-class layout (all entries classified
-// and moved, a 40-byte record a row, then the runs of equal level copied)
+// and moved, a 32-byte record a row, then the runs of equal level copied)
 // took 0.31 ms, this takes 0.10 ms (mark 64 us, list 27 us).
 #include "tc_internal.h"
 

@@ -3,17 +3,19 @@
 //
 // The additions go to the entry (u, v), u < v, of an edge; a second pass
 // copies every sum to the entry (v, u), one search per edge instead of three
-// searches and atomics per triangle.  The entries are found by binary search
-// in the sorted rows, a triangle's three searches advancing together.
+// searches and atomics per triangle.
 //
 // Atomics to memory bound it (six a triangle, the hubs' edges on the same
-// addresses: 3.8 ms for the triangles of R-MAT scale 16).  A triangle list
-// comes in runs with a common vertex (tc_list_triangles: an anchor's), whose
-// two edges repeat through the run: a wave takes the vertex shared by its
-// first and last triangle, and the edges at that vertex are summed in a table
-// of the block in LDS.  The same triangles then take 0.84 ms (1.7 without the
-// table, 1.2 with all three edges in it: the third edge rarely repeats and
-// takes the slots).
+// addresses: 3.8 ms for the 15.6 M triangles of R-MAT scale 16).  A triangle
+// list comes in runs with a common vertex (tc_list_triangles: an anchor's),
+// whose two edges repeat through the run: a wave takes the vertex shared by
+// its first and last triangle, and the edges at that vertex are summed by
+// their two ids in a table of the block in LDS, so that they are searched and
+// added once a block.  The same triangles then take 0.76 ms, 31 G atomics a
+// second (0.84 with positions as keys, which every triangle had to search,
+// 1.7 without the table, 1.0 with all three edges in it: the third edge rarely
+// repeats and takes the slots; a table of 4096 edges 0.99, of 1024 for 1024
+// triangles 0.78).
 #include "tc_internal.h"
 
 namespace tc {
@@ -22,8 +24,9 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTri = 2048;      // consecutive triangles of a block
-constexpr int kTable = 4096;    // sums kept in LDS (32 KB); a slot holds the first edge that hashes to it
-constexpr uint32_t kFree = 0xFFFFFFFFu;
+constexpr int kTable = 2048;    // edges summed in LDS (24 KB)
+constexpr int kProbes = 4;      // slots an edge may take
+constexpr unsigned long long kFree = ~0ull;
 
 __device__ __forceinline__ void order2(int32_t& x, int32_t& y) {
   const int32_t t = min(x, y);
@@ -31,31 +34,61 @@ __device__ __forceinline__ void order2(int32_t& x, int32_t& y) {
   x = t;
 }
 
-// kLds: entries fit in 32 bits.
-template <bool kLds>
+// Adds s[q] to the entry (u[q], v[q]) where there is one, N searches
+// advancing together (s[q] = 0: none).
+template <int N>
+__device__ __forceinline__ void add_edges(const int64_t* off, const int32_t* cols, const int32_t (&u)[N],
+                                          const int32_t (&v)[N], const int32_t (&s)[N], int32_t* sup) {
+  int64_t lo[N], hi[N], end[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) lo[q] = s[q] ? off[u[q]] : 0;
+#pragma unroll
+  for (int q = 0; q < N; ++q) hi[q] = end[q] = s[q] ? off[u[q] + 1] : 0;
+  for (;;) {
+    int32_t m[N];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < N; ++q) m[q] = lo[q] < hi[q] ? cols[lo[q] + ((hi[q] - lo[q]) >> 1)] : 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      if (lo[q] >= hi[q]) continue;
+      const int64_t mid = lo[q] + ((hi[q] - lo[q]) >> 1);
+      if (m[q] < v[q]) lo[q] = mid + 1;
+      else hi[q] = mid;
+      any |= lo[q] < hi[q];
+    }
+    if (!any) break;
+  }
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    if (lo[q] < end[q] && cols[lo[q]] == v[q]) atomicAdd(&sup[lo[q]], s[q]);
+}
+
 __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, const int32_t* cols, int64_t n,
                                                            const int32_t* tri, int64_t ntri, int32_t* sup) {
-  __shared__ uint32_t s_key[kLds ? kTable : 1];
-  __shared__ int32_t s_sum[kLds ? kTable : 1];
-  auto add = [&](int64_t p, bool shared) {
-    if (kLds && shared) {
-      const uint32_t key = static_cast<uint32_t>(p), slot = (key * 0x9E3779B1u) >> 20;  // kTable = 2^12
-      const uint32_t was = atomicCAS(&s_key[slot], kFree, key);
+  __shared__ unsigned long long s_key[kTable];  // u << 32 | v
+  __shared__ int32_t s_sum[kTable];
+  auto keep = [&](int32_t u, int32_t v) {
+    const unsigned long long key = (static_cast<unsigned long long>(static_cast<uint32_t>(u)) << 32) |
+                                   static_cast<uint32_t>(v);
+    uint32_t slot = ((static_cast<uint32_t>(u) * 0x85EBCA6Bu + static_cast<uint32_t>(v)) * 0x9E3779B1u) >>
+                    (32 - __builtin_ctz(kTable));
+    for (int q = 0; q < kProbes; ++q) {
+      const unsigned long long was = atomicCAS(&s_key[slot], kFree, key);
       if (was == kFree || was == key) {
         atomicAdd(&s_sum[slot], 1);
-        return;
+        return true;
       }
+      slot = (slot + 1) & (kTable - 1);
     }
-    atomicAdd(&sup[p], 1);
+    return false;
   };
   for (int64_t t0 = blockIdx.x * static_cast<int64_t>(kTri); t0 < ntri; t0 += static_cast<int64_t>(gridDim.x) * kTri) {
-    if (kLds) {
-      for (int i = threadIdx.x; i < kTable; i += kThreads) {
-        s_key[i] = kFree;
-        s_sum[i] = 0;
-      }
-      __syncthreads();
+    for (int i = threadIdx.x; i < kTable; i += kThreads) {
+      s_key[i] = kFree;
+      s_sum[i] = 0;
     }
+    __syncthreads();
     const int64_t t1 = min(t0 + kTri, ntri);
     for (int64_t w0 = t0 + (threadIdx.x & ~(kWave - 1)); w0 < t1; w0 += kThreads) {  // uniform per wave
       const int64_t i = w0 + lane();
@@ -79,40 +112,37 @@ __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, c
       order2(a, b);
       order2(b, c);
       order2(a, b);
-      const int32_t u[3] = {a, a, b}, v[3] = {b, c, c};
-      int64_t lo[3], hi[3], end[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) lo[q] = off[u[q]];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) hi[q] = end[q] = off[u[q] + 1];
-      for (;;) {
-        int32_t m[3];
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) m[q] = lo[q] < hi[q] ? cols[lo[q] + ((hi[q] - lo[q]) >> 1)] : 0;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-          if (lo[q] >= hi[q]) continue;
-          const int64_t mid = lo[q] + ((hi[q] - lo[q]) >> 1);
-          if (m[q] < v[q]) lo[q] = mid + 1;
-          else hi[q] = mid;
-          any |= lo[q] < hi[q];
-        }
-        if (!any) break;
+      if (x < 0) {  // uniform
+        const int32_t u[3] = {a, a, b}, v[3] = {b, c, c}, one[3] = {1, 1, 1};
+        add_edges<3>(off, cols, u, v, one, sup);
+        continue;
       }
-      bool found[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) found[q] = lo[q] < end[q] && cols[lo[q]] == v[q];
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        if (found[q]) add(lo[q], u[q] == x || v[q] == x);
+      uint32_t left = 7u;  // edges not kept
+      if ((a == x || b == x) && keep(a, b)) left &= ~1u;
+      if ((a == x || c == x) && keep(a, c)) left &= ~2u;
+      if ((b == x || c == x) && keep(b, c)) left &= ~4u;
+      while (left) {  // mostly one
+        const bool ab = (left & 1u) != 0u, ac = !ab && (left & 2u) != 0u;
+        left &= left - 1;
+        const int32_t u[1] = {ab || ac ? a : b}, v[1] = {ab ? b : c}, one[1] = {1};
+        add_edges<1>(off, cols, u, v, one, sup);
+      }
     }
-    if (kLds) {
-      __syncthreads();
-      for (int i = threadIdx.x; i < kTable; i += kThreads)
-        if (s_sum[i]) atomicAdd(&sup[s_key[i]], s_sum[i]);
-      __syncthreads();
+    __syncthreads();
+    constexpr int kAtOnce = 4;
+    static_assert(kTable % (kThreads * kAtOnce) == 0, "whole rounds");
+    for (int i = threadIdx.x; i < kTable; i += kThreads * kAtOnce) {
+      int32_t u[kAtOnce], v[kAtOnce], s[kAtOnce];
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const unsigned long long key = s_key[i + q * kThreads];
+        s[q] = s_sum[i + q * kThreads];
+        u[q] = static_cast<int32_t>(key >> 32);
+        v[q] = static_cast<int32_t>(key & 0xFFFFFFFFull);
+      }
+      add_edges<kAtOnce>(off, cols, u, v, s, sup);
     }
+    __syncthreads();
   }
 }
 
@@ -148,10 +178,7 @@ int support_run(const tc_csr* g, const int32_t* tri, int64_t ntri, int32_t* supp
   TC_TRY(fill_i32(support, 0, g->nnz, s));
   if (ntri <= 0 || g->n == 0) return TC_OK;
   const unsigned blocks = grid_for(ntri, kTri, 65536);
-  if (g->nnz < static_cast<int64_t>(kFree))
-    support_kernel<true><<<blocks, kThreads, 0, s>>>(g->row_offsets, g->cols, g->n, tri, ntri, support);
-  else
-    support_kernel<false><<<blocks, kThreads, 0, s>>>(g->row_offsets, g->cols, g->n, tri, ntri, support);
+  support_kernel<<<blocks, kThreads, 0, s>>>(g->row_offsets, g->cols, g->n, tri, ntri, support);
   mirror_kernel<<<grid_for(g->nnz, kMirror * (kThreads / kWave), 16384), kThreads, 0, s>>>(g->row_offsets, g->cols, g->n,
                                                                                           g->nnz, support);
   TC_HIP(hipGetLastError());
