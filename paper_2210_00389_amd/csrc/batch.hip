@@ -845,7 +845,8 @@ BatchPlan plan_batch(void* base, int64_t total_n, int64_t total_nnz, int32_t G, 
   BatchPlan p;
   Carver c(base);
   p.parity = c.take<uint32_t>(total_n / 32 + G + 2);
-  p.pieces = c.take<int2>(total_nnz / auto_piece(total_nnz) + G + 2);
+  // the most slots any call of this size has: the default piece may be larger than the smallest to ask for
+  p.pieces = c.take<int2>(total_nnz / std::min(auto_piece(total_nnz), kPieceMin) + G + 2);
   p.rec = with_rec ? c.take<FwdRec>(total_n + 1) : nullptr;
   p.bytes = c.used();
   return p;

@@ -82,3 +82,19 @@ def test_in_a_batch(tuning, noalloc):
         r = tc.count_batch(tc.Batch.from_graphs([graphs[i] for i in pick]), tuning, noalloc=noalloc)
         got = list(zip(r.triangles.tolist(), r.h_count.tolist()))
         assert got == [want[i] for i in pick], [NAMES[i % len(NAMES)] for i in pick]
+
+
+@pytest.mark.parametrize("tuning", [None, dict(batch_piece=1024), dict(batch_piece=1024, batch_block=64),
+                                    dict(batch_piece=1500, batch_block=512)])
+def test_pieces_below_a_large_batchs_default(tuning):
+    """34 M entries: the default piece is longer than the smallest to ask for, and the workspace serves both."""
+    import paper_2210_00389_amd as tc
+    g = graphgen.erdos_renyi(65536, 12.0 / 65535, 8)
+    other = graphgen.barabasi_albert(30011, 9, 3)
+    pick = [g, other] * 27
+    want = [_want(g)[1:], _want(other)[1:]] * 27
+    b = tc.Batch.from_graphs(pick)
+    assert b.cols.numel() > 1 << 25
+    print(f"case: 54 graphs, {b.cols.numel()} entries, {tuning}", flush=True)
+    r = tc.count_batch(b, tuning, ws=tc.Workspace())
+    assert list(zip(r.triangles.tolist(), r.h_count.tolist())) == want
