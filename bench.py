@@ -586,8 +586,9 @@ def theoretical_waves_per_simd(vgpr, agpr, lds, wg):
 
 def summarize_counters(args):
     """Per-kernel figures of one count call (the last of the pmc program's
-    calls: dispatches from the last --call-start kernel, root_key_kernel by
-    default, to the next stats_kernel) from
+    calls: dispatches from the last --call-start kernel, clear_state_kernel
+    (root_key_kernel in older traces) by default, to the next finish_kernel or,
+    in older traces, stats_kernel) from
     rocprofv3 --pmc runs (any of TCC_EA0_RDREQ_DRAM_32B,
     TCC_EA0_WRREQ_WRITE_DRAM_32B, TCC_HIT, TCC_MISS, FETCH_SIZE, WRITE_SIZE,
     MeanOccupancyPerCU) and a --kernel-trace run (durations, registers, LDS,
@@ -611,11 +612,11 @@ def summarize_counters(args):
         ids = sorted(nm)
         if args.whole_run:
             return ids
-        starts = [k for k in ids if nm[k].startswith(args.call_start)]
+        starts = [k for k in ids if nm[k].startswith(args.call_start or ("clear_state_kernel", "root_key_kernel"))]
         if not starts:
             return ids
         a = starts[-1]
-        b = next((k for k in ids if k > a and nm[k].startswith("stats_kernel")), ids[-1])
+        b = next((k for k in ids if k > a and nm[k].startswith(("stats_kernel", "finish_kernel"))), ids[-1])
         return [k for k in ids if a <= k <= b]
 
     def copy_value(c):
@@ -684,7 +685,7 @@ def summarize_counters(args):
     tot_b = sum(t.get("dram_read", 0.0) + t.get("dram_write", 0.0) for t in table.values())
     heavy = {}
     for kn, t in table.items():
-        if kn.startswith("heavy_kernel"):
+        if kn.startswith(("heavy_kernel", "core_kernel")):
             for f in ("n", "ms", "dram_read", "dram_write", "fetch", "write"):
                 heavy[f] = heavy.get(f, 0.0) + t.get(f, 0.0)
     rec = {"calibration": calib, "kernel_ms": tot_ms, "dram_bytes": tot_b, "kernels": table,
@@ -740,7 +741,7 @@ def summarize_counters(args):
                           f"{float(r['AverageNs'])/1e3:.1f} | {float(r['Percentage']):.1f}% |")
         out_md.append("")
     if heavy.get("ms") and has_dram:
-        out_md += [f"Heavy stage (heavy_kernel, {int(heavy.get('n', 0))} dispatches): {heavy['ms']:.3f} ms, "
+        out_md += [f"Heavy stage (heavy_kernel and core_kernel, {int(heavy.get('n', 0))} dispatches): {heavy['ms']:.3f} ms, "
                    f"DRAM traffic {rec['heavy']['traffic_bytes'] / 1e9 if rec['heavy']['traffic_bytes'] else 0:.2f} GB "
                    f"per call (source sha256 {rec['heavy']['source_sha256'][:16]}).", ""]
     with open(args.out + ".md", "w") as f:
@@ -1018,7 +1019,7 @@ def main():
     ap.add_argument("--trace-dir", default=None)
     ap.add_argument("--pmc-dir", action="append", default=None, help="a rocprofv3 --pmc output folder (repeatable)")
     ap.add_argument("--whole-run", action="store_true", help="summaries: every dispatch of the run, not one call")
-    ap.add_argument("--call-start", default="root_key_kernel",
+    ap.add_argument("--call-start", default=None,
                     help="summaries: the first kernel of a call (forward_meta_kernel for the comparator)")
     ap.add_argument("--out", default=None)
     ap.add_argument("--title", default="rocprofv3 summary")
