@@ -25,6 +25,7 @@
 // The lists streamed are N+(v) instead of N(v): 2.3 times fewer elements on
 // G(n, p) graphs (n = 20000, mean degree 36: 4.3 M against 10.2 M for the
 // whole lists of the horizontal edges) and on R-MAT scale 10 to 13.
+#include "direct_rule.h"
 #include "tc_internal.h"
 
 namespace tc {
@@ -39,7 +40,6 @@ constexpr int kRowLoads = 8;     // row entries a thread loads at once in a bott
 constexpr int kRestCap = 6144;   // unreached vertices of other components levelled together (LDS left beside L)
 constexpr int kPieceMin = 1024;  // smallest piece size a caller may ask for
 constexpr int kAutoMin = 16;     // smallest piece size chosen by auto_piece
-constexpr int kTile = 512;       // entries of a piece counted together (their streams are kept in LDS)
 
 // Piece slots of graph g start at row_offsets[vbase[g]] / piece + g, parity
 // words at vbase[g] / 32 + g: both leave room for ceil(size / unit) entries.
@@ -410,14 +410,13 @@ __global__ __launch_bounds__(kBfsThreads) void batch_first_kernel(const int64_t*
   }
 }
 
-constexpr int kBChunk = 8;  // consecutive list entries a lane takes at once
 constexpr int kRows = 2;                 // rows a thread looks at for a tile
 constexpr int kCols = 1024;
 constexpr int kQueue = 256;              // hits of a tile looked up together
 constexpr int kSumTiles = 64;            // tiles added up in 32 bits (fewer than 2^22 chunks of 8 each)
 constexpr int kFilterBits = TC_BATCH_MAX_N;
 constexpr int kWinTiles = 64;            // 64-chunk groups whose stream starts are marked at once
-constexpr uint32_t kLongList = TC_BATCH_MAX_N - kBChunk;
+static_assert(kLongList == TC_BATCH_MAX_N - kBChunk, "a graph of a batch has at most 28 longer lists in a tile");
 constexpr int kLongMany = 64;
 constexpr uint32_t kRowStep = 40503u;    // odd: rows of a tile start at spread places of the filter
 
@@ -658,9 +657,11 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
         }
       }
       uint32_t beg[kPer], len[kPer];
-      // chunks | streams << 22: fewer than 2^22 chunks in all, as at most 28
-      // entries of a tile have lists beyond kLongList in a simple graph (their
-      // ids are below 8); in any other kLongMany keep their length
+      // chunks | streams << kChunkBits.  Lists of up to kLongList always fit
+      // the chunks' bits.  Longer ones: a graph counted alone (kWide) has none
+      // (direct_fits); in a batch their ids are below 8 in a simple graph (n is
+      // at most TC_BATCH_MAX_N), so at most 28 entries of a tile have one; in
+      // any other batch kLongMany keep their length
       uint32_t mine = 0;
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
@@ -682,7 +683,7 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
         const uint32_t h = (static_cast<uint32_t>(v[j]) + off[j]) & (kFilterBits - 1);
         atomicOr(&s_filt[h >> 5], 1u << (h & 31));
         if (len[j] > kLongList && atomicAdd(&s_long, 1) >= kLongMany) len[j] = kLongList;
-        if (len[j]) mine += (len[j] + kBChunk - 1) / kBChunk + (1u << 22);
+        if (len[j]) mine += (len[j] + kBChunk - 1) / kBChunk + (1u << kChunkBits);
       }
       {
         const uint32_t toff = static_cast<uint32_t>(nrows - 1) * step;
@@ -698,10 +699,10 @@ __global__ __launch_bounds__(THREADS, THREADS == kWave ? 2 : (kWide ? 6 : 7)) vo
       if (total > kTile) cur = s_cur;
       uint32_t tot;
       const uint32_t pre = block_excl_scan(mine, sh, &tot);
-      constexpr uint32_t kChunks = (1u << 22) - 1u;
-      const int C = static_cast<int>(tot & kChunks), nst = static_cast<int>(tot >> 22);
+      constexpr uint32_t kChunks = (1u << kChunkBits) - 1u;
+      const int C = static_cast<int>(tot & kChunks), nst = static_cast<int>(tot >> kChunkBits);
       {
-        int slot = static_cast<int>(pre >> 22), ch = static_cast<int>(pre & kChunks);
+        int slot = static_cast<int>(pre >> kChunkBits), ch = static_cast<int>(pre & kChunks);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           if (!len[j]) continue;
@@ -1018,23 +1019,6 @@ __global__ __launch_bounds__(kWave) void direct_sum_kernel(const int64_t* sums, 
 }  // namespace
 
 size_t direct_ws_bytes(int64_t n, int64_t nnz) { return plan_direct(nullptr, n, nnz).bytes; }
-
-// The streams are sum over v of d+(v) (d(v) - d+(v)) elements, about a sixth
-// of the squared degrees whatever the graph (within 10% on G(n, p), Chung-Lu
-// and R-MAT graphs).  The relabelled path streams fewer on graphs with hubs
-// but has its layout, plan and resolution to pay.  Measured, both ways, us
-// (relabelled / direct): G(300007, d 24) 783 / 293, G(2000003, d 40) 12100 /
-// 2340; Chung-Lu n = 300007 mean degree 12 (35 elements an entry) 700 / 673,
-// 20 (48) 941 / 1036, 40 (73) 1383 / 1845; n = 1000003 degree 12 (56) 1629 /
-// 1463, 20 (76) 2234 / 2440; n = 2000003 degree 6 (49) 2178 / 1809, 12 (74)
-// 2724 / 2847; R-MAT scale 14 (61) 358 / 149, 15 (84) 437 / 316, 16 (114) 501
-// / 1034, 17 with edge factor 6 (75) 492 / 712.  The line lies at 48 elements
-// an entry and 2^25 more, which is what the launches alone are worth.
-bool direct_fits(int64_t n, int64_t nnz, const BfsInfo& info) {
-  // list lengths of 16 bits and positions of 32 in the streams
-  if (n >= INT32_MAX || nnz >= (int64_t(1) << 31) || info.maxdeg > kFwdLenMax) return false;
-  return info.deg2 / 6 <= 48ull * static_cast<uint64_t>(nnz) + (1ull << 25);
-}
 
 int direct_count_run(const tc_csr* g, const int32_t* L, const BfsInfo& info, int64_t* stats, int64_t* triangles,
                      int64_t* h_count, void* ws, hipStream_t s) {

@@ -3,6 +3,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include "direct_rule.h"
 #include "tc_internal.h"
 
 using namespace tc;
@@ -208,7 +209,7 @@ int cover_call(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles
   prof_stage("bfs");
   BfsInfo info;
   TC_TRY(bfs_run(g, root, L, p.bfs, s, &info));
-  if (direct && direct_fits(g->n, g->nnz, info))
+  if (direct && direct_fits(g->n, g->nnz, info.maxdeg, info.deg2))
     return direct_count_run(g, L, info, p.stats, triangles, h_count, p.region, s);
   const int32_t nl = info.num_levels, d0 = info.first_levels;
   // per-vertex counts and listing report ids of the streamed lists

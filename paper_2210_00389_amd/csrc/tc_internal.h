@@ -224,11 +224,10 @@ int batch_run(const tc_batch* b, const tc_tuning* t, uint32_t flags, int64_t* tr
 size_t small_ws_bytes(int64_t n, int64_t nnz);
 bool small_path_fits(int64_t n, int64_t nnz, int64_t max_n, int64_t max_nnz);
 // One graph of any size whose levels are known, counted on the caller's CSR
-// by the batched counting kernel (no relabelling): see direct_fits for the
-// graphs that are faster so.  stats: the tc_stats mirror (n, nnz, |H| and the
+// by the batched counting kernel (no relabelling), for the graphs that
+// direct_fits (direct_rule.h) takes.  stats: the tc_stats mirror (n, nnz, |H| and the
 // level count are written).
 size_t direct_ws_bytes(int64_t n, int64_t nnz);
-bool direct_fits(int64_t n, int64_t nnz, const BfsInfo& info);
 int direct_count_run(const tc_csr* g, const int32_t* L, const BfsInfo& info, int64_t* stats, int64_t* triangles,
                      int64_t* h_count, void* ws, hipStream_t s);
 int small_count_run(const tc_csr* g, int64_t root, int64_t* triangles, int64_t* h_count, int32_t* levels,
