@@ -34,6 +34,10 @@ namespace {
 
 constexpr int kBfsThreads = 1024;
 constexpr uint16_t kUnvisited = 0xFFFF;
+// Level 65535 is kUnvisited.  Only the last vertex of a path of 65536 searched
+// from its other end has it: once level 65534 is reached, all vertices but one
+// are, and that one, if it is not isolated, is its neighbour.
+constexpr int kLastLevel = TC_BATCH_MAX_N - 2;
 constexpr int kFrontCap = 2048;  // frontier vertices of a top-down level (at most n / 32 there)
 constexpr int kRowLanes = 16;    // lanes that expand a frontier row together
 constexpr int kRowLoads = 8;     // row entries a thread loads at once in a bottom-up level
@@ -74,14 +78,14 @@ struct LevelLds {
   int cnt, num;
 };
 
-// Level-synchronous BFS from `root` (level 0, set by the caller), with L
-// resident in LDS.
-__device__ void bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
+// Level-synchronous BFS from the vertex of level 0 (set by the caller), with
+// L resident in LDS.  Returns its last level.
+__device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
   const int tid = threadIdx.x, nt = blockDim.x, ln = lane();
   uint16_t* L = s.L;
   int level = 0;
   int last = 1;  // vertices found at the previous level
-  for (;;) {
+  while (level < kLastLevel) {
     bool bottom_up = last > n / 32;
     if (tid == 0) s.cnt = s.num = 0;
     __syncthreads();
@@ -148,6 +152,7 @@ __device__ void bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* 
     if (last == 0) break;
     ++level;
   }
+  return level;
 }
 
 // The remaining components together, when they hold at most kRestCap
@@ -245,12 +250,12 @@ __device__ void graph_levels(LevelLds& s, int g, int64_t v0, int64_t n64, const 
                                            : static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key & 0xFFFFFFFF));
   if (tid == 0) L[root] = 0;  // a given root of degree 0 is level 0 already
   __syncthreads();
-  bfs_levels_lds(s, rows, cols, n);
+  const int last = bfs_levels_lds(s, rows, cols, n);
   // remaining components: together if they are few vertices, else one search
   // from the smallest unvisited id until they are; every id below the last
   // such root is visited, so each scan starts there
   int from = 0;
-  while (!rest_levels_lds(s, rows, cols, n)) {
+  while (last < kLastLevel && !rest_levels_lds(s, rows, cols, n)) {
     int64_t cand = -1;  // max of (n - i) over unvisited i = smallest i
     for (int i = from + tid; i < n; i += nt)
       if (L[i] == kUnvisited) {
