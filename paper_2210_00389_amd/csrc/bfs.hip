@@ -38,7 +38,12 @@ __device__ __forceinline__ int64_t row_deg(const int64_t* off, int64_t v) { retu
 // (a row below it is expanded by one wave: R-MAT S14's root, 3644 entries,
 // took 0.12 ms that way under a bound of 4096, against 5 us listed)
 constexpr int kBig = 1024;
-constexpr int kBigCap = 1024;      // listed rows per level (more: all expanded by their waves)
+// Listed rows per level (more: all expanded by their waves), and how many of
+// them a block's prefix of lengths holds at once.  With room for 1024 only, a
+// level of 1500 rows of 1100 entries and one of 2 M left the long one to a
+// wave: 88 ms for the search, 0.7 ms with all of them listed.
+constexpr int kBigCap = 65536;
+constexpr int kBigPart = 1024;
 constexpr int kRowLoads = 8;       // row entries a bottom-up scan loads at once
 constexpr int kSlots = 16;         // partial sums of a level: one atomic per block, spread over them
 constexpr int kKeyBlocks = 1024;   // blocks of the first kernel at most (one key each)
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(const int64_t* off, cons
   __shared__ int64_t sh[kThreads / kWave + 1];
   __shared__ int32_t s_off[kThreads / kWave][kWave + 1];
   __shared__ int64_t s_beg[kThreads / kWave][kWave];
-  __shared__ int64_t s_pre[kBigCap + 1];
+  __shared__ int64_t s_pre[kBigPart + 1];
   const BfsState st = state_of(d, k, n);
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) {
@@ -201,25 +206,26 @@ __global__ __launch_bounds__(kThreads) void step_kernel(const int64_t* off, cons
       edg += deg;
       list_big(nbig, big, w, deg);
     };
-    // the listed rows of this frontier, by a flat entry index (each block
-    // computes the prefix of their lengths)
-    const int32_t* mine = bigs + (k & 1) * kBigCap;
+    // the listed rows of this frontier, kBigPart at a time, by a flat entry
+    // index (each block computes the prefix of their lengths)
     const int nb = d->nbig[k % 3];
     const bool listed = nb <= kBigCap;
-    if (listed && nb > 0) {
+    for (int p0 = 0; listed && p0 < nb; p0 += kBigPart) {
+      const int32_t* mine = bigs + (k & 1) * kBigCap + p0;
+      const int np = min(nb - p0, kBigPart);
       int64_t run = 0;
-      for (int b0 = 0; b0 < nb; b0 += kThreads) {
+      for (int b0 = 0; b0 < np; b0 += kThreads) {
         const int i = b0 + threadIdx.x;
-        const int64_t dg = i < nb ? off[mine[i] + 1] - off[mine[i]] : 0;
+        const int64_t dg = i < np ? off[mine[i] + 1] - off[mine[i]] : 0;
         int64_t tot;
         const int64_t ex = block_excl_scan(dg, sh, &tot);
-        if (i < nb) s_pre[i] = run + ex;
+        if (i < np) s_pre[i] = run + ex;
         run += tot;
       }
-      if (threadIdx.x == 0) s_pre[nb] = run;
+      if (threadIdx.x == 0) s_pre[np] = run;
       __syncthreads();
       for (int64_t i = t0; i < run; i += stride) {
-        int lo = 0, hi = nb;  // last row with s_pre <= i
+        int lo = 0, hi = np;  // last row with s_pre <= i
         while (hi - lo > 1) {
           const int mid = (lo + hi) >> 1;
           if (s_pre[mid] <= i) lo = mid;
@@ -227,6 +233,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(const int64_t* off, cons
         }
         claim(cols[off[mine[lo]] + (i - s_pre[lo])]);
       }
+      __syncthreads();  // the next part's prefix replaces this one's
     }
     // 64 consecutive vertices per wave and round; the rows of the group's
     // frontier vertices are flattened across the lanes

@@ -1,0 +1,68 @@
+"""Searches whose frontier has more long rows than one part of the list of them
+holds, up to and past the list's end, and the time of one far longer row among
+them.  Levels are known from the construction (integers: no tolerance); a time
+is compared with that of the same search with fewer long rows."""
+import statistics
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _hubs(hubs, leaves, longest, n):
+    """Vertex 0 joined to `hubs` vertices of `leaves` leaves each and one of `longest`; isolated vertices up to n."""
+    import paper_2210_00389_amd as tc
+    dev = "cuda"
+    size = torch.tensor([leaves] * hubs + [longest], device=dev)
+    hub = torch.arange(1, hubs + 2, device=dev)
+    leaf = hubs + 2 + torch.arange(int(size.sum()), device=dev)
+    s = torch.cat([torch.zeros_like(hub), torch.repeat_interleave(hub, size)])
+    G = tc.build_csr(n, s.to(torch.int32), torch.cat([hub, leaf]).to(torch.int32))
+    want = torch.zeros(n, dtype=torch.int32, device=dev)
+    want[hub], want[leaf] = 1, 2
+    return G, want
+
+
+@pytest.mark.parametrize("hubs", [1023, 1024, 1025, 2047, 3000])
+def test_parts_of_the_list(hubs):
+    import paper_2210_00389_amd as tc
+    print(f"case: {hubs} hubs", flush=True)
+    G, want = _hubs(hubs, 1030, 5000, 4_000_000)
+    lev, num = tc.bfs_levels(G, root=0)
+    assert num == 3 and torch.equal(lev, want)
+
+
+@pytest.mark.parametrize("rows", [65535, 65536, 65537])
+def test_end_of_the_list(rows):
+    import paper_2210_00389_amd as tc
+    print(f"case: {rows} rows of 1100", flush=True)
+    n, a = 17_200_000, 1100
+    s = torch.arange(rows, device="cuda", dtype=torch.int32).add_(a).repeat_interleave(a)
+    d = torch.arange(a, device="cuda", dtype=torch.int32).repeat(rows)
+    G = tc.build_csr(n, s, d)
+    want = torch.zeros(n, dtype=torch.int32, device="cuda")
+    want[1:a], want[a:a + rows] = 2, 1
+    lev, num = tc.bfs_levels(G, root=0)
+    assert num == 3 and torch.equal(lev, want)
+
+
+def test_time_of_a_far_longer_row():
+    import paper_2210_00389_amd as tc
+
+    def ms(hubs):
+        G, _ = _hubs(hubs, 1100, 2_000_000, 4_000_000)
+        tc.bfs_levels(G, root=0)
+        t = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            tc.bfs_levels(G, root=0)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return statistics.median(t)
+
+    print("case: 900 and 1500 hubs beside one of 2000000 leaves", flush=True)
+    few, many = ms(900), ms(1500)
+    assert many < 10 * few, (few, many)
