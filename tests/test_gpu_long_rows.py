@@ -66,3 +66,54 @@ def test_time_of_a_far_longer_row():
     print("case: 900 and 1500 hubs beside one of 2000000 leaves", flush=True)
     few, many = ms(900), ms(1500)
     assert many < 10 * few, (few, many)
+
+
+def _rest(k, leaves, hub_last):
+    """A clique of k vertices, then a star whose hub has its smallest or its largest id."""
+    import paper_2210_00389_amd as tc
+    i = torch.arange(k, device="cuda")
+    s, d = i.repeat_interleave(k), i.repeat(k)
+    hub = k + (leaves if hub_last else 0)
+    leaf = k + torch.arange(leaves, device="cuda") + (0 if hub_last else 1)
+    G = tc.build_csr(k + 1 + leaves, torch.cat([s, torch.full_like(leaf, hub)]).to(torch.int32),
+                     torch.cat([d, leaf]).to(torch.int32))
+    want = torch.ones(k + 1 + leaves, dtype=torch.int32, device="cuda")
+    want[0] = 0
+    if hub_last:
+        want[k:] = 2
+        want[k], want[hub] = 0, 1
+    else:
+        want[hub] = 0
+    return G, want
+
+
+@pytest.mark.parametrize("leaves", [1, 63, 64, 65, 1023, 1024, 1025, 32768, 32769, 40000])
+@pytest.mark.parametrize("hub_last", [False, True])
+def test_star_beside_a_component(leaves, hub_last):
+    import paper_2210_00389_amd as tc
+    print(f"case: {leaves} leaves, hub last {hub_last}", flush=True)
+    G, want = _rest(400, leaves, hub_last)
+    lev, num = tc.bfs_levels(G, root=0)
+    assert num == (3 if hub_last and leaves > 1 else 2) and torch.equal(lev, want)
+
+
+@pytest.mark.parametrize("hub_last", [False, True])
+def test_time_of_a_star_beside_a_component(hub_last):
+    import paper_2210_00389_amd as tc
+
+    def ms(leaves):
+        G, _ = _rest(2, leaves, hub_last)
+        tc.bfs_levels(G, root=0)
+        t = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            tc.bfs_levels(G, root=0)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return statistics.median(t)
+
+    print(f"case: stars of 60 and 30000 leaves, hub last {hub_last}", flush=True)
+    few, many = ms(60), ms(30000)
+    assert many < 10 * few, (few, many)
