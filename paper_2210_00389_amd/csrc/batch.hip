@@ -42,6 +42,9 @@ constexpr int kFrontCap = 2048;  // frontier vertices of a top-down level (at mo
 constexpr int kRowLanes = 16;    // lanes that expand a frontier row together
 constexpr int kRowLoads = 8;     // row entries a thread loads at once in a bottom-up level
 constexpr int kRestCap = 6144;   // unreached vertices of other components levelled together (LDS left beside L)
+constexpr int kRestEntries = 65536;  // and their row entries
+constexpr int kRestRow = 64;     // a longer row of theirs is a wave's, not a thread's
+constexpr int kRestLong = kRestEntries / (kRestRow + 1);  // such rows at most
 constexpr int kPieceMin = 1024;  // smallest piece size a caller may ask for
 constexpr int kAutoMin = 16;     // smallest piece size chosen by auto_piece
 
@@ -72,10 +75,11 @@ struct LevelLds {
     struct {
       uint16_t v[kRestCap];    // an unreached vertex
       uint16_t low[kRestCap];  // the smallest vertex known of its component
+      uint16_t row[kRestLong];  // places of those with rows longer than kRestRow
     } rest;
   };
   int64_t sh[kBfsThreads / kWave + 1];
-  int cnt, num;
+  int cnt, num, nlong;
 };
 
 // Level-synchronous BFS from the vertex of level 0 (set by the caller), with
@@ -156,25 +160,35 @@ __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* c
 }
 
 // The remaining components together, when they hold at most kRestCap
-// vertices: L of a listed vertex is its place in the list while the smallest
-// vertex of every component spreads through it (each pass also jumps to the
-// label of the label), then levels from those vertices.  One search per
-// component instead took 0.94 ms on a Chung-Lu graph of 8001 vertices and mean
-// degree 6, whose hundreds of small components each cost passes over all
-// vertices.  Returns false if there are more.
+// vertices and kRestEntries entries: L of a listed vertex is its place in the
+// list while the smallest vertex of every component spreads through it (each
+// pass also jumps to the label of the label), then levels from those vertices.
+// One search per component instead took 0.94 ms on a Chung-Lu graph of 8001
+// vertices and mean degree 6, whose hundreds of small components each cost
+// passes over all vertices.  With every row walked by a thread, a star of 6000
+// vertices beside one of 20000 took 2.8 ms, 3.5 where its hub has the largest
+// id; the two together now take 0.77 and 0.73.  Returns false if there are more: a search of
+// their own levels dense components sooner.
 __device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
-  const int tid = threadIdx.x, nt = blockDim.x;
+  const int tid = threadIdx.x, nt = blockDim.x, wv = tid / kWave, nw = nt / kWave, ln = lane();
   uint16_t* L = s.L;
-  if (tid == 0) s.num = 0;
+  if (tid == 0) s.num = s.cnt = s.nlong = 0;
   __syncthreads();
   for (int i = tid; i < n; i += nt)
     if (L[i] == kUnvisited) {
       const int q = atomicAdd(&s.num, 1);
-      if (q < kRestCap) s.rest.v[q] = static_cast<uint16_t>(i);
+      if (q >= kRestCap) continue;
+      s.rest.v[q] = static_cast<uint16_t>(i);
+      const int64_t dg = rows[i + 1] - rows[i];
+      atomicAdd(&s.cnt, static_cast<int>(min(dg, static_cast<int64_t>(kRestEntries + 1))));
+      if (dg > kRestRow) {
+        const int at = atomicAdd(&s.nlong, 1);
+        if (at < kRestLong) s.rest.row[at] = static_cast<uint16_t>(q);
+      }
     }
   __syncthreads();
-  const int m = s.num;
-  if (m > kRestCap) return false;
+  const int m = s.num, nl = s.nlong;
+  if (m > kRestCap || s.cnt > kRestEntries) return false;  // then nl fits as well
   if (m == 0) return true;
   for (int q = tid; q < m; q += nt) {
     s.rest.low[q] = s.rest.v[q];
@@ -183,19 +197,31 @@ __device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t*
   // a neighbour of an unreached vertex is unreached, so L of it is a place
   // (min: in a list that is not symmetric it may be a level)
   auto place = [&](int v) { return min(static_cast<int>(L[v]), m - 1); };
+  auto low_of = [&](int v) { return static_cast<int>(s.rest.low[place(v)]); };
   for (int more = 1; more;) {
     __syncthreads();
     int changed = 0;
-    for (int q = tid; q < m; q += nt) {
-      const int v = s.rest.v[q];
-      const int was = s.rest.low[q];
-      int low = was;
-      for (int64_t k = rows[v], e = rows[v + 1]; k < e; ++k) low = min(low, static_cast<int>(s.rest.low[place(cols[k])]));
-      low = min(low, static_cast<int>(s.rest.low[place(low)]));
-      if (low < was) {
+    auto take = [&](int q, int low) {
+      low = min(low, low_of(low));
+      if (low < s.rest.low[q]) {
         s.rest.low[q] = static_cast<uint16_t>(low);
         changed = 1;
       }
+    };
+    for (int q = tid; q < m; q += nt) {
+      const int v = s.rest.v[q];
+      const int64_t b = rows[v], e = rows[v + 1];
+      if (e - b > kRestRow) continue;
+      int low = s.rest.low[q];
+      for (int64_t k = b; k < e; ++k) low = min(low, low_of(cols[k]));
+      take(q, low);
+    }
+    for (int i = wv; i < nl; i += nw) {
+      const int q = s.rest.row[i], v = s.rest.v[q];
+      int low = s.rest.low[q];
+      for (int64_t k = rows[v] + ln, e = rows[v + 1]; k < e; k += kWave) low = min(low, low_of(cols[k]));
+      low = kUnvisited - wave_max(kUnvisited - low);
+      if (ln == 0) take(q, low);
     }
     more = __syncthreads_or(changed);
   }
@@ -206,14 +232,22 @@ __device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t*
   for (int level = 0, more = 1; more; ++level) {
     __syncthreads();
     int found = 0;
+    auto reach = [&](int w) {
+      if (L[w] != kUnvisited) return;
+      L[w] = static_cast<uint16_t>(level + 1);
+      found = 1;
+    };
     for (int q = tid; q < m; q += nt) {
       const int v = s.rest.v[q];
       if (L[v] != level) continue;
-      for (int64_t k = rows[v], e = rows[v + 1]; k < e; ++k)
-        if (L[cols[k]] == kUnvisited) {
-          L[cols[k]] = static_cast<uint16_t>(level + 1);
-          found = 1;
-        }
+      const int64_t b = rows[v], e = rows[v + 1];
+      if (e - b > kRestRow) continue;
+      for (int64_t k = b; k < e; ++k) reach(cols[k]);
+    }
+    for (int i = wv; i < nl; i += nw) {
+      const int v = s.rest.v[s.rest.row[i]];
+      if (L[v] != level) continue;
+      for (int64_t k = rows[v] + ln, e = rows[v + 1]; k < e; k += kWave) reach(cols[k]);
     }
     more = __syncthreads_or(found);
   }

@@ -1,0 +1,85 @@
+"""Levels of small graphs searched by one workgroup, where a row's length
+decides who expands it: stars, wheels and cliques as the searched component and
+beside it, around the bounds of a remainder that is levelled at once.  T, |H|
+and levels equal the oracle's, alone and in a batch (integers: no tolerance);
+times are compared with those of the same search without the long row."""
+import statistics
+
+import numpy as np
+import pytest
+import torch
+
+import graphgen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+U = graphgen.disjoint_union
+
+
+def _rev(g):
+    return graphgen.Graph(g.n, (g.n - 1 - g.src).astype(np.int32), (g.n - 1 - g.dst).astype(np.int32))
+
+
+def _rest(h):
+    """h beside a larger star, in both orders of the ids."""
+    g = U([graphgen.star(8000), h])
+    return [g, _rev(g)]
+
+
+REST = {
+    **{f"star {k}": (lambda k=k: _rest(graphgen.star(k))) for k in (2, 64, 65, 66, 67, 1000, 6143, 6144, 6145)},
+    **{f"clique {k}": (lambda k=k: _rest(graphgen.complete(k))) for k in (64, 65, 66, 67, 256, 257, 400)},
+    "wheels": lambda: _rest(U([graphgen.wheel(k) for k in (5, 64, 66, 80, 700)])),
+    "stars and paths": lambda: _rest(graphgen.relabel(U([graphgen.star(k) for k in (3, 70, 2, 500, 66)] +
+                                                        [graphgen.path(k) for k in (40, 1, 9)]), 4)),
+    "many stars": lambda: _rest(U([graphgen.star(70)] * 60)),
+}
+
+
+def _check(graphs):
+    import paper_2210_00389_amd as tc
+    want = []
+    for g in graphs:
+        c = oracle.from_graph(g)
+        lv = oracle.bfs_levels(c)
+        want.append((oracle.count(c, lv.levels).triangles, len(oracle.cover_edges(c, lv.levels)[0]), lv.levels))
+        r = tc.count(tc.from_host_csr(c.n, c.row_offsets, c.cols), return_levels=True)
+        assert np.array_equal(r.levels.cpu().numpy(), lv.levels)
+        assert (r.T, r.h) == want[-1][:2]
+    r = tc.count_batch(tc.Batch.from_graphs(graphs), return_levels=True)
+    assert r.triangles.cpu().tolist() == [w[0] for w in want] and r.h_count.cpu().tolist() == [w[1] for w in want]
+    assert np.array_equal(r.levels.cpu().numpy(), np.concatenate([w[2] for w in want]))
+
+
+@pytest.mark.parametrize("name", list(REST))
+def test_rows_of_a_remainder(name):
+    print(f"case: {name}", flush=True)
+    _check(REST[name]())
+
+
+def _us(g, root=-1):
+    import paper_2210_00389_amd as tc
+    G = tc.from_host_pairs(g.n, g.src, g.dst)
+    tc.count(G, root=root)
+    t = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        tc.count(G, root=root)
+        b.record()
+        b.synchronize()
+        t.append(a.elapsed_time(b) * 1e3)
+    return statistics.median(t)
+
+
+@pytest.mark.parametrize("rev", [False, True])
+def test_time_of_a_star_in_the_remainder(rev):
+    print(f"case: stars of 60 and 6000 beside an edge that is searched first, ids reversed {rev}", flush=True)
+
+    def us(k):
+        g = U([graphgen.path(2), graphgen.star(k)])
+        return _us(_rev(g), g.n - 1) if rev else _us(g, 0)
+
+    few, many = us(60), us(6000)
+    assert many < 5 * few, (few, many)
