@@ -7,8 +7,8 @@
 // the highest-degree vertex (smallest id on ties); every other component is
 // then searched from its smallest unvisited id, as in the scan order of
 // Alg. 1, and isolated vertices get level 0.  Each level is one pass over the
-// vertices: top-down from the frontier (vertices of degree above kBigDeg are
-// expanded by a whole wave) or, when the last level was large, bottom-up.
+// vertices: top-down from the listed frontier (16 lanes a row, longer rows a
+// wave or more) or, when the last level was large, bottom-up.
 // The block writes the level parity as a bit array (Lemma 1: for adjacent
 // vertices L(x) = L(y) iff their parities agree, so the parity is all that
 // |H| needs) and the optional int32 levels.
@@ -40,6 +40,9 @@ constexpr uint16_t kUnvisited = 0xFFFF;
 constexpr int kLastLevel = TC_BATCH_MAX_N - 2;
 constexpr int kFrontCap = 2048;  // frontier vertices of a top-down level (at most n / 32 there)
 constexpr int kRowLanes = 16;    // lanes that expand a frontier row together
+// A longer frontier row is expanded by a wave or more (bounds of 64 to 384
+// alike: 48 small graphs 88 to 92 us, R-MAT scale 10 27 to 28).
+constexpr int kLongRow = 128;
 constexpr int kRowLoads = 8;     // row entries a thread loads at once in a bottom-up level
 constexpr int kRestCap = 6144;   // unreached vertices of other components levelled together (LDS left beside L)
 constexpr int kRestEntries = 65536;  // and their row entries
@@ -71,7 +74,10 @@ __device__ __forceinline__ int64_t block_max_i64(int64_t v, int64_t* sh) {
 struct LevelLds {
   uint16_t L[TC_BATCH_MAX_N];
   union {
-    uint16_t front[kFrontCap];
+    struct {
+      uint16_t all[kFrontCap];
+      uint16_t row[kFrontCap];  // of them, those with rows longer than kLongRow
+    } front;
     struct {
       uint16_t v[kRestCap];    // an unreached vertex
       uint16_t low[kRestCap];  // the smallest vertex known of its component
@@ -91,17 +97,37 @@ __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* c
   int last = 1;  // vertices found at the previous level
   while (level < kLastLevel) {
     bool bottom_up = last > n / 32;
-    if (tid == 0) s.cnt = s.num = 0;
+    if (tid == 0) s.cnt = s.num = s.nlong = 0;
     __syncthreads();
     int found = 0;
     const uint16_t cur = static_cast<uint16_t>(level), nxt = static_cast<uint16_t>(level + 1);
+    // every lanes-th of the row entries [k0, e), where `lanes` lanes share a row
+    auto expand = [&](int64_t k0, int64_t e, int lanes) {
+      for (; k0 < e; k0 += lanes * 4) {
+        int32_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = k0 + u * lanes < e ? cols[k0 + u * lanes] : -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (w[u] >= 0 && L[w[u]] == kUnvisited) {
+            L[w[u]] = nxt;
+            ++found;
+          }
+      }
+    };
+    // `found` may count a vertex more than once in the top-down pass (two
+    // parents in one level); it only steers the direction and the stop test
+    auto add_found = [&]() {
+      const int f = wave_sum(found);
+      if (ln == 0 && f) atomicAdd(&s.cnt, f);
+    };
     if (!bottom_up) {
       // the frontier is listed; with the same level of components searched
       // before it may not fit (an unvisited vertex has no neighbour there)
       for (int i = tid; i < n; i += nt)
         if (L[i] == cur) {
           const int q = atomicAdd(&s.num, 1);
-          if (q < kFrontCap) s.front[q] = static_cast<uint16_t>(i);
+          if (q < kFrontCap) s.front.all[q] = static_cast<uint16_t>(i);
         }
       __syncthreads();
       bottom_up = s.num > kFrontCap;
@@ -127,30 +153,30 @@ __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* c
         }
       }
     } else {
-      // kRowLanes lanes expand a row together
       const int m = s.num;
-      const int sub = tid % kRowLanes;
       for (int q = tid / kRowLanes; q < m; q += nt / kRowLanes) {
-        const int i = s.front[q];
-        const int64_t e = rows[i + 1];
-        for (int64_t k0 = rows[i] + sub; k0 < e; k0 += kRowLanes * 4) {
-          int32_t w[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) w[u] = k0 + u * kRowLanes < e ? cols[k0 + u * kRowLanes] : -1;
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (w[u] >= 0 && L[w[u]] == kUnvisited) {
-              L[w[u]] = nxt;
-              ++found;
-            }
-        }
+        const int i = s.front.all[q];
+        const int64_t b = rows[i], e = rows[i + 1];
+        if (e - b <= kLongRow) expand(b + tid % kRowLanes, e, kRowLanes);
+        else if (tid % kRowLanes == 0) s.front.row[atomicAdd(&s.nlong, 1)] = static_cast<uint16_t>(i);
       }
     }
-    // `found` may count a vertex more than once in the top-down pass (two
-    // parents in one level); it only steers the direction and the stop test
-    found = wave_sum(found);
-    if (ln == 0 && found) atomicAdd(&s.cnt, found);
+    add_found();
     __syncthreads();
+    const int nl = s.nlong;
+    if (nl > 0) {  // uniform
+      // the long rows share the block, a wave each at least (with 16 lanes for
+      // any row a star of 65536 vertices took 750 us, 334 so)
+      int sh = __builtin_ctz(kBfsThreads);
+      while ((1 << sh) > kWave && (nl << sh) > nt) --sh;
+      found = 0;
+      for (int q = tid >> sh; q < nl; q += nt >> sh) {
+        const int i = s.front.row[q];
+        expand(rows[i] + (tid & ((1 << sh) - 1)), rows[i + 1], 1 << sh);
+      }
+      add_found();
+      __syncthreads();
+    }
     last = s.cnt;
     __syncthreads();
     if (last == 0) break;

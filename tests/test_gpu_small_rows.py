@@ -58,6 +58,30 @@ def test_rows_of_a_remainder(name):
     _check(REST[name]())
 
 
+def _tree(hubs, leaves, n=65536):
+    """Vertex 0 joined to hubs of as many leaves as listed, isolated vertices up to n."""
+    s = [np.zeros(hubs, np.int64), np.repeat(np.arange(1, hubs + 1), leaves)]
+    d = [np.arange(1, hubs + 1), hubs + 1 + np.arange(int(np.sum(leaves)))]
+    return graphgen.Graph(n, np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32))
+
+
+@pytest.mark.parametrize("hubs", [1, 2, 3, 4, 5, 8, 9, 16, 17, 40, 200])
+@pytest.mark.parametrize("leaves", [15, 63, 127, 128, 129, 300])
+def test_long_rows_of_a_frontier(hubs, leaves):
+    import paper_2210_00389_amd as tc
+    print(f"case: {hubs} hubs of {leaves} leaves", flush=True)
+    size = np.full(hubs, leaves)
+    size[hubs // 2] += 1700  # one far longer
+    for n in (65536, int(size.sum()) + hubs + 1):
+        g = _tree(hubs, size, n)
+        c = oracle.from_graph(g)
+        for root in (0, 1 + hubs // 2, c.n - 1):
+            lv = oracle.bfs_levels(c, root)
+            r = tc.count(tc.from_host_csr(c.n, c.row_offsets, c.cols), root=root, return_levels=True)
+            assert np.array_equal(r.levels.cpu().numpy(), lv.levels), (n, root)
+            assert (r.T, r.h) == (0, 0)
+
+
 def _us(g, root=-1):
     import paper_2210_00389_amd as tc
     G = tc.from_host_pairs(g.n, g.src, g.dst)
@@ -83,3 +107,24 @@ def test_time_of_a_star_in_the_remainder(rev):
 
     few, many = us(60), us(6000)
     assert many < 5 * few, (few, many)
+
+
+def _search_us(g, root):
+    """The search alone: the first stage of the call (the second counts the triangles)."""
+    import paper_2210_00389_amd as tc
+    G = tc.from_host_pairs(g.n, g.src, g.dst)
+    tc.profile_enable(True)
+    try:
+        t = []
+        for _ in range(8):
+            tc.count(G, root=root)
+            t.append(dict(tc.profile_read())["batch_bfs"] * 1e3)
+    finally:
+        tc.profile_enable(False)
+    return statistics.median(t[1:])
+
+
+def test_time_of_one_long_row():
+    print("case: 64000 leaves of one hub and of 64", flush=True)
+    one, many = _search_us(_tree(1, [64000]), 0), _search_us(_tree(64, [1000] * 64), 0)
+    assert one < 1.5 * many, (one, many)
