@@ -3,7 +3,7 @@
 //
 // The additions go to the entry (u, v), u < v, of an edge; a second pass
 // copies every sum to the entry (v, u), one search per edge instead of three
-// searches and atomics per triangle.
+// searches and atomics per triangle (short lists add to both, see kFew).
 //
 // Atomics to memory bound it (six a triangle, the hubs' edges on the same
 // addresses: 3.8 ms for the 15.6 M triangles of R-MAT scale 16).  A triangle
@@ -23,9 +23,18 @@ namespace tc {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTri = 2048;      // consecutive triangles of a block
+constexpr int kTri = 2048;      // consecutive triangles of a block at most
 constexpr int kTable = 2048;    // edges summed in LDS (24 KB)
 constexpr int kProbes = 4;      // slots an edge may take
+// Lists of up to kFew triangles are added one by one, without the table; lists
+// of up to a tenth of the entries add to both orientations, since the mirror
+// pass over all entries takes longer than their second searches.  us, all
+// lists with the mirror pass and shares of kTri / so: 1 triangle on
+// G(1000003, d 16) 618 / 28; R-MAT scale 20, 31.4 M entries, 4096 triangles
+// 1885 / 54, 0.49 M 1904 / 206, 2.0 M 2047 / 533, in random order 1903 / 54,
+// 1977 / 495, 2702 / 1955.  With 3.9 M, an eighth, adding to both takes 1169
+// against 2322, but in random order 4067 against 3689.
+constexpr int64_t kFew = 4096, kMirrorRatio = 10;
 constexpr unsigned long long kFree = ~0ull;
 
 __device__ __forceinline__ void order2(int32_t& x, int32_t& y) {
@@ -34,9 +43,9 @@ __device__ __forceinline__ void order2(int32_t& x, int32_t& y) {
   x = t;
 }
 
-// Adds s[q] to the entry (u[q], v[q]) where there is one, N searches
-// advancing together (s[q] = 0: none).
-template <int N>
+// Adds s[q] to the entry (u[q], v[q]) where there is one, and to (v[q], u[q])
+// if kBoth, N searches advancing together (s[q] = 0: none).
+template <bool kBoth, int N>
 __device__ __forceinline__ void add_edges(const int64_t* off, const int32_t* cols, const int32_t (&u)[N],
                                           const int32_t (&v)[N], const int32_t (&s)[N], int32_t* sup) {
   int64_t lo[N], hi[N], end[N];
@@ -62,12 +71,15 @@ __device__ __forceinline__ void add_edges(const int64_t* off, const int32_t* col
 #pragma unroll
   for (int q = 0; q < N; ++q)
     if (lo[q] < end[q] && cols[lo[q]] == v[q]) atomicAdd(&sup[lo[q]], s[q]);
+  if constexpr (kBoth) add_edges<false, N>(off, cols, v, u, s, sup);
 }
 
+template <bool kBoth>
 __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, const int32_t* cols, int64_t n,
-                                                           const int32_t* tri, int64_t ntri, int32_t* sup) {
+                                                           const int32_t* tri, int64_t ntri, int share, int32_t* sup) {
   __shared__ unsigned long long s_key[kTable];  // u << 32 | v
   __shared__ int32_t s_sum[kTable];
+  const bool plain = kBoth && ntri <= kFew;
   auto keep = [&](int32_t u, int32_t v) {
     const unsigned long long key = (static_cast<unsigned long long>(static_cast<uint32_t>(u)) << 32) |
                                    static_cast<uint32_t>(v);
@@ -83,13 +95,13 @@ __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, c
     }
     return false;
   };
-  for (int64_t t0 = blockIdx.x * static_cast<int64_t>(kTri); t0 < ntri; t0 += static_cast<int64_t>(gridDim.x) * kTri) {
-    for (int i = threadIdx.x; i < kTable; i += kThreads) {
+  for (int64_t t0 = blockIdx.x * static_cast<int64_t>(share); t0 < ntri; t0 += static_cast<int64_t>(gridDim.x) * share) {
+    for (int i = threadIdx.x; i < (plain ? 0 : kTable); i += kThreads) {
       s_key[i] = kFree;
       s_sum[i] = 0;
     }
     __syncthreads();
-    const int64_t t1 = min(t0 + kTri, ntri);
+    const int64_t t1 = min(t0 + share, ntri);
     for (int64_t w0 = t0 + (threadIdx.x & ~(kWave - 1)); w0 < t1; w0 += kThreads) {  // uniform per wave
       const int64_t i = w0 + lane();
       int32_t a = -1, b = -1, c = -1;
@@ -112,9 +124,9 @@ __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, c
       order2(a, b);
       order2(b, c);
       order2(a, b);
-      if (x < 0) {  // uniform
+      if (plain || x < 0) {  // uniform
         const int32_t u[3] = {a, a, b}, v[3] = {b, c, c}, one[3] = {1, 1, 1};
-        add_edges<3>(off, cols, u, v, one, sup);
+        add_edges<kBoth, 3>(off, cols, u, v, one, sup);
         continue;
       }
       uint32_t left = 7u;  // edges not kept
@@ -125,10 +137,11 @@ __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, c
         const bool ab = (left & 1u) != 0u, ac = !ab && (left & 2u) != 0u;
         left &= left - 1;
         const int32_t u[1] = {ab || ac ? a : b}, v[1] = {ab ? b : c}, one[1] = {1};
-        add_edges<1>(off, cols, u, v, one, sup);
+        add_edges<kBoth, 1>(off, cols, u, v, one, sup);
       }
     }
     __syncthreads();
+    if (plain) continue;
     constexpr int kAtOnce = 4;
     static_assert(kTable % (kThreads * kAtOnce) == 0, "whole rounds");
     for (int i = threadIdx.x; i < kTable; i += kThreads * kAtOnce) {
@@ -140,7 +153,7 @@ __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, c
         u[q] = static_cast<int32_t>(key >> 32);
         v[q] = static_cast<int32_t>(key & 0xFFFFFFFFull);
       }
-      add_edges<kAtOnce>(off, cols, u, v, s, sup);
+      add_edges<kBoth, kAtOnce>(off, cols, u, v, s, sup);
     }
     __syncthreads();
   }
@@ -177,10 +190,17 @@ __global__ __launch_bounds__(kThreads) void mirror_kernel(const int64_t* off, co
 int support_run(const tc_csr* g, const int32_t* tri, int64_t ntri, int32_t* support, hipStream_t s) {
   TC_TRY(fill_i32(support, 0, g->nnz, s));
   if (ntri <= 0 || g->n == 0) return TC_OK;
-  const unsigned blocks = grid_for(ntri, kTri, 65536);
-  support_kernel<<<blocks, kThreads, 0, s>>>(g->row_offsets, g->cols, g->n, tri, ntri, support);
-  mirror_kernel<<<grid_for(g->nnz, kMirror * (kThreads / kWave), 16384), kThreads, 0, s>>>(g->row_offsets, g->cols, g->n,
-                                                                                          g->nnz, support);
+  // short lists in smaller shares, so that they still fill the chip
+  const int64_t even = (ntri / (4 * static_cast<int64_t>(num_cus())) + kThreads - 1) / kThreads * kThreads;
+  const int share = static_cast<int>(std::min<int64_t>(std::max<int64_t>(even, kThreads), kTri));
+  const unsigned blocks = grid_for(ntri, share, 65536);
+  if (ntri <= std::max(kFew, g->nnz / kMirrorRatio)) {
+    support_kernel<true><<<blocks, kThreads, 0, s>>>(g->row_offsets, g->cols, g->n, tri, ntri, share, support);
+  } else {
+    support_kernel<false><<<blocks, kThreads, 0, s>>>(g->row_offsets, g->cols, g->n, tri, ntri, share, support);
+    mirror_kernel<<<grid_for(g->nnz, kMirror * (kThreads / kWave), 16384), kThreads, 0, s>>>(
+        g->row_offsets, g->cols, g->n, g->nnz, support);
+  }
   TC_HIP(hipGetLastError());
   return TC_OK;
 }
