@@ -27,7 +27,7 @@ constexpr int kManyRows = 8 * kTile;  // rows of a tile (nearly all empty) beyon
 struct CoverWs {
   uint8_t* lev8;      // levels modulo 256
   int32_t* wide;      // [kPrepBlocks]: a level outside 0..255 was seen
-  int32_t* tile_row;  // [tiles + 1]: row of a tile's first entry
+  int32_t* tile_row;  // [tiles]: row of a tile's first entry
   int32_t* tile_cnt;  // list entries of a tile
   int64_t* tile_off;  // their scan
   uint8_t* bits;      // a byte for the kItems entries of a thread
@@ -59,8 +59,8 @@ __global__ __launch_bounds__(kThreads) void cover_prep_kernel(const int64_t* off
     lev8[v] = static_cast<uint8_t>(l);
     w |= l < 0 || l > 255;
     const int64_t b = off[v], e = off[v + 1];
-    for (int64_t t = (b + kTile - 1) / kTile; t * kTile < e; ++t) tile_row[t] = static_cast<int32_t>(v);
-    if (v == n - 1) tile_row[tiles] = static_cast<int32_t>(v);
+    for (int64_t t = v == 0 ? 0 : (b + kTile - 1) / kTile; t < tiles && t * kTile < e; ++t)
+      tile_row[t] = static_cast<int32_t>(v);
   }
   w = __syncthreads_or(w);
   if (threadIdx.x == 0) wide[blockIdx.x] = w;
@@ -71,6 +71,27 @@ struct TileLds {
   int32_t own[kTile];     // there: the row, from the tile's first one
   int last[kThreads / kWave];
 };
+
+// The entries of the block's tile that lie in a row, [from, tn) of its kTile (tn
+// = 0: none), and its first and last row.  The offsets may begin after 0 and end
+// before nnz (a column buffer with room to spare): the tiles past their end
+// have no row, and what tile_row holds there is not used.
+struct TileRange {
+  int64_t t0;
+  int from, tn;
+  int32_t r0, r1;
+};
+__device__ __forceinline__ TileRange tile_range(const int64_t* off, int64_t n, const int32_t* tile_row, int64_t nnz) {
+  TileRange r;
+  r.t0 = blockIdx.x * static_cast<int64_t>(kTile);
+  const int64_t end = min(nnz, off[n]) - r.t0, tile = kTile;
+  r.from = static_cast<int>(min(max(off[0] - r.t0, static_cast<int64_t>(0)), tile));
+  r.tn = static_cast<int>(min(max(end, static_cast<int64_t>(0)), tile));
+  const int32_t a = tile_row[blockIdx.x], z = tile_row[blockIdx.x + 1];
+  r.r0 = r.tn > 0 ? a : 0;
+  r.r1 = end > tile ? z : static_cast<int32_t>(n - 1);
+  return r;
+}
 
 // Rows of the thread's entries (tile t0 .. t0 + tn).  Contains __syncthreads.
 __device__ __forceinline__ void tile_rows(TileLds& s, const int64_t* off, int32_t r0, int32_t r1, int64_t t0, int tn,
@@ -83,7 +104,7 @@ __device__ __forceinline__ void tile_rows(TileLds& s, const int64_t* off, int32_
       const int64_t p = t0 + min(tid * kItems + q, tn - 1);
       x[q] = q ? x[q - 1] : 0;
       if (q == 0 || p >= next) {
-        x[q] = static_cast<int32_t>(upper_bound_dev(off, static_cast<int64_t>(r0), static_cast<int64_t>(r1) + 1, p)) - 1;
+        x[q] = max(r0, static_cast<int32_t>(upper_bound_dev(off, static_cast<int64_t>(r0), static_cast<int64_t>(r1) + 1, p)) - 1);
         next = off[x[q] + 1];
       }
     }
@@ -122,7 +143,7 @@ __device__ __forceinline__ void tile_rows(TileLds& s, const int64_t* off, int32_
   }
 }
 
-__global__ __launch_bounds__(kThreads) void cover_mark_kernel(const int64_t* off, const int32_t* cols,
+__global__ __launch_bounds__(kThreads) void cover_mark_kernel(const int64_t* off, const int32_t* cols, int64_t n,
                                                               const int32_t* L, const uint8_t* lev8,
                                                               const int32_t* wide, int nwide, const int32_t* tile_row,
                                                               int64_t nnz, uint8_t* bits, int32_t* tile_cnt) {
@@ -130,17 +151,22 @@ __global__ __launch_bounds__(kThreads) void cover_mark_kernel(const int64_t* off
   __shared__ int32_t sh[kThreads / kWave + 1];
   const int tid = threadIdx.x;
   const int64_t t0 = blockIdx.x * static_cast<int64_t>(kTile);
-  const int tn = static_cast<int>(min(static_cast<int64_t>(kTile), nnz - t0));
   int32_t y[kItems], x[kItems];
 #pragma unroll
-  for (int q = 0; q < kItems; ++q) {
-    const int e = tid * kItems + q;
-    y[q] = e < tn ? cols[t0 + e] : -1;
+  for (int q = 0; q < kItems; ++q) y[q] = t0 + tid * kItems + q < nnz ? cols[t0 + tid * kItems + q] : -1;
+  const TileRange r = tile_range(off, n, tile_row, nnz);
+  if (r.tn == 0) {  // uniform
+    bits[blockIdx.x * static_cast<int64_t>(kThreads) + tid] = 0;
+    if (tid == 0) tile_cnt[blockIdx.x] = 0;
+    return;
   }
+#pragma unroll
+  for (int q = 0; q < kItems; ++q)
+    if (tid * kItems + q < r.from || tid * kItems + q >= r.tn) y[q] = -1;
   int wd = 0;
   for (int i = tid; i < nwide; i += kThreads) wd |= wide[i];
   wd = __syncthreads_or(wd);
-  tile_rows(s, off, tile_row[blockIdx.x], tile_row[blockIdx.x + 1], t0, tn, x);
+  tile_rows(s, off, r.r0, r.r1, r.t0, r.tn, x);
   uint32_t take = 0;
   auto mark = [&](const auto* lev) {
     int32_t lx[kItems], ly[kItems];
@@ -159,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void cover_mark_kernel(const int64_t* off
   if (tid == 0) tile_cnt[blockIdx.x] = c;
 }
 
-__global__ __launch_bounds__(kThreads) void cover_emit_kernel(const int64_t* off, const int32_t* cols,
+__global__ __launch_bounds__(kThreads) void cover_emit_kernel(const int64_t* off, const int32_t* cols, int64_t n,
                                                               const int32_t* tile_row, int64_t nnz,
                                                               const uint8_t* bits, const int64_t* tile_off,
                                                               int64_t cap, int32_t* h_u, int32_t* h_v,
@@ -169,13 +195,13 @@ __global__ __launch_bounds__(kThreads) void cover_emit_kernel(const int64_t* off
   __shared__ int32_t sh[kThreads / kWave + 1];
   const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid == 0) *h_count = tile_off[gridDim.x];
-  const int64_t t0 = blockIdx.x * static_cast<int64_t>(kTile);
-  const int tn = static_cast<int>(min(static_cast<int64_t>(kTile), nnz - t0));
+  const TileRange r = tile_range(off, n, tile_row, nnz);
+  if (r.tn == 0) return;  // uniform
   const uint32_t take = bits[blockIdx.x * static_cast<int64_t>(kThreads) + tid];
   int32_t y[kItems], x[kItems];
 #pragma unroll
-  for (int q = 0; q < kItems; ++q) y[q] = (take >> q) & 1u ? cols[t0 + tid * kItems + q] : 0;
-  tile_rows(s, off, tile_row[blockIdx.x], tile_row[blockIdx.x + 1], t0, tn, x);
+  for (int q = 0; q < kItems; ++q) y[q] = (take >> q) & 1u ? cols[r.t0 + tid * kItems + q] : 0;
+  tile_rows(s, off, r.r0, r.r1, r.t0, r.tn, x);
   int32_t total;
   int32_t at = block_excl_scan(static_cast<int32_t>(__popc(take)), sh, &total);
 #pragma unroll
@@ -200,7 +226,7 @@ int cover_run(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t* h_v
   CoverWs w = plan_cover(ws, n, nnz);
   const unsigned prep = grid_for(n, kThreads, kPrepBlocks);
   cover_prep_kernel<<<prep, kThreads, 0, s>>>(g->row_offsets, levels, n, tiles, w.lev8, w.wide, w.tile_row);
-  cover_mark_kernel<<<static_cast<unsigned>(tiles), kThreads, 0, s>>>(g->row_offsets, g->cols, levels, w.lev8, w.wide,
+  cover_mark_kernel<<<static_cast<unsigned>(tiles), kThreads, 0, s>>>(g->row_offsets, g->cols, n, levels, w.lev8, w.wide,
                                                                       static_cast<int>(prep), w.tile_row, nnz, w.bits,
                                                                       w.tile_cnt);
   TC_HIP(hipGetLastError());
@@ -208,7 +234,7 @@ int cover_run(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t* h_v
     Carver sc(w.scratch);
     TC_TRY(scan_exclusive<int32_t>(w.tile_cnt, w.tile_off, tiles, sc, s));
   }
-  cover_emit_kernel<<<static_cast<unsigned>(tiles), kThreads, 0, s>>>(g->row_offsets, g->cols, w.tile_row, nnz, w.bits,
+  cover_emit_kernel<<<static_cast<unsigned>(tiles), kThreads, 0, s>>>(g->row_offsets, g->cols, n, w.tile_row, nnz, w.bits,
                                                                       w.tile_off, cap, h_u, h_v, h_count);
   TC_HIP(hipGetLastError());
   return TC_OK;
