@@ -245,11 +245,12 @@ int tc_cover_edges(const tc_csr* g, const int32_t* levels, int32_t* h_u, int32_t
  * (relabelling, layout, count) is asynchronous.  Graphs within the
  * small-graph bounds (TC_SMALL_MAX_N vertices, TC_SMALL_MAX_NNZ entries)
  * take the path of tc_count_tuned, which never synchronises.  A larger graph
- * whose degrees are even enough (sum of squared degrees at most about 288
- * per entry) is counted on the caller's CSR by the kernels of tc_count_batch
- * after its BFS, without the relabelling.  A graph in
- * which a vertex could reach degree 2^29 (n - 1 and nnz / 2 both at least
- * 2^29) gives TC_ERR_TOO_LARGE: the count keeps list lengths below 2^29
+ * of fewer than 2^31 entries whose degrees are even enough and at most 65528
+ * (with d the largest and D2 the sum of their squares, D2 <= nnz^2 / n + d^2 +
+ * 168 nnz + 150 n + 2^28) is counted on the caller's CSR by the kernels of
+ * tc_count_batch after its BFS, without the relabelling.  A graph in which a
+ * vertex could reach degree 2^29 (n - 1 and nnz / 2 both at least 2^29) gives
+ * TC_ERR_TOO_LARGE: the count keeps list lengths below 2^29
  * (tc_list_triangles and tc_count_edge_baseline share the limit). */
 int tc_count(const tc_csr* g, int64_t root, uint32_t flags, int64_t* triangles,
              int64_t* h_count, int32_t* levels, int64_t* per_vertex, void* ws,

@@ -54,3 +54,34 @@ def test_longest_lists_fit_a_tile(rule):
 def test_sizes_of_ids_and_positions(rule):
     assert rule(2**31 - 2, 1000, 3, 3000) == [1] and rule(2**31 - 1, 1000, 3, 3000) == [0]
     assert rule(10**6, 2**31 - 1, 3000, 10**9) == [1] and rule(10**6, 2**31, 3000, 10**9) == [0]
+
+
+# (n, entries, largest degree, sum of squared degrees, whether the direct count was the faster), timed both ways
+TIMED = [
+    (300007, 7199792, 51, 179940000, True),       # uniform, degree 24: 701 / 241 us
+    (20011, 19517012, 1107, 19056000000, True),   # degree 1000: 2896 / 1882
+    (100003, 49876292, 596, 24924000000, True),   # degree 500: 4391 / 3148
+    (300007, 11989096, 21611, 2007000000, True),  # preferential, degree 40: 1177 / 760
+    (30011, 592634, 732, 71640000, True),         # power law 2.1, degree 20: 290 / 140
+    (100003, 1981764, 1380, 374640000, True),     # 354 / 314
+    (100003, 3956514, 1942, 1147800000, False),   # degree 40: 467 / 730
+    (150001, 4458896, 2042, 1258800000, False),   # degree 30: 567 / 813
+    (300007, 1790248, 1348, 249600000, True),     # degree 6: 475 / 387
+    (300007, 5958376, 2368, 1710000000, False),   # degree 20: 725 / 1015
+    (500009, 5966818, 2389, 1534200000, False),   # degree 12: 777 / 971
+    (1000003, 8959056, 2991, 2546400000, False),  # degree 9: 1185 / 1390
+    (2000003, 23900808, 4777, 10662000000, False),  # degree 12: 2381 / 2868
+    (1000003, 23997626, 4879, 4887000000, True),  # power law 2.5, degree 24: 2331 / 1331
+    (16384, 426048, 3620, 156300000, True),       # R-MAT scale 14: 282 / 142
+    (32768, 883218, 5979, 444900000, True),       # 15: 357 / 305
+    (65536, 1819000, 9584, 1242600000, False),    # 16: 415 / 1024
+    (131072, 1942810, 9868, 1089000000, False),   # 17, edge factor 8: 414 / 909
+    (262144, 7609464, 25380, 9510000000, False),  # 18: 875 / 4494
+    (1000003, 16129894, 65016, 4501200000, True),  # one hub of 65000: 1081 / 758
+    (1000003, 17039874, 65028, 34104000000, False),  # eight of them: 1180 / 2003
+]
+
+
+@pytest.mark.parametrize("n,nnz,maxdeg,deg2,faster", TIMED)
+def test_faster_path_of_timed_graphs(rule, n, nnz, maxdeg, deg2, faster):
+    assert rule(n, nnz, maxdeg, deg2) == [int(faster)]
