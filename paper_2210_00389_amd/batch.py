@@ -10,6 +10,9 @@ knobs of the counting kernel on a given batch and keeps the fastest.
 from __future__ import annotations
 
 import ctypes
+import functools
+import glob
+import hashlib
 import json
 import os
 from dataclasses import dataclass, field
@@ -179,6 +182,33 @@ def _cache_path() -> str:
     return os.path.join(os.path.dirname(os.path.abspath(__file__)), "_build", "autotune.json")
 
 
+@functools.lru_cache(maxsize=None)
+def kernels_id() -> str:
+    """Identity of the kernels a tuning was chosen for (a digest of their sources)."""
+    h = hashlib.sha256()
+    for f in sorted(glob.glob(os.path.join(L.HERE, "csrc", "*"))):
+        h.update(os.path.basename(f).encode())
+        h.update(open(f, "rb").read())
+    return h.hexdigest()[:16]
+
+
+def load_tunings(path: str) -> dict:
+    """The tunings cached in `path` that were chosen for the present kernels:
+    those of others may rule out what is faster now."""
+    try:
+        cache = json.load(open(path))
+        return {k: e for k, e in cache.items() if e.get("kernels") == kernels_id()}
+    except (OSError, ValueError, AttributeError):
+        return {}
+
+
+def store_tuning(path: str, cache: dict, key: str, **entry):
+    cache[key] = dict(entry, kernels=kernels_id())
+    os.makedirs(os.path.dirname(path), exist_ok=True)
+    with open(path, "w") as f:
+        json.dump(cache, f, indent=1)
+
+
 def shape_key(b: Batch) -> str:
     """Coarse batch shape: graph count, total vertices and entries (log2)."""
     lg = lambda v: int(np.log2(max(v, 1)))  # noqa: E731
@@ -188,17 +218,13 @@ def shape_key(b: Batch) -> str:
 def autotune(b: Batch, candidates=None, reps: int = 3, use_cache: bool = True, verbose: bool = False) -> dict:
     """Time every candidate tuning on `b` (median of `reps` launches, HIP
     events on the launch stream) and return the fastest; results are
-    checked equal across candidates.  The choice is cached per shape_key."""
+    checked equal across candidates.  The choice is cached per shape_key, for
+    the present kernels."""
     key = shape_key(b)
     path = _cache_path()
-    cache = {}
-    if use_cache and os.path.exists(path):
-        try:
-            cache = json.load(open(path))
-        except (OSError, ValueError):
-            cache = {}
-        if key in cache:
-            return dict(cache[key]["tuning"])
+    cache = load_tunings(path) if use_cache else {}
+    if key in cache:
+        return dict(cache[key]["tuning"])
     cands = candidates or _TUNE_CANDIDATES
     stream = torch.cuda.current_stream()
     ws = Workspace(b.cols.device)
@@ -225,8 +251,5 @@ def autotune(b: Batch, candidates=None, reps: int = 3, use_cache: bool = True, v
         if ms < best_ms:
             best, best_ms = t, ms
     if use_cache:
-        cache[key] = dict(tuning=best, ms=best_ms, table=[[t, ms] for t, ms in table])
-        os.makedirs(os.path.dirname(path), exist_ok=True)
-        with open(path, "w") as f:
-            json.dump(cache, f, indent=1)
+        store_tuning(path, cache, key, tuning=best, ms=best_ms, table=[[t, ms] for t, ms in table])
     return dict(best)

@@ -9,12 +9,11 @@ coordinate descent from the compiled defaults: each knob in turn takes every
 value of its list with the others at their best so far, timed on the device
 (median of `reps` calls, HIP events on the call's stream), and is kept when it
 is faster by more than `min_gain`.  Every candidate must give the same count.
-The choice is cached per graph class (path, log2 n, log2 nnz) in
-_build/autotune.json beside the batch autotuner's entries.
+The choice is cached per graph class (path, log2 n, log2 nnz), for the present
+kernels, in _build/autotune.json beside the batch autotuner's entries.
 """
 from __future__ import annotations
 
-import json
 import os
 import statistics
 
@@ -22,6 +21,7 @@ import numpy as np
 import torch
 
 from .api import Graph, TcError, Workspace, count, count_edge_baseline
+from .batch import load_tunings, store_tuning
 
 SPACE = {
     # which path: the one-workgroup path for graphs within 65536 vertices
@@ -80,14 +80,9 @@ def autotune_count(g: Graph, path: str = "cover", reps: int = 3, space: dict | N
     "edge": the comparator), as a dict of tc_tuning fields ({} = defaults)."""
     key = graph_key(g, path)
     cpath = _cache_path()
-    cache = {}
-    if use_cache and os.path.exists(cpath):
-        try:
-            cache = json.load(open(cpath))
-        except (OSError, ValueError):
-            cache = {}
-        if key in cache:
-            return dict(cache[key]["tuning"])
+    cache = load_tunings(cpath) if use_cache else {}
+    if key in cache:
+        return dict(cache[key]["tuning"])
     space = space or (SPACE if path == "cover" else EDGE_SPACE)
     ws = ws or Workspace(g.cols.device)
     if path == "cover":
@@ -121,8 +116,5 @@ def autotune_count(g: Graph, path: str = "cover", reps: int = 3, space: dict | N
             if ms < best_ms * (1.0 - min_gain):
                 best, best_ms = cand, ms
     if use_cache:
-        cache[key] = dict(tuning=best, ms=best_ms, default_ms=table[0][1], table=table)
-        os.makedirs(os.path.dirname(cpath), exist_ok=True)
-        with open(cpath, "w") as f:
-            json.dump(cache, f, indent=1)
+        store_tuning(cpath, cache, key, tuning=best, ms=best_ms, default_ms=table[0][1], table=table)
     return dict(best)
