@@ -48,6 +48,9 @@ constexpr int kRestCap = 6144;   // unreached vertices of other components level
 constexpr int kRestEntries = 65536;  // and their row entries
 constexpr int kRestRow = 64;     // a longer row of theirs is a wave's, not a thread's
 constexpr int kRestLong = kRestEntries / (kRestRow + 1);  // such rows at most
+constexpr int kSearches = 4;     // searches of one component each before all are labelled
+constexpr int kLabelEntries = 65536;  // entries to label per search so far (each costs about what a search does)
+constexpr int kLabelLong = 8192; // long rows among them
 constexpr int kPieceMin = 1024;  // smallest piece size a caller may ask for
 constexpr int kAutoMin = 16;     // smallest piece size chosen by auto_piece
 
@@ -83,21 +86,30 @@ struct LevelLds {
       uint16_t low[kRestCap];  // the smallest vertex known of its component
       uint16_t row[kRestLong];  // places of those with rows longer than kRestRow
     } rest;
+    struct {
+      uint32_t out[TC_BATCH_MAX_N / 32];  // bits of the unreached vertices
+      uint16_t row[kLabelLong];           // those with rows longer than kRestRow
+    } label;
   };
   int64_t sh[kBfsThreads / kWave + 1];
   int cnt, num, nlong;
 };
 
 // Level-synchronous BFS from the vertex of level 0 (set by the caller), with
-// L resident in LDS.  Returns its last level.
+// L resident in LDS; kLong: rows may be longer than kLongRow.  Returns its last
+// level.
+template <bool kLong>
 __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
   const int tid = threadIdx.x, nt = blockDim.x, ln = lane();
   uint16_t* L = s.L;
   int level = 0;
   int last = 1;  // vertices found at the previous level
-  while (level < kLastLevel) {
+  for (;;) {
     bool bottom_up = last > n / 32;
-    if (tid == 0) s.cnt = s.num = s.nlong = 0;
+    if (tid == 0) {
+      s.cnt = s.num = 0;
+      if (kLong) s.nlong = 0;
+    }
     __syncthreads();
     int found = 0;
     const uint16_t cur = static_cast<uint16_t>(level), nxt = static_cast<uint16_t>(level + 1);
@@ -157,13 +169,14 @@ __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* c
       for (int q = tid / kRowLanes; q < m; q += nt / kRowLanes) {
         const int i = s.front.all[q];
         const int64_t b = rows[i], e = rows[i + 1];
-        if (e - b <= kLongRow) expand(b + tid % kRowLanes, e, kRowLanes);
+        if (!kLong || e - b <= kLongRow) expand(b + tid % kRowLanes, e, kRowLanes);
         else if (tid % kRowLanes == 0) s.front.row[atomicAdd(&s.nlong, 1)] = static_cast<uint16_t>(i);
       }
     }
     add_found();
     __syncthreads();
-    const int nl = s.nlong;
+    last = s.cnt;
+    const int nl = kLong ? s.nlong : 0;
     if (nl > 0) {  // uniform
       // the long rows share the block, a wave each at least (with 16 lanes for
       // any row a star of 65536 vertices took 750 us, 334 so)
@@ -176,42 +189,48 @@ __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* c
       }
       add_found();
       __syncthreads();
+      last = s.cnt;
     }
-    last = s.cnt;
     __syncthreads();
-    if (last == 0) break;
-    ++level;
+    if (last == 0 || ++level == kLastLevel) break;
   }
   return level;
 }
 
-// The remaining components together, when they hold at most kRestCap
-// vertices and kRestEntries entries: L of a listed vertex is its place in the
-// list while the smallest vertex of every component spreads through it (each
-// pass also jumps to the label of the label), then levels from those vertices.
-// One search per component instead took 0.94 ms on a Chung-Lu graph of 8001
-// vertices and mean degree 6, whose hundreds of small components each cost
-// passes over all vertices.  With every row walked by a thread, a star of 6000
-// vertices beside one of 20000 took 2.8 ms, 3.5 where its hub has the largest
-// id; the two together now take 0.77 and 0.73.  Returns false if there are more: a search of
-// their own levels dense components sooner.
-__device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n) {
+// The remaining components together, when they hold at most kRestCap vertices
+// and, where rows may be longer than kRestRow (may_long), kRestEntries entries:
+// L of a listed vertex is its place in the list while the smallest vertex of
+// every component spreads through it (each pass also jumps to the label of the
+// label), then levels from those vertices.  One search per component instead
+// took 0.94 ms on a Chung-Lu graph of 8001 vertices and mean degree 6, whose
+// hundreds of small components each cost passes over all vertices.  With every
+// row walked by a thread, a star of 6000 vertices beside one of 20000 took 2.8
+// ms, 3.5 where its hub has the largest id; the two together now take 0.67.
+// Returns false if there are more: a search of their own levels dense
+// components sooner.
+__device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n, bool may_long) {
   const int tid = threadIdx.x, nt = blockDim.x, wv = tid / kWave, nw = nt / kWave, ln = lane();
   uint16_t* L = s.L;
   if (tid == 0) s.num = s.cnt = s.nlong = 0;
   __syncthreads();
+  int entries = 0;
   for (int i = tid; i < n; i += nt)
     if (L[i] == kUnvisited) {
       const int q = atomicAdd(&s.num, 1);
       if (q >= kRestCap) continue;
       s.rest.v[q] = static_cast<uint16_t>(i);
+      if (!may_long) continue;  // rows short enough for a thread each, whatever their sum
       const int64_t dg = rows[i + 1] - rows[i];
-      atomicAdd(&s.cnt, static_cast<int>(min(dg, static_cast<int64_t>(kRestEntries + 1))));
+      entries += static_cast<int>(min(dg, static_cast<int64_t>(kRestEntries + 1)));
       if (dg > kRestRow) {
         const int at = atomicAdd(&s.nlong, 1);
         if (at < kRestLong) s.rest.row[at] = static_cast<uint16_t>(q);
       }
     }
+  if (may_long) {
+    entries = wave_sum(entries);
+    if (ln == 0 && entries) atomicAdd(&s.cnt, entries);
+  }
   __syncthreads();
   const int m = s.num, nl = s.nlong;
   if (m > kRestCap || s.cnt > kRestEntries) return false;  // then nl fits as well
@@ -237,7 +256,7 @@ __device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t*
     for (int q = tid; q < m; q += nt) {
       const int v = s.rest.v[q];
       const int64_t b = rows[v], e = rows[v + 1];
-      if (e - b > kRestRow) continue;
+      if (may_long && e - b > kRestRow) continue;
       int low = s.rest.low[q];
       for (int64_t k = b; k < e; ++k) low = min(low, low_of(cols[k]));
       take(q, low);
@@ -267,7 +286,7 @@ __device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t*
       const int v = s.rest.v[q];
       if (L[v] != level) continue;
       const int64_t b = rows[v], e = rows[v + 1];
-      if (e - b > kRestRow) continue;
+      if (may_long && e - b > kRestRow) continue;
       for (int64_t k = b; k < e; ++k) reach(cols[k]);
     }
     for (int i = wv; i < nl; i += nw) {
@@ -277,6 +296,68 @@ __device__ bool rest_levels_lds(LevelLds& s, const int64_t* rows, const int32_t*
     }
     more = __syncthreads_or(found);
   }
+  return true;
+}
+
+// Any number of remaining components, at most `most` entries: L of an unreached
+// vertex is the smallest vertex known of its component (as above), and level 0
+// or kUnvisited in the end, so that one search levels them all.  One search
+// after another took 3.4 s on 30000 disjoint edges.  Returns false if there are
+// more entries or long rows.
+__device__ bool label_lds(LevelLds& s, const int64_t* rows, const int32_t* cols, int n, int64_t most) {
+  const int tid = threadIdx.x, nt = blockDim.x, wv = tid / kWave, nw = nt / kWave, ln = lane();
+  uint16_t* L = s.L;
+  if (tid == 0) s.nlong = 0;
+  __syncthreads();
+  int64_t entries = 0;
+  for (int i0 = tid - ln; i0 < n; i0 += nt) {
+    const int i = i0 + ln;
+    const bool out = i < n && L[i] == kUnvisited;
+    const uint64_t m = __ballot(out);
+    if ((ln & 31) == 0 && i < n) s.label.out[i >> 5] = static_cast<uint32_t>(m >> ln);
+    if (!out) continue;
+    const int64_t dg = rows[i + 1] - rows[i];
+    entries += dg;
+    if (dg <= kRestRow) continue;
+    const int q = atomicAdd(&s.nlong, 1);
+    if (q < kLabelLong) s.label.row[q] = static_cast<uint16_t>(i);
+  }
+  entries = block_sum(entries, s.sh);
+  const int nl = s.nlong;
+  if (entries > most || nl > kLabelLong) return false;
+  auto out = [&](int i) { return (s.label.out[i >> 5] >> (i & 31)) & 1u; };
+  for (int i = tid; i < n; i += nt)
+    if (out(i)) L[i] = static_cast<uint16_t>(i);
+  for (int more = 1; more;) {
+    __syncthreads();
+    int changed = 0;
+    auto take = [&](int i, int low) {
+      low = min(low, static_cast<int>(L[low]));
+      if (low < L[i]) {
+        L[i] = static_cast<uint16_t>(low);
+        changed = 1;
+      }
+    };
+    for (int i = tid; i < n; i += nt) {
+      if (!out(i)) continue;
+      const int64_t b = rows[i], e = rows[i + 1];
+      if (e - b > kRestRow) continue;
+      int low = L[i];
+      for (int64_t k = b; k < e; ++k) low = min(low, static_cast<int>(L[cols[k]]));
+      take(i, low);
+    }
+    for (int q = wv; q < nl; q += nw) {
+      const int i = s.label.row[q];
+      int low = L[i];
+      for (int64_t k = rows[i] + ln, e = rows[i + 1]; k < e; k += kWave) low = min(low, static_cast<int>(L[cols[k]]));
+      low = kUnvisited - wave_max(kUnvisited - low);
+      if (ln == 0) take(i, low);
+    }
+    more = __syncthreads_or(changed);
+  }
+  for (int i = tid; i < n; i += nt)
+    if (out(i)) L[i] = L[i] == i ? 0 : kUnvisited;
+  __syncthreads();
   return true;
 }
 
@@ -310,12 +391,20 @@ __device__ void graph_levels(LevelLds& s, int g, int64_t v0, int64_t n64, const 
                                            : static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key & 0xFFFFFFFF));
   if (tid == 0) L[root] = 0;  // a given root of degree 0 is level 0 already
   __syncthreads();
-  const int last = bfs_levels_lds(s, rows, cols, n);
+  const int64_t maxdeg = key >> 32;
+  auto search = [&]() { return maxdeg > kLongRow ? bfs_levels_lds<true>(s, rows, cols, n) : bfs_levels_lds<false>(s, rows, cols, n); };
+  const int last = search();
   // remaining components: together if they are few vertices, else one search
   // from the smallest unvisited id until they are; every id below the last
-  // such root is visited, so each scan starts there
+  // such root is visited, so each scan starts there.  Where the searches have
+  // taken about as long as labelling the rest does, one search levels it.
   int from = 0;
-  while (last < kLastLevel && !rest_levels_lds(s, rows, cols, n)) {
+  for (int searches = 1; last < kLastLevel && !rest_levels_lds(s, rows, cols, n, maxdeg > kRestRow); ++searches) {
+    if (searches >= kSearches && (searches & (searches - 1)) == 0 &&
+        label_lds(s, rows, cols, n, static_cast<int64_t>(searches) * kLabelEntries)) {
+      search();
+      break;
+    }
     int64_t cand = -1;  // max of (n - i) over unvisited i = smallest i
     for (int i = from + tid; i < n; i += nt)
       if (L[i] == kUnvisited) {
@@ -326,7 +415,7 @@ __device__ void graph_levels(LevelLds& s, int g, int64_t v0, int64_t n64, const 
     from = static_cast<int>(n - cand);
     if (tid == 0) L[from] = 0;
     __syncthreads();
-    bfs_levels_lds(s, rows, cols, n);
+    search();
   }
   __syncthreads();
   // outputs: parity bits (a wave's 64 vertices are two words), levels

@@ -37,6 +37,34 @@ REST = {
 }
 
 
+def _gap(g, n):
+    """g's ids spread over n, the last one on the last."""
+    at = (np.arange(g.n, dtype=np.int64) * (n - 1)) // max(g.n - 1, 1)
+    return graphgen.Graph(n, at[g.src].astype(np.int32), at[g.dst].astype(np.int32))
+
+
+# more components than are searched one by one, in all orders of ids
+MANY = {
+    "3072 edges": lambda: U([graphgen.path(2)] * 3072), "3080 edges": lambda: U([graphgen.path(2)] * 3080),
+    "32768 edges": lambda: U([graphgen.path(2)] * 32768),
+    "edges apart": lambda: _gap(U([graphgen.path(2)] * 9000), 65536),
+    "stars of 70": lambda: U([graphgen.star(70)] * 900), "wheels of 67": lambda: U([graphgen.wheel(67)] * 400),
+    "stars of 3000": lambda: U([graphgen.star(3000)] * 20),
+    "paths": lambda: U([graphgen.path(1 + i % 40) for i in range(3000)]),
+    "long paths": lambda: U([graphgen.path(900)] * 70),
+    "cliques": lambda: U([graphgen.complete(12)] * 1500), "dense": lambda: U([graphgen.complete(130)] * 60),
+    "sparse random": lambda: graphgen.erdos_renyi(60000, 1.0 / 60000, 3),
+    "a large one last": lambda: U([graphgen.path(3)] * 5000 + [graphgen.erdos_renyi(30000, 6.0 / 30000, 4)]),
+}
+
+
+@pytest.mark.parametrize("name", list(MANY))
+def test_many_components(name):
+    print(f"case: {name}", flush=True)
+    g = MANY[name]()
+    _check([g, _rev(g), graphgen.relabel(g, 11)])
+
+
 def _check(graphs):
     import paper_2210_00389_amd as tc
     want = []
@@ -128,3 +156,9 @@ def test_time_of_one_long_row():
     print("case: 64000 leaves of one hub and of 64", flush=True)
     one, many = _search_us(_tree(1, [64000]), 0), _search_us(_tree(64, [1000] * 64), 0)
     assert one < 1.5 * many, (one, many)
+
+
+def test_time_of_many_components():
+    print("case: 2000 and 20000 disjoint edges", flush=True)
+    few, many = _us(U([graphgen.path(2)] * 2000)), _us(U([graphgen.path(2)] * 20000))
+    assert many < 50 * few, (few, many)
