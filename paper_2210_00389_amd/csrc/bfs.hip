@@ -54,17 +54,19 @@ constexpr int kKeyBlocks = 1024;   // blocks of the first kernel at most (one ke
 constexpr int kFirstLevels = 6;
 constexpr int kNextLevels = 4;     // also the first group of the remaining components, usually shallow
 constexpr int kMaxLevels = 64;
-// Unreached vertices whose rows hold at most this many entries are levelled
+// Up to kRestNow unreached vertices of at most kRestEntries entries are levelled
 // by one block (R-MAT scale 16: a few dozen vertices in components of two and
-// three); beyond, the grid does it.
+// three).  With more vertices the grid finds the components and takes their
+// first levels, and one block goes on from there.  us, one block from the
+// start / so: 4000 disjoint edges 43 / 90, 10000 113 / 60, 30000 392 / 70; a
+// path of 20000 vertices 26000 either way, 110000 with a launch a level.
+constexpr int64_t kRestNow = 16384;
 constexpr int64_t kRestEntries = 65536;
 constexpr int kRestThreads = 1024;
-// There, rows above this length (fewer than kRestThreads of them) are expanded
-// by the whole block: with every row by a thread of its own, a star of 30000
-// leaves took 23.6 ms, 55 ms where the hub has the largest id, now 0.16 and
-// 0.20 ms.
+// There, rows above this length are expanded by the whole block: with every row
+// by a thread of its own, a star of 30000 leaves took 23.6 ms, 55 ms where the
+// hub has the largest id.
 constexpr int kRestRow = 64;
-static_assert(kRestEntries / (kRestRow + 1) < kRestThreads, "a thread per long row");
 
 // State before a level's step.
 struct BfsState {
@@ -81,6 +83,7 @@ struct BfsDev {
   unsigned long long acc[3][kSlots][2]; // per level: new vertices and their entries, at [k % 3]
   int32_t nbig[3];                      // rows listed for step k, at [k % 3]
   int32_t rest_n;                       // listed unreached vertices
+  int32_t rest_long;                    // a row of theirs is longer than kRestRow
   int64_t maxdeg;
   unsigned long long deg2;              // sum of squared degrees
 };
@@ -358,7 +361,7 @@ __global__ __launch_bounds__(kKeyBlocks) void start_kernel(const int64_t* off, i
   d->nbig[0] = dg > kBig;
   d->nbig[1] = d->nbig[2] = 0;
   if (dg > kBig) bigs[0] = static_cast<int32_t>(r);
-  d->rest_n = 0;
+  d->rest_n = d->rest_long = 0;
   d->maxdeg = static_cast<int64_t>(best >> 32);
   d->deg2 = d2;
   d->state[0] = BfsState{nnz - dg, goes_up(1, dg, nnz - dg, n), 0, 1, 0};
@@ -379,17 +382,21 @@ __global__ __launch_bounds__(kThreads) void unreached_kernel(const int64_t* off,
   const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (comp0)
     for (int64_t i = t0; i < words; i += stride) comp0[i] = vis[i];
-  for (int64_t v = t0; v < n; v += stride) {
-    if ((vis[v >> 5] >> (v & 31)) & 1u) continue;
-    if (st.unexplored == 0 || row_deg(off, v) == 0) {
-      L[v] = 0;
-    } else if (few) {
-      parent[v] = static_cast<int32_t>(v);
-      // each has an entry, so they are at most kRestEntries (more, from
-      // offsets that disagree with nnz, are left to the grid)
-      const int q = atomicAdd(&d->rest_n, 1);
-      if (q < kRestEntries) list[q] = static_cast<int32_t>(v);
-    }
+  for (int64_t v0 = t0 - lane(); v0 < n; v0 += stride) {  // the whole wave takes part
+    const int64_t v = v0 + lane();
+    const bool out = v < n && !((vis[v >> 5] >> (v & 31)) & 1u);
+    const bool lone = out && (st.unexplored == 0 || row_deg(off, v) == 0);
+    if (lone) L[v] = 0;
+    const bool take = few && out && !lone;
+    const uint64_t m = __ballot(take);
+    if (m == 0) continue;  // uniform
+    // one addition a wave; past kRestNow they are left to the grid
+    int at = 0;
+    if (lane() == 0) at = atomicAdd(&d->rest_n, __popcll(m));
+    const int q = wave_read(at, 0) + __popcll(m & lanemask_lt());
+    if (!take) continue;
+    parent[v] = static_cast<int32_t>(v);
+    if (q < kRestNow) list[q] = static_cast<int32_t>(v);
   }
 }
 
@@ -421,26 +428,29 @@ __device__ __forceinline__ void uf_union(int32_t* parent, int32_t a, int32_t b) 
   }
 }
 
+template <int THREADS>
 struct RestLds {
   int len[2], nlong;
-  int32_t row[kRestThreads];  // rows longer than kRestRow
-  int pre[kRestThreads];      // entries of those before
-  int sh[kRestThreads / kWave + 1];
+  int32_t row[THREADS];  // rows longer than kRestRow
+  int64_t pre[THREADS];  // entries of those before
+  int64_t sh[THREADS / kWave + 1];
 };
 
-// f(v, w) for every entry w of the rows of v[0 .. m).  All threads.
-template <class F>
-__device__ __forceinline__ void each_entry(RestLds& s, const int64_t* off, const int32_t* cols, const int32_t* v, int m,
-                                           F f) {
+// f(v, w) for every entry w of the rows of v = vertex(i), 0 <= i < m (negative:
+// none; !kLong: no row is longer than kRestRow).  All threads of the block; the
+// caller has cleared s.nlong and synchronised it, and it is synchronised on
+// return.
+template <int THREADS, bool kLong, class V, class F>
+__device__ __forceinline__ void each_entry(RestLds<THREADS>& s, const int64_t* off, const int32_t* cols, int m,
+                                           V vertex, F f) {
   const int tid = threadIdx.x;
-  if (tid == 0) s.nlong = 0;
-  __syncthreads();
-  for (int i = tid; i < m; i += kRestThreads) {
-    const int32_t x = v[i];
+  for (int i = tid; i < m; i += THREADS) {
+    const int32_t x = vertex(i);
+    if (x < 0) continue;
     const int64_t b = off[x], e = off[x + 1];
-    if (e - b > kRestRow) {
+    if (kLong && e - b > kRestRow) {
       const int q = atomicAdd(&s.nlong, 1);
-      if (q < kRestThreads) {
+      if (q < THREADS) {
         s.row[q] = x;
         continue;
       }
@@ -448,13 +458,12 @@ __device__ __forceinline__ void each_entry(RestLds& s, const int64_t* off, const
     for (int64_t j = b; j < e; ++j) f(x, cols[j]);
   }
   __syncthreads();
-  const int nl = min(s.nlong, kRestThreads);
+  const int nl = kLong ? min(s.nlong, THREADS) : 0;
   if (nl == 0) return;  // uniform
-  const int mine = tid < nl ? static_cast<int>(row_deg(off, s.row[tid])) : 0;
-  int total;
-  s.pre[tid] = block_excl_scan(mine, s.sh, &total);
+  int64_t total;
+  s.pre[tid] = block_excl_scan(tid < nl ? row_deg(off, s.row[tid]) : int64_t(0), s.sh, &total);
   __syncthreads();
-  for (int i = tid; i < total; i += kRestThreads) {
+  for (int64_t i = tid; i < total; i += THREADS) {
     int lo = 0, hi = nl;  // last row with pre <= i
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -467,48 +476,89 @@ __device__ __forceinline__ void each_entry(RestLds& s, const int64_t* off, const
   __syncthreads();
 }
 
+// The levels after `level`, whose s.len[0] vertices are in the first queue (two
+// of kRestEntries vertices; a vertex is claimed once), by one block that has
+// cleared s.len[1] and s.nlong.  Returns the level count.
+template <bool kLong>
+__device__ __forceinline__ int finish_levels(RestLds<kRestThreads>& s, const int64_t* off, const int32_t* cols,
+                                             int32_t* L, int32_t* queues, int level) {
+  int at = 0;
+  for (int len = min(s.len[0], static_cast<int>(kRestEntries)); len > 0; at ^= 1) {
+    const int32_t* cur = queues + at * kRestEntries;
+    int32_t* nxt = queues + (at ^ 1) * kRestEntries;
+    int* n = &s.len[at ^ 1];
+    ++level;
+    each_entry<kRestThreads, kLong>(s, off, cols, len, [&](int i) { return cur[i]; }, [&](int32_t, int32_t w) {
+      if (load_relaxed(&L[w]) < 0 && atomicCAS(&L[w], -1, level) == -1) {
+        const int q = atomicAdd(n, 1);
+        if (q < kRestEntries) nxt[q] = w;
+      }
+    });
+    len = min(*n, static_cast<int>(kRestEntries));
+    if (threadIdx.x == 0) s.len[at] = s.nlong = 0;  // the queue just read
+    __syncthreads();
+  }
+  return level;
+}
+
 // Levels the listed vertices (one block), and writes the state for the host.
 // A neighbour without a level is itself listed.
 __global__ __launch_bounds__(kRestThreads) void rest_kernel(const int64_t* off, const int32_t* cols, int64_t n, int k,
                                                             BfsDev* d, int32_t* L, int32_t* parent,
                                                             int32_t* list, BfsHost* out) {
-  __shared__ RestLds s;
+  __shared__ RestLds<kRestThreads> s;
   const BfsState st = state_of(d, k, n);
   const int m = d->rest_n;
   int levels = 0;
-  if (st.done && (st.unexplored > kRestEntries || m > kRestEntries)) {
+  if (st.done && (st.unexplored > kRestEntries || m > kRestNow)) {
     levels = -1;
   } else if (st.done && st.unexplored > 0) {
-    each_entry(s, off, cols, list, m, [&](int32_t v, int32_t w) {
+    if (threadIdx.x == 0) s.len[0] = s.len[1] = s.nlong = 0;
+    __syncthreads();
+    each_entry<kRestThreads, true>(s, off, cols, m, [&](int i) { return list[i]; }, [&](int32_t v, int32_t w) {
       if (w < v && L[w] < 0) uf_union(parent, v, w);
     });
-    // the frontiers are two queues behind the list; a vertex is claimed once
-    int32_t* queue[2] = {list + kRestEntries, list + 2 * kRestEntries};
-    if (threadIdx.x < 2) s.len[threadIdx.x] = 0;
-    __syncthreads();
+    const bool lng = s.nlong > 0;
+    int32_t* queues = list + kRestEntries;
     for (int i = threadIdx.x; i < m; i += kRestThreads) {
       const int32_t v = list[i];
       if (uf_find(parent, v) != v) continue;
       L[v] = 0;
-      queue[0][atomicAdd(&s.len[0], 1)] = v;
+      queues[atomicAdd(&s.len[0], 1)] = v;
     }
     __syncthreads();
-    for (int len = s.len[0]; len > 0;) {
-      const int32_t* cur = queue[levels & 1];
-      int32_t* nxt = queue[(levels + 1) & 1];
-      int* at = &s.len[(levels + 1) & 1];
-      ++levels;
-      each_entry(s, off, cols, cur, len, [&](int32_t, int32_t w) {
-        if (load_relaxed(&L[w]) < 0 && atomicCAS(&L[w], -1, levels) == -1) nxt[atomicAdd(at, 1)] = w;
-      });
-      __syncthreads();
-      len = *at;
-      if (threadIdx.x == 0) s.len[(levels + 1) & 1] = 0;  // the queue just read
-      __syncthreads();
-    }
+    if (threadIdx.x == 0) s.nlong = 0;
+    __syncthreads();
+    levels = lng ? finish_levels<true>(s, off, cols, L, queues, 0) : finish_levels<false>(s, off, cols, L, queues, 0);
   }
   if (threadIdx.x == 0)
     *out = BfsHost{st.unexplored, d->maxdeg, d->deg2, st.done, st.num_levels, levels, 0};
+}
+
+// The rest of the levels of the remaining components after their step k - 1,
+// in one block (their rows are at most kRestEntries entries), and the state
+// for the host.
+__global__ __launch_bounds__(kRestThreads) void rest_tail_kernel(const int64_t* off, const int32_t* cols, int64_t n,
+                                                                 int k, const BfsDev* d, int32_t* L,
+                                                                 const uint32_t* bms, int32_t* queues, BfsHost* out) {
+  __shared__ RestLds<kRestThreads> s;
+  const BfsState st = state_of(d, k, n);
+  int levels = st.num_levels;
+  if (!st.done) {
+    const int64_t words = (n + 31) / 32 + 1;
+    const uint32_t* cur = bms + static_cast<int64_t>(k % 3) * words;
+    if (threadIdx.x == 0) s.len[0] = s.len[1] = s.nlong = 0;
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < words; i += kRestThreads)
+      for (uint32_t b = cur[i]; b; b &= b - 1) {
+        const int q = atomicAdd(&s.len[0], 1);
+        if (q < kRestEntries) queues[q] = static_cast<int32_t>(32 * i + __ffs(static_cast<int>(b)) - 1);
+      }
+    __syncthreads();
+    levels = d->rest_long ? finish_levels<true>(s, off, cols, L, queues, k)
+                          : finish_levels<false>(s, off, cols, L, queues, k);
+  }
+  if (threadIdx.x == 0) *out = BfsHost{0, d->maxdeg, d->deg2, 1, levels, 0, 0};
 }
 
 __global__ void uf_init_kernel(int32_t* parent, int64_t n) {
@@ -517,15 +567,22 @@ __global__ void uf_init_kernel(int32_t* parent, int64_t n) {
     parent[v] = static_cast<int32_t>(v);
 }
 
-__global__ void uf_hook_kernel(const int64_t* off, const int32_t* cols, int64_t n,
-                               const uint32_t* vis, int32_t* parent) {
-  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
-       v += (int64_t)gridDim.x * blockDim.x) {
-    if (vis[v >> 5] & (1u << (v & 31))) continue;
-    for (int64_t j = off[v], e = off[v + 1]; j < e; ++j) {
-      int32_t w = cols[j];
-      if (w < v) uf_union(parent, static_cast<int32_t>(v), w);
-    }
+__global__ __launch_bounds__(kThreads) void uf_hook_kernel(const int64_t* off, const int32_t* cols, int64_t n,
+                                                           const uint32_t* vis, int32_t* parent, BfsDev* d) {
+  __shared__ RestLds<kThreads> s;
+  for (int64_t v0 = blockIdx.x * (int64_t)kThreads; v0 < n; v0 += (int64_t)gridDim.x * kThreads) {
+    if (threadIdx.x == 0) s.nlong = 0;
+    __syncthreads();
+    each_entry<kThreads, true>(
+        s, off, cols, kThreads,
+        [&](int i) {
+          const int64_t v = v0 + i;
+          return v < n && !((vis[v >> 5] >> (v & 31)) & 1u) ? static_cast<int32_t>(v) : -1;
+        },
+        [&](int32_t v, int32_t w) {
+          if (w < v) uf_union(parent, v, w);
+        });
+    if (threadIdx.x == 0 && s.nlong > 0) d->rest_long = 1;
   }
 }
 
@@ -594,7 +651,7 @@ BfsWs bfs_reserve(Carver& c, int64_t n) {
   w.bms = c.take<uint32_t>(3 * words);
   w.big = c.take<int32_t>(2 * kBigCap);
   w.parent = c.take<int32_t>(n + 1);
-  w.list = c.take<int32_t>(3 * kRestEntries);  // and two queues
+  w.list = c.take<int32_t>(3 * kRestEntries);  // and two queues (the list itself holds up to kRestNow)
   w.keys = c.take<unsigned long long>(2 * kKeyBlocks);
   w.st = c.take<char>(sizeof(BfsDev));
   w.host = c.take<char>(sizeof(BfsHost));
@@ -688,7 +745,7 @@ int bfs_run(const tc_csr* g, int64_t root, int32_t* L, BfsWs& w, hipStream_t s, 
   // smallest id as root.
   const int64_t rest = h.unexplored;
   uf_init_kernel<<<grid_for(n, kThreads, 65536), kThreads, 0, s>>>(w.parent, n);
-  uf_hook_kernel<<<grid_for(n, kThreads, 65536), kThreads, 0, s>>>(g->row_offsets, g->cols, n, w.vis, w.parent);
+  uf_hook_kernel<<<grid_for(n, kThreads, 65536), kThreads, 0, s>>>(g->row_offsets, g->cols, n, w.vis, w.parent, d);
   TC_TRY(fill_i32(reinterpret_cast<int32_t*>(w.bms), 0, 3 * words, s));
   rest_clear_kernel<<<1, 3 * kSlots * 2, 0, s>>>(d);
   uf_roots_kernel<<<step_grid(n), kThreads, 0, s>>>(g->row_offsets, n, w.parent, L, w.vis, w.bms, w.big, d);
@@ -698,7 +755,10 @@ int bfs_run(const tc_csr* g, int64_t root, int32_t* L, BfsWs& w, hipStream_t s, 
   for (int group = kNextLevels;; group = std::min(2 * group, kMaxLevels)) {
     TC_TRY(launch_steps(g, L, w, k, group, s));
     k += group;
-    rest_state_kernel<<<1, kWave, 0, s>>>(n, k, d, state_target(w));
+    if (rest <= kRestEntries)
+      rest_tail_kernel<<<1, kRestThreads, 0, s>>>(g->row_offsets, g->cols, n, k, d, L, w.bms, w.list, state_target(w));
+    else
+      rest_state_kernel<<<1, kWave, 0, s>>>(n, k, d, state_target(w));
     TC_HIP(hipGetLastError());
     TC_TRY(read_state(w, &h, s));
     if (h.done) break;

@@ -117,3 +117,24 @@ def test_time_of_a_star_beside_a_component(hub_last):
     print(f"case: stars of 60 and 30000 leaves, hub last {hub_last}", flush=True)
     few, many = ms(60), ms(30000)
     assert many < 10 * few, (few, many)
+
+
+@pytest.mark.parametrize("pairs", [8191, 8192, 8193, 20000, 32768, 32769])
+@pytest.mark.parametrize("tail", [0, 3, 4, 5, 6, 300])
+def test_remainders_around_their_bounds(pairs, tail):
+    """A clique, disjoint edges, and a path on the last ids, with at most `pairs` edges in all beside the clique."""
+    import paper_2210_00389_amd as tc
+    print(f"case: {pairs} edges, {tail} of them a path", flush=True)
+    k, e = 30, pairs - tail
+    i = torch.arange(k, device="cuda")
+    a = k + 2 * torch.arange(e, device="cuda")
+    p = k + 2 * e + torch.arange(tail, device="cuda")
+    n = k + 2 * e + (tail + 1 if tail else 0)
+    G = tc.build_csr(n, torch.cat([i.repeat_interleave(k), a, p]).to(torch.int32),
+                     torch.cat([i.repeat(k), a + 1, p + 1]).to(torch.int32))
+    want = torch.ones(n, dtype=torch.int32, device="cuda")
+    want[0], want[a] = 0, 0
+    if tail:
+        want[p[0]:] = torch.arange(tail + 1, device="cuda", dtype=torch.int32)
+    lev, num = tc.bfs_levels(G, root=0)
+    assert num == max(2, tail + 1) and torch.equal(lev, want)
