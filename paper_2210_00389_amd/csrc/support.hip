@@ -30,11 +30,12 @@ constexpr int kProbes = 4;      // slots an edge may take
 // of up to a tenth of the entries add to both orientations, since the mirror
 // pass over all entries takes longer than their second searches.  us, all
 // lists with the mirror pass and shares of kTri / so: 1 triangle on
-// G(1000003, d 16) 618 / 28; R-MAT scale 20, 31.4 M entries, 4096 triangles
-// 1885 / 54, 0.49 M 1904 / 206, 2.0 M 2047 / 533, in random order 1903 / 54,
-// 1977 / 495, 2702 / 1955.  With 3.9 M, an eighth, adding to both takes 1169
-// against 2322, but in random order 4067 against 3689.
-constexpr int64_t kFew = 4096, kMirrorRatio = 10;
+// G(1000003, d 16) 612 / 28; R-MAT scale 20, 31.4 M entries, 65536 triangles
+// 1911 / 77 (122 with the table), 131072 1907 / 92 (118), 0.49 M 1945 / 209, 2.0
+// M 2061 / 540, in random order 1928 / 77, 1930 / 138, 1988 / 521, 2694 / 2010.
+// With 3.9 M, an eighth, adding to both takes 1169 against 2322, but in random
+// order 4067 against 3689.
+constexpr int64_t kFew = 131072, kMirrorRatio = 10;
 constexpr unsigned long long kFree = ~0ull;
 
 __device__ __forceinline__ void order2(int32_t& x, int32_t& y) {
@@ -125,8 +126,17 @@ __global__ __launch_bounds__(kThreads) void support_kernel(const int64_t* off, c
       order2(b, c);
       order2(a, b);
       if (plain || x < 0) {  // uniform
-        const int32_t u[3] = {a, a, b}, v[3] = {b, c, c}, one[3] = {1, 1, 1};
-        add_edges<kBoth, 3>(off, cols, u, v, one, sup);
+        const int32_t u[3] = {a, a, b}, v[3] = {b, c, c};
+        int32_t some[3] = {1, 1, 1};
+        if (plain) {  // an edge that all triangles of the wave have is added once
+          const uint64_t in = __ballot(true);
+          const int first = __ffsll(static_cast<unsigned long long>(in)) - 1;
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            if (__ballot(u[q] == wave_read(u[q], first) && v[q] == wave_read(v[q], first)) == in)
+              some[q] = lane() == first ? __popcll(in) : 0;
+        }
+        add_edges<kBoth, 3>(off, cols, u, v, some, sup);
         continue;
       }
       uint32_t left = 7u;  // edges not kept

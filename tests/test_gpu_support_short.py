@@ -14,6 +14,8 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
+A, B = 129998, 129999  # the edge of many triangles
+
 
 def _want(c, tri):
     n = c.n
@@ -32,26 +34,27 @@ def _want(c, tri):
 
 @pytest.fixture(scope="module")
 def graph():
-    g = graphgen.rmat(14, 16, seed=3)
+    g = graphgen.rmat(16, 16, seed=3)
     r = np.arange(60000)  # two more vertices share 60000 triangles with as many others
-    g = graphgen.Graph(80000, np.concatenate([g.src, [79998], 0 * r + 79998, 0 * r + 79999]).astype(np.int32),
-                       np.concatenate([g.dst, [79999], r + 16384, r + 16384]).astype(np.int32))
+    g = graphgen.Graph(130000, np.concatenate([g.src, [A], 0 * r + A, 0 * r + B]).astype(np.int32),
+                       np.concatenate([g.dst, [B], r + 65536, r + 65536]).astype(np.int32))
     c = oracle.from_graph(g)
     tri = np.asarray(oracle.list_triangles(c, oracle.bfs_levels(c).levels), dtype=np.int64).reshape(-1, 3)
     return c, tri
 
 
 @pytest.mark.parametrize("form", ["runs", "any order", "random", "one edge"])
-@pytest.mark.parametrize("count", [1, 255, 256, 257, 4095, 4096, 4097, 20000, "tenth", "tenth + 1", 300000])
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 255, 256, 257, 20000, 131071, 131072, 131073, 150000, "tenth", "tenth + 1",
+                                   300000])
 def test_short_lists(graph, form, count):
     import paper_2210_00389_amd as tc
     c, tri = graph
     tenth = len(c.cols) // 10
-    assert 20000 < tenth < 300000
+    assert 150000 < tenth < 300000
     k = {"tenth": tenth, "tenth + 1": tenth + 1}.get(count, count)
     rng = np.random.RandomState(k)
     if form == "one edge":
-        t = np.stack([np.full(k, 79998), 16384 + np.arange(k) % 60000, np.full(k, 79999)], axis=1)
+        t = np.stack([np.full(k, A), 65536 + np.arange(k) % 60000, np.full(k, B)], axis=1)
     elif form == "random":
         t = rng.randint(0, c.n, (k, 3))
     else:
