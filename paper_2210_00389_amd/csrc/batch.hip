@@ -75,7 +75,7 @@ __device__ __forceinline__ int64_t block_max_i64(int64_t v, int64_t* sh) {
 // LDS of a level block.  L is the level array; the rest beside it serves the
 // frontier of a top-down level and, at other times, the unreached vertices.
 struct LevelLds {
-  uint16_t L[TC_BATCH_MAX_N];
+  alignas(4) uint16_t L[TC_BATCH_MAX_N];
   union {
     struct {
       uint16_t all[kFrontCap];
@@ -135,12 +135,17 @@ __device__ int bfs_levels_lds(LevelLds& s, const int64_t* rows, const int32_t* c
     };
     if (!bottom_up) {
       // the frontier is listed; with the same level of components searched
-      // before it may not fit (an unvisited vertex has no neighbour there)
-      for (int i = tid; i < n; i += nt)
-        if (L[i] == cur) {
-          const int q = atomicAdd(&s.num, 1);
-          if (q < kFrontCap) s.front.all[q] = static_cast<uint16_t>(i);
-        }
+      // before it may not fit (an unvisited vertex has no neighbour there).
+      // Two levels are read at once: a grid of 100 x 100 443 us one by one, 404 so
+      auto list = [&](int i) {
+        const int q = atomicAdd(&s.num, 1);
+        if (q < kFrontCap) s.front.all[q] = static_cast<uint16_t>(i);
+      };
+      for (int i = 2 * tid; i < n; i += 2 * nt) {
+        const uint32_t w = *reinterpret_cast<const uint32_t*>(L + i);
+        if ((w & 0xFFFF) == cur) list(i);
+        if (w >> 16 == cur && i + 1 < n) list(i + 1);
+      }
       __syncthreads();
       bottom_up = s.num > kFrontCap;
     }
