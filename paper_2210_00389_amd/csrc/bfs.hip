@@ -437,7 +437,10 @@ struct RestLds {
 };
 
 // f(v, w) for every entry w of the rows of v = vertex(i), 0 <= i < m (negative:
-// none; !kLong: no row is longer than kRestRow).  All threads of the block; the
+// none; !kLong: no row is longer than kRestRow), twice for the first of a long
+// row: before the block shares it, so that the threads joining its entries find
+// its vertex in a tree by then (a clique of 2000 beside a star of 200000 leaves:
+// 1.34 ms without that and the look at the parents in uf_hook_kernel, 0.78 so).  All threads of the block; the
 // caller has cleared s.nlong and synchronised it, and it is synchronised on
 // return.
 template <int THREADS, bool kLong, class V, class F>
@@ -452,6 +455,7 @@ __device__ __forceinline__ void each_entry(RestLds<THREADS>& s, const int64_t* o
       const int q = atomicAdd(&s.nlong, 1);
       if (q < THREADS) {
         s.row[q] = x;
+        f(x, cols[b]);
         continue;
       }
     }
@@ -567,20 +571,30 @@ __global__ void uf_init_kernel(int32_t* parent, int64_t n) {
     parent[v] = static_cast<int32_t>(v);
 }
 
+// Vertices a block takes at a time (at most kThreads): fewer where the vertices
+// are, as a block shares its long rows among its threads only.  With kThreads a
+// clique of 600 vertices was three blocks' work: 1.09 ms for the search beside
+// one of 700, 0.30 so (524033 vertices and more: kThreads either way).
+__host__ __device__ inline int hook_chunk(int64_t n) {
+  const int64_t c = (n + 2047) / 2048;
+  return c < 8 ? 8 : c < kThreads ? static_cast<int>(c) : kThreads;
+}
+
 __global__ __launch_bounds__(kThreads) void uf_hook_kernel(const int64_t* off, const int32_t* cols, int64_t n,
                                                            const uint32_t* vis, int32_t* parent, BfsDev* d) {
   __shared__ RestLds<kThreads> s;
-  for (int64_t v0 = blockIdx.x * (int64_t)kThreads; v0 < n; v0 += (int64_t)gridDim.x * kThreads) {
+  const int chunk = hook_chunk(n);
+  for (int64_t v0 = blockIdx.x * (int64_t)chunk; v0 < n; v0 += (int64_t)gridDim.x * chunk) {
     if (threadIdx.x == 0) s.nlong = 0;
     __syncthreads();
     each_entry<kThreads, true>(
-        s, off, cols, kThreads,
+        s, off, cols, chunk,
         [&](int i) {
           const int64_t v = v0 + i;
           return v < n && !((vis[v >> 5] >> (v & 31)) & 1u) ? static_cast<int32_t>(v) : -1;
         },
         [&](int32_t v, int32_t w) {
-          if (w < v) uf_union(parent, v, w);
+          if (w < v && load_relaxed(&parent[w]) != load_relaxed(&parent[v])) uf_union(parent, v, w);
         });
     if (threadIdx.x == 0 && s.nlong > 0) d->rest_long = 1;
   }
@@ -745,7 +759,7 @@ int bfs_run(const tc_csr* g, int64_t root, int32_t* L, BfsWs& w, hipStream_t s, 
   // smallest id as root.
   const int64_t rest = h.unexplored;
   uf_init_kernel<<<grid_for(n, kThreads, 65536), kThreads, 0, s>>>(w.parent, n);
-  uf_hook_kernel<<<grid_for(n, kThreads, 65536), kThreads, 0, s>>>(g->row_offsets, g->cols, n, w.vis, w.parent, d);
+  uf_hook_kernel<<<grid_for(n, hook_chunk(n), 65536), kThreads, 0, s>>>(g->row_offsets, g->cols, n, w.vis, w.parent, d);
   TC_TRY(fill_i32(reinterpret_cast<int32_t*>(w.bms), 0, 3 * words, s));
   rest_clear_kernel<<<1, 3 * kSlots * 2, 0, s>>>(d);
   uf_roots_kernel<<<step_grid(n), kThreads, 0, s>>>(g->row_offsets, n, w.parent, L, w.vis, w.bms, w.big, d);

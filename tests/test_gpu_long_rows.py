@@ -138,3 +138,48 @@ def test_remainders_around_their_bounds(pairs, tail):
         want[p[0]:] = torch.arange(tail + 1, device="cuda", dtype=torch.int32)
     lev, num = tc.bfs_levels(G, root=0)
     assert num == max(2, tail + 1) and torch.equal(lev, want)
+
+
+def _cliques(sizes):
+    """Cliques on consecutive ids: each has its first vertex at level 0, the others at 1."""
+    import paper_2210_00389_amd as tc
+    size = torch.tensor(sizes, device="cuda")
+    first = size.cumsum(0) - size
+    i = torch.arange(int(size.sum()), device="cuda")
+    own, lo = size.repeat_interleave(size), first.repeat_interleave(size)
+    s = i.repeat_interleave(own)
+    d = torch.arange(s.numel(), device="cuda") - (own.cumsum(0) - own).repeat_interleave(own) + lo.repeat_interleave(own)
+    want = torch.ones(i.numel(), dtype=torch.int32, device="cuda")
+    want[first] = 0
+    return tc.build_csr(i.numel(), s.to(torch.int32), d.to(torch.int32)), want
+
+
+@pytest.mark.parametrize("sizes", [[700, 600], [300, 257, 256, 255, 66, 65, 64, 9, 8, 7, 2], [2000, 1999],
+                                   [400] + [120] * 200, [200] + [66] * 9000])
+def test_dense_remainders(sizes):
+    import paper_2210_00389_amd as tc
+    print(f"case: cliques of {sizes[:12]} ({len(sizes)})", flush=True)
+    G, want = _cliques(sizes)
+    lev, num = tc.bfs_levels(G, root=0)
+    assert num == 2 and torch.equal(lev, want)
+
+
+def test_time_of_a_dense_remainder():
+    import paper_2210_00389_amd as tc
+
+    def ms(k):
+        G, _ = _cliques([700, k])
+        tc.bfs_levels(G, root=0)
+        t = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            tc.bfs_levels(G, root=0)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return statistics.median(t)
+
+    print("case: cliques of 60 and 600 beside one of 700", flush=True)
+    few, many = ms(60), ms(600)
+    assert many < 6 * few, (few, many)
