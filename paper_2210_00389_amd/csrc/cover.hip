@@ -59,8 +59,8 @@ __global__ __launch_bounds__(kThreads) void cover_prep_kernel(const int64_t* off
     lev8[v] = static_cast<uint8_t>(l);
     w |= l < 0 || l > 255;
     const int64_t b = off[v], e = off[v + 1];
-    for (int64_t t = v == 0 ? 0 : (b + kTile - 1) / kTile; t < tiles && t * kTile < e; ++t)
-      tile_row[t] = static_cast<int32_t>(v);
+    const int64_t t1 = min(tiles, (e + kTile - 1) / kTile);
+    for (int64_t t = v == 0 ? 0 : (b + kTile - 1) / kTile; t < t1; ++t) tile_row[t] = static_cast<int32_t>(v);
   }
   w = __syncthreads_or(w);
   if (threadIdx.x == 0) wide[blockIdx.x] = w;
