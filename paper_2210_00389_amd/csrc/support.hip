@@ -27,15 +27,16 @@ constexpr int kTri = 2048;      // consecutive triangles of a block at most
 constexpr int kTable = 2048;    // edges summed in LDS (24 KB)
 constexpr int kProbes = 4;      // slots an edge may take
 // Lists of up to kFew triangles are added one by one, without the table; lists
-// of up to a tenth of the entries add to both orientations, since the mirror
+// of up to a fifth of the entries add to both orientations, since the mirror
 // pass over all entries takes longer than their second searches.  us, all
 // lists with the mirror pass and shares of kTri / so: 1 triangle on
 // G(1000003, d 16) 612 / 28; R-MAT scale 20, 31.4 M entries, 65536 triangles
 // 1911 / 77 (122 with the table), 131072 1907 / 92 (118), 0.49 M 1945 / 209, 2.0
-// M 2061 / 540, in random order 1928 / 77, 1930 / 138, 1988 / 521, 2694 / 2010.
-// With 3.9 M, an eighth, adding to both takes 1169 against 2322, but in random
-// order 4067 against 3689.
-constexpr int64_t kFew = 131072, kMirrorRatio = 10;
+// M 2061 / 540.  Near the line a list as it is written gains what one in random
+// order loses (mirror pass / both): at an eighth of the entries 2319 / 1163 and
+// 3619 / 4123, a fifth 2521 / 1658 and 4775 / 6718, a quarter 2596 / 1975 and
+// 5612 / 8477; a wheel of 10^6 vertices at a quarter 191 / 123 and 322 / 357.
+constexpr int64_t kFew = 131072, kMirrorRatio = 5;
 constexpr unsigned long long kFree = ~0ull;
 
 __device__ __forceinline__ void order2(int32_t& x, int32_t& y) {

@@ -44,14 +44,14 @@ def graph():
 
 
 @pytest.mark.parametrize("form", ["runs", "any order", "random", "one edge"])
-@pytest.mark.parametrize("count", [1, 63, 64, 65, 255, 256, 257, 20000, 131071, 131072, 131073, 150000, "tenth", "tenth + 1",
-                                   300000])
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 255, 256, 257, 20000, 131071, 131072, 131073, 150000, 300000, "fifth",
+                                   "fifth + 1", 500000])
 def test_short_lists(graph, form, count):
     import paper_2210_00389_amd as tc
     c, tri = graph
-    tenth = len(c.cols) // 10
-    assert 150000 < tenth < 300000
-    k = {"tenth": tenth, "tenth + 1": tenth + 1}.get(count, count)
+    fifth = len(c.cols) // 5
+    assert 300000 < fifth < 500000
+    k = {"fifth": fifth, "fifth + 1": fifth + 1}.get(count, count)
     rng = np.random.RandomState(k)
     if form == "one edge":
         t = np.stack([np.full(k, A), 65536 + np.arange(k) % 60000, np.full(k, B)], axis=1)
@@ -88,3 +88,26 @@ def test_time_of_a_short_list():
     print("case: 100 triples on 160 thousand and on 16 million entries", flush=True)
     small, large = us(10007), us(1000003)
     assert large < 5 * small, (small, large)
+
+
+def test_time_of_a_list_of_a_seventh_of_the_entries():
+    import paper_2210_00389_amd as tc
+    g = graphgen.rmat(18, 16, seed=1)
+    G = tc.from_host_pairs(g.n, g.src, g.dst)
+    tri = tc.list_triangles(G).tri
+
+    def us(k):
+        tc.edge_support(G, tri[:k])
+        t = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            tc.edge_support(G, tri[:k])
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) * 1e3)
+        return statistics.median(t)
+
+    print("case: a seventh and a quarter of the entries as triangles", flush=True)
+    short, long = us(G.nnz // 7), us(G.nnz // 4)
+    assert short < 0.75 * long, (short, long)
