@@ -359,10 +359,11 @@ int tc_count_batch(const tc_batch* b, const tc_tuning* tuning, uint32_t flags,
  * tc_count_batch takes from `ws` lives instead in a static device array of
  * tc_noalloc_scratch_bytes() bytes (32 MiB) that each GPU holds until the
  * process ends.  The call allocates and frees nothing.
- *   - A batch needing more scratch than that (a bit per vertex and 8 bytes
- *     per 512 entries; tc_count_batch's 8-byte records per vertex are used
- *     only where they fit as well) gives TC_ERR_TOO_LARGE before any device
- *     work; about 1.3 G entries in total fit.
+ *   - A batch needing more scratch than that (a bit per vertex, 12 bytes per
+ *     graph and 8 bytes per 1024 entries, per fewer in a batch below 2 M;
+ *     tc_count_batch's 8-byte records per vertex are used only where they fit
+ *     as well) gives TC_ERR_TOO_LARGE before any device work: entries and 16
+ *     times the vertices may come to about 4.2 G.
  *   - TC_VALIDATE is not supported (TC_ERR_INVALID_ARG): check a batch with
  *     tc_count_batch first.
  *   - Every call on one GPU shares that GPU's array: calls that overlap on

@@ -1,14 +1,18 @@
-// batch.hip -- tc_count_batch: Alg. 1 on many small graphs (n <= 65536 each)
-// in three kernels that issue no host synchronisation and no memset, so a
-// caller can capture the whole call in one hipGraph.
+// batch.hip -- tc_count_batch: levels, |H| and T of many small graphs (n <=
+// 65536 each) in three kernels that issue no host synchronisation and no
+// memset, so a caller can capture the whole call in one hipGraph.  The levels
+// and |H| are those of Alg. 1; T is summed by edges over forward lists, which
+// reads less here than Alg. 1's horizontal edges do.
 //
 // The level kernel (one block per graph): BFS levels of Alg. 1 with the level array
 // resident in LDS as uint16 (128 KB for 65536 vertices).  The first root is
-// the highest-degree vertex (smallest id on ties); every other component is
-// then searched from its smallest unvisited id, as in the scan order of
-// Alg. 1, and isolated vertices get level 0.  Each level is one pass over the
-// vertices: top-down from the listed frontier (16 lanes a row, longer rows a
-// wave or more) or, when the last level was large, bottom-up.
+// the highest-degree vertex (smallest id on ties); the root of every other
+// component is its smallest id, as in the scan order of Alg. 1, and isolated
+// vertices get level 0.  The other components are levelled together where they
+// are few vertices, else one after another, and after a few of those together
+// again, from labels of all of them.  Each level of a search is one pass over
+// the vertices: top-down from the listed frontier (16 lanes a row, longer rows
+// a wave or more) or, when the last level was large, bottom-up.
 // The block writes the level parity as a bit array (Lemma 1: for adjacent
 // vertices L(x) = L(y) iff their parities agree, so the parity is all that
 // |H| needs) and the optional int32 levels.

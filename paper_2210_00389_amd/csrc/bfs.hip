@@ -17,13 +17,14 @@
 //     first hit; a wave composes its 64 vertices' bits with ballots;
 //   * after a group of levels two kernels, which do nothing unless the search
 //     has ended, level the isolated vertices and list the other unreached
-//     ones, and level those in one block if they are few; the state goes to
-//     the host once per group, usually once in all;
+//     ones, and level those in one block if they are few vertices of few
+//     entries; the state goes to the host once per group, usually once in all;
 //   * otherwise the remaining components: union-find over the unreached vertices where
 //     a root is always hooked under the smaller root, so every component's
 //     final root is its smallest id; those roots then start one multi-source
 //     BFS (components are disjoint, so the per-component distances are
-//     exactly those of separate BFS runs).
+//     exactly those of separate BFS runs), whose levels after the first group
+//     are one block's where all its entries are few.
 #include "tc_internal.h"
 
 namespace tc {

@@ -59,8 +59,9 @@ int tc_count_batch_noalloc(const tc_batch* b, const tc_tuning* tuning, uint32_t 
   if (flags & TC_VALIDATE)
     return tc::fail(TC_ERR_INVALID_ARG,
                     "tc_count_batch_noalloc: TC_VALIDATE is not supported (check the batch with tc_count_batch)");
-  // a batch takes the forward records where they fit; the rest (parity bits,
-  // piece slots) is at most a bit per vertex and a byte per 64 entries
+  // a batch takes the forward records where they fit; the rest is parity bits, a
+  // bit per vertex, and piece slots, 8 bytes per piece of the default size, at
+  // most 1024 entries (a 2048th of all entries where that is less, 16 at least)
   const bool with_rec = tc::batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs, true) <= kScratchBytes;
   const size_t need = tc::batch_ws_bytes(b->total_vertices, b->total_nnz, b->num_graphs, with_rec);
   if (need > kScratchBytes)

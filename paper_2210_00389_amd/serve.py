@@ -454,9 +454,8 @@ class GpuExecutor:
             cols = torch.cat([g.cols for g in graphs]) if eb[-1] > 0 else torch.zeros(1, dtype=torch.int32,
                                                                                         device=self.dev)
             b = B.Batch(vbase, row_offsets, cols[: int(eb[-1])], list(zip(ns, zs)))
-            # one-wave counting blocks over pieces of 1024 entries: a handful of
-            # small graphs then spreads over many waves instead of one block
-            # per graph
+            # default tuning: the pieces are cut so that a handful of small
+            # graphs spreads over the chip as well
             res = B.count_batch(b, ws=self.ws[slot], stream=s, return_levels=self.levels_hash)
             T = res.triangles[: len(reqs)].cpu().tolist()
             H = res.h_count[: len(reqs)].cpu().tolist()
